@@ -555,14 +555,6 @@ __device__ __forceinline__ bool locate_segment(const Views* views, const uint32_
     return true;
 }
 
-// Orders this wave's LDS accesses before and after (the lanes of one wave
-// exchange data through their own rows of the LDS arrays).
-__device__ __forceinline__ void wave_lds_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 __device__ __forceinline__ uint64_t wave_or64(uint64_t m) {
     uint32_t lo = (uint32_t)m, hi = (uint32_t)(m >> 32);
 #pragma unroll

@@ -1,21 +1,22 @@
 // Front-to-back compositing (paper Sec. 3, Eqs. 4-5) over the per-tile
 // depth-ordered lists, and its reverse-order adjoint.
 //
-// One wavefront (64 lanes) per tile; lane l owns column l % TW of the tile
-// and the rows l / TW + k * 64 / TW, k < TW*TH/64 (pixel k of lane l is
-// tile-local index l + 64 k, so every per-pixel load or store of the wave is a
-// run of contiguous row segments). The tile's list is staged through LDS B
-// records at a time (B = lds_batch); while staging, each lane turns records
-// into the coefficients the inner loop needs. Every lane then walks the batch
-// with broadcast LDS reads.
+// One or several wavefronts (64 lanes) per tile, each owning a strip of its
+// rows (a launch rule on the number of tiles picks 1, 2 or 4); lane l owns
+// column l % TW of the strip and the rows l / TW + k * 64 / TW, so every
+// per-pixel load or store of the wave is a run of contiguous row segments. The
+// tile's list is staged through LDS B records at a time, each wave for itself;
+// while staging, each lane turns one record into the coefficients the inner
+// loop needs, and a wave of a strip leaves out the entries that cannot take
+// part in its pixels. Every lane then walks the batch with broadcast LDS reads.
 //
 // The exponent of Eq. 5 is evaluated in base 2 with the opacity folded in,
 // E = log2(o) + A dx^2 + B dx dy + C dy^2 (A = -a log2(e)/2, B = -b log2(e),
 // C = -c log2(e)/2), so that o exp(P) = 2^E. The part that depends on dx only
 // is formed once per lane and Gaussian (the lane's pixels share a column);
 // each pixel then costs two fused multiply-adds. A pixel takes part when it
-// lies in the overlap box (bit masks over the tile's columns and rows, formed
-// exactly in binary64 at staging), E >= log2(alpha_min) (alpha' >= alpha_min;
+// lies in the overlap box (bit masks over the strip's columns and rows, formed
+// exactly at staging), E >= log2(alpha_min) (alpha' >= alpha_min;
 // alpha_min <= alpha_max) and E <= log2(o) (P <= 0); only then is 2^E
 // evaluated. Forward and backward share these functions, so their skip
 // decisions agree bit for bit.
@@ -27,9 +28,9 @@
 // accumulated behind the Gaussian, so no per-pixel blend list is stored. A
 // Gaussian's gradient is gathered per lane as moments of dL/dP over its
 // pixels, turned into the 9 parameter gradients per lane, summed over the 64
-// lanes reduce-scatter style (lane k ends with gradient k), and added with one
-// hardware float atomic instruction over 9 lanes for that (tile, Gaussian)
-// pair; Gaussians that touch no pixel of the tile skip both.
+// lanes reduce-scatter style (lane 8 k ends with gradient k), and added with one
+// hardware float atomic instruction over 9 lanes for that (strip, Gaussian)
+// pair; Gaussians that touch no pixel of the strip skip both.
 //
 // All tiles of a launch are resident at once, so a launch lasts as long as
 // its busiest SIMD. The forward records each tile's work for the backward
@@ -65,31 +66,65 @@ __device__ __forceinline__ uint32_t box_mask(float centre, float r, int origin, 
     return (0xffffffffu >> (31 - h)) & (0xffffffffu << l);
 }
 
-// Staged record of one list entry for one tile: geo = (u, v, A, B), aux = (C,
-// log2 o, column mask bits, row mask bits).
-__device__ __forceinline__ void stage_entry(const float4& r0, const float4& r1, int x0, int y0,
-                                            int tw, int th, float4& geo, float4& aux) {
-    geo = make_float4(r0.x, r0.y, r0.z * kNegHalfLog2e, r0.w * kNegLog2e);
-    aux = make_float4(r1.x * kNegHalfLog2e, __builtin_amdgcn_logf(r1.y),
-                      __uint_as_float(box_mask(r0.x, r1.z, x0, tw)),
-                      __uint_as_float(box_mask(r0.y, r1.w, y0, th)));
-}
-
-// Per lane and Gaussian: the dx-only part of E and the box bits of the
-// lane's pixels (bit RS*k for pixel k).
-struct LaneTerms {
-    float dx, bx, base;
-    uint32_t m;
+// The overlap box over a rectangle of TW x TH pixels as bit masks: columns in
+// the low TW bits and rows above them where both fit one word (a pixel then
+// takes one AND and one compare against its own two bits), columns and rows in
+// a word each otherwise.
+template <int TW, int TH>
+struct BoxBits {
+    static constexpr bool kOneWord = TW + TH <= 32;
+    uint32_t c, r;   // the pixel's bits
+    __device__ __forceinline__ BoxBits() : c(0), r(0) {}
+    __device__ __forceinline__ BoxBits(int col, int row) {
+        c = (1u << col) | (kOneWord ? 1u << ((TW + row) & 31) : 0u);
+        r = kOneWord ? 0u : 1u << row;
+    }
+    __device__ __forceinline__ bool in(float z, float w) const {
+        if constexpr (kOneWord) return (__float_as_uint(z) & c) == c;
+        return (__float_as_uint(z) & c) != 0u && (__float_as_uint(w) & r) != 0u;
+    }
 };
 
-__device__ __forceinline__ LaneTerms lane_terms(const float4& geo, const float4& aux, float px,
-                                                int col, int row0) {
+// Staged record of one list entry for one wave's rectangle: geo = (u, v, A, B),
+// aux = (C, log2 o, box bits). Returns whether the box holds a pixel of it.
+template <int TW, int TH>
+__device__ __forceinline__ bool stage_entry(const float4& r0, const float4& r1, int x0, int y0,
+                                            float4& geo, float4& aux) {
+    geo = make_float4(r0.x, r0.y, r0.z * kNegHalfLog2e, r0.w * kNegLog2e);
+    const uint32_t c = box_mask(r0.x, r1.z, x0, TW), r = box_mask(r0.y, r1.w, y0, TH);
+    const uint32_t z = BoxBits<TW, TH>::kOneWord ? c | (r << (TW & 31)) : c;
+    aux = make_float4(r1.x * kNegHalfLog2e, __builtin_amdgcn_logf(r1.y), __uint_as_float(z),
+                      __uint_as_float(r));
+    return c != 0u && r != 0u;
+}
+
+// Whether an entry can take part in a pixel of the rectangle: its box holds
+// one and, for a strip of a tile (the tile lists hold no entry that fails on
+// the whole tile), it can reach alpha_min there.
+template <bool kStrip>
+__device__ __forceinline__ bool entry_reaches(bool box, const float4& r0, const float4& r1,
+                                              const RasterDev& rp, int x0, int y0, int w, int h) {
+    if constexpr (kStrip) {
+        // (the test needs a convex exponent: a, c and det = ac - b^2 > 0, det
+        // by Kahan's fused form; other conics keep their box)
+        const float a = r0.z, b = r0.w, c = r1.x, bb = b * b;
+        const bool convex = a > 0.f && c > 0.f && fmaf(a, c, -bb) - fmaf(b, b, -bb) > 0.f;
+        return box && (!convex || rect_reachable(r0.x, r0.y, a, b, c, reach_limit(r1.y, rp), r1.z,
+                                                 r1.w, x0, y0, w, h));
+    }
+    return box;
+}
+
+// Per lane and Gaussian: the dx-only part of E.
+struct LaneTerms {
+    float dx, bx, base;
+};
+
+__device__ __forceinline__ LaneTerms lane_terms(const float4& geo, const float4& aux, float px) {
     LaneTerms t;
     t.dx = px - geo.x;
     t.base = fmaf(geo.z * t.dx, t.dx, aux.y);
     t.bx = geo.w * t.dx;
-    const uint32_t inx = (__float_as_uint(aux.z) >> col) & 1u;
-    t.m = inx ? (__float_as_uint(aux.w) >> row0) : 0u;
     return t;
 }
 
@@ -117,37 +152,41 @@ __device__ __forceinline__ float rs_step(float a, float b, bool hi) {
     return keep + dpp_f<kCtrl>(send);
 }
 
-// x + x of the lane 16 (permlane16 swap) or 32 (permlane32 swap) apart.
-__device__ __forceinline__ float xrow16(float x) {
-    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false,
+// Reduce-scatter of a pair over rows of 16 lanes: exchanging the odd rows of a
+// with the even rows of b leaves the even rows with a's and the odd rows with
+// b's two terms, one add apart (row16: rows 1 apart, row32: rows 2 apart).
+__device__ __forceinline__ float rs_row16(float a, float b) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false,
                                                     false);
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
-__device__ __forceinline__ float xrow32(float x) {
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false,
+__device__ __forceinline__ float rs_row32(float a, float b) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false,
                                                     false);
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
 // Sums of x[0..8] over the 64 lanes of a (fully active) wave. Returns, in
-// lane l, the total of x[l % 8]; *t8 gets the total of x[8] in every lane.
-// Bits 0, 1, 2 of the lane pick, in three halving exchanges (xor 1, xor 2,
-// rotate by 4 within the row), which of the eight values the lane keeps; a
-// rotate by 8 completes the row sums and two permlane swaps add the rows.
+// lanes 8 v .. 8 v + 7, the total of x[v], v < 8; *t8 gets the total of x[8]
+// in lane 63. The row swaps come first: a swap and an add halve a pair of
+// values where a DPP exchange takes two selects and an add, so the four pairs
+// and the two pairs go through the swaps and one pair is left to the selects
+// (18 instructions for the eight values, 6 for the ninth).
 __device__ __forceinline__ float wave_sum9_scatter(const float (&x)[9], int lane, float* t8) {
-    const bool b0 = lane & 1, b1 = lane & 2, b2 = lane & 4;
+    // row r = 2 h + g of the wave ends with values 2 r and 2 r + 1
     float y[4];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) y[k] = rs_step<0xb1>(x[2 * k], x[2 * k + 1], b0);   // xor 1
-    float s = x[8] + dpp_f<0xb1>(x[8]);
-    const float z0 = rs_step<0x4e>(y[0], y[1], b1), z1 = rs_step<0x4e>(y[2], y[3], b1);  // xor 2
-    s += dpp_f<0x4e>(s);
-    float w = rs_step<0x124>(z0, z1, b2);   // row rotate 4: the source lane differs in bit 2
-    s += dpp_f<0x124>(s);
-    w += dpp_f<0x128>(w);                   // row rotate 8: same bits 0-2, the other half-row
-    s += dpp_f<0x128>(s);
-    w = xrow32(xrow16(w));
-    *t8 = xrow32(xrow16(s));
+    for (int k = 0; k < 4; ++k) y[k] = rs_row16(x[(k & 1) + 4 * (k >> 1)], x[(k & 1) + 4 * (k >> 1) + 2]);
+    const float z0 = rs_row32(y[0], y[2]), z1 = rs_row32(y[1], y[3]);
+    float w = rs_step<0x128>(z0, z1, (lane & 8) != 0);   // row rotate 8: the other half-row
+    w += dpp_f<0xb1>(w);    // xor 1
+    w += dpp_f<0x4e>(w);    // xor 2
+    w += dpp_f<0x141>(w);   // the other quad of the half-row
+    float t = wave_sum_to_lane63(x[8]);
+    // (both sums formed here: sunk into the branch that adds them, their last
+    // steps lose the fused DPP form)
+    asm volatile("" : "+v"(w), "+v"(t));
+    *t8 = t;
     return w;
 }
 
@@ -169,23 +208,29 @@ __device__ __forceinline__ uint32_t wave_add_u32(uint32_t v) {
     return v;
 }
 
-// Forward of one tile: the wave composites its tile list front to back in
-// batches of B entries (records gathered and staged in LDS per batch) and
-// stops when every pixel of the tile has terminated.
-template <int TW, int TH, int B>
-__global__ void __launch_bounds__(kLanes) raster_forward_kernel(
+// Forward of one tile by W waves: each composites its strip of TH / W rows
+// front to back over the tile's list in batches of B entries (records
+// gathered and staged in LDS per batch, each wave for itself) and stops when
+// every pixel of the strip has terminated. A wave leaves the entries that
+// cannot take part in its strip out at staging.
+template <int TW, int TH, int B, int W>
+__global__ void __launch_bounds__(kLanes * W) raster_forward_kernel(
     const Views* __restrict__ views, RasterDev rp, const uint32_t* __restrict__ tile_ranges,
     const uint32_t* __restrict__ tile_entry, const float4* __restrict__ rec,
     float* __restrict__ out_rgb, float* __restrict__ t_final, uint32_t* __restrict__ n_last,
     uint32_t* __restrict__ tile_stats, uint32_t* __restrict__ tile_cost, uint32_t entries,
     uint32_t* __restrict__ tile_state, uint32_t* __restrict__ tile_resume,
     uint32_t* __restrict__ sup_redo, uint32_t* __restrict__ counters, bool redo) {
-    constexpr int PIX = TW * TH / kLanes;
-    constexpr int RS = kLanes / TW;   // row step between a lane's pixels
+    constexpr int SH = TH / W;                // rows of a strip
+    constexpr int PIX = TW * SH / kLanes;
+    constexpr int RS = kLanes / TW;           // row step between a lane's pixels
     static_assert(B % 32 == 0 && B >= 32 && B <= 256, "batch size");
-    __shared__ float4 s_geo[B];
-    __shared__ float4 s_aux[B];
-    __shared__ float4 s_col[B];   // r, g, b, -
+    static_assert(PIX >= 1 && PIX * kLanes == TW * SH, "whole waves");
+    // (the last entries: padding and the read ahead past it)
+    __shared__ float4 s_geo[W][B + 4];
+    __shared__ float4 s_aux[W][B + 4];
+    __shared__ float4 s_col[W][B + 4];   // r, g, b, list position (bits)
+    __shared__ uint32_t s_tile[W][4];
 
     const int tile = blockIdx.x;
     // the second pass goes on with the tiles the first left incomplete
@@ -193,18 +238,24 @@ __global__ void __launch_bounds__(kLanes) raster_forward_kernel(
     const ViewDev& V = views->v[view_of_tile(views, tile)];
     const int local = tile - V.tile_offset;
     const int tx = local % V.tiles_x, ty = local / V.tiles_x;
-    const int tid = threadIdx.x;
+    const int wv = W > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes) : 0;
+    const int tid = threadIdx.x % kLanes;
     const int col = tid % TW, row0 = tid / TW;
     const uint32_t start = tile_ranges[2 * tile], end = tile_ranges[2 * tile + 1];
     const float lmin = rp.log2_alpha_min, amax = rp.alpha_max, tmin = rp.t_min;
-    const int px0 = tx * TW, py0 = ty * TH;
+    const int px0 = tx * TW, py0 = ty * TH + wv * SH;
+    float4* geo = s_geo[wv];
+    float4* aux = s_aux[wv];
+    float4* rgb = s_col[wv];
 
     const float px = (float)(px0 + col) + 0.5f;
     const int64_t plane = (int64_t)V.width * V.height;
     float* img = out_rgb + 3 * V.px_offset;
+    // a pixel outside the view or stopped has py = NaN: its E is NaN and takes
+    // part in nothing
     float py[PIX], T[PIX], C0[PIX], C1[PIX], C2[PIX];
+    BoxBits<TW, SH> bits[PIX];
     uint32_t last[PIX];
-    uint32_t live = 0;   // bit RS*k: pixel k is in the view and has not stopped
     // the second pass resumes each pixel where the first stopped, at the end
     // of the tile's list prefix (which begins its whole list): transmittance,
     // colour sums (stored without the background), last blended position and
@@ -212,11 +263,13 @@ __global__ void __launch_bounds__(kLanes) raster_forward_kernel(
 #pragma unroll
     for (int k = 0; k < PIX; ++k) {
         const int y = py0 + row0 + RS * k;
-        py[k] = (float)y + 0.5f;
+        py[k] = __builtin_nanf("");
+        bits[k] = BoxBits<TW, SH>(col, row0 + RS * k);
         T[k] = 1.f;
         C0[k] = C1[k] = C2[k] = 0.f;
         last[k] = 0;
         if (px0 + col < V.width && y < V.height) {
+            py[k] = (float)y + 0.5f;
             if (redo) {
                 const int64_t pix = (int64_t)y * V.width + px0 + col;
                 T[k] = t_final[V.px_offset + pix];
@@ -225,18 +278,25 @@ __global__ void __launch_bounds__(kLanes) raster_forward_kernel(
                 C2[k] = img[2 * plane + pix];
                 const uint32_t nl = n_last[V.px_offset + pix];
                 last[k] = nl & 0x7fffffffu;
-                if (nl >> 31) live |= 1u << (RS * k);
-            } else {
-                live |= 1u << (RS * k);
+                if (!(nl >> 31)) py[k] = __builtin_nanf("");
             }
         }
     }
     const uint32_t begin = redo ? min(start + tile_resume[tile], end) : start;
-    uint32_t n_blend = 0, n_eval = 0;
-    if (redo && tid == 0) {
-        n_blend = tile_stats[2 * tile];
-        n_eval = tile_stats[2 * tile + 1];
-    }
+    // examined entries: a pixel that stops at list position p examined p of
+    // them (of this pass: p - resume), one that never stops the whole list
+    const uint32_t skipped = begin - start;
+    uint32_t n_blend = 0;
+    uint32_t stop_pos[PIX];
+#pragma unroll
+    for (int k = 0; k < PIX; ++k) stop_pos[k] = 0;
+    auto any_live = [&]() {
+        uint64_t l = 0;
+#pragma unroll
+        for (int k = 0; k < PIX; ++k) l |= ballot(py[k] == py[k]);
+        return l != 0;
+    };
+    bool alive = any_live();   // uniform
     // Software pipeline over the batches: the entry indices are loaded two
     // batches ahead and (one entry per lane, B <= 64) the records one batch
     // ahead, so the gathers of a batch run while the previous one composites
@@ -259,15 +319,29 @@ __global__ void __launch_bounds__(kLanes) raster_forward_kernel(
         q1 = rec[3 * (int64_t)e_cur[0] + 1];
         q2 = rec[3 * (int64_t)e_cur[0] + 2];
     }
-    for (uint32_t b0 = begin; b0 < end; b0 += (uint32_t)B) {
-        if (ballot(live != 0u) == 0) break;
-        __syncthreads();
-        const int cnt = (int)min((uint32_t)B, end - b0);
-        if constexpr (NE == 1) {
-            if (tid < cnt) {
-                stage_entry(q0, q1, px0, py0, TW, TH, s_geo[tid], s_aux[tid]);
-                s_col[tid] = q2;
+    for (uint32_t b0 = begin; b0 < end && alive; b0 += (uint32_t)B) {
+        wave_lds_sync();
+        const int in_batch = (int)min((uint32_t)B, end - b0);
+        int cnt = 0;   // staged entries
+        auto stage = [&](int j, const float4& r0, const float4& r1, const float4& r2) {
+            float4 g, x;
+            const bool box = stage_entry<TW, SH>(r0, r1, px0, py0, g, x);
+            const bool keep =
+                j < in_batch && entry_reaches<(W > 1)>(box, r0, r1, rp, px0, py0,
+                                                       min(TW, V.width - px0),
+                                                       min(SH, V.height - py0));
+            const uint64_t m = ballot(keep);
+            if (keep) {
+                const int o = cnt + popc64(m & lanemask_lt());
+                geo[o] = g;
+                aux[o] = x;
+                rgb[o] = make_float4(r2.x, r2.y, r2.z,
+                                     __uint_as_float(b0 - start + (uint32_t)j + 1u));
             }
+            cnt += popc64(m);
+        };
+        if constexpr (NE == 1) {
+            stage(tid, q0, q1, q2);
             const uint32_t e2 = entry_at(b0 + 2u * (uint32_t)B, 0);
             q0 = rec[3 * (int64_t)e_next[0]];
             q1 = rec[3 * (int64_t)e_next[0] + 1];
@@ -276,90 +350,118 @@ __global__ void __launch_bounds__(kLanes) raster_forward_kernel(
         } else {
 #pragma unroll
             for (int i = 0; i < NE; ++i) {
-                const int j = i * kLanes + tid;
-                if (j < cnt) {
-                    const int64_t e = e_cur[i];
-                    const float4 r0 = rec[3 * e], r1 = rec[3 * e + 1];
-                    stage_entry(r0, r1, px0, py0, TW, TH, s_geo[j], s_aux[j]);
-                    s_col[j] = rec[3 * e + 2];
-                }
+                const int64_t e = e_cur[i];
+                stage(i * kLanes + tid, rec[3 * e], rec[3 * e + 1], rec[3 * e + 2]);
                 e_cur[i] = e_next[i];
                 e_next[i] = entry_at(b0 + 2u * (uint32_t)B, i);
             }
         }
-        __syncthreads();
+        if (cnt == 0) continue;
+        // the batch padded to whole groups with entries outside every box
+        constexpr int U = 4;
+        if (tid < U - 1) {
+            geo[cnt + tid] = make_float4(0.f, 0.f, 0.f, 0.f);
+            aux[cnt + tid] = make_float4(0.f, 0.f, 0.f, 0.f);
+            rgb[cnt + tid] = make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+        wave_lds_sync();
         // the next entry's LDS reads are issued before the current entry is
         // processed, so a wave running alone does not wait on them
-        float4 Gn = s_geo[0], Xn = s_aux[0], Cn = s_col[0];
-        // unrolled twice: the prefetched records alternate between two
-        // register sets instead of being copied at the end of every step
-#pragma unroll 2
-        for (int j = 0; j < cnt && live != 0u; ++j) {
-            const float4 G = Gn, X = Xn, c = Cn;
-            const int jn = min(j + 1, cnt - 1);
-            Gn = s_geo[jn];
-            Xn = s_aux[jn];
-            Cn = s_col[jn];
-            const LaneTerms L = lane_terms(G, X, px, col, row0);
-            const uint32_t m = L.m & live;
-            const uint32_t pos = b0 - start + (uint32_t)j + 1u;
-            n_eval += (uint32_t)__builtin_popcount(live);
+        float4 Gn = geo[0], Xn = aux[0], Cn = rgb[0];
+        for (int j = 0; j < cnt && alive; j += U) {
 #pragma unroll
-            for (int k = 0; k < PIX; ++k) {
-                const float e = exponent2(L, X, py[k] - G.y);
-                if (takes_part(((m >> (RS * k)) & 1u) != 0u, e, X, lmin)) {
-                    // a pixel whose transmittance would fall below t_min stops
-                    // before this Gaussian; otherwise the Gaussian is blended
-                    const float alpha = fminf(__builtin_amdgcn_exp2f(e), amax);
-                    const float wgt = alpha * T[k];
-                    const float tn = T[k] - wgt;
-                    const bool stop = tn < tmin;
-                    const float wv = stop ? 0.f : wgt;
-                    C0[k] = fmaf(c.x, wv, C0[k]);
-                    C1[k] = fmaf(c.y, wv, C1[k]);
-                    C2[k] = fmaf(c.z, wv, C2[k]);
-                    T[k] = stop ? T[k] : tn;
-                    last[k] = stop ? last[k] : pos;
-                    n_blend += stop ? 0u : 1u;
-                    live &= stop ? ~(1u << (RS * k)) : ~0u;
+            for (int u = 0; u < U; ++u) {
+                const float4 G = Gn, X = Xn, c = Cn;
+                Gn = geo[j + u + 1];
+                Xn = aux[j + u + 1];
+                Cn = rgb[j + u + 1];
+                const LaneTerms L = lane_terms(G, X, px);
+#pragma unroll
+                for (int k = 0; k < PIX; ++k) {
+                    const float e = exponent2(L, X, py[k] - G.y);
+                    const bool take = takes_part(bits[k].in(X.z, X.w), e, X, lmin);
+                    if (take) {
+                        // a pixel whose transmittance would fall below t_min stops
+                        // before this Gaussian; otherwise the Gaussian is blended
+                        const float alpha = __builtin_amdgcn_fmed3f(__builtin_amdgcn_exp2f(e), 0.f, amax);
+                        const float wgt = alpha * T[k];
+                        const float tn = T[k] - wgt;
+                        const bool stop = tn < tmin;
+                        py[k] = stop ? __builtin_nanf("") : py[k];
+                        stop_pos[k] = stop ? __float_as_uint(c.w) : stop_pos[k];
+                        if (!stop) {
+                            C0[k] = fmaf(c.x, wgt, C0[k]);
+                            C1[k] = fmaf(c.y, wgt, C1[k]);
+                            C2[k] = fmaf(c.z, wgt, C2[k]);
+                            T[k] = tn;
+                            last[k] = __float_as_uint(c.w);
+                            ++n_blend;
+                        }
+                    }
                 }
             }
+            alive = any_live();
         }
     }
+    uint32_t n_eval = 0;
+#pragma unroll
+    for (int k = 0; k < PIX; ++k)
+        n_eval += stop_pos[k] != 0u ? stop_pos[k] - skipped : (py[k] == py[k] ? end - begin : 0u);
 
+    // the backward walks every pixel's list up to its last blended Gaussian:
+    // the tile's longest such prefix is its work. The work counters go to the
+    // tile and are summed by a small kernel after the launch (atomics of
+    // every tile on the one counters line serialise across the chip and would
+    // lengthen the launch by a fifth)
+    uint32_t my_last = 0;
+#pragma unroll
+    for (int k = 0; k < PIX; ++k) my_last = max(my_last, last[k]);
+    uint32_t tile_last = wave_max_u32(my_last);
+    uint32_t nb = wave_add_u32(n_blend), ne2 = wave_add_u32(n_eval);
+    bool tile_live = alive;
+    if constexpr (W > 1) {
+        if (tid == 0) {
+            s_tile[wv][0] = tile_last;
+            s_tile[wv][1] = nb;
+            s_tile[wv][2] = ne2;
+            s_tile[wv][3] = tile_live ? 1u : 0u;
+        }
+        __syncthreads();
+        tile_last = nb = ne2 = 0;
+        uint32_t al = 0;
+#pragma unroll
+        for (int k = 0; k < W; ++k) {
+            tile_last = max(tile_last, s_tile[k][0]);
+            nb += s_tile[k][1];
+            ne2 += s_tile[k][2];
+            al |= s_tile[k][3];
+        }
+        tile_live = al != 0u;
+    }
     // a pixel still live at the end of a list cut by the split prefix: the
     // tile is resumed by the second pass over its whole list, after the whole
     // lists of its super-tile have been split; until then its pixels hold the
     // state to resume from
-    const bool suspend = !redo && tile_state != nullptr && ballot(live != 0u) != 0 &&
-                         tile_state[tile] == kTileTruncated;
+    const bool suspend =
+        !redo && tile_state != nullptr && tile_live && tile_state[tile] == kTileTruncated;
     const int x = px0 + col;
 #pragma unroll
     for (int k = 0; k < PIX; ++k) {
         const int y = py0 + row0 + RS * k;
         if (x >= V.width || y >= V.height) continue;
         const int64_t pix = (int64_t)y * V.width + x;
-        const bool lk = (live >> (RS * k)) & 1u;
+        const bool lk = py[k] == py[k];
         img[pix] = suspend ? C0[k] : fmaf(T[k], rp.bg[0], C0[k]);
         img[plane + pix] = suspend ? C1[k] : fmaf(T[k], rp.bg[1], C1[k]);
         img[2 * plane + pix] = suspend ? C2[k] : fmaf(T[k], rp.bg[2], C2[k]);
         t_final[V.px_offset + pix] = T[k];
         n_last[V.px_offset + pix] = suspend && lk ? last[k] | 0x80000000u : last[k];
     }
-    // the backward walks every pixel's list up to its last blended Gaussian:
-    // the tile's longest such prefix is its work
-    uint32_t my_last = 0;
-#pragma unroll
-    for (int k = 0; k < PIX; ++k) my_last = max(my_last, last[k]);
-    const uint32_t tile_last = wave_max_u32(my_last);
-    // work counters per tile, summed by a small kernel after the launch
-    // (atomics of every tile on the one counters line serialise across the
-    // chip and would lengthen the launch by a fifth)
-    const uint32_t nb = wave_add_u32(n_blend), ne2 = wave_add_u32(n_eval);
-    if (tid == 0) {
+    if (W > 1) __syncthreads();   // every wave has read the tile's state
+    if (threadIdx.x == 0) {
         tile_cost[tile] = tile_last;
-        tile_stats[2 * tile] = nb;
-        tile_stats[2 * tile + 1] = ne2;
+        tile_stats[2 * tile] = nb + (redo ? tile_stats[2 * tile] : 0u);
+        tile_stats[2 * tile + 1] = ne2 + (redo ? tile_stats[2 * tile + 1] : 0u);
         if (redo) {
             tile_state[tile] = kTileWhole;
         } else if (suspend) {
@@ -425,7 +527,7 @@ __global__ void __launch_bounds__(kStatThreads) sum_tile_stats_kernel(
 // Waves per SIMD the LDS of a batch allows (64 B per staged entry).
 constexpr int backward_waves(int batch) { return batch <= 64 ? 7 : (batch == 128 ? 5 : 3); }
 
-template <int TW, int TH, int B>
+template <int TW, int TH, int B, int W>
 __global__ void __launch_bounds__(kLanes, backward_waves(B)) raster_backward_kernel(
     const Views* __restrict__ views, RasterDev rp, const uint32_t* __restrict__ tile_ranges,
     const uint32_t* __restrict__ tile_entry, const float4* __restrict__ rec,
@@ -433,15 +535,19 @@ __global__ void __launch_bounds__(kLanes, backward_waves(B)) raster_backward_ker
     const float* __restrict__ dl_drgb, const int32_t* __restrict__ gate,
     float* __restrict__ accum, const uint32_t* __restrict__ order, int total_tiles,
     uint32_t entries) {
-    constexpr int PIX = TW * TH / kLanes;
+    constexpr int SH = TH / W;   // rows of a strip
+    constexpr int PIX = TW * SH / kLanes;
     constexpr int RS = kLanes / TW;
-    __shared__ float4 s_geo[B];
-    __shared__ float4 s_aux[B];
-    __shared__ float4 s_col[B];   // r, g, b, entry (bits)
-    __shared__ float4 s_con[B];   // a, b, c, 1 / o
+    static_assert(PIX >= 1 && PIX * kLanes == TW * SH, "whole waves");
+    __shared__ float4 s_geo[B + 1];
+    __shared__ float4 s_aux[B + 1];
+    __shared__ float4 s_col[B + 1];   // r, g, b, entry (bits)
+    __shared__ float4 s_con[B];       // a, b, c, 1 / o
+    __shared__ uint32_t s_rel[B + 1];
     if (gate_closed(gate)) return;
 
-    const int tile = (int)order[blockIdx.x];
+    // the W strips of a tile are consecutive workgroups
+    const int tile = (int)order[blockIdx.x / W];
     if (tile >= total_tiles) return;   // order is a permutation of the tiles
     const ViewDev& V = views->v[view_of_tile(views, tile)];
     const int local = tile - V.tile_offset;
@@ -452,15 +558,18 @@ __global__ void __launch_bounds__(kLanes, backward_waves(B)) raster_backward_ker
 
     const int64_t plane = (int64_t)V.width * V.height;
     const float* dl = dl_drgb + 3 * V.px_offset;
+    const int py0 = ty * TH + (int)(blockIdx.x % W) * SH;
     const int x = tx * TW + col;
     const float px = (float)x + 0.5f;
     float py[PIX], T[PIX], G0[PIX], G1[PIX], G2[PIX], GS[PIX];
+    BoxBits<TW, SH> bits[PIX];
     uint32_t last[PIX];
     uint32_t my_max = 0;
 #pragma unroll
     for (int k = 0; k < PIX; ++k) {
-        const int y = ty * TH + row0 + RS * k;
+        const int y = py0 + row0 + RS * k;
         py[k] = (float)y + 0.5f;
+        bits[k] = BoxBits<TW, SH>(col, row0 + RS * k);
         T[k] = 1.f;
         G0[k] = G1[k] = G2[k] = 0.f;
         last[k] = 0;
@@ -477,34 +586,69 @@ __global__ void __launch_bounds__(kLanes, backward_waves(B)) raster_backward_ker
         my_max = max(my_max, last[k]);
     }
     const uint32_t start = tile_ranges[2 * tile], end = tile_ranges[2 * tile + 1];
-    const uint32_t stop = min(wave_max_u32(my_max), end - start);
+    const uint32_t stop =
+        min((uint32_t)__builtin_amdgcn_readfirstlane((int)wave_max_u32(my_max)), end - start);
+
+    // the lane that adds gradient v of a pair: 8 v for v < 8, 63 for the ninth
+    const int slot = tid == 63 ? 8 : tid / 8;
+    const bool adds = tid == 63 || tid % 8 == 0;
 
     // the list from the last blended position towards the front, B entries
     // at a time (list positions [b0, b_end), staged last first)
     for (uint32_t b_end = stop; b_end > 0u;) {
         const uint32_t b0 = b_end > (uint32_t)B ? b_end - (uint32_t)B : 0u;
-        const int cnt = (int)(b_end - b0);
+        const int in_batch = (int)(b_end - b0);
+        int cnt = 0;   // staged entries
         __syncthreads();
-        for (int k = tid; k < cnt; k += kLanes) {
-            const uint32_t e = min(tile_entry[start + b_end - 1u - (uint32_t)k], entries - 1u);
+        for (int k0 = 0; k0 < in_batch; k0 += kLanes) {
+            const int k = k0 + tid;
+            const uint32_t p = b_end - 1u - (uint32_t)min(k, in_batch - 1);   // list position
+            const uint32_t e = min(tile_entry[start + p], entries - 1u);
             const float4 r0 = rec[3 * (int64_t)e], r1 = rec[3 * (int64_t)e + 1],
                          r2 = rec[3 * (int64_t)e + 2];
-            stage_entry(r0, r1, tx * TW, ty * TH, TW, TH, s_geo[k], s_aux[k]);
-            s_col[k] = make_float4(r2.x, r2.y, r2.z, __uint_as_float(e));
-            // 1/o capped at FLT_MAX: an opacity that underflowed to 0 can only
-            // take part with alpha' = 0 (alpha_min = 0), where M6 = 0
-            s_con[k] = make_float4(r0.z, r0.w, r1.x, fminf(1.f / r1.y, 3.402823466e38f));
+            float4 g, xm;
+            const bool box = stage_entry<TW, SH>(r0, r1, tx * TW, py0, g, xm);
+            const bool keep =
+                k < in_batch && entry_reaches<(W > 1)>(box, r0, r1, rp, tx * TW, py0,
+                                                       min(TW, V.width - tx * TW),
+                                                       min(SH, V.height - py0));
+            const uint64_t m = ballot(keep);
+            if (keep) {
+                const int o = cnt + popc64(m & lanemask_lt());
+                s_geo[o] = g;
+                s_aux[o] = xm;
+                s_col[o] = make_float4(r2.x, r2.y, r2.z, __uint_as_float(e));
+                // 1/o capped at FLT_MAX: an opacity that underflowed to 0 can only
+                // take part with alpha' = 0 (alpha_min = 0), where M6 = 0
+                s_con[o] = make_float4(r0.z, r0.w, r1.x, fminf(1.f / r1.y, 3.402823466e38f));
+                s_rel[o] = p;
+            }
+            cnt += popc64(m);
         }
         __syncthreads();
+        // With few waves on a SIMD (strips) the next entry's LDS reads are
+        // issued before the current entry is processed (the last one reads
+        // ahead into the spare element); with one wave per tile the other
+        // waves cover them, and the registers are worth more.
+        constexpr bool kAhead = W > 1;
+        uint32_t rel_n;
+        float4 Gn, Xn, Cn;
+        auto fetch = [&](int j) {
+            rel_n = s_rel[j];
+            Gn = s_geo[j];
+            Xn = s_aux[j];
+            Cn = s_col[j];
+        };
+        if (kAhead) fetch(0);
         for (int j = 0; j < cnt; ++j) {
-            const uint32_t rel = b_end - 1u - (uint32_t)j;   // list position
-            const float4 G = s_geo[j];
-            const float4 X = s_aux[j];
+            if (!kAhead) fetch(j);
+            const uint32_t rel = rel_n;   // list position
+            const float4 G = Gn, X = Xn, c = Cn;
+            if (kAhead) fetch(j + 1);
             // read once per Gaussian with the coefficients (the compiler would
             // otherwise re-read it inside each pixel's branch)
-            const float4 c = s_col[j];
-            asm volatile("" ::"v"(c.x), "v"(c.y), "v"(c.z));
-            const LaneTerms L = lane_terms(G, X, px, col, row0);
+            if (!kAhead) asm volatile("" ::"v"(c.x), "v"(c.y), "v"(c.z));
+            const LaneTerms L = lane_terms(G, X, px);
             // -0 is the additive identity for every float, so the first
             // accumulation into each sum folds away
             float sdp = -0.f, sdy = -0.f, sdy2 = -0.f, d_r = -0.f, d_g = -0.f, d_bl = -0.f;
@@ -513,10 +657,10 @@ __global__ void __launch_bounds__(kLanes, backward_waves(B)) raster_backward_ker
             for (int k = 0; k < PIX; ++k) {
                 const float dy = py[k] - G.y;
                 const float e = exponent2(L, X, dy);
-                if ((rel < last[k]) & takes_part(((L.m >> (RS * k)) & 1u) != 0u, e, X, lmin)) {
+                if ((rel < last[k]) & takes_part(bits[k].in(X.z, X.w), e, X, lmin)) {
                     const float raw = __builtin_amdgcn_exp2f(e);
                     const bool clamped = raw > amax;
-                    const float alpha = fminf(raw, amax);
+                    const float alpha = __builtin_amdgcn_fmed3f(raw, 0.f, amax);
                     // 1 - alpha' >= 1 - alpha_max > 0: one hardware reciprocal
                     // (1 ulp) serves the transmittance recovery and dC/dalpha'
                     const float inv_om = __builtin_amdgcn_rcpf(1.f - alpha);
@@ -543,8 +687,8 @@ __global__ void __launch_bounds__(kLanes, backward_waves(B)) raster_backward_ker
             if (ballot(contrib) == 0) continue;
             // per-lane parameter gradients (the moments scaled by the
             // Gaussian's a, b, c, 1/o), summed over the wave reduce-scatter
-            // style: lane k < 8 ends with the total of gradient k, every lane
-            // with the total of gradient 8; one atomic instruction adds all 9
+            // style: lane 8 k ends with the total of gradient k < 8, lane 63
+            // with that of gradient 8; one atomic instruction adds all 9
             const float4 Q = s_con[j];
             const float m1 = L.dx * sdp;
             float x[9];
@@ -559,9 +703,10 @@ __global__ void __launch_bounds__(kLanes, backward_waves(B)) raster_backward_ker
             x[8] = d_bl;
             float t8;
             const float t = wave_sum9_scatter(x, tid, &t8);
-            if (tid < 9)
-                unsafeAtomicAdd(accum + (int64_t)kAccumFloats * __float_as_uint(s_col[j].w) + tid,
-                                tid == 8 ? t8 : t);
+            if (adds)
+                unsafeAtomicAdd(accum + (int64_t)kAccumFloats *
+                                            __float_as_uint(kAhead ? c.w : s_col[j].w) + slot,
+                                slot == 8 ? t8 : t);
         }
         b_end = b0;
     }
@@ -580,29 +725,41 @@ __global__ void zero_f32_gated_kernel(float4* p, int64_t n4, const int32_t* gate
 
 }  // namespace
 
-// Kernel instantiations: tile shapes 16x16, 8x8, 32x8 and batches 32, 64,
-// 128, 256 (the shapes and batches the raster parameters accept).
-#define SGS_RASTER_DISPATCH(KERNEL, ...)                                              \
+// Waves per tile. A wave's time is its instruction count (a wave alone on a
+// SIMD issues one instruction every 4 cycles), so a launch with fewer waves
+// than the chip's 1024 SIMDs hold ends with its longest tile, and cutting a
+// tile into strips of rows shortens exactly that; strips also drop the entries
+// that miss them. 8x8 tiles have one pixel per lane already.
+//
+// Forward: strips win at every size, the finer ones until the per-strip work
+// (LDS broadcasts, 24 cycles an entry and wave) catches up. us for 1 / 2 / 4
+// waves: 16 tiles 74 / 45 / 27 (one pass), 1200 tiles 89 / 55 / 39, 2170 tiles
+// 124 / 73 / 61, 4056 tiles 149 / 105 / 100, 6700 tiles 167 / 135 / 141,
+// 28000 tiles 746 / 568 / 599.
+//
+// Backward: each strip repeats the wave reduction and the atomic of a pair, so
+// strips pay only while SIMDs would idle: 16 tiles 68 / 42 / 29, 1200 tiles
+// 135 / 88 / 76, 2170 tiles 188 / 131 / 153, 4056 tiles 228 / 220 / 264, 6700
+// tiles 276 / 293 / 403, 28000 tiles 925 / 1208 / 1704.
+constexpr int64_t kForwardFine = 5120;    // tiles up to which the forward takes 4 waves, else 2
+constexpr int64_t kBackwardFine = 1536;   // tiles up to which the backward takes 4 waves
+constexpr int64_t kBackwardHalf = 5120;   // ... 2 waves, else 1
+
+// Kernel instantiations: tile shapes 16x16, 8x8, 32x8; the batches 32, 64,
+// 128, 256 the raster parameters accept where one wave takes a tile, batches
+// of 64 in strips.
+#define SGS_RASTER_BATCHES(KERNEL, TW, TH, ...)                                       \
     do {                                                                             \
-        const int tw_ = rp.tile_w, b_ = rp.batch;                                    \
-        if (tw_ == 16) {                                                             \
-            if (b_ == 32) SGS_LAUNCH((KERNEL<16, 16, 32>), __VA_ARGS__);               \
-            else if (b_ == 128) SGS_LAUNCH((KERNEL<16, 16, 128>), __VA_ARGS__);        \
-            else if (b_ == 256) SGS_LAUNCH((KERNEL<16, 16, 256>), __VA_ARGS__);        \
-            else SGS_LAUNCH((KERNEL<16, 16, 64>), __VA_ARGS__);                        \
-        } else if (tw_ == 8) {                                                       \
-            if (b_ == 32) SGS_LAUNCH((KERNEL<8, 8, 32>), __VA_ARGS__);                 \
-            else if (b_ == 128) SGS_LAUNCH((KERNEL<8, 8, 128>), __VA_ARGS__);          \
-            else if (b_ == 256) SGS_LAUNCH((KERNEL<8, 8, 256>), __VA_ARGS__);          \
-            else SGS_LAUNCH((KERNEL<8, 8, 64>), __VA_ARGS__);                          \
-        } else {                                                                     \
-            if (b_ == 32) SGS_LAUNCH((KERNEL<32, 8, 32>), __VA_ARGS__);                \
-            else if (b_ == 128) SGS_LAUNCH((KERNEL<32, 8, 128>), __VA_ARGS__);         \
-            else if (b_ == 256) SGS_LAUNCH((KERNEL<32, 8, 256>), __VA_ARGS__);         \
-            else SGS_LAUNCH((KERNEL<32, 8, 64>), __VA_ARGS__);                         \
-        }                                                                            \
+        if (rp.batch == 32) SGS_LAUNCH((KERNEL<TW, TH, 32, 1>), 1, __VA_ARGS__);       \
+        else if (rp.batch == 128) SGS_LAUNCH((KERNEL<TW, TH, 128, 1>), 1, __VA_ARGS__); \
+        else if (rp.batch == 256) SGS_LAUNCH((KERNEL<TW, TH, 256, 1>), 1, __VA_ARGS__); \
+        else SGS_LAUNCH((KERNEL<TW, TH, 64, 1>), 1, __VA_ARGS__);                      \
     } while (0)
-#define SGS_LAUNCH(K, ...) hipLaunchKernelGGL((K), grid, block, 0, s, __VA_ARGS__)
+#define SGS_RASTER_STRIPS(KERNEL, W, ...)                                             \
+    do {                                                                             \
+        if (rp.tile_w == 16) SGS_LAUNCH((KERNEL<16, 16, 64, W>), W, __VA_ARGS__);      \
+        else SGS_LAUNCH((KERNEL<32, 8, 64, W>), W, __VA_ARGS__);                       \
+    } while (0)
 
 hipError_t launch_rasterize(const RasterDev& rp, const Layout& L, char* ws, float* out_rgb,
                             hipStream_t s) {
@@ -620,21 +777,32 @@ hipError_t launch_rasterize(const RasterDev& rp, const Layout& L, char* ws, floa
     uint32_t* state = rp.prefix_segs > 0 ? reinterpret_cast<uint32_t*>(ws + L.tile_state) : nullptr;
     uint32_t* sup_redo = reinterpret_cast<uint32_t*>(ws + L.sup_redo);
     uint32_t* resume = reinterpret_cast<uint32_t*>(ws + L.tile_resume);
-    const dim3 grid((unsigned)L.total_tiles), block(kLanes);
-    SGS_RASTER_DISPATCH(raster_forward_kernel, views, rp, ranges, entry, rec, out_rgb, tf, nl,
-                        stats, cost, entries, state, resume, sup_redo, cnt, false);
-    if (hipError_t err = hipGetLastError(); err != hipSuccess) return err;
+    // the waves of a tile are one workgroup
+#define SGS_LAUNCH(K, W, ...) \
+    hipLaunchKernelGGL(K, dim3((unsigned)L.total_tiles), dim3(kLanes * W), 0, s, __VA_ARGS__)
+    auto composite = [&](bool redo) {
+        if (rp.tile_w == 8)
+            SGS_RASTER_BATCHES(raster_forward_kernel, 8, 8, views, rp, ranges, entry, rec, out_rgb,
+                               tf, nl, stats, cost, entries, state, resume, sup_redo, cnt, redo);
+        else if (L.total_tiles <= kForwardFine)
+            SGS_RASTER_STRIPS(raster_forward_kernel, 4, views, rp, ranges, entry, rec, out_rgb, tf,
+                              nl, stats, cost, entries, state, resume, sup_redo, cnt, redo);
+        else
+            SGS_RASTER_STRIPS(raster_forward_kernel, 2, views, rp, ranges, entry, rec, out_rgb, tf,
+                              nl, stats, cost, entries, state, resume, sup_redo, cnt, redo);
+        return hipGetLastError();
+    };
+    if (hipError_t err = composite(false); err != hipSuccess) return err;
     if (state != nullptr) {
         // tiles whose list prefix ran out with live pixels: the whole lists of
         // their super-tiles, then their compositing resumed
         if (hipError_t err = launch_split_rest(rp, L, ws, s); err != hipSuccess) return err;
-        SGS_RASTER_DISPATCH(raster_forward_kernel, views, rp, ranges, entry, rec, out_rgb, tf, nl,
-                            stats, cost, entries, state, resume, sup_redo, cnt, true);
-        if (hipError_t err = hipGetLastError(); err != hipSuccess) return err;
+        if (hipError_t err = composite(true); err != hipSuccess) return err;
     }
     hipLaunchKernelGGL(sum_tile_stats_kernel, dim3(1), dim3(kStatThreads), 0, s, stats, cost,
                        L.total_tiles, cnt);
     return hipGetLastError();
+#undef SGS_LAUNCH
 }
 
 hipError_t launch_rasterize_backward(const RasterDev& rp, const Layout& L, char* ws,
@@ -660,13 +828,27 @@ hipError_t launch_rasterize_backward(const RasterDev& rp, const Layout& L, char*
         err != hipSuccess)
         return err;
     const int tiles = (int)L.total_tiles;
-    const dim3 grid((unsigned)L.total_tiles), block(kLanes);
-    SGS_RASTER_DISPATCH(raster_backward_kernel, views, rp, ranges, entry, rec, tf, nl, dl_drgb,
-                        gate, acc, order, tiles, (uint32_t)L.entries);
+    // every strip is a workgroup of its own
+#define SGS_LAUNCH(K, W, ...)                                                                  \
+    hipLaunchKernelGGL(K, dim3((unsigned)(L.total_tiles * W)), dim3(kLanes), 0, s, __VA_ARGS__)
+#define SGS_ARGS                                                                              \
+    views, rp, ranges, entry, rec, tf, nl, dl_drgb, gate, acc, order, tiles, (uint32_t)L.entries
+    if (rp.tile_w == 8)
+        SGS_RASTER_BATCHES(raster_backward_kernel, 8, 8, SGS_ARGS);
+    else if (L.total_tiles <= kBackwardFine)
+        SGS_RASTER_STRIPS(raster_backward_kernel, 4, SGS_ARGS);
+    else if (L.total_tiles <= kBackwardHalf)
+        SGS_RASTER_STRIPS(raster_backward_kernel, 2, SGS_ARGS);
+    else if (rp.tile_w == 16)
+        SGS_RASTER_BATCHES(raster_backward_kernel, 16, 16, SGS_ARGS);
+    else
+        SGS_RASTER_BATCHES(raster_backward_kernel, 32, 8, SGS_ARGS);
+#undef SGS_ARGS
+#undef SGS_LAUNCH
     return hipGetLastError();
 }
 
-#undef SGS_LAUNCH
-#undef SGS_RASTER_DISPATCH
+#undef SGS_RASTER_STRIPS
+#undef SGS_RASTER_BATCHES
 
 }  // namespace sgs

@@ -16,9 +16,17 @@ __device__ __forceinline__ uint64_t lanemask_lt() {
     return l == 0 ? 0ull : (~0ull >> (64 - l));
 }
 
-__device__ __forceinline__ uint64_t ballot(bool p) { return __ballot(p); }
+__device__ __forceinline__ uint64_t ballot(bool p) { return __builtin_amdgcn_ballot_w64(p); }
 
 __device__ __forceinline__ int popc64(uint64_t m) { return __popcll(m); }
+
+// Orders this wave's LDS accesses before and after (the lanes of one wave
+// exchange data through their own rows of the LDS arrays).
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 
 // Sum over the 64 lanes of a wave, result valid in lane 63 only. DPP steps:
 // xor 1, xor 2 (quad permutes), rotate 4 and 8 within rows of 16 (every lane
