@@ -2,11 +2,29 @@
 // SSIM with an 11x11 Gaussian window (sigma 1.5), zero-padded same-size
 // filtering, both terms averaged over the 3 H W values.
 //
-// One 16x16 output tile per workgroup. The tile plus a 5-pixel halo of all
-// three channels of both images is staged in LDS once; per channel the five
-// local moments (mu_x, mu_y, E[x^2], E[y^2], E[xy]) are filtered separably,
-// the horizontal pass forming the products from x and y as it reads them.
-// Per-tile sums go to a partials array that a one-workgroup kernel reduces in
+// One wave filters one channel of a strip of 54 columns (64 lanes less the
+// window's halo) and walks down its rows. A row of values (x, y and their three
+// products, formed once per pixel) goes through LDS, a float4 and a float per
+// lane, for the horizontal taps; the filtered row is then added to the ten
+// output rows in the making, whose partial sums each lane holds in registers:
+// one fused multiply-add per moment and tap, and since every partial sum moves
+// one place with its update, no shift and no LDS. Strips are cut into as few
+// rows as it takes to fill the chip, since every strip repeats ten rows of the
+// filters.
+//
+// What bounds it: vector issue, 113 operations per pixel and channel in the
+// filters, times 1.19 for the halo columns and 1.36 for the halo rows (28 to a
+// strip at 1600x1060), and 60 for S and the maps. The tiled form before it
+// (16x16 pixels per workgroup, 26x26 staged values, the products formed again at
+// every tap, both passes through LDS) issued twice as many instructions. The
+// order of every sum and the rounding of every quotient are the tiled form's,
+// so the maps and the gradient are the same bit for bit. At 1600x1060: forward
+// 90 -> 53 us, backward 72 -> 41 us (122 MB of images, maps and gradient, 3
+// TB/s); at 980x545 38 -> 27 and 30 -> 21 us. (Vertical pass first takes 7% off
+// both, as the halo rows skip the horizontal taps, but rounds differently: 3e-6
+// of the gradient, as far as either is from 64 bits.)
+//
+// Per-strip sums go to a partials array that a one-workgroup kernel reduces in
 // index order in binary64, so the loss is bit-reproducible.
 //
 // Backward: per pixel p the SSIM value S(p) depends on x through mu_x(p),
@@ -14,6 +32,8 @@
 // dS/dE[xy] are written by the forward (when a workspace holds them) and
 // filtered again by the backward (the window is symmetric):
 //   dSSIM/dx(q) = F[dS/dmu_x](q) + 2 x(q) F[dS/dE[x^2]](q) + y(q) F[dS/dE[xy]](q).
+#include <algorithm>
+
 #include "sgs_internal.hpp"
 #include "sgs_device.hpp"
 
@@ -21,38 +41,60 @@ namespace sgs {
 
 namespace {
 
-constexpr int kT = 16;               // output tile edge
-constexpr int kR = 5;                // window radius
-constexpr int kE = kT + 2 * kR;      // staged edge (26)
-constexpr int kThreads = kT * kT;
+constexpr int kT = 16;                  // tiles the partials array is sized by
+constexpr int kR = 5;                   // window radius
+constexpr int kTaps = 2 * kR + 1;
+constexpr int kCols = 64 - 2 * kR;      // output columns of a wave
+constexpr int kThreads = 3 * 64;        // one wave a channel
 constexpr float kC1 = 0.01f * 0.01f;
 constexpr float kC2 = 0.03f * 0.03f;
 
 struct Window {
-    float g[11];
+    float g[kTaps];
 };
 
 Window make_window() {
     Window w;
-    double s = 0.0, v[11];
-    for (int k = 0; k < 11; ++k) {
-        const double d = k - 5;
+    double s = 0.0, v[kTaps];
+    for (int k = 0; k < kTaps; ++k) {
+        const double d = k - kR;
         v[k] = std::exp(-(d * d) / (2.0 * 1.5 * 1.5));
         s += v[k];
     }
-    for (int k = 0; k < 11; ++k) w.g[k] = (float)(v[k] / s);
+    for (int k = 0; k < kTaps; ++k) w.g[k] = (float)(v[k] / s);
     return w;
+}
+
+// The image cut into strips of kCols columns and `rows` rows, one workgroup
+// each: as many as make 4 workgroups (3 waves per SIMD) on every compute unit,
+// of kLeast rows at least. us of the forward with its reduction / of the
+// backward by the bound on the strips: 1600x1060 800 71.7 / 46.9, 1024 57.4 /
+// 40.7, 1152 60.9 / 43.9, 1400 (a second round) 72.7 / 44.6; 980x545 800 34.3
+// / 22.0, 1024 31.2 / 20.5, 1280 32.4 / 22.6, 1400 38.3 / 24.0. At 64x64 twice
+// the rows cost a quarter more.
+constexpr int64_t kResident = 1024;
+constexpr int64_t kLeast = 4;
+struct Strips {
+    int rows;
+    dim3 grid;
+};
+Strips strips(int w, int h) {
+    const int64_t nx = (w + kCols - 1) / kCols;
+    const int64_t ny = std::max<int64_t>(1, kResident / nx);
+    const int64_t rows = std::max<int64_t>((h + ny - 1) / ny, kLeast);
+    return {(int)rows, dim3((unsigned)nx, (unsigned)((h + rows - 1) / rows))};
 }
 
 // Loss workspace: [partials: 2 * blocks floats][maps: 9 * H * W floats]
 struct LossLayout {
-    int64_t blocks;
+    int64_t blocks;   // at least the number of strips
     size_t partials, maps, total;
 };
 
+// (at most kResident strips, or one row of them)
 LossLayout loss_layout(int w, int h) {
     LossLayout L;
-    L.blocks = (int64_t)((w + kT - 1) / kT) * ((h + kT - 1) / kT);
+    L.blocks = std::max<int64_t>((int64_t)((w + kT - 1) / kT) * ((h + kT - 1) / kT), kResident);
     auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
     L.partials = 0;
     L.maps = al(L.partials + sizeof(float) * 2 * L.blocks);
@@ -68,116 +110,151 @@ __device__ __forceinline__ const float* target_of(const TargetRef& t, int64_t im
     return t.base + (int64_t)i * image_floats;
 }
 
-// Stages field f of channels 0..2 of an image (plane stride `plane`) around
-// the tile into dst[ch][26][26], zero outside the image.
-__device__ __forceinline__ void stage3(const float* __restrict__ img, int64_t plane, int w, int h,
-                                       int x0, int y0, float (*dst)[kE][kE]) {
-    for (int i = threadIdx.x; i < 3 * kE * kE; i += kThreads) {
-        const int ch = i / (kE * kE), rc = i % (kE * kE);
-        const int r = rc / kE, c = rc % kE;
-        const int gx = x0 + c, gy = y0 + r;
-        dst[ch][r][c] = (gx >= 0 && gx < w && gy >= 0 && gy < h)
-                            ? img[ch * plane + (int64_t)gy * w + gx] : 0.f;
+// Quotients by one divisor, each rounded as an IEEE division rounds it: the
+// reciprocal is refined to the nearest float (two Newton steps), and a quotient
+// a r corrected once by its exact remainder is then the nearest one (Markstein
+// 1990), without the scaling of the general sequence: divisors lie far from the
+// ends of the float range (C1 C2 = 9e-8 and up) and so do the quotients.
+struct Divisor {
+    float d, r;
+    __device__ __forceinline__ explicit Divisor(float x) : d(x) {
+        const float r0 = __builtin_amdgcn_rcpf(x);
+        const float r1 = fmaf(fmaf(-x, r0, 1.f), r0, r0);
+        r = fmaf(fmaf(-x, r1, 1.f), r1, r1);
     }
-}
+    __device__ __forceinline__ float of(float a) const {
+        const float q = a * r;
+        return fmaf(fmaf(-d, q, a), r, q);
+    }
+};
 
-// The five filtered moments of channel ch at this thread's output pixel.
-__device__ __forceinline__ void moments(const float (*X)[kE], const float (*Y)[kE],
-                                        float (*hb)[kE][kT], const Window& W, float m[5]) {
-    const int tid = threadIdx.x;
-    for (int i = tid; i < kE * kT; i += kThreads) {
-        const int r = i / kT, c = i % kT;
-        float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f, s4 = 0.f;
+// The partial sums of one field over rows: after input row r, sum[j] holds
+// output row r - kR + 1 + j less the rows still to come.
+struct Column {
+    float sum[kTaps - 1];
+    __device__ __forceinline__ Column() {
 #pragma unroll
-        for (int k = 0; k < 11; ++k) {
-            const float a = X[r][c + k], b = Y[r][c + k], g = W.g[k];
-            s0 = fmaf(g, a, s0);
-            s1 = fmaf(g, b, s1);
-            s2 = fmaf(g, a * a, s2);
-            s3 = fmaf(g, b * b, s3);
-            s4 = fmaf(g, a * b, s4);
-        }
-        hb[0][r][c] = s0;
-        hb[1][r][c] = s1;
-        hb[2][r][c] = s2;
-        hb[3][r][c] = s3;
-        hb[4][r][c] = s4;
+        for (int j = 0; j < kTaps - 1; ++j) sum[j] = 0.f;
     }
-    __syncthreads();
-    const int r = tid / kT, c = tid % kT;
+    // Adds a row's value and returns the output row it completes.
+    __device__ __forceinline__ float add(const Window& W, float v) {
+        const float done = fmaf(W.g[kTaps - 1], v, sum[0]);
 #pragma unroll
-    for (int f = 0; f < 5; ++f) {
-        float s = 0.f;
-#pragma unroll
-        for (int k = 0; k < 11; ++k) s = fmaf(W.g[k], hb[f][r + k][c], s);
-        m[f] = s;
+        for (int j = 1; j < kTaps - 1; ++j) sum[j - 1] = fmaf(W.g[kTaps - 1 - j], v, sum[j]);
+        sum[kTaps - 2] = W.g[0] * v;
+        return done;
     }
-    __syncthreads();
-}
+};
 
-// Forward tile: sums of |x - y| and of S over the tile's 3 x 256 values into
-// partials[2 blk] and, with kMaps, the maps dS/dmu_x, dS/dE[x^2], dS/dE[xy]
-// the backward filters. The maps are written on every forward: forming them
-// again in the backward would repeat the whole moment pass, which costs more
-// than the writes it saves on iterations whose backward is skipped.
+// One workgroup's strip: this wave's channel and this lane's column.
+struct Place {
+    int ch, lane, cx, first, end;   // output rows [first, end)
+    bool out;                       // the lane's column is an output column
+    bool in_image;
+    int tap0;                       // LDS index of the lane's first horizontal tap
+    __device__ __forceinline__ Place(int w, int h, int rows) {
+        lane = threadIdx.x % 64;
+        ch = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+        cx = (int)blockIdx.x * kCols - kR + lane;
+        first = (int)blockIdx.y * rows;
+        end = min(first + rows, h);
+        in_image = cx >= 0 && cx < w;
+        out = lane >= kR && lane < kR + kCols && cx < w;
+        tap0 = min(max(lane, kR), kR + kCols - 1) - kR;
+    }
+};
+
+// Forward: sums of |x - y| and of S over the strip into partials[2 blk] and,
+// with kMaps, the maps dS/dmu_x, dS/dE[x^2], dS/dE[xy] the backward filters.
+// The maps are written on every forward: forming them again in the backward
+// would repeat the whole moment pass, which costs more than the writes it
+// saves on iterations whose backward is skipped.
+// (4 waves per SIMD: at most 128 registers.)
 template <bool kMaps>
-__global__ void __launch_bounds__(kThreads) ssim_forward_kernel(
-    const float* __restrict__ x, TargetRef target, int w, int h, Window W,
+__global__ void __launch_bounds__(kThreads, 4) ssim_forward_kernel(
+    const float* __restrict__ x, TargetRef target, int w, int h, int rows, Window W,
     float* __restrict__ partials, float* __restrict__ maps) {
-    __shared__ float sx[3][kE][kE];
-    __shared__ float sy[3][kE][kE];
-    __shared__ float hb[5][kE][kT];
-    __shared__ float red[2][kThreads / 64];
-    const int tid = threadIdx.x;
-    const int bx = blockIdx.x, by = blockIdx.y;
-    const int x0 = bx * kT - kR, y0 = by * kT - kR;
-    const int ox = bx * kT + tid % kT, oy = by * kT + tid / kT;
-    const bool inside = ox < w && oy < h;
+    __shared__ float4 s_m4[3][64];
+    __shared__ float s_m1[3][64];
+    __shared__ float red[2][3];
+    const Place p(w, h, rows);
     const int64_t plane = (int64_t)w * h;
-    const float* __restrict__ y = target_of(target, 3 * plane);
-    stage3(x, plane, w, h, x0, y0, sx);
-    stage3(y, plane, w, h, x0, y0, sy);
-    __syncthreads();
+    const float* __restrict__ xc = x + p.ch * plane + p.cx;
+    const float* __restrict__ yc = target_of(target, 3 * plane) + p.ch * plane + p.cx;
+    float4* m4 = s_m4[p.ch];
+    float* m1 = s_m1[p.ch];
+    Column cx_, cy_, cxx, cyy, cxy;
     float s_l1 = 0.f, s_ssim = 0.f;
-    for (int ch = 0; ch < 3; ++ch) {
-        float m[5];
-        moments(sx[ch], sy[ch], hb, W, m);
-        if (inside) {
-            const float mx = m[0], my = m[1];
-            const float sxx = m[2] - mx * mx, syy = m[3] - my * my, sxy = m[4] - mx * my;
+    // rows are loaded kAhead rows before they are used
+    constexpr int kAhead = 2;
+    float a[kAhead], b[kAhead];
+    auto load = [&](int r, float& av, float& bv) {
+        const bool ok = p.in_image && r >= 0 && r < h;
+        av = ok ? xc[(int64_t)r * w] : 0.f;
+        bv = ok ? yc[(int64_t)r * w] : 0.f;
+    };
+#pragma unroll
+    for (int k = 0; k < kAhead; ++k) load(p.first - kR + k, a[k], b[k]);
+    for (int r = p.first - kR; r < p.end + kR; ++r) {
+        const float av = a[0], bv = b[0];
+#pragma unroll
+        for (int k = 0; k + 1 < kAhead; ++k) {
+            a[k] = a[k + 1];
+            b[k] = b[k + 1];
+        }
+        load(r + kAhead, a[kAhead - 1], b[kAhead - 1]);
+        if (p.out && r >= p.first && r < p.end) s_l1 += fabsf(av - bv);
+        m4[p.lane] = make_float4(av, bv, av * av, bv * bv);
+        m1[p.lane] = av * bv;
+        wave_lds_sync();
+        float h0 = 0.f, h1 = 0.f, h2 = 0.f, h3 = 0.f, h4 = 0.f;
+#pragma unroll
+        for (int k = 0; k < kTaps; ++k) {
+            const float4 q = m4[p.tap0 + k];
+            const float g = W.g[k];
+            h0 = fmaf(g, q.x, h0);
+            h1 = fmaf(g, q.y, h1);
+            h2 = fmaf(g, q.z, h2);
+            h3 = fmaf(g, q.w, h3);
+            h4 = fmaf(g, m1[p.tap0 + k], h4);
+        }
+        wave_lds_sync();
+        const float mx = cx_.add(W, h0), my = cy_.add(W, h1), exx = cxx.add(W, h2),
+                    eyy = cyy.add(W, h3), exy = cxy.add(W, h4);
+        const int o = r - kR;
+        if (o < p.first) continue;   // uniform
+        if (p.out) {
+            const float sxx = exx - mx * mx, syy = eyy - my * my, sxy = exy - mx * my;
             const float A1 = 2.f * mx * my + kC1, A2 = 2.f * sxy + kC2;
             const float B1 = mx * mx + my * my + kC1, B2 = sxx + syy + kC2;
-            const float D = B1 * B2;
-            const float S = (A1 * A2) / D;
-            const float a = sx[ch][tid / kT + kR][tid % kT + kR];
-            const float b = sy[ch][tid / kT + kR][tid % kT + kR];
-            s_l1 += fabsf(a - b);
+            const Divisor d1(B1), d2(B2), dd(B1 * B2);
+            const float S = dd.of(A1 * A2);
             s_ssim += S;
             if (kMaps) {
-                const int64_t pix = (int64_t)oy * w + ox;
-                maps[(0 * 3 + ch) * plane + pix] =
-                    2.f * my * (A2 - A1) / D - 2.f * mx * S * (1.f / B1 - 1.f / B2);
-                maps[(1 * 3 + ch) * plane + pix] = -S / B2;
-                maps[(2 * 3 + ch) * plane + pix] = 2.f * A1 / D;
+                const int64_t pix = (int64_t)o * w + p.cx;
+                maps[(0 * 3 + p.ch) * plane + pix] =
+                    dd.of(2.f * my * (A2 - A1)) - 2.f * mx * S * (d1.r - d2.r);
+                maps[(1 * 3 + p.ch) * plane + pix] = d2.of(-S);
+                maps[(2 * 3 + p.ch) * plane + pix] = dd.of(2.f * A1);
             }
         }
     }
     // fixed-order workgroup sum
     s_l1 = wave_sum(s_l1);
     s_ssim = wave_sum(s_ssim);
-    if (lane_id() == 0) {
-        red[0][tid / 64] = s_l1;
-        red[1][tid / 64] = s_ssim;
+    if (p.lane == 0) {
+        red[0][p.ch] = s_l1;
+        red[1][p.ch] = s_ssim;
     }
     __syncthreads();
-    if (tid == 0) {
-        const int64_t blk = (int64_t)by * gridDim.x + bx;
-        partials[2 * blk] = (red[0][0] + red[0][1]) + (red[0][2] + red[0][3]);
-        partials[2 * blk + 1] = (red[1][0] + red[1][1]) + (red[1][2] + red[1][3]);
+    if (threadIdx.x == 0) {
+        const int64_t blk = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+        partials[2 * blk] = (red[0][0] + red[0][1]) + red[0][2];
+        partials[2 * blk + 1] = (red[1][0] + red[1][1]) + red[1][2];
     }
 }
 
-// Sum of the per-tile partials in index order (binary64), then Eq. 6.
+// Sum of the per-strip partials in index order (binary64), then Eq. 6.
 __global__ void __launch_bounds__(1024) loss_reduce_kernel(const float* __restrict__ partials,
                                                            int64_t nb, double count, float lambda,
                                                            float* __restrict__ d_loss) {
@@ -205,65 +282,67 @@ __global__ void __launch_bounds__(1024) loss_reduce_kernel(const float* __restri
 }
 
 __global__ void __launch_bounds__(kThreads) ssim_backward_kernel(
-    const float* __restrict__ x, TargetRef target, int w, int h, float lambda,
+    const float* __restrict__ x, TargetRef target, int w, int h, int rows, float lambda,
     Window W, const float* __restrict__ maps, const int32_t* __restrict__ gate,
     float* __restrict__ dl) {
     if (gate_closed(gate)) return;
-    __shared__ float sm[3][kE][kE];   // the three maps of one channel
-    __shared__ float hb[3][kE][kT];
-    const int tid = threadIdx.x;
-    const int bx = blockIdx.x, by = blockIdx.y;
-    const int x0 = bx * kT - kR, y0 = by * kT - kR;
-    const int ox = bx * kT + tid % kT, oy = by * kT + tid / kT;
-    const bool inside = ox < w && oy < h;
+    __shared__ float4 s_m[3][64];   // a row of the three maps
+    const Place p(w, h, rows);
     const int64_t plane = (int64_t)w * h;
-    const float* __restrict__ y = target_of(target, 3 * plane);
+    const float* __restrict__ xc = x + p.ch * plane + p.cx;
+    const float* __restrict__ yc = target_of(target, 3 * plane) + p.ch * plane + p.cx;
+    const float* __restrict__ mc = maps + p.ch * plane + p.cx;
+    float* __restrict__ dc = dl + p.ch * plane + p.cx;
+    float4* m = s_m[p.ch];
+    Column c0, c1, c2;
     const float inv = 1.f / (3.f * (float)w * (float)h);
-    for (int ch = 0; ch < 3; ++ch) {
-        for (int i = tid; i < 3 * kE * kE; i += kThreads) {
-            const int f = i / (kE * kE), rc = i % (kE * kE);
-            const int r = rc / kE, c = rc % kE;
-            const int gx = x0 + c, gy = y0 + r;
-            sm[f][r][c] = (gx >= 0 && gx < w && gy >= 0 && gy < h)
-                              ? maps[(f * 3 + ch) * plane + (int64_t)gy * w + gx] : 0.f;
+    // map rows are loaded kAhead rows before they are used, the output row's
+    // pixels one row before
+    constexpr int kAhead = 3;
+    float q[kAhead][3];
+    auto load = [&](int r, float (&v)[3]) {
+        const bool ok = p.in_image && r >= 0 && r < h;
+#pragma unroll
+        for (int f = 0; f < 3; ++f) v[f] = ok ? mc[3 * f * plane + (int64_t)r * w] : 0.f;
+    };
+    float an = 0.f, bn = 0.f;
+    auto pixel = [&](int o) {
+        const bool ok = p.out && o >= p.first && o < p.end;
+        an = ok ? xc[(int64_t)o * w] : 0.f;
+        bn = ok ? yc[(int64_t)o * w] : 0.f;
+    };
+#pragma unroll
+    for (int k = 0; k < kAhead; ++k) load(p.first - kR + k, q[k]);
+    for (int r = p.first - kR; r < p.end + kR; ++r) {
+        float v[3];
+#pragma unroll
+        for (int f = 0; f < 3; ++f) {
+            v[f] = q[0][f];
+#pragma unroll
+            for (int k = 0; k + 1 < kAhead; ++k) q[k][f] = q[k + 1][f];
         }
-        __syncthreads();
-        // horizontal pass: two neighbouring outputs per thread share 10 of
-        // their 12 inputs (kE rows x kT / 2 pairs: one round of the workgroup)
-        for (int i = tid; i < kE * (kT / 2); i += kThreads) {
-            const int r = i / (kT / 2), c = 2 * (i % (kT / 2));
+        load(r + kAhead, q[kAhead - 1]);
+        const int o = r - kR;
+        const float a = an, b = bn;
+        pixel(o + 1);
+        m[p.lane] = make_float4(v[0], v[1], v[2], 0.f);
+        wave_lds_sync();
+        float h0 = 0.f, h1 = 0.f, h2 = 0.f;
 #pragma unroll
-            for (int f = 0; f < 3; ++f) {
-                float v[12];
-#pragma unroll
-                for (int k = 0; k < 12; ++k) v[k] = sm[f][r][c + k];
-                float s0 = 0.f, s1 = 0.f;
-#pragma unroll
-                for (int k = 0; k < 11; ++k) {
-                    s0 = fmaf(W.g[k], v[k], s0);
-                    s1 = fmaf(W.g[k], v[k + 1], s1);
-                }
-                hb[f][r][c] = s0;
-                hb[f][r][c + 1] = s1;
-            }
+        for (int k = 0; k < kTaps; ++k) {
+            const float4 t = m[p.tap0 + k];
+            h0 = fmaf(W.g[k], t.x, h0);
+            h1 = fmaf(W.g[k], t.y, h1);
+            h2 = fmaf(W.g[k], t.z, h2);
         }
-        __syncthreads();
-        const int r = tid / kT, c = tid % kT;
-        float F0 = 0.f, F1 = 0.f, F2 = 0.f;
-#pragma unroll
-        for (int k = 0; k < 11; ++k) {
-            F0 = fmaf(W.g[k], hb[0][r + k][c], F0);
-            F1 = fmaf(W.g[k], hb[1][r + k][c], F1);
-            F2 = fmaf(W.g[k], hb[2][r + k][c], F2);
-        }
-        if (inside) {
-            const int64_t pix = (int64_t)oy * w + ox;
-            const float a = x[ch * plane + pix], b = y[ch * plane + pix];
+        wave_lds_sync();
+        const float F0 = c0.add(W, h0), F1 = c1.add(W, h1), F2 = c2.add(W, h2);
+        if (o < p.first) continue;   // uniform
+        if (p.out) {
             const float d_ssim = F0 + 2.f * a * F1 + b * F2;
             const float sgn = a > b ? 1.f : (a < b ? -1.f : 0.f);
-            dl[ch * plane + pix] = (1.f - lambda) * sgn * inv - lambda * d_ssim * inv;
+            dc[(int64_t)o * w] = (1.f - lambda) * sgn * inv - lambda * d_ssim * inv;
         }
-        __syncthreads();
     }
 }
 
@@ -275,35 +354,34 @@ int64_t loss_partial_floats(int w, int h) { return 2 * loss_layout(w, h).blocks;
 
 hipError_t launch_loss_partials(const float* rgb, TargetRef target, int w, int h, float lambda,
                                 float* partials, float* d_loss, hipStream_t s) {
-    const LossLayout L = loss_layout(w, h);
-    const dim3 grid((unsigned)((w + kT - 1) / kT), (unsigned)((h + kT - 1) / kT));
-    hipLaunchKernelGGL((ssim_forward_kernel<false>), grid, dim3(kThreads), 0, s, rgb, target, w, h,
-                       make_window(), partials, nullptr);
-    hipLaunchKernelGGL(loss_reduce_kernel, dim3(1), dim3(1024), 0, s, partials, L.blocks,
-                       3.0 * (double)w * (double)h, lambda, d_loss);
+    const Strips st = strips(w, h);
+    hipLaunchKernelGGL((ssim_forward_kernel<false>), st.grid, dim3(kThreads), 0, s, rgb, target, w,
+                       h, st.rows, make_window(), partials, nullptr);
+    hipLaunchKernelGGL(loss_reduce_kernel, dim3(1), dim3(1024), 0, s, partials,
+                       (int64_t)st.grid.x * st.grid.y, 3.0 * (double)w * (double)h, lambda, d_loss);
     return hipGetLastError();
 }
 
 hipError_t launch_loss_forward(const float* rgb, TargetRef target, int w, int h, float lambda,
                                char* ws, float* d_loss, hipStream_t s) {
     const LossLayout L = loss_layout(w, h);
-    const dim3 grid((unsigned)((w + kT - 1) / kT), (unsigned)((h + kT - 1) / kT));
+    const Strips st = strips(w, h);
     float* partials = reinterpret_cast<float*>(ws + L.partials);
     float* maps = reinterpret_cast<float*>(ws + L.maps);
-    hipLaunchKernelGGL((ssim_forward_kernel<true>), grid, dim3(kThreads), 0, s, rgb, target, w, h,
-                       make_window(), partials, maps);
-    hipLaunchKernelGGL(loss_reduce_kernel, dim3(1), dim3(1024), 0, s, partials, L.blocks,
-                       3.0 * (double)w * (double)h, lambda, d_loss);
+    hipLaunchKernelGGL((ssim_forward_kernel<true>), st.grid, dim3(kThreads), 0, s, rgb, target, w,
+                       h, st.rows, make_window(), partials, maps);
+    hipLaunchKernelGGL(loss_reduce_kernel, dim3(1), dim3(1024), 0, s, partials,
+                       (int64_t)st.grid.x * st.grid.y, 3.0 * (double)w * (double)h, lambda, d_loss);
     return hipGetLastError();
 }
 
 hipError_t launch_loss_backward(const float* rgb, TargetRef target, int w, int h, float lambda,
                                 char* ws, const int32_t* gate, float* dl, hipStream_t s) {
     const LossLayout L = loss_layout(w, h);
-    const dim3 grid((unsigned)((w + kT - 1) / kT), (unsigned)((h + kT - 1) / kT));
+    const Strips st = strips(w, h);
     const float* maps = reinterpret_cast<const float*>(ws + L.maps);
-    hipLaunchKernelGGL(ssim_backward_kernel, grid, dim3(kThreads), 0, s, rgb, target, w, h, lambda,
-                       make_window(), maps, gate, dl);
+    hipLaunchKernelGGL(ssim_backward_kernel, st.grid, dim3(kThreads), 0, s, rgb, target, w, h,
+                       st.rows, lambda, make_window(), maps, gate, dl);
     return hipGetLastError();
 }
 
