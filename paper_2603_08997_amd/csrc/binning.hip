@@ -43,28 +43,12 @@ constexpr int kScanTile = kScanThreads * kScanItems;
 // associative, so the block and grand totals are the saturated true sums): a
 // batch whose pair count does not fit ends with the all-ones total, which no
 // capacity (< 2^31) reaches, and every offset past the overflow saturates.
-struct VisibleSrc {  // 1 for every visible entry
+struct PairCountSrc {  // super-tiles touched, in depth order
     const uint32_t* tiles;
-    int64_t n;
-    __device__ int64_t count() const { return n; }
-    __device__ uint32_t operator()(int64_t e) const { return tiles[e] ? 1u : 0u; }
-};
-struct CompactSink {  // visible entries -> (depth bits, entry), in entry order
-    const uint32_t* depth;
-    uint32_t* dkey;
-    uint32_t* dval;
-    __device__ void operator()(int64_t e, uint32_t v, uint32_t pos) const {
-        if (v) {
-            dkey[pos] = depth[e];
-            dval[pos] = (uint32_t)e;
-        }
-    }
-};
-struct PairCountSrc {  // super-tiles touched, in depth order (gathered by the depth sort)
-    const uint32_t* counts_sorted;
+    const uint32_t* sorted_entry;
     const uint32_t* n_dev;
     __device__ int64_t count() const { return *n_dev; }
-    __device__ uint32_t operator()(int64_t k) const { return counts_sorted[k]; }
+    __device__ uint32_t operator()(int64_t k) const { return tiles[sorted_entry[k]]; }
 };
 // Pair offset of every Gaussian in depth order, and for every emission window
 // (kEmitWindow consecutive emission units, windows 0 .. n_windows) the
@@ -128,13 +112,10 @@ __device__ __forceinline__ uint32_t block_excl_sat_scan(uint32_t v, uint32_t* sm
     return r;
 }
 
-// Block sums of the scan input. Block 0 also zeroes `clear[0..nclear)` (the
-// counters a binning pass accumulates into), saving a launch.
+// Block sums of the scan input.
 template <class Src>
-__global__ void __launch_bounds__(kScanThreads) scan_reduce_kernel(Src src, uint32_t* sums,
-                                                                   uint32_t* clear, int nclear) {
+__global__ void __launch_bounds__(kScanThreads) scan_reduce_kernel(Src src, uint32_t* sums) {
     __shared__ uint32_t smem[kScanThreads / 64 + 1];
-    if (blockIdx.x == 0 && (int)threadIdx.x < nclear) clear[threadIdx.x] = 0u;
     const int64_t n = src.count();
     // blocks past the count (the grid covers a bound) contribute 0
     if ((int64_t)blockIdx.x * kScanTile >= n) {
@@ -188,23 +169,13 @@ __global__ void __launch_bounds__(kScanThreads) scan_down_kernel(Src src, Sink s
 
 template <class Src, class Sink>
 hipError_t device_scan(Src src, Sink sink, int64_t n_max, uint32_t* sums, uint32_t* total,
-                       hipStream_t s, uint32_t* clear = nullptr, int nclear = 0) {
+                       hipStream_t s) {
     const int nb = (int)((n_max + kScanTile - 1) / kScanTile);
     if (nb == 0) return hipSuccess;
-    hipLaunchKernelGGL(scan_reduce_kernel<Src>, dim3(nb), dim3(kScanThreads), 0, s, src, sums, clear,
-                       nclear);
+    hipLaunchKernelGGL(scan_reduce_kernel<Src>, dim3(nb), dim3(kScanThreads), 0, s, src, sums);
     hipLaunchKernelGGL((scan_down_kernel<Src, Sink>), dim3(nb), dim3(kScanThreads), 0, s, src,
                        sink, sums, total);
     return hipGetLastError();
-}
-
-// Reach limit of a super-tile: the tile test's limit (reach_limit) widened by
-// 1e-3 (1 + lim), more than twice the rounding bound of either evaluation, so
-// that an entry the compositing forward's tile test keeps on any tile of the
-// super-tile is never dropped from the super-tile's list (the minimum over
-// the super-tile's pixels is at most the minimum over one tile's).
-__device__ __forceinline__ float super_limit(float lim) {
-    return lim == INFINITY ? lim : lim + 1e-3f * (1.f + fabsf(lim));
 }
 
 // Pair emission, load balanced over emission units (a few header units per
@@ -360,6 +331,283 @@ __global__ void __launch_bounds__(kEmitThreads) emit_kernel(
     }
 }
 
+// ---- pairs of few super-tiles, placed without emission and sort ----
+//
+// The lists of at most kDirectSupers super-tiles are the result of one counting
+// sort over the depth-ordered entries, each expanded in place. The projection
+// leaves every visible entry's tile rectangle and, from the reach test of its
+// super-tiles, which pairs are kept (the record is in registers there; read
+// again in depth order it costs a cache line per entry). A count kernel gathers
+// that word in depth order and counts the pairs per super-tile and block (with
+// sums over groups of blocks); a place kernel expands the pairs of kPairEntries
+// entries at a time in LDS, ranks them stably by super-tile with ballots, as a
+// radix scatter does, and writes them out in runs. The order inside a
+// super-tile is the entries' depth order.
+//
+// Against emitting pairs to memory by an offset scan and radix-sorting them by
+// super-tile (which more super-tiles still take), the pair arrays are written
+// once instead of twice and read never, and 8 launches become 2. At 3M
+// Gaussians (2.05M entries, 3.8M pairs) 130 -> 112 us, 15 of them new in the
+// projection; at 300k 57 -> 26 us. The count kernel is bound by its gather, a
+// cache line an entry (54 us, 4.8 TB/s of lines at 3M), the place kernel by the
+// latency of its LDS passes.
+
+// Calls f(q, x, y, super-tile) for the candidates of an entry.
+template <class F>
+__device__ __forceinline__ void for_candidates(const ViewDev& V, int S, const uint4& info, F f) {
+    int sx0, sx1, sy0, sy1;
+    super_rect((int)(info.x & 0xffffu), (int)(info.x >> 16), (int)(info.y & 0xffffu),
+               (int)(info.y >> 16), S, &sx0, &sx1, &sy0, &sy1);
+    uint32_t q = 0;
+    for (int y = sy0; y < sy1; ++y)
+        for (int x = sx0; x < sx1; ++x, ++q)
+            if (pair_kept(info, q)) f(x, y, (uint32_t)(V.sup_offset + y * V.sup_x + x));
+}
+
+__device__ __forceinline__ const ViewDev& view_of_entry(const Views* views, uint32_t e,
+                                                        uint32_t n) {
+    return views->v[views->n > 1 ? e / n : 0u];
+}
+
+__global__ void __launch_bounds__(kPairThreads) pair_count_kernel(
+    const Views* __restrict__ views, RasterDev rp, uint32_t n,
+    const uint32_t* __restrict__ sorted_entry, const uint4* __restrict__ info,
+    const uint32_t* __restrict__ counters, int rounds, uint4* __restrict__ sorted_info,
+    uint32_t* __restrict__ hist, uint32_t* __restrict__ groups) {
+    extern __shared__ uint32_t s_cnt[];   // per super-tile
+    const int tid = threadIdx.x;
+    const int ns = views->total_supers, S = rp.super_tile;
+    const int64_t nvis = counters[kVisible];
+    const int64_t tile = (int64_t)kPairEntries * rounds;
+    const int active = (int)((nvis + tile - 1) / tile);
+    if ((int)blockIdx.x >= active) return;   // uniform
+    const int blk = xcd_block(blockIdx.x, active);
+    for (int s = tid; s < ns; s += kPairThreads) s_cnt[s] = 0u;
+    __syncthreads();
+    constexpr int kEach = kPairEntries / kPairThreads;
+    for (int r = 0; r < rounds; ++r) {
+        const int64_t k0 = (int64_t)blk * tile + (int64_t)r * kPairEntries + tid;
+        uint32_t e[kEach];
+        uint4 c[kEach];
+#pragma unroll
+        for (int j = 0; j < kEach; ++j) {
+            const int64_t k = k0 + j * kPairThreads;
+            e[j] = k < nvis ? sorted_entry[k] : 0u;
+        }
+#pragma unroll
+        for (int j = 0; j < kEach; ++j) {
+            c[j] = info[e[j]];
+            c[j].w = e[j];
+        }
+#pragma unroll
+        for (int j = 0; j < kEach; ++j) {
+            const int64_t k = k0 + j * kPairThreads;
+            if (k >= nvis) break;
+            sorted_info[k] = c[j];
+            for_candidates(view_of_entry(views, e[j], n), S, c[j],
+                           [&](int, int, uint32_t s) { atomicAdd(&s_cnt[s], 1u); });
+        }
+    }
+    __syncthreads();
+    for (int s = tid; s < ns; s += kPairThreads) {
+        const uint32_t c = s_cnt[s];
+        hist[(int64_t)blk * ns + s] = c;
+        if (c != 0u) atomicAdd(&groups[(int64_t)(blk / kPairGroup) * ns + s], c);
+    }
+}
+
+// Position, key and entry of every kept pair; block 0 also writes the super-tile
+// ranges and the pair counts. Pairs past the capacity are not written (the
+// overflow is flagged when more pairs are needed than fit).
+constexpr int kChunkEach = 8;                            // pairs of a chunk per thread
+constexpr int kChunk = kPairThreads * kChunkEach;         // pairs expanded at a time
+__global__ void __launch_bounds__(kPairThreads, 4) pair_place_kernel(
+    const Views* __restrict__ views, RasterDev rp, uint32_t n, uint32_t* __restrict__ counters,
+    int rounds, const uint4* __restrict__ sorted_info, const uint32_t* __restrict__ hist,
+    const uint32_t* __restrict__ groups, int64_t capacity, uint32_t* __restrict__ ranges,
+    uint32_t* __restrict__ pkey, uint32_t* __restrict__ pentry) {
+    constexpr int NW = kPairThreads / 64;
+    constexpr int kEach = kPairEntries / kPairThreads;
+    constexpr int kPerWave = kChunk / NW;
+    extern __shared__ uint32_t s_dyn[];   // [NW][ns] counts, [ns] next positions, [ns] starts
+    __shared__ uint32_t lkey[kChunk];
+    __shared__ uint32_t lent[kChunk];
+    __shared__ uint32_t smem[NW + 1];
+    const int tid = threadIdx.x, w = tid / 64, lane = tid % 64;
+    const int ns = views->total_supers, S = rp.super_tile;
+    uint32_t* wcnt = s_dyn;
+    uint32_t* gpos = s_dyn + NW * ns;
+    uint32_t* start = gpos + ns;
+    const int64_t nvis = counters[kVisible];
+    const int64_t tile = (int64_t)kPairEntries * rounds;
+    const int active = (int)((nvis + tile - 1) / tile);
+    if ((int)blockIdx.x >= max(active, 1)) return;   // uniform; block 0 always writes the ranges
+    const int blk = active > 0 ? xcd_block(blockIdx.x, active) : 0;
+    // positions of this block's first pairs: 2^k threads add up a row of
+    // super-tile counts each, the rows' sums in LDS (lkey, lent)
+    {
+        int sp = 64;
+        while (sp < ns && sp < kPairThreads) sp *= 2;
+        const int part = tid / sp, parts = kPairThreads / sp;
+        const int ng = (active + (int)kPairGroup - 1) / (int)kPairGroup, g = blk / (int)kPairGroup;
+        const uint32_t cap = (uint32_t)capacity;
+        uint32_t carry = 0;
+        for (int s0 = 0; s0 < ns; s0 += sp) {
+            const int s = s0 + (tid & (sp - 1));
+            uint32_t tot = 0, before = 0;
+            if (s < ns) {
+                for_rows(groups + s, ns, part, ng, parts, [&](int j, uint32_t c) {
+                    tot += c;
+                    before += j < g ? c : 0u;
+                });
+                for_rows(hist + s, ns, g * (int)kPairGroup + part, blk, parts,
+                         [&](int, uint32_t c) { before += c; });
+            }
+            lkey[tid] = tot;
+            lent[tid] = before;
+            __syncthreads();
+            tot = before = 0;
+            if (tid < sp)
+                for (int k = 0; k < parts; ++k) {
+                    tot += lkey[k * sp + tid];
+                    before += lent[k * sp + tid];
+                }
+            uint32_t all;
+            const uint32_t ex = carry + block_excl_scan<kPairThreads>(tot, smem, &all);
+            carry += all;
+            if (tid < sp && s < ns) {
+                gpos[s] = ex + before;
+                if (blockIdx.x == 0) {
+                    const uint32_t a = min(ex, cap), b = min(ex + tot, cap);
+                    ranges[2 * s] = a < b ? a : 0u;
+                    ranges[2 * s + 1] = a < b ? b : 0u;
+                }
+            }
+        }
+        if (blockIdx.x == 0 && tid == 0) {
+            const uint32_t needed = counters[kPairs];
+            counters[kPairsWritten] = min(needed, cap);
+            counters[kPairsKept] = min(carry, cap);
+            if ((int64_t)needed > capacity) counters[kStatus] |= SGS_STATUS_PAIR_OVERFLOW;
+        }
+    }
+    if (active == 0) return;
+    const int rb = rp.rect_bits, kb = rp.key_bits;
+    const uint32_t kmask = (1u << kb) - 1u;
+    for (int r = 0; r < rounds; ++r) {
+        const int64_t k0 = (int64_t)blk * tile + (int64_t)r * kPairEntries;
+        if (k0 >= nvis) break;   // uniform
+        // thread t expands entries k0 + kEach t ...
+        uint4 c[kEach];
+        uint32_t mine = 0;
+#pragma unroll
+        for (int j = 0; j < kEach; ++j) {
+            const int64_t k = k0 + (int64_t)tid * kEach + j;
+            c[j] = k < nvis ? sorted_info[k] : make_uint4(0u, 0u, 0u, 0u);
+            mine += k < nvis ? kept_pairs(c[j], S) : 0u;
+        }
+        uint32_t total;
+        const uint32_t first = block_excl_scan<kPairThreads>(mine, smem, &total);
+        for (uint32_t c0 = 0; c0 < total; c0 += (uint32_t)kChunk) {
+            uint32_t at = first - c0;   // wraps below the chunk, which no check passes
+#pragma unroll
+            for (int j = 0; j < kEach; ++j) {
+                if (k0 + (int64_t)tid * kEach + j >= nvis) break;
+                const int x0 = (int)(c[j].x & 0xffffu), x1 = (int)(c[j].x >> 16);
+                const int y0 = (int)(c[j].y & 0xffffu), y1 = (int)(c[j].y >> 16);
+                for_candidates(view_of_entry(views, c[j].w, n), S, c[j],
+                               [&](int x, int y, uint32_t s) {
+                    if (at < (uint32_t)kChunk) {
+                        // the tile rectangle inside the super-tile, relative to its first tile
+                        const int ox = x * S, oy = y * S;
+                        const uint32_t lx0 = (uint32_t)(max(x0, ox) - ox);
+                        const uint32_t lx1 = (uint32_t)(min(x1, ox + S) - 1 - ox);
+                        const uint32_t ly0 = (uint32_t)(max(y0, oy) - oy);
+                        const uint32_t ly1 = (uint32_t)(min(y1, oy + S) - 1 - oy);
+                        const uint32_t rect =
+                            lx0 | (lx1 << rb) | (ly0 << (2 * rb)) | (ly1 << (3 * rb));
+                        lkey[at] = s | (rect << kb);
+                        lent[at] = c[j].w;
+                    }
+                    ++at;
+                });
+            }
+            for (int i = tid; i < NW * ns; i += kPairThreads) wcnt[i] = 0u;
+            __syncthreads();
+            // stable ranking, wave by wave: lanes of one super-tile found with
+            // ballots, the wave's counters carry on across its rounds
+            const int have = (int)min(total - c0, (uint32_t)kChunk);
+            uint32_t key[kChunkEach], ent[kChunkEach], rank[kChunkEach];
+            uint32_t* cnt = wcnt + w * ns;
+#pragma unroll
+            for (int it = 0; it < kChunkEach; ++it) {
+                const int li = w * kPerWave + it * 64 + lane;
+                const bool valid = li < have;
+                key[it] = valid ? lkey[li] : 0u;
+                ent[it] = valid ? lent[li] : 0u;
+                rank[it] = 0u;
+                if (w * kPerWave + it * 64 >= have) continue;   // uniform over the wave
+                const uint32_t s = key[it] & kmask;
+                uint64_t peers = ballot(valid);
+                for (int b = 0; b < kb; ++b) {
+                    const bool bit = (s >> b) & 1u;
+                    const uint64_t m = ballot(bit);
+                    peers &= bit ? m : ~m;
+                }
+                const uint32_t before = (uint32_t)popc64(peers & lanemask_lt());
+                if (valid) rank[it] = cnt[s] + before;
+                // every lane has read the counters before the leaders advance them
+                __builtin_amdgcn_wave_barrier();
+                if (valid && before == 0) cnt[s] += (uint32_t)popc64(peers);
+                __builtin_amdgcn_wave_barrier();
+            }
+            __syncthreads();
+            uint32_t carry = 0;
+            for (int s0 = 0; s0 < ns; s0 += kPairThreads) {
+                const int s = s0 + tid;
+                uint32_t sum = 0;
+                if (s < ns) {
+#pragma unroll
+                    for (int k = 0; k < NW; ++k) sum += wcnt[k * ns + s];
+                }
+                uint32_t tot;
+                uint32_t run = carry + block_excl_scan<kPairThreads>(sum, smem, &tot);
+                carry += tot;
+                if (s < ns) {
+                    // start[s] turns a local position into the global one
+                    start[s] = gpos[s] - run;
+                    gpos[s] += sum;
+#pragma unroll
+                    for (int k = 0; k < NW; ++k) {
+                        const uint32_t x = wcnt[k * ns + s];
+                        wcnt[k * ns + s] = run;
+                        run += x;
+                    }
+                }
+            }
+            __syncthreads();
+#pragma unroll
+            for (int it = 0; it < kChunkEach; ++it) {
+                const int li = w * kPerWave + it * 64 + lane;
+                if (li >= have) break;
+                const uint32_t pos = cnt[key[it] & kmask] + rank[it];
+                lkey[pos] = key[it];
+                lent[pos] = ent[it];
+            }
+            __syncthreads();
+            for (int li = tid; li < have; li += kPairThreads) {
+                const uint32_t k = lkey[li];
+                const uint32_t out = start[k & kmask] + (uint32_t)li;
+                if (out < (uint32_t)capacity) {
+                    pkey[out] = k;
+                    pentry[out] = lent[li];
+                }
+            }
+            __syncthreads();
+        }
+    }
+}
+
 // [start, end) of every super-tile by binary search in the sorted keys
 // (the super-tile index is the low key_bits bits; empty super-tiles: [0, 0)).
 __global__ void __launch_bounds__(256) ranges_kernel(const uint32_t* __restrict__ pkey,
@@ -417,10 +665,8 @@ __global__ void __launch_bounds__(kOrderThreads) order_tiles_kernel(
 // The call's view table into the workspace, word by word: the views passed
 // by value or, with a camera table, its entry *d_view (clamped into range) as
 // view 0 of a one-view batch (table entries are stored for that position).
-__global__ void __launch_bounds__(64) store_views_kernel(Views v, const ViewDev* __restrict__ table,
-                                                         int n_table,
-                                                         const int32_t* __restrict__ d_view,
-                                                         Views* __restrict__ dst) {
+__device__ __forceinline__ void store_views(const Views& v, const ViewDev* table, int n_table,
+                                            const int32_t* d_view, Views* dst) {
     static_assert(sizeof(Views) % 4 == 0 && sizeof(ViewDev) % 4 == 0, "word copy");
     constexpr int kWords = (int)(sizeof(Views) / 4), kViewWords = (int)(sizeof(ViewDev) / 4);
     const uint32_t* src = reinterpret_cast<const uint32_t*>(&v);
@@ -430,8 +676,29 @@ __global__ void __launch_bounds__(64) store_views_kernel(Views v, const ViewDev*
         sel = reinterpret_cast<const uint32_t*>(table + i);
     }
     uint32_t* out = reinterpret_cast<uint32_t*>(dst);
-    for (int w = threadIdx.x; w < kWords; w += 64)
+    for (int w = threadIdx.x; w < kWords; w += blockDim.x)
         out[w] = (sel != nullptr && w < kViewWords) ? sel[w] : src[w];
+}
+
+__global__ void __launch_bounds__(64) store_views_kernel(Views v, Views* __restrict__ dst) {
+    store_views(v, nullptr, 0, nullptr, dst);
+}
+
+// The first launch of a call that bins: block 0 stores the views and clears the
+// counters binning and the compositing forward accumulate into (the status word
+// stays), all blocks clear the sums binning accumulates.
+constexpr int kBeginThreads = 256;
+__global__ void __launch_bounds__(kBeginThreads) begin_bin_kernel(
+    Views v, const ViewDev* __restrict__ table, int n_table, const int32_t* __restrict__ d_view,
+    Views* __restrict__ dst, uint32_t* __restrict__ counters, uint4* __restrict__ clear,
+    int64_t n4) {
+    if (blockIdx.x == 0) {
+        store_views(v, table, n_table, d_view, dst);
+        if (threadIdx.x >= kVisible && threadIdx.x <= kRedo) counters[threadIdx.x] = 0u;
+    }
+    for (int64_t i = (int64_t)blockIdx.x * kBeginThreads + threadIdx.x; i < n4;
+         i += (int64_t)gridDim.x * kBeginThreads)
+        clear[i] = make_uint4(0u, 0u, 0u, 0u);
 }
 
 __global__ void fill_u32_kernel(uint32_t* p, int64_t n, uint32_t v) {
@@ -870,10 +1137,19 @@ __global__ void __launch_bounds__(256) tile_ranges_kernel(
 
 }  // namespace
 
-hipError_t launch_store_views(const Views& views, const ViewDev* table, int n_table,
-                              const int32_t* d_view, Views* dst, hipStream_t s) {
-    hipLaunchKernelGGL(store_views_kernel, dim3(1), dim3(64), 0, s, views, table, n_table, d_view,
-                       dst);
+hipError_t launch_store_views(const Views& views, Views* dst, hipStream_t s) {
+    hipLaunchKernelGGL(store_views_kernel, dim3(1), dim3(64), 0, s, views, dst);
+    return hipGetLastError();
+}
+
+hipError_t launch_begin_bin(const Views& views, const ViewDev* table, int n_table,
+                            const int32_t* d_view, const Layout& L, char* ws, hipStream_t s) {
+    const int64_t n4 = (int64_t)(L.clear_words / 4);   // regions are 256-byte aligned
+    const int64_t nb = std::min<int64_t>(std::max<int64_t>(1, n4 / (2 * kBeginThreads)), 1024);
+    hipLaunchKernelGGL(begin_bin_kernel, dim3((unsigned)nb), dim3(kBeginThreads), 0, s, views, table,
+                       n_table, d_view, reinterpret_cast<Views*>(ws + L.views),
+                       reinterpret_cast<uint32_t*>(ws + L.counters),
+                       reinterpret_cast<uint4*>(ws + L.clear_begin), n4);
     return hipGetLastError();
 }
 
@@ -969,60 +1245,63 @@ hipError_t launch_bin(const RasterDev& rp, int64_t n, const Layout& L, char* ws,
                          reinterpret_cast<uint32_t*>(ws + L.dkey[1])};
     uint32_t* dval[2] = {reinterpret_cast<uint32_t*>(ws + L.dval[0]),
                          reinterpret_cast<uint32_t*>(ws + L.dval[1])};
-    uint32_t* offsets = reinterpret_cast<uint32_t*>(ws + L.offsets);
-    uint32_t* window_first = reinterpret_cast<uint32_t*>(ws + L.window_first);
-    uint32_t* sums = reinterpret_cast<uint32_t*>(ws + L.scan_sums);
     uint32_t* hist = reinterpret_cast<uint32_t*>(ws + L.sort_hist);
-    uint32_t* totals = reinterpret_cast<uint32_t*>(ws + L.sort_totals);
+    uint32_t* ranges = reinterpret_cast<uint32_t*>(ws + L.sup_ranges);
     uint32_t* pkey[2] = {reinterpret_cast<uint32_t*>(ws + L.pair_key[0]),
                          reinterpret_cast<uint32_t*>(ws + L.pair_key[1])};
     uint32_t* pentry[2] = {reinterpret_cast<uint32_t*>(ws + L.pair_entry[0]),
                            reinterpret_cast<uint32_t*>(ws + L.pair_entry[1])};
-    uint32_t* ranges = reinterpret_cast<uint32_t*>(ws + L.sup_ranges);
     hipError_t err;
-    // counters this stage and the compositing forward accumulate into
-    constexpr int kClear = kRedo + 1 - kVisible;
-
-    // visible entries -> (depth, entry), entry order; count -> counters[kVisible]
-    // (the first scan kernel also clears the counters)
-    if (E == 0 && (err = fill_u32(counters + kVisible, kClear, 0u, s)) != hipSuccess) return err;
     if (E > 0) {
-        err = device_scan(VisibleSrc{tiles, E},
-                          CompactSink{reinterpret_cast<const uint32_t*>(ws + L.depth), dkey[0],
-                                      dval[0]},
-                          E, sums, counters + kVisible, s, counters + kVisible, kClear);
+        // visible entries by depth, ties in entry order; their number and the
+        // number of their pairs -> counters[kVisible], [kPairs]
+        err = sort_entries(reinterpret_cast<const uint32_t*>(ws + L.depth), tiles, E, dkey, dval,
+                           hist, reinterpret_cast<uint32_t*>(ws + L.sort_groups),
+                           reinterpret_cast<uint64_t*>(ws + L.sort_weights), counters + kVisible,
+                           counters + kPairs, s);
         if (err != hipSuccess) return err;
-        // stable sort by depth (ties keep ascending entry order); the last
-        // pass also gathers each entry's super-tile count into `offsets`, in
-        // depth order, for the scan below to read linearly and overwrite in place
-        int res = 0;
-        err = radix_sort(dkey, dval, counters + kVisible, E, 32, hist, totals, s, &res, nullptr,
-                         tiles, offsets);
-        if (err != hipSuccess) return err;
+    }
+    const uint32_t* sorted = dval[1];
+    if (E > 0 && L.direct) {
+        const uint4* info = reinterpret_cast<const uint4*>(ws + L.pair_info);
+        uint4* sinfo = reinterpret_cast<uint4*>(ws + L.pair_sorted);
+        uint32_t* phist = reinterpret_cast<uint32_t*>(ws + L.pair_hist);
+        uint32_t* pgroups = reinterpret_cast<uint32_t*>(ws + L.pair_groups);
+        const dim3 grid((unsigned)L.pair_blocks);
+        const size_t ns = (size_t)L.total_supers;
+        hipLaunchKernelGGL(pair_count_kernel, grid, dim3(kPairThreads), ns * sizeof(uint32_t), s,
+                           views, rp, (uint32_t)n, sorted, info, counters, L.pair_rounds, sinfo,
+                           phist, pgroups);
+        hipLaunchKernelGGL(pair_place_kernel, grid, dim3(kPairThreads),
+                           (kPairThreads / 64 + 2) * ns * sizeof(uint32_t), s, views, rp,
+                           (uint32_t)n, counters, L.pair_rounds, sinfo, phist, pgroups, L.capacity,
+                           ranges, pkey[0], pentry[0]);
+        if ((err = hipGetLastError()) != hipSuccess) return err;
+    } else if (E > 0) {
+        uint32_t* offsets = reinterpret_cast<uint32_t*>(ws + L.offsets);
+        uint32_t* window_first = reinterpret_cast<uint32_t*>(ws + L.window_first);
+        uint32_t* sums = reinterpret_cast<uint32_t*>(ws + L.scan_sums);
         // pair offsets in depth order; total -> counters[kPairs]
         const uint32_t n_windows = (uint32_t)emit_windows(E, L.capacity);
-        err = device_scan(PairCountSrc{offsets, counters + kVisible},
+        err = device_scan(PairCountSrc{tiles, sorted, counters + kVisible},
                           OffsetSink{offsets, window_first, n_windows}, E, sums,
                           counters + kPairs, s);
         if (err != hipSuccess) return err;
         // at least one workgroup: block 0 also records the written pair count
         const dim3 egrid((unsigned)std::max<int64_t>(1, emit_windows(E, L.capacity)));
-        hipLaunchKernelGGL(emit_kernel, egrid, dim3(kEmitThreads), 0, s, dval[res], offsets,
+        hipLaunchKernelGGL(emit_kernel, egrid, dim3(kEmitThreads), 0, s, sorted, offsets,
                            window_first, rec, counters, n, views, rp, L.capacity, pkey[0],
                            pentry[0]);
         if ((err = hipGetLastError()) != hipSuccess) return err;
         // stable sort of the pairs by super-tile; the first pass drops culled
-        // pairs and counts the rest into counters[kPairsKept]; a one-pass sort
-        // (at most 255 super-tiles) also writes the super-tile ranges
-        int kres = 0;
-        const bool one_pass = L.key_passes == 1 && L.total_supers > 0;
-        err = radix_sort(pkey, pentry, counters + kPairsWritten, L.capacity, L.key_bits, hist,
-                         totals, s, &kres, counters + kPairsKept, nullptr, nullptr,
-                         one_pass ? ranges : nullptr, one_pass ? (int)L.total_supers : 0);
+        // pairs and counts the rest into counters[kPairsKept]
+        err = sort_pairs(pkey, pentry, counters + kPairsWritten, L.capacity, L.key_bits, hist,
+                         reinterpret_cast<uint32_t*>(ws + L.pair_sort_groups),
+                         counters + kPairsKept, s);
         if (err != hipSuccess) return err;
     }
     const dim3 rgrid((unsigned)((L.total_supers + 255) / 256));
-    if (L.total_supers > 0 && (E == 0 || L.key_passes != 1))
+    if (L.total_supers > 0 && (E == 0 || !L.direct))
         hipLaunchKernelGGL(ranges_kernel, rgrid, dim3(256), 0, s, pkey[L.key_result], counters,
                            L.total_supers, L.key_bits, ranges);
     if ((err = hipGetLastError()) != hipSuccess) return err;

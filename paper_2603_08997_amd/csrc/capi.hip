@@ -216,7 +216,14 @@ void make_layout(const Views& views, const RasterDev& rp, int64_t n, int64_t cap
     const int64_t tt = (int64_t)rp.super_tile * rp.super_tile;
     // the scans run over the entries and over the (segment, tile) counts
     L->scan_blocks = (std::max(L->entries, L->seg_slots * tt) + 2047) / 2048;
-    L->sort_blocks = radix_blocks(std::max(L->entries, capacity));
+    // few super-tiles: pairs placed directly, in at most 2048 blocks
+    L->direct = L->total_supers <= kDirectSupers;
+    L->pair_rounds = 1;
+    while (L->entries > int64_t(2048) * kPairEntries * L->pair_rounds) L->pair_rounds *= 2;
+    const int64_t pair_tile = (int64_t)kPairEntries * L->pair_rounds;
+    L->pair_blocks = std::max<int64_t>(1, (L->entries + pair_tile - 1) / pair_tile);
+    const int64_t sort_blocks =
+        std::max(radix_blocks(L->entries), L->direct ? 0 : radix_blocks(capacity));
     // super-tile index bits: 2^bits > total_supers, so that no index has all
     // bits set (at least one: the first sort pass drops culled pairs)
     int bits = 1;
@@ -225,8 +232,7 @@ void make_layout(const Views& views, const RasterDev& rp, int64_t n, int64_t cap
     while ((1 << rbits) < rp.super_tile) ++rbits;
     L->key_bits = bits;
     L->rect_bits = rbits;
-    L->key_passes = radix_passes(bits);
-    L->key_result = L->key_passes & 1;
+    L->key_result = L->direct ? 0 : radix_passes(bits) & 1;
     const int64_t E = L->entries;
     size_t off = 0;
     auto take = [&](size_t bytes) {
@@ -244,15 +250,31 @@ void make_layout(const Views& views, const RasterDev& rp, int64_t n, int64_t cap
     L->dkey[1] = take(sizeof(uint32_t) * (size_t)E);
     L->dval[0] = take(sizeof(uint32_t) * (size_t)E);
     L->dval[1] = take(sizeof(uint32_t) * (size_t)E);
-    L->offsets = take(sizeof(uint32_t) * (size_t)E);
-    L->window_first = take(sizeof(uint32_t) * (size_t)(emit_windows(E, capacity) + 1));
+    // the direct path's region or the emission's and the pair sort's
+    const size_t DE = L->direct ? (size_t)E : 0, SE = L->direct ? 0 : (size_t)E;
+    const size_t SC = L->direct ? 0 : (size_t)capacity;
+    L->pair_info = take(sizeof(uint32_t) * 4 * DE);
+    L->pair_sorted = take(sizeof(uint32_t) * 4 * DE);
+    L->pair_hist = take(DE ? sizeof(uint32_t) * (size_t)(L->pair_blocks * L->total_supers) : 0);
+    L->offsets = take(sizeof(uint32_t) * SE);
+    L->window_first =
+        take(SE ? sizeof(uint32_t) * (size_t)(emit_windows(E, capacity) + 1) : 0);
     L->scan_sums = take(sizeof(uint32_t) * (size_t)(L->scan_blocks + 1));
     L->pair_key[0] = take(sizeof(uint32_t) * (size_t)capacity);
-    L->pair_key[1] = take(sizeof(uint32_t) * (size_t)capacity);
+    L->pair_key[1] = take(sizeof(uint32_t) * SC);
     L->pair_entry[0] = take(sizeof(uint32_t) * (size_t)capacity);
-    L->pair_entry[1] = take(sizeof(uint32_t) * (size_t)capacity);
-    L->sort_hist = take(sizeof(uint32_t) * 256 * (size_t)L->sort_blocks);
-    L->sort_totals = take(sizeof(uint32_t) * 256);
+    L->pair_entry[1] = take(sizeof(uint32_t) * SC);
+    L->sort_hist = take(sizeof(uint32_t) * 256 * (size_t)sort_blocks);
+    L->sort_weights = take(sizeof(uint64_t) * (size_t)sort_blocks);
+    L->clear_begin = off;
+    L->sort_groups = take(sizeof(uint32_t) * (size_t)radix_group_words(E, kDepthPasses));
+    L->pair_groups =
+        take(DE ? sizeof(uint32_t) *
+                      (size_t)((L->pair_blocks + kPairGroup - 1) / kPairGroup * L->total_supers)
+                : 0);
+    L->pair_sort_groups =
+        take(SC ? sizeof(uint32_t) * (size_t)radix_group_words(capacity, radix_passes(bits)) : 0);
+    L->clear_words = (off - L->clear_begin) / sizeof(uint32_t);
     L->sup_ranges = take(sizeof(uint32_t) * 2 * (size_t)L->total_supers);
     L->seg_first = take(sizeof(uint32_t) * (size_t)(L->total_supers + 1));
     L->seg_cnt = take(sizeof(uint32_t) * (size_t)(L->seg_slots * tt));
@@ -374,17 +396,20 @@ sgs_status sgs_get_workspace_layout(const sgs_raster_params* rp, int64_t n, cons
 namespace {
 
 // Validated arguments of a render-path call and the call's view table stored
-// into its workspace (the first launch of every call).
+// into its workspace (the first launch of every call); bins: the call bins, and
+// what binning accumulates into is cleared too.
 sgs_status begin_call(const sgs_raster_params* rp, int64_t n, const sgs_camera* cams,
                       int32_t n_views, void* workspace, size_t workspace_bytes,
-                      int64_t pair_capacity, hipStream_t s, Prepared* P) {
+                      int64_t pair_capacity, hipStream_t s, Prepared* P, bool bins = false) {
     sgs_status st = prepare(rp, n, cams, n_views, pair_capacity, P);
     if (st != SGS_OK) return st;
     if ((st = check_ws(*P, workspace, workspace_bytes)) != SGS_OK) return st;
     char* ws = static_cast<char*>(workspace);
-    SGS_HIP(sgs::launch_store_views(P->views, nullptr, 0, nullptr,
-                                    reinterpret_cast<sgs::Views*>(ws + P->L.views), s),
-            "store views");
+    if (bins)
+        SGS_HIP(sgs::launch_begin_bin(P->views, nullptr, 0, nullptr, P->L, ws, s), "store views");
+    else
+        SGS_HIP(sgs::launch_store_views(P->views, reinterpret_cast<sgs::Views*>(ws + P->L.views), s),
+                "store views");
     return SGS_OK;
 }
 
@@ -430,7 +455,8 @@ sgs_status sgs_bin(const sgs_camera* cams, int32_t n_views, int64_t n, const sgs
                    void* workspace, size_t workspace_bytes, int64_t pair_capacity, void* stream) {
     hipStream_t s = static_cast<hipStream_t>(stream);
     Prepared P;
-    sgs_status st = begin_call(rp, n, cams, n_views, workspace, workspace_bytes, pair_capacity, s, &P);
+    sgs_status st = begin_call(rp, n, cams, n_views, workspace, workspace_bytes, pair_capacity, s,
+                               &P, true);
     if (st != SGS_OK) return st;
     SGS_HIP(sgs::launch_bin(P.rd, n, P.L, static_cast<char*>(workspace), s), "bin");
     return SGS_OK;
@@ -458,7 +484,7 @@ sgs_status sgs_render_forward(const sgs_gaussians* g, const sgs_camera* cams, in
     hipStream_t s = static_cast<hipStream_t>(stream);
     Prepared P;
     if ((st = begin_call(rp, g->n, cams, n_views, workspace, workspace_bytes, pair_capacity, s,
-                         &P)) != SGS_OK)
+                         &P, true)) != SGS_OK)
         return st;
     char* ws = static_cast<char*>(workspace);
     SGS_HIP(sgs::launch_project(g->data, g->n, g->stride, g->sh_degree, P.rd, P.L, ws, s),
@@ -838,8 +864,8 @@ sgs_status sgs_train_iteration(const sgs_gaussians* g, const sgs_camera* cams,
     char* ws = static_cast<char*>(workspace);
     char* lws = static_cast<char*>(loss_workspace);
     const sgs::TargetRef tgt{targets, d_view, n_cams};
-    SGS_HIP(sgs::launch_store_views(P.views, static_cast<const sgs::ViewDev*>(d_table), n_cams,
-                                    d_view, reinterpret_cast<sgs::Views*>(ws + P.L.views), s),
+    SGS_HIP(sgs::launch_begin_bin(P.views, static_cast<const sgs::ViewDev*>(d_table), n_cams,
+                                  d_view, P.L, ws, s),
             "select view");
     SGS_HIP(sgs::launch_project(g->data, g->n, g->stride, g->sh_degree, P.rd, P.L, ws, s),
             "project");

@@ -156,7 +156,8 @@ __device__ __forceinline__ void project_entry(const float mu[3], const float ls[
                                               const ViewDev& V, const RasterDev& rp, int64_t e,
                                               float4* __restrict__ rec,
                                               uint32_t* __restrict__ tiles,
-                                              uint32_t* __restrict__ dkey) {
+                                              uint32_t* __restrict__ dkey,
+                                              uint4* __restrict__ info) {
     uint32_t ntiles = 0;
     float depth = 0.f;
     float4 r0 = make_float4(0.f, 0.f, 0.f, 0.f), r1 = r0, r2 = r0;
@@ -209,6 +210,7 @@ __device__ __forceinline__ void project_entry(const float mu[3], const float ls[
                 r2 = make_float4(fmaxf(col[0], 0.f), fmaxf(col[1], 0.f), fmaxf(col[2], 0.f),
                                  __uint_as_float(mask));
                 depth = G.tz;
+                if (info != nullptr) info[e] = pair_info(r0, r1, x0, x1, y0, y1, V, rp);
             }
         }
     }
@@ -225,7 +227,8 @@ __global__ void __launch_bounds__(256) project_kernel(const float* __restrict__ 
                                                       int64_t stride, const Views* __restrict__ views,
                                                       RasterDev rp, float4* __restrict__ rec,
                                                       uint32_t* __restrict__ tiles,
-                                                      uint32_t* __restrict__ dkey) {
+                                                      uint32_t* __restrict__ dkey,
+                                                      uint4* __restrict__ info) {
     const int64_t entries = n * views->n;
     const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= entries) return;
@@ -238,7 +241,7 @@ __global__ void __launch_bounds__(256) project_kernel(const float* __restrict__ 
     for (int k = 0; k < 11; ++k) p[k] = P.load(k, off);
     project_entry<sh_degree>(
         p, p + 3, p + 6, p[10], [&](int j) { return P.load(11 + j, off); }, views->v[vi], rp, e,
-        rec, tiles, dkey);
+        rec, tiles, dkey, info);
 }
 
 // One thread per Gaussian, over the views of the batch: its parameters are
@@ -249,7 +252,7 @@ template <int sh_degree>
 __global__ void __launch_bounds__(256) project_views_kernel(
     const float* __restrict__ planes, int64_t n, int64_t stride, const Views* __restrict__ views,
     RasterDev rp, float4* __restrict__ rec, uint32_t* __restrict__ tiles,
-    uint32_t* __restrict__ dkey) {
+    uint32_t* __restrict__ dkey, uint4* __restrict__ info) {
     constexpr int NP = 11 + 3 * (sh_degree + 1) * (sh_degree + 1);
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
@@ -261,7 +264,7 @@ __global__ void __launch_bounds__(256) project_views_kernel(
     for (int vi = 0; vi < views->n; ++vi)
         project_entry<sh_degree>(
             p, p + 3, p + 6, p[10], [&](int j) { return p[11 + j]; }, views->v[vi], rp,
-            (int64_t)vi * n + i, rec, tiles, dkey);
+            (int64_t)vi * n + i, rec, tiles, dkey, info);
 }
 
 __global__ void __launch_bounds__(256) load_records_kernel(
@@ -270,7 +273,7 @@ __global__ void __launch_bounds__(256) load_records_kernel(
     const float* __restrict__ conic, const float* __restrict__ opacity,
     const float* __restrict__ rgb, const Views* __restrict__ views, RasterDev rp,
     float4* __restrict__ rec,
-    uint32_t* __restrict__ tiles, uint32_t* __restrict__ dkey) {
+    uint32_t* __restrict__ tiles, uint32_t* __restrict__ dkey, uint4* __restrict__ info) {
     const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= entries) return;
     int64_t i;
@@ -288,6 +291,7 @@ __global__ void __launch_bounds__(256) load_records_kernel(
             r0 = make_float4(u[e], v[e], conic[3 * e], conic[3 * e + 1]);
             r1 = make_float4(conic[3 * e + 2], opacity[e], (float)rx, (float)ry);
             r2 = make_float4(rgb[3 * e], rgb[3 * e + 1], rgb[3 * e + 2], __uint_as_float(7u));
+            if (info != nullptr) info[e] = pair_info(r0, r1, x0, x1, y0, y1, V, rp);
         }
     }
     rec[3 * e + 0] = r0;
@@ -636,13 +640,14 @@ hipError_t launch_project(const float* planes, int64_t n, int64_t stride, int sh
     float4* rec = reinterpret_cast<float4*>(ws + L.records);
     uint32_t* tiles = reinterpret_cast<uint32_t*>(ws + L.tiles);
     uint32_t* dkey = reinterpret_cast<uint32_t*>(ws + L.depth);
+    uint4* info = L.direct ? reinterpret_cast<uint4*>(ws + L.pair_info) : nullptr;
 #define SGS_PK(D)                                                                            \
     if (loop)                                                                                \
         hipLaunchKernelGGL(project_views_kernel<D>, dim3((unsigned)nb), dim3(nt), 0, s, planes, \
-                           n, stride, views, rp, rec, tiles, dkey);                          \
+                           n, stride, views, rp, rec, tiles, dkey, info);                        \
     else                                                                                     \
         hipLaunchKernelGGL(project_kernel<D>, dim3((unsigned)nb), dim3(nt), 0, s, planes, n, \
-                           stride, views, rp, rec, tiles, dkey)
+                           stride, views, rp, rec, tiles, dkey, info)
     switch (sh_degree) {
         case 0: SGS_PK(0); break;
         case 1: SGS_PK(1); break;
@@ -666,7 +671,8 @@ hipError_t launch_load_records(const float* u, const float* v, const float* dept
                        reinterpret_cast<const Views*>(ws + L.views), rp,
                        reinterpret_cast<float4*>(ws + L.records),
                        reinterpret_cast<uint32_t*>(ws + L.tiles),
-                       reinterpret_cast<uint32_t*>(ws + L.depth));
+                       reinterpret_cast<uint32_t*>(ws + L.depth),
+                       L.direct ? reinterpret_cast<uint4*>(ws + L.pair_info) : nullptr);
     return hipGetLastError();
 }
 

@@ -141,6 +141,25 @@ struct PlaneBuf {
     }
 };
 
+// Calls f(row, count) for the rows first, first + step, ... below end of a
+// column of counts: batches of 16 loads in flight, past the end masked off (a
+// loop with a remainder would wait for the remainder's loads one by one).
+template <class F>
+__device__ __forceinline__ void for_rows(const uint32_t* column, int64_t row_words, int first,
+                                         int end, int step, F f) {
+    constexpr int kBatch = 16;
+    for (int j0 = first; j0 < end; j0 += kBatch * step) {
+        uint32_t c[kBatch];
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            const int j = j0 + u * step;
+            c[u] = j < end ? column[j * row_words] : 0u;
+        }
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) f(j0 + u * step, c[u]);
+    }
+}
+
 // Logical block index that gives each XCD a contiguous range of blocks. The
 // gfx950 dispatcher hands workgroups to its 8 XCDs round-robin (workgroup w to
 // XCD w % 8); with this mapping, blocks that write neighbouring addresses (the
@@ -154,33 +173,31 @@ __device__ __forceinline__ int xcd_block(int wg, int nblocks) {
     return x * q + min(x, r) + k;
 }
 
-__device__ __forceinline__ int floordiv(int a, int b) {
-    const int q = a / b;
-    return (a % b != 0 && ((a < 0) != (b < 0))) ? q - 1 : q;
-}
-
 // Tile rectangle [x0, x1) x [y0, y1) of the box |x - u| <= rx, |y - v| <= ry.
 // With rx, ry and the tile size integers, floor((u - rx)/tw) =
 // floor((floor(u) - rx)/tw), so the rectangle is exact in integer arithmetic
-// on floor(u) (|u| < 2^24).
+// on floor(u) (|u| < 2^24); tile sizes are powers of two (an arithmetic shift).
 __device__ __forceinline__ void tile_rect(float u, float v, int rx, int ry, int tw, int th,
                                           int tx_n, int ty_n, int* x0, int* x1, int* y0,
                                           int* y1) {
     const int fu = (int)floorf(u), fv = (int)floorf(v);
-    *x0 = min(max(floordiv(fu - rx, tw), 0), tx_n);
-    *x1 = min(max(floordiv(fu + rx, tw) + 1, 0), tx_n);
-    *y0 = min(max(floordiv(fv - ry, th), 0), ty_n);
-    *y1 = min(max(floordiv(fv + ry, th) + 1, 0), ty_n);
+    const int lw = __builtin_ctz((unsigned)tw), lh = __builtin_ctz((unsigned)th);
+    *x0 = min(max((fu - rx) >> lw, 0), tx_n);
+    *x1 = min(max(((fu + rx) >> lw) + 1, 0), tx_n);
+    *y0 = min(max((fv - ry) >> lh, 0), ty_n);
+    *y1 = min(max(((fv + ry) >> lh) + 1, 0), ty_n);
 }
 
 // Super-tiles [sx0, sx1) x [sy0, sy1) (edge S tiles) holding the non-empty
 // tile rectangle [x0, x1) x [y0, y1), and their number.
 __device__ __forceinline__ void super_rect(int x0, int x1, int y0, int y1, int S, int* sx0,
                                            int* sx1, int* sy0, int* sy1) {
-    *sx0 = x0 / S;
-    *sx1 = (x1 - 1) / S + 1;
-    *sy0 = y0 / S;
-    *sy1 = (y1 - 1) / S + 1;
+    // x / S by the rounded-up 16-bit reciprocal: exact for x < 65536 / S
+    const uint32_t inv = (65536u + (uint32_t)S - 1u) / (uint32_t)S;
+    *sx0 = (int)(((uint32_t)x0 * inv) >> 16);
+    *sx1 = (int)(((uint32_t)(x1 - 1) * inv) >> 16) + 1;
+    *sy0 = (int)(((uint32_t)y0 * inv) >> 16);
+    *sy1 = (int)(((uint32_t)(y1 - 1) * inv) >> 16) + 1;
 }
 __device__ __forceinline__ uint32_t super_count(int x0, int x1, int y0, int y1, int S) {
     int a, b, c, d;
@@ -237,6 +254,46 @@ __device__ __forceinline__ bool rect_reachable(float u, float v, float a, float 
         at(fminf(fmaxf(-b * ey * __builtin_amdgcn_rcpf(a), x0), x1), ey);
     }
     return best <= lim;
+}
+
+// Reach limit of a super-tile: the tile test's limit (reach_limit) widened by
+// 1e-3 (1 + lim), more than twice the rounding bound of either evaluation, so
+// that an entry the compositing forward's tile test keeps on any tile of the
+// super-tile is never dropped from the super-tile's list (the minimum over
+// the super-tile's pixels is at most the minimum over one tile's).
+__device__ __forceinline__ float super_limit(float lim) {
+    return lim == INFINITY ? lim : lim + 1e-3f * (1.f + fabsf(lim));
+}
+
+// What binning few super-tiles needs of a visible entry, formed where its
+// record is. x: tile columns first | end << 16, y: tile rows likewise, z: bit q
+// set: the pair with candidate super-tile q (row-major in the rectangle) is
+// kept, i.e. with alpha_min > 0 the entry can reach alpha_min there; candidates
+// past the 32nd are kept untested. w: unused.
+constexpr uint32_t kTested = 32;
+__device__ __forceinline__ bool pair_kept(const uint4& info, uint32_t q) {
+    return q >= kTested || ((info.z >> q) & 1u) != 0u;
+}
+__device__ __forceinline__ uint32_t kept_pairs(const uint4& info, int S) {
+    const uint32_t c = super_count((int)(info.x & 0xffffu), (int)(info.x >> 16),
+                                   (int)(info.y & 0xffffu), (int)(info.y >> 16), S);
+    return (uint32_t)__builtin_popcount(info.z) + (c > kTested ? c - kTested : 0u);
+}
+__device__ __forceinline__ uint4 pair_info(const float4& r0, const float4& r1, int x0, int x1,
+                                           int y0, int y1, const ViewDev& V, const RasterDev& rp) {
+    const int S = rp.super_tile, sw = S * rp.tile_w, sh = S * rp.tile_h;
+    int sx0, sx1, sy0, sy1;
+    super_rect(x0, x1, y0, y1, S, &sx0, &sx1, &sy0, &sy1);
+    const float lim = super_limit(reach_limit(r1.y, rp));
+    uint32_t q = 0, keep = 0;
+    for (int y = sy0; y < sy1 && q < kTested; ++y)
+        for (int x = sx0; x < sx1 && q < kTested; ++x, ++q)
+            if (lim == INFINITY ||
+                rect_reachable(r0.x, r0.y, r0.z, r0.w, r1.x, lim, r1.z, r1.w, x * sw, y * sh,
+                               min(sw, V.width - x * sw), min(sh, V.height - y * sh)))
+                keep |= 1u << q;
+    return make_uint4((uint32_t)x0 | ((uint32_t)x1 << 16), (uint32_t)y0 | ((uint32_t)y1 << 16),
+                      keep, 0u);
 }
 
 // Adam element update, shared by the plain step and the fused backward step

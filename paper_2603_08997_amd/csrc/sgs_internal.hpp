@@ -101,6 +101,13 @@ constexpr int kMaxSuperTile = 8;   // S x S tiles of a super-tile fit a 64-bit t
 // most kEmitWindow / (kEmitHead + 1) + 2 Gaussians.
 constexpr int64_t kEmitWindow = 1024;
 constexpr int64_t kEmitHead = 2;
+// Super-tiles up to which the pairs are counted and placed without a sort (the
+// place kernel keeps 24 bytes of LDS for each).
+constexpr int64_t kDirectSupers = 512;
+constexpr int kPairThreads = 256;
+constexpr int kPairEntries = 768;   // entries expanded at a time
+constexpr int64_t kPairGroup = 32;   // blocks whose pair counts are summed up together
+
 // Windows of an emission over `entries` entries and `capacity` pairs.
 constexpr int64_t emit_windows(int64_t entries, int64_t capacity) {
     return (capacity + kEmitHead * entries + kEmitWindow - 1) / kEmitWindow;
@@ -133,13 +140,19 @@ enum TileState : uint32_t {
 struct Layout {
     int64_t entries, total_tiles, total_pixels, total_supers, capacity, seg_slots;
     int n_views;
-    int64_t scan_blocks, sort_blocks;
-    int key_bits, rect_bits, key_passes, key_result;  // result buffer (0/1) of the super-tile sort
+    int64_t scan_blocks;
+    int64_t pair_blocks;   // blocks of the direct pair path
+    int pair_rounds;       // kPairEntries entries each there
+    int key_bits, rect_bits, key_result;  // result buffer (0/1) of the super-tile lists
     int batch;
+    bool direct;           // pairs counted and placed directly (few super-tiles)
     size_t views, records, tiles, depth, dkey[2], dval[2], offsets, window_first, scan_sums,
-        pair_key[2], pair_entry[2], sort_hist, sort_totals, sup_ranges, seg_first, seg_cnt,
+        pair_info, pair_sorted, pair_hist, pair_groups, pair_key[2], pair_entry[2], sort_hist, sort_groups,
+        pair_sort_groups, sort_weights, sup_ranges, seg_first, seg_cnt,
         seg_off, pair_mask, tile_entry, tile_ranges, tile_state, tile_resume, sup_redo, tile_cost,
         tile_stats, tile_order, t_final, n_last, accum, counters, total;
+    // the region a binning pass accumulates into and finds cleared
+    size_t clear_begin, clear_words;
 };
 
 bool make_views(const sgs_camera* cams, int n_views, const sgs_raster_params* rp, Views* out,
@@ -147,11 +160,14 @@ bool make_views(const sgs_camera* cams, int n_views, const sgs_raster_params* rp
 void make_layout(const Views& views, const RasterDev& rp, int64_t n, int64_t capacity, Layout* L);
 RasterDev make_raster(const sgs_raster_params* rp);
 
-// The call's views into the workspace's view table: from the host (by value)
-// or, when `table` is non-null, view `*d_view` of a device camera table
-// (clamped into [0, n_table)) as the batch's single view.
-hipError_t launch_store_views(const Views& views, const ViewDev* table, int n_table,
-                              const int32_t* d_view, Views* dst, hipStream_t s);
+// The call's views into the workspace's view table.
+hipError_t launch_store_views(const Views& views, Views* dst, hipStream_t s);
+// The same for a call that bins: the views from the host (by value) or, when
+// `table` is non-null, view `*d_view` of a device camera table (clamped into
+// [0, n_table)) as the batch's single view; and the counters and the region of
+// the workspace that binning accumulates into cleared.
+hipError_t launch_begin_bin(const Views& views, const ViewDev* table, int n_table,
+                            const int32_t* d_view, const Layout& L, char* ws, hipStream_t s);
 
 // ---- launch wrappers (all asynchronous on `s`). Kernels read the views from
 // the workspace's view table (ws + L.views); L carries the sizes. ----
@@ -182,24 +198,24 @@ hipError_t fill_u32(uint32_t* p, int64_t n, uint32_t v, hipStream_t s);
 hipError_t launch_order_tiles(const uint32_t* cost, int64_t tiles, int shift, uint32_t* order,
                               const int32_t* gate, hipStream_t s);
 
-// Stable LSD radix sort of (key, uint32 value) pairs over key bits [0, bits).
-// n is read on the device from *n_dev; n_max bounds it for the grid size.
-// Returns the index (0/1) of the buffer holding the result.
+// Stable LSD radix sorts of (key, uint32 value) pairs. `hist`: 256 words per
+// block; `groups`: radix_group_words words of zeros per call.
+constexpr int64_t kSortGroup = 32;   // blocks whose digit counts are summed up together
+constexpr int kDepthPasses = 4;
 int radix_passes(int bits);
-// K is uint32_t. kept_dev (nullable, must hold 0): the first
-// pass drops keys with all bits set (kCulledTile) and adds the number of
-// remaining pairs there; later passes sort that many.
-// gather_dst (nullable): the last pass also writes gather_src[value] at each
-// sorted position.
-// ranges_out (nullable; one-pass sorts only): [start, end) of the run of each
-// digit d < n_ranges in the sorted output ([0, 0) when empty).
-template <typename K>
-hipError_t radix_sort(K* keys[2], uint32_t* vals[2], const uint32_t* n_dev, int64_t n_max,
-                      int bits, uint32_t* hist, uint32_t* totals, hipStream_t s, int* result,
-                      uint32_t* kept_dev = nullptr, const uint32_t* gather_src = nullptr,
-                      uint32_t* gather_dst = nullptr, uint32_t* ranges_out = nullptr,
-                      int n_ranges = 0);
 int64_t radix_blocks(int64_t n_max);
+int64_t radix_group_words(int64_t n_max, int passes);
+// The visible entries (tiles[e] != 0) of `entries` by their depth bits, ties in
+// entry order, into vals[1]; their number to *n_visible and the saturated sum
+// of tiles[] to *pairs. weights: a word of 8 bytes per block.
+hipError_t sort_entries(const uint32_t* depth, const uint32_t* tiles, int64_t entries,
+                        uint32_t* keys[2], uint32_t* vals[2], uint32_t* hist, uint32_t* groups,
+                        uint64_t* weights, uint32_t* n_visible, uint32_t* pairs, hipStream_t s);
+// *n_dev (<= n_max) pairs by the low `bits` bits of their keys, those with all
+// bits set (kCulledTile) left out; the number of the others to *kept. The
+// result is in keys[radix_passes(bits) & 1], vals likewise.
+hipError_t sort_pairs(uint32_t* keys[2], uint32_t* vals[2], const uint32_t* n_dev, int64_t n_max,
+                      int bits, uint32_t* hist, uint32_t* groups, uint32_t* kept, hipStream_t s);
 
 // Adaptive density control. Thresholds as the kernels compare them (float32
 // values formed in binary64 on the host).

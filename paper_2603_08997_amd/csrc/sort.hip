@@ -1,14 +1,26 @@
 // Stable least-significant-digit radix sort of (key, uint32 value) pairs over
-// the low bits of uint32 keys (the kernels are templates over the key type),
-// digits of at most 8 bits, reduce-then-scan:
-//   hist:    per-block digit counts, stored digit-major [256][blocks];
-//   scan:    one block per digit row scans the row and records its total;
-//   scatter: each block ranks its keys stably (each wave ranks a contiguous
-//            quarter of the block with ballots and its own digit counters;
-//            per-wave counts give the order across waves), sorts them into
-//            LDS, and writes digit runs out coalesced.
-// Each block owns a contiguous range of kTile keys, so equal digits keep
-// their input order and the sort is stable; no pass waits on another block.
+// the low bits of uint32 keys, digits of at most 8 bits, two launches a pass:
+//   hist:    per-block digit counts [blocks][256], and their sums over groups
+//            of kSortGroup blocks [groups][256] by atomics;
+//   scatter: each block adds up the groups and the blocks before it (a digit a
+//            thread, whole rows of counts at a time), ranks its keys stably
+//            (each wave ranks a contiguous part of the block with ballots and
+//            its own digit counters; per-wave counts give the order across
+//            waves), sorts them into LDS, and writes digit runs out coalesced.
+// Each block owns a contiguous range of keys, so equal digits keep their input
+// order and the sort is stable; no pass waits on another block.
+//
+// The depth sort's first pass reads the uncompacted entries and drops the
+// invisible ones, which makes the compaction of the visible entries part of
+// it, and its last pass leaves the keys out.
+//
+// What bounds a pass: latency, the chain of loads, LDS passes and scattered
+// stores of a block; its 32 bytes a key take a sixth of its time. Before, a
+// scan kernel between the two walked the counts digit by digit and a separate
+// scan compacted the entries: 12 + 2 launches for the depth sort instead of 8,
+// and on sets that do not fill the chip a launch is most of a kernel's time.
+#include <algorithm>
+
 #include "sgs_internal.hpp"
 #include "sgs_device.hpp"
 
@@ -16,13 +28,42 @@ namespace sgs {
 
 namespace {
 
-constexpr int kThreads = 256;
-constexpr int kItems = 8;
-constexpr int kTile = kThreads * kItems;  // keys per block
-constexpr int kRadix = 256;
+// Keys per block: us a pass of the 1M, 3M and 6M scenes (0.7, 2.05 and 4.1M
+// keys) with 2048 12.4 / 20.5 / 44.5, with 4096 11.6 / 19.5 / 35.3, with 8192
+// 14.2 / 29.2 / 45.4 (one block per compute unit is left); 21k keys 10.2 / 10.8 /
+// 12.6.
+constexpr int kThreads = 512;
+constexpr int kKeys = 8;
+constexpr int kTile = kThreads * kKeys;
 constexpr int kWaves = kThreads / 64;
-constexpr int kScanThreads = 1024;
+constexpr int kRadix = 256;
 constexpr int kHistCopies = 4;
+
+// What a pass sorts: key and value of input i, and whether it is kept.
+struct EntrySrc {   // the visible entries, by depth bits
+    const uint32_t* depth;
+    const uint32_t* tiles;
+    int64_t n;
+    __device__ int64_t count() const { return n; }
+    __device__ bool load(int64_t i, uint32_t& key, uint32_t& val) const {
+        key = depth[i];
+        val = (uint32_t)i;
+        return tiles[i] != 0u;
+    }
+    __device__ uint32_t weight(int64_t i) const { return tiles[i]; }
+};
+template <bool kDrop>   // kDrop: keys with all bits set (culled pairs) are left out
+struct PairSrc {
+    const uint32_t* keys;
+    const uint32_t* vals;
+    const uint32_t* n;
+    __device__ int64_t count() const { return *n; }
+    __device__ bool load(int64_t i, uint32_t& key, uint32_t& val) const {
+        key = keys[i];
+        val = vals[i];
+        return !kDrop || key != kCulledTile;
+    }
+};
 
 __device__ __forceinline__ uint32_t digit_of(uint32_t k, int shift, uint32_t mask) {
     return (k >> shift) & mask;
@@ -39,185 +80,152 @@ __device__ __forceinline__ uint64_t match_digit(uint32_t d, bool valid, int bits
     return peers;
 }
 
-// Culled-pair sentinel of a key type (all bits set).
-template <typename K>
-__device__ __forceinline__ constexpr uint32_t culled_key() {
-    return (uint32_t)(K)~(K)0;
-}
-
-// Digit counts of one block's keys. Counting does not depend on order, so the
-// keys are read as uint4 (4 or 8 keys) and counted into several LDS histograms.
-template <typename K>
-__global__ void __launch_bounds__(kThreads) radix_hist_kernel(const K* __restrict__ keys,
-                                                              const uint32_t* __restrict__ n_dev,
-                                                              int shift, int bits,
-                                                              uint32_t* __restrict__ hist,
-                                                              int nblocks, bool skip_culled) {
-    constexpr int VEC = 16 / (int)sizeof(K);
-    static_assert(kItems % VEC == 0, "keys per thread");
+// Digit counts of one block's kept keys (counting does not depend on order).
+// kWeights: also the block's sum of the inputs' weights, to weights[block].
+template <class Src, bool kWeights>
+__global__ void __launch_bounds__(kThreads) radix_hist_kernel(Src src, int shift, int bits,
+                                                        uint32_t* __restrict__ hist,
+                                                        uint32_t* __restrict__ groups,
+                                                        uint64_t* __restrict__ weights) {
     // kHistCopies counters per digit, lane l counting into copy l % kHistCopies,
     // so that fewer lanes of one atomic instruction hit the same address
     __shared__ uint32_t cnt[kHistCopies][kRadix];
-    const int tid = threadIdx.x, w = tid % kHistCopies;
-#pragma unroll
-    for (int k = 0; k < kHistCopies; ++k) cnt[k][tid] = 0;
-    __syncthreads();
-    const uint32_t n = *n_dev;
-    const uint32_t mask = (1u << bits) - 1u;
-    // the grid covers the capacity; the first ceil(n / kTile) workgroups work
-    const int active = (int)(((int64_t)n + kTile - 1) / kTile);
-    const int blk = (int)blockIdx.x < active ? xcd_block(blockIdx.x, active) : (int)blockIdx.x;
+    __shared__ uint64_t wsum[kThreads / 64];
+    const int tid = threadIdx.x;
+    const int64_t n = src.count();
+    // the grid covers a bound; the first ceil(n / kTile) workgroups work
+    const int active = (int)((n + kTile - 1) / kTile);
+    if ((int)blockIdx.x >= active) return;
+    const int blk = xcd_block(blockIdx.x, active);
     const int64_t base = (int64_t)blk * kTile;
-    if (base < (int64_t)n) {
-        const uint4* k4 = reinterpret_cast<const uint4*>(keys + base);
-        const int64_t left = (int64_t)n - base;
-        // all loads first, then the counts
-        uint4 q[kItems / VEC];
+    for (int i = tid; i < kHistCopies * kRadix; i += kThreads) cnt[i / kRadix][i % kRadix] = 0;
+    // all loads first, then the counts
+    uint32_t key[kKeys], val;
+    bool ok[kKeys];
+    uint64_t w = 0;
 #pragma unroll
-        for (int it = 0; it < kItems / VEC; ++it) {
-            const int64_t j = (int64_t)(it * kThreads + tid) * VEC;
-            if (j + VEC - 1 < left) {
-                q[it] = k4[it * kThreads + tid];
-            } else {
-                K kk[VEC];
-#pragma unroll
-                for (int c = 0; c < VEC; ++c)
-                    kk[c] = j + c < left ? keys[base + j + c] : (K)culled_key<K>();
-                __builtin_memcpy(&q[it], kk, sizeof(q[it]));
-            }
-        }
-#pragma unroll
-        for (int it = 0; it < kItems / VEC; ++it) {
-            const int64_t j = (int64_t)(it * kThreads + tid) * VEC;
-            K kk[VEC];
-            __builtin_memcpy(kk, &q[it], sizeof(q[it]));
-#pragma unroll
-            for (int c = 0; c < VEC; ++c) {
-                const uint32_t k = kk[c];
-                if (j + c < left && !(skip_culled && k == culled_key<K>()))
-                    atomicAdd(&cnt[w][digit_of(k, shift, mask)], 1u);
-            }
-        }
+    for (int it = 0; it < kKeys; ++it) {
+        const int64_t i = base + it * kThreads + tid;
+        ok[it] = i < n && src.load(i, key[it], val);
+        if constexpr (kWeights)
+            if (i < n) w += src.weight(i);
     }
     __syncthreads();
-    uint32_t total = 0;
+    const uint32_t mask = (1u << bits) - 1u;
 #pragma unroll
-    for (int k = 0; k < kHistCopies; ++k) total += cnt[k][tid];
-    // only the rows of digits this pass can produce (each write is a separate
-    // cache line of the digit-major table)
-    if (tid < (1 << bits)) hist[(int64_t)tid * nblocks + blk] = total;
-}
-
-// Exclusive scan of each digit row hist[d][0..nblocks) in place; totals[d] =
-// row sum. Each thread takes a run of up to kScanItems consecutive entries
-// (kept in registers), so a row of up to kScanThreads * kScanItems entries
-// needs one block scan; longer rows go in chunks of that size.
-constexpr int kScanItems = 16;
-__global__ void __launch_bounds__(kScanThreads) radix_scan_kernel(uint32_t* __restrict__ hist,
-                                                                  int nblocks,
-                                                                  uint32_t* __restrict__ totals,
-                                                                  uint32_t* __restrict__ kept) {
-    __shared__ uint32_t smem[kScanThreads / 64 + 1];
-    uint32_t* row = hist + (int64_t)blockIdx.x * nblocks;
-    const int per = min(kScanItems, (nblocks + kScanThreads - 1) / kScanThreads);
-    const int chunk = per * kScanThreads;
-    uint32_t carry = 0;
-    for (int base = 0; base < nblocks; base += chunk) {
-        const int first = base + (int)threadIdx.x * per;
-        uint32_t v[kScanItems];
-        uint32_t sum = 0;
+    for (int it = 0; it < kKeys; ++it)
+        if (ok[it]) atomicAdd(&cnt[tid % kHistCopies][digit_of(key[it], shift, mask)], 1u);
+    if constexpr (kWeights) {
 #pragma unroll
-        for (int k = 0; k < kScanItems; ++k) {
-            const int i = first + k;
-            v[k] = (k < per && i < nblocks) ? row[i] : 0u;
-            sum += v[k];
-        }
-        uint32_t tot;
-        uint32_t run = carry + block_excl_scan<kScanThreads>(sum, smem, &tot);
-#pragma unroll
-        for (int k = 0; k < kScanItems; ++k) {
-            const int i = first + k;
-            if (k < per && i < nblocks) row[i] = run;
-            run += v[k];
-        }
-        carry += tot;
+        for (int d = 32; d > 0; d >>= 1) w += __shfl_xor(w, d, 64);
+        if (tid % 64 == 0) wsum[tid / 64] = w;
     }
-    if (threadIdx.x == 0) {
-        totals[blockIdx.x] = carry;
-        // the first tile-sort pass: the kept pairs are the sum of the rows
-        if (kept != nullptr) atomicAdd(kept, carry);
+    __syncthreads();
+    if (tid < kRadix) {
+        uint32_t total = 0;
+#pragma unroll
+        for (int k = 0; k < kHistCopies; ++k) total += cnt[k][tid];
+        hist[(int64_t)blk * kRadix + tid] = total;
+        if (total != 0u) atomicAdd(&groups[(int64_t)(blk / kSortGroup) * kRadix + tid], total);
+    }
+    if constexpr (kWeights) {
+        if (tid == 0) {
+            w = 0;
+            for (int k = 0; k < kThreads / 64; ++k) w += wsum[k];
+            weights[blk] = w;
+        }
     }
 }
 
-// Scatter of one block's kTile keys. Wave w owns the contiguous key range
-// [w kTile/kWaves, (w+1) kTile/kWaves) and ranks it in kItems rounds of 64
+// Scatter of one block's keys. Wave w owns the contiguous key range
+// [w kPerWave, (w+1) kPerWave) and ranks it in kKeys rounds of 64
 // consecutive keys with its own LDS digit counters, so ranking needs no
 // block barrier: within a round, lanes with the same digit are found with
 // ballots and ordered by lane; across rounds the wave's counter carries the
 // count. One barrier later, the digit's start in the block plus the counts of
 // the earlier waves give every key its block-local position; keys are sorted
-// into LDS and written out in digit runs.
-template <typename K>
+// into LDS and written out in digit runs. Block 0 also writes the number of
+// kept keys (kept, nullable) and, with kWeights, the saturated sum of the
+// weights.
+template <class Src, bool kWeights, bool kKeysOut>
 __global__ void __launch_bounds__(kThreads) radix_scatter_kernel(
-    const K* __restrict__ keys_in, const uint32_t* __restrict__ vals_in,
-    K* __restrict__ keys_out, uint32_t* __restrict__ vals_out,
-    const uint32_t* __restrict__ n_dev, int shift, int bits, const uint32_t* __restrict__ hist,
-    const uint32_t* __restrict__ totals, int nblocks, bool skip_culled,
-    const uint32_t* __restrict__ gather_src, uint32_t* __restrict__ gather_dst,
-    uint32_t* __restrict__ ranges_out, int n_ranges) {
-    __shared__ K lkeys[kTile];
+    Src src, uint32_t* __restrict__ keys_out, uint32_t* __restrict__ vals_out, int shift, int bits,
+    const uint32_t* __restrict__ hist, const uint32_t* __restrict__ groups,
+    const uint64_t* __restrict__ weights, uint32_t* __restrict__ kept,
+    uint32_t* __restrict__ weight_sum) {
+    constexpr int kPerWave = kTile / kWaves;
+    constexpr int kParts = kThreads / kRadix;         // threads adding up a digit's counts
+    __shared__ uint32_t lkeys[kTile];
     __shared__ uint32_t lvals[kTile];
     __shared__ uint32_t gbase[kRadix];          // global start of this block's digit run
     __shared__ uint32_t wcnt[kWaves][kRadix];   // keys of each digit per wave
     __shared__ uint32_t smem[kThreads / 64 + 1];
 
-    const uint32_t n = *n_dev;
-    const int active = (int)(((int64_t)n + kTile - 1) / kTile);
+    const int64_t n = src.count();
+    const int active = (int)((n + kTile - 1) / kTile);
     const int tid = threadIdx.x, w = tid / 64, lane = tid % 64;
-    if (ranges_out != nullptr && blockIdx.x == 0) {
-        // a one-pass sort: [start, end) of every digit's run in the output
-        // (empty runs: [0, 0)), from the digit totals
-        uint32_t tot;
-        const bool used = tid < (1 << bits);
-        const uint32_t c = used ? totals[tid] : 0u;
-        const uint32_t ex = block_excl_scan<kThreads>(c, smem, &tot);
-        if (tid < n_ranges) {
-            ranges_out[2 * tid] = c ? ex : 0u;
-            ranges_out[2 * tid + 1] = c ? ex + c : 0u;
+    if ((int)blockIdx.x >= active) {   // uniform across the block
+        if (active == 0 && blockIdx.x == 0 && tid == 0) {
+            if (kept != nullptr) *kept = 0u;
+            if (kWeights) *weight_sum = 0u;
         }
+        return;
     }
-    if ((int)blockIdx.x >= active) return;  // uniform across the block
     const int blk = xcd_block(blockIdx.x, active);
     const int64_t base = (int64_t)blk * kTile;
     const uint32_t mask = (1u << bits) - 1u;
-    const int nvalid = (int)min((int64_t)kTile, (int64_t)n - base);
-    constexpr int kPerWave = kTile / kWaves;
 
     // all loads first: wave w, round it, lane l holds key w*kPerWave + 64*it + l
-    uint32_t key[kItems], val[kItems];
+    uint32_t key[kKeys], val[kKeys];
+    uint32_t ok = 0;
 #pragma unroll
-    for (int it = 0; it < kItems; ++it) {
-        const int li = w * kPerWave + it * 64 + lane;
-        const bool valid = li < nvalid;
-        key[it] = valid ? (uint32_t)keys_in[base + li] : culled_key<K>();
-        val[it] = valid ? vals_in[base + li] : 0u;
+    for (int it = 0; it < kKeys; ++it) {
+        const int64_t i = base + w * kPerWave + it * 64 + lane;
+        key[it] = val[it] = 0u;
+        if (i < n && src.load(i, key[it], val[it])) ok |= 1u << it;
     }
     {
-        uint32_t tot;
-        const bool used = tid < (1 << bits);   // rows beyond 2^bits are not written
-        const uint32_t ex = block_excl_scan<kThreads>(used ? totals[tid] : 0u, smem, &tot);
-        gbase[tid] = ex + (used ? hist[(int64_t)tid * nblocks + blk] : 0u);
-    }
+        // lkeys serves as scratch: [part][digit] totals, lvals: counts before
+        const int d = tid % kRadix, part = tid / kRadix;
+        const int ng = (active + kSortGroup - 1) / kSortGroup, g = blk / kSortGroup;
+        uint32_t tot = 0, before = 0;
+        for_rows(groups + d, kRadix, part, ng, kParts, [&](int j, uint32_t c) {
+            tot += c;
+            before += j < g ? c : 0u;
+        });
+        for_rows(hist + d, kRadix, g * (int)kSortGroup + part, blk, kParts,
+                 [&](int, uint32_t c) { before += c; });
+        lkeys[tid] = tot;
+        lvals[tid] = before;
+        __syncthreads();
+        tot = before = 0;
+        if (tid < kRadix) {
 #pragma unroll
-    for (int k = 0; k < kWaves; ++k) wcnt[k][tid] = 0;
+            for (int k = 0; k < kParts; ++k) {
+                tot += lkeys[k * kRadix + tid];
+                before += lvals[k * kRadix + tid];
+            }
+        }
+        uint32_t all;
+        const uint32_t ex = block_excl_scan<kThreads>(tot, smem, &all);
+        if (tid < kRadix) gbase[tid] = ex + before;
+        if (blockIdx.x == 0 && tid == 0 && kept != nullptr) *kept = all;
+    }
+    if (kWeights && blockIdx.x == 0 && w == 0) {
+        uint64_t s = 0;
+        for (int j = lane; j < active; j += 64) s += weights[j];
+#pragma unroll
+        for (int d = 32; d > 0; d >>= 1) s += __shfl_xor(s, d, 64);
+        if (lane == 0) *weight_sum = (uint32_t)min(s, (uint64_t)0xffffffffull);
+    }
+    for (int i = tid; i < kWaves * kRadix; i += kThreads) wcnt[i / kRadix][i % kRadix] = 0;
     __syncthreads();
 
     // wave-private stable ranking (dropped keys take no position)
-    uint32_t rank[kItems];
+    uint32_t rank[kKeys];
 #pragma unroll
-    for (int it = 0; it < kItems; ++it) {
-        const int li = w * kPerWave + it * 64 + lane;
-        const bool valid = li < nvalid && !(skip_culled && key[it] == culled_key<K>());
+    for (int it = 0; it < kKeys; ++it) {
+        const bool valid = (ok >> it) & 1u;
         const uint32_t d = digit_of(key[it], shift, mask);
         const uint64_t peers = match_digit(d, valid, bits);
         const uint32_t before = (uint32_t)popc64(peers & lanemask_lt());
@@ -233,23 +241,29 @@ __global__ void __launch_bounds__(kThreads) radix_scatter_kernel(
     // per digit (thread tid): start in the block and the counts of earlier waves
     int nkept;
     {
-        uint32_t c[kWaves], sum = 0;
+        uint32_t sum = 0;
+        if (tid < kRadix) {
 #pragma unroll
-        for (int k = 0; k < kWaves; ++k) { c[k] = wcnt[k][tid]; sum += c[k]; }
+            for (int k = 0; k < kWaves; ++k) sum += wcnt[k][tid];
+        }
         uint32_t tot;
         uint32_t start = block_excl_scan<kThreads>(sum, smem, &tot);
+        if (tid < kRadix) {
 #pragma unroll
-        for (int k = 0; k < kWaves; ++k) { wcnt[k][tid] = start; start += c[k]; }
+            for (int k = 0; k < kWaves; ++k) {
+                const uint32_t c = wcnt[k][tid];
+                wcnt[k][tid] = start;
+                start += c;
+            }
+        }
         nkept = (int)tot;
     }
     __syncthreads();
 #pragma unroll
-    for (int it = 0; it < kItems; ++it) {
-        const int li = w * kPerWave + it * 64 + lane;
-        if (li < nvalid && !(skip_culled && key[it] == culled_key<K>())) {
-            const uint32_t d = digit_of(key[it], shift, mask);
-            const uint32_t pos = wcnt[w][d] + rank[it];
-            lkeys[pos] = (K)key[it];
+    for (int it = 0; it < kKeys; ++it) {
+        if ((ok >> it) & 1u) {
+            const uint32_t pos = wcnt[w][digit_of(key[it], shift, mask)] + rank[it];
+            lkeys[pos] = key[it];
             lvals[pos] = val[it];
         }
     }
@@ -257,19 +271,41 @@ __global__ void __launch_bounds__(kThreads) radix_scatter_kernel(
     // wcnt[0][d] is now the block-local start of digit d
 #pragma unroll 4
     for (int li = tid; li < nkept; li += kThreads) {
-        const K k = lkeys[li];
+        const uint32_t k = lkeys[li];
         const uint32_t d = digit_of(k, shift, mask);
         const uint32_t out = gbase[d] + (uint32_t)li - wcnt[0][d];
-        const uint32_t val = lvals[li];
-        keys_out[out] = k;
-        vals_out[out] = val;
-        if (gather_dst != nullptr) gather_dst[out] = gather_src[val];
+        if (kKeysOut) keys_out[out] = k;
+        vals_out[out] = lvals[li];
     }
+}
+
+struct Pass {
+    int shift, bits;
+    uint32_t *hist, *groups;
+    uint64_t* weights;
+    uint32_t *kept, *weight_sum;
+};
+
+template <class Src, bool kWeights = false, bool kKeysOut = true>
+void run_pass(const Src& src, const Pass& p, uint32_t* keys_out, uint32_t* vals_out, int64_t n_max,
+              hipStream_t s) {
+    const dim3 grid((unsigned)radix_blocks(n_max)), block(kThreads);
+    hipLaunchKernelGGL((radix_hist_kernel<Src, kWeights>), grid, block, 0, s, src, p.shift, p.bits,
+                       p.hist, p.groups, p.weights);
+    hipLaunchKernelGGL((radix_scatter_kernel<Src, kWeights, kKeysOut>), grid, block, 0, s, src,
+                       keys_out, vals_out, p.shift, p.bits, p.hist, p.groups, p.weights, p.kept,
+                       p.weight_sum);
 }
 
 }  // namespace
 
-int64_t radix_blocks(int64_t n_max) { return n_max <= 0 ? 1 : (n_max + kTile - 1) / kTile; }
+int64_t radix_blocks(int64_t n_max) {
+    return std::max<int64_t>(1, (n_max + kTile - 1) / kTile);
+}
+
+int64_t radix_group_words(int64_t n_max, int passes) {
+    return passes * kRadix * ((radix_blocks(n_max) + kSortGroup - 1) / kSortGroup);
+}
 
 int radix_passes(int bits) { return bits <= 0 ? 0 : (bits + 7) / 8; }
 
@@ -284,41 +320,42 @@ static int pass_bits(int bits, int p, int* shift) {
     return base + (p < extra ? 1 : 0);
 }
 
-template <typename K>
-hipError_t radix_sort(K* keys[2], uint32_t* vals[2], const uint32_t* n_dev, int64_t n_max,
-                      int bits, uint32_t* hist, uint32_t* totals, hipStream_t s, int* result,
-                      uint32_t* kept_dev, const uint32_t* gather_src, uint32_t* gather_dst,
-                      uint32_t* ranges_out, int n_ranges) {
-    const int passes = radix_passes(bits);
-    if (ranges_out != nullptr && (passes != 1 || n_ranges > (1 << bits)))
-        return hipErrorInvalidValue;   // digit runs are the sorted runs of one pass only
-    const int nb = (int)radix_blocks(n_max);
-    int cur = 0;
-    for (int p = 0; p < passes; ++p) {
-        int shift;
-        const int pb = pass_bits(bits, p, &shift);
-        const bool skip = kept_dev != nullptr && p == 0;
-        const uint32_t* n_p = (kept_dev != nullptr && p > 0) ? kept_dev : n_dev;
-        hipLaunchKernelGGL(radix_hist_kernel<K>, dim3(nb), dim3(kThreads), 0, s, keys[cur], n_p,
-                           shift, pb, hist, nb, skip);
-        // rows and totals of digits >= 2^pb are never read for a key of this pass
-        hipLaunchKernelGGL(radix_scan_kernel, dim3(1u << pb), dim3(kScanThreads), 0, s, hist, nb,
-                           totals, skip ? kept_dev : nullptr);
-        const bool last = p == passes - 1;
-        hipLaunchKernelGGL(radix_scatter_kernel<K>, dim3(nb), dim3(kThreads), 0, s, keys[cur],
-                           vals[cur], keys[cur ^ 1], vals[cur ^ 1], n_p, shift, pb, hist, totals,
-                           nb, skip, last ? gather_src : nullptr, last ? gather_dst : nullptr,
-                           ranges_out, n_ranges);
-        cur ^= 1;
+hipError_t sort_entries(const uint32_t* depth, const uint32_t* tiles, int64_t entries,
+                        uint32_t* keys[2], uint32_t* vals[2], uint32_t* hist, uint32_t* groups,
+                        uint64_t* weights, uint32_t* n_visible, uint32_t* pairs, hipStream_t s) {
+    const int64_t gw = radix_group_words(entries, 1);
+    Pass p{0, 8, hist, groups, weights, n_visible, pairs};
+    run_pass<EntrySrc, true>(EntrySrc{depth, tiles, entries}, p, keys[0], vals[0], entries, s);
+    p.weights = nullptr;
+    p.kept = p.weight_sum = nullptr;
+    for (int k = 1; k < kDepthPasses; ++k) {
+        p.shift = 8 * k;
+        p.groups = groups + k * gw;
+        const int in = (k - 1) & 1;
+        const PairSrc<false> src{keys[in], vals[in], n_visible};
+        if (k == kDepthPasses - 1)
+            run_pass<PairSrc<false>, false, false>(src, p, nullptr, vals[in ^ 1], entries, s);
+        else
+            run_pass<PairSrc<false>>(src, p, keys[in ^ 1], vals[in ^ 1], entries, s);
     }
-    if (kept_dev != nullptr && passes == 0)
-        return hipErrorInvalidValue;  // a kept count needs at least one pass
-    *result = cur;
     return hipGetLastError();
 }
 
-template hipError_t radix_sort<uint32_t>(uint32_t* keys[2], uint32_t* vals[2], const uint32_t*,
-                                         int64_t, int, uint32_t*, uint32_t*, hipStream_t, int*,
-                                         uint32_t*, const uint32_t*, uint32_t*, uint32_t*, int);
+hipError_t sort_pairs(uint32_t* keys[2], uint32_t* vals[2], const uint32_t* n_dev, int64_t n_max,
+                      int bits, uint32_t* hist, uint32_t* groups, uint32_t* kept, hipStream_t s) {
+    const int passes = radix_passes(bits);
+    const int64_t gw = radix_group_words(n_max, 1);
+    for (int k = 0; k < passes; ++k) {
+        Pass p{0, 0, hist, groups + k * gw, nullptr, k == 0 ? kept : nullptr, nullptr};
+        p.bits = pass_bits(bits, k, &p.shift);
+        const int in = k & 1;
+        if (k == 0)
+            run_pass(PairSrc<true>{keys[0], vals[0], n_dev}, p, keys[1], vals[1], n_max, s);
+        else
+            run_pass(PairSrc<false>{keys[in], vals[in], kept}, p, keys[in ^ 1], vals[in ^ 1],
+                     n_max, s);
+    }
+    return hipGetLastError();
+}
 
 }  // namespace sgs
