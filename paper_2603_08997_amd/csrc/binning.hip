@@ -38,7 +38,7 @@ constexpr int kScanThreads = 256;
 constexpr int kScanItems = 8;
 constexpr int kScanTile = kScanThreads * kScanItems;
 
-// ---- sources and sinks of the two device-wide scans ----
+// ---- source and sink of the emission's device-wide scan ----
 // The scans add in uint32 with saturation at 2^32 - 1 (saturating addition is
 // associative, so the block and grand totals are the saturated true sums): a
 // batch whose pair count does not fit ends with the all-ones total, which no
@@ -707,58 +707,54 @@ __global__ void fill_u32_kernel(uint32_t* p, int64_t n, uint32_t v) {
 }
 
 // ---- the split of the super-tile lists into tile lists ----
+//
+// Two launches: the count kernel forms the tile masks and the counts per
+// (segment, tile), their sums over groups of segments and the number of list
+// entries per super-tile; the write kernel adds up what comes before a segment
+// (the super-tiles in LDS, the groups and segments of its super-tile row by row,
+// a tile a lane), stores the entries and the tiles' ranges. A scan over all
+// (super-tile, tile, segment) counts and the ranges took three launches more.
 
-__device__ __forceinline__ uint32_t list_segments(const uint32_t* ranges, int64_t s) {
+// Pairs of super-tile s's list that a split covers: before compositing
+// (kRest = false) its prefix, in the completing split the whole list of the
+// super-tiles flagged in sup_redo.
+template <bool kRest>
+__device__ __forceinline__ uint32_t pairs_to_split(const uint32_t* ranges, const uint32_t* sup_redo,
+                                                   uint32_t prefix_segs, int64_t s) {
     const uint32_t len = ranges[2 * s + 1] - ranges[2 * s];
-    return (uint32_t)((len + kSegPairs - 1) / kSegPairs);
+    if (kRest) return sup_redo[s] ? len : 0u;
+    return split_pairs(len, prefix_segs);
 }
-// Segments of every super-tile's list split before compositing (the scan
-// numbers them): all, or the first `prefix` of a long list.
+__device__ __forceinline__ uint32_t segments_of(uint32_t pairs, int seg_log2) {
+    return (uint32_t)(((uint64_t)pairs + (1ull << seg_log2) - 1ull) >> seg_log2);
+}
+// Segments of every super-tile's list (the scan numbers them).
+template <bool kRest>
 struct SegCountSrc {
-    const uint32_t* ranges;
-    int64_t n;
-    uint32_t prefix;   // 0: all
-    __device__ int64_t count() const { return n; }
-    __device__ uint32_t operator()(int64_t s) const {
-        return split_segments(list_segments(ranges, s), prefix);
-    }
-};
-// The completing split: every segment of the super-tiles flagged in
-// sup_redo, none of the others; nothing unless *redo is set.
-struct RestSegSrc {
     const uint32_t* ranges;
     const uint32_t* sup_redo;
     const uint32_t* redo;
     int64_t n;
-    __device__ int64_t count() const { return *redo ? n : 0; }
+    uint32_t prefix;
+    int seg_log2;
+    __device__ int64_t count() const { return !kRest || *redo ? n : 0; }
     __device__ uint32_t operator()(int64_t s) const {
-        return sup_redo[s] ? list_segments(ranges, s) : 0u;
+        return segments_of(pairs_to_split<kRest>(ranges, sup_redo, prefix, s), seg_log2);
     }
 };
-// (super-tile, tile, segment) counts, in that order, for the list positions.
+// List entries of every super-tile.
 struct ItemCountSrc {
-    const uint32_t* cnt;
-    const uint32_t* n_seg;
-    int tt;
-    __device__ int64_t count() const { return (int64_t)*n_seg * tt; }
-    __device__ uint32_t operator()(int64_t i) const { return cnt[i]; }
-};
-struct ItemOffSink {
-    uint32_t* off;
-    const uint32_t* base;   // nullable: list positions start there (after the prefix lists)
-    __device__ void operator()(int64_t k, uint32_t, uint32_t pos) const {
-        off[k] = base != nullptr ? sat_add(pos, *base) : pos;
+    const uint64_t* items;
+    int64_t n;
+    __device__ int64_t count() const { return n; }
+    __device__ uint32_t operator()(int64_t s) const {
+        return (uint32_t)min(items[s], (uint64_t)0xffffffffull);
     }
 };
 
-// Tile-list entries of both splits (saturating).
-__device__ __forceinline__ uint32_t items_total(const uint32_t* counters) {
-    return sat_add(counters[kItems], counters[kItemsRest]);
-}
-
-// Exclusive saturating scan of the segment counts of all super-tiles in one
-// workgroup (a few hundred to a few ten thousand counts): first[s] for every
-// super-tile and the total in first[n].
+// Exclusive saturating scan of the counts of all super-tiles in one workgroup (a
+// few hundred to a few ten thousand counts): first[s] for every super-tile and
+// the total in first[n].
 constexpr int kSegScanThreads = 1024;
 constexpr int kSegScanItems = 4;
 template <class Src>
@@ -787,6 +783,22 @@ __global__ void __launch_bounds__(kSegScanThreads) seg_scan_kernel(Src src, uint
     if (threadIdx.x == 0) first[src.n] = carry;
 }
 
+// The same within every workgroup of a kernel, into LDS (first[0..ns]).
+template <int NT, class Src>
+__device__ __forceinline__ void scan_supers(const Src& src, int ns, uint32_t* first,
+                                            uint32_t* smem) {
+    uint32_t carry = 0;
+    for (int s0 = 0; s0 < ns; s0 += NT) {
+        const int s = s0 + (int)threadIdx.x;
+        const uint32_t v = s < ns ? src(s) : 0u;
+        uint32_t tot;
+        const uint32_t ex = sat_add(carry, block_excl_sat_scan<NT>(v, smem, &tot));
+        if (s < ns) first[s] = ex;
+        carry = sat_add(carry, tot);
+    }
+    if (threadIdx.x == 0) first[ns] = carry;
+}
+
 // Segment g of the split: super-tile s (global index), segment k of nseg in
 // its list, pairs [a, b), the super-tile's first tile (tx0, ty0) in its view.
 struct Segment {
@@ -796,10 +808,11 @@ struct Segment {
     const ViewDev* V;
 };
 
+template <bool kRest>
 __device__ __forceinline__ bool locate_segment(const Views* views, const uint32_t* seg_first,
-                                               const uint32_t* sup_ranges, int S, uint32_t g,
-                                               Segment* out) {
-    const int ns = views->total_supers;
+                                               const uint32_t* sup_ranges, const RasterDev& rp,
+                                               uint32_t g, Segment* out) {
+    const int ns = views->total_supers, S = rp.super_tile;
     if (g >= seg_first[ns]) return false;
     int lo = 0, hi = ns;   // first super-tile whose first segment lies past g
     while (lo < hi) {
@@ -814,8 +827,10 @@ __device__ __forceinline__ bool locate_segment(const Views* views, const uint32_
     out->s = s;
     out->k = g - seg_first[s];
     out->nseg = seg_first[s + 1] - seg_first[s];
-    out->a = sup_ranges[2 * s] + out->k * (uint32_t)kSegPairs;
-    out->b = min(sup_ranges[2 * s + 1], out->a + (uint32_t)kSegPairs);
+    const uint32_t begin = sup_ranges[2 * s], len = sup_ranges[2 * s + 1] - begin;
+    const uint32_t end = begin + (kRest ? len : split_pairs(len, (uint32_t)rp.prefix_segs));
+    out->a = begin + (out->k << rp.seg_log2);
+    out->b = min(end, out->a + (1u << rp.seg_log2));
     out->tx0 = (ls % V->sup_x) * S;
     out->ty0 = (ls / V->sup_x) * S;
     out->V = V;
@@ -947,35 +962,27 @@ __device__ __forceinline__ void band_columns(const Reach& R, float u, float v, f
 //
 // With `local` (at most kLocalSupers super-tiles) every workgroup first forms
 // the segment index (the exclusive scan of src over the super-tiles) in LDS,
-// and workgroup 0 also stores it for the kernels after this one, which saves
-// the scan's own launch; otherwise seg_first holds it already.
+// and workgroup 0 also stores it for the write kernel, which saves the scan's
+// own launch; otherwise seg_first holds it already.
 constexpr int kLocalSupers = 1024;
-template <class Src>
+template <bool kRest>
 __global__ void __launch_bounds__(kSplitWaves * 64) split_count_kernel(
-    const Views* __restrict__ views, RasterDev rp, Src src, bool local,
+    const Views* __restrict__ views, RasterDev rp, SegCountSrc<kRest> src, bool local,
     uint32_t* __restrict__ seg_first_g, const uint32_t* __restrict__ sup_ranges,
     const uint32_t* __restrict__ skey, const uint32_t* __restrict__ sentry,
     const float4* __restrict__ rec, uint32_t entries, uint64_t* __restrict__ mask,
-    uint32_t* __restrict__ seg_cnt) {
+    uint32_t* __restrict__ seg_cnt, uint32_t* __restrict__ seg_groups,
+    unsigned long long* __restrict__ sup_items) {
     constexpr int NT = kSplitWaves * 64;
     __shared__ uint32_t s_first[kLocalSupers + 1];
     __shared__ uint32_t s_scan[NT / 64 + 1];
+    if (kRest && src.count() == 0) return;   // uniform: no tile needs more
     const int w = threadIdx.x / 64, lane = threadIdx.x % 64;
     const int S = rp.super_tile, TT = S * S;
     const uint32_t* seg_first = seg_first_g;
     if (local) {   // uniform
         const int ns = views->total_supers;
-        const bool on = src.count() > 0;
-        uint32_t carry = 0;
-        for (int s0 = 0; s0 < ns; s0 += NT) {
-            const int s = s0 + (int)threadIdx.x;
-            const uint32_t v = (on && s < ns) ? src(s) : 0u;
-            uint32_t tot;
-            const uint32_t ex = sat_add(carry, block_excl_sat_scan<NT>(v, s_scan, &tot));
-            if (s < ns) s_first[s] = ex;
-            carry = sat_add(carry, tot);
-        }
-        if (threadIdx.x == 0) s_first[ns] = carry;
+        scan_supers<NT>(src, ns, s_first, s_scan);
         __syncthreads();
         if (blockIdx.x == 0)
             for (int s = threadIdx.x; s <= ns; s += NT) seg_first_g[s] = s_first[s];
@@ -985,7 +992,7 @@ __global__ void __launch_bounds__(kSplitWaves * 64) split_count_kernel(
     // for the capacity's bound on the segment count)
     for (uint32_t g = blockIdx.x * kSplitWaves + w;; g += gridDim.x * kSplitWaves) {
         Segment sg;
-        if (!locate_segment(views, seg_first, sup_ranges, S, g, &sg)) return;   // uniform
+        if (!locate_segment<kRest>(views, seg_first, sup_ranges, rp, g, &sg)) return;   // uniform
         const ViewDev& V = *sg.V;
         const int rb = rp.rect_bits;
         const uint32_t rmask = (1u << rb) - 1u;
@@ -1029,8 +1036,14 @@ __global__ void __launch_bounds__(kSplitWaves * 64) split_count_kernel(
             // lane t counts the pairs of this step whose mask has tile t
             cnt += (uint32_t)popc64(wave_transpose64(M));
         }
-        if (lane < TT)
-            seg_cnt[(size_t)seg_first[sg.s] * TT + (size_t)lane * sg.nseg + sg.k] = cnt;
+        if (lane < TT) {
+            seg_cnt[(size_t)g * TT + lane] = cnt;
+            const size_t grp = (size_t)(seg_first[sg.s] / (uint32_t)kSegGroup) + (size_t)sg.s +
+                               sg.k / (uint32_t)kSegGroup;
+            if (cnt != 0u) atomicAdd(&seg_groups[grp * TT + lane], cnt);
+        }
+        const uint32_t items = wave_incl_scan(cnt);   // lanes past TT count nothing
+        if (lane == 63 && items != 0u) atomicAdd(&sup_items[sg.s], (unsigned long long)items);
     }
 }
 
@@ -1042,25 +1055,112 @@ __global__ void __launch_bounds__(kSplitWaves * 64) split_count_kernel(
 // stores of neighbouring lanes mostly share cache lines. A step of more than
 // kStepItems items (a few pairs covering most of their super-tile) is stored
 // directly by the tile lanes.
+//
+// Before that, the segment's list positions: super-tile after super-tile (their
+// entry counts scanned in LDS, or in sup_base beyond kLocalSupers), tile after
+// tile, segment after segment. The first segment of a super-tile stores its
+// tiles' ranges: before compositing (kRest = false) every tile's, with its state
+// (whether its super-tile's list was cut by the prefix), in the completing split
+// those of the tiles marked incomplete, which now take their whole lists. Lists
+// that do not fit the capacity are left empty and flagged.
 constexpr int kWriteWaves = 4;
 constexpr int kStepItems = 1024;
+template <bool kRest>
 __global__ void __launch_bounds__(kWriteWaves * 64) split_write_kernel(
-    const Views* __restrict__ views, RasterDev rp, const uint32_t* __restrict__ seg_first,
-    const uint32_t* __restrict__ sup_ranges, const uint32_t* __restrict__ sentry,
-    const uint64_t* __restrict__ mask, const uint32_t* __restrict__ seg_off,
-    const uint32_t* __restrict__ counters, int64_t capacity, uint32_t* __restrict__ tile_entry) {
+    const Views* __restrict__ views, RasterDev rp, SegCountSrc<kRest> src, bool local,
+    const uint32_t* __restrict__ seg_first_g, const uint32_t* __restrict__ sup_base,
+    ItemCountSrc items, const uint32_t* __restrict__ sup_ranges,
+    const uint32_t* __restrict__ sentry, const uint64_t* __restrict__ mask,
+    const uint32_t* __restrict__ seg_cnt, const uint32_t* __restrict__ seg_groups,
+    uint32_t* __restrict__ counters, int64_t capacity, uint32_t* __restrict__ tile_entry,
+    uint32_t* __restrict__ tile_ranges, uint32_t* __restrict__ tile_state,
+    uint32_t* __restrict__ sup_redo) {
+    constexpr int NT = kWriteWaves * 64;
     __shared__ uint32_t s_ent[kWriteWaves][64];
     __shared__ uint32_t s_item[kWriteWaves][kStepItems];
     __shared__ uint32_t s_pos[kWriteWaves][kStepItems];
+    __shared__ uint32_t s_base[kLocalSupers + 1];
+    __shared__ uint32_t s_scan[NT / 64 + 1];
+    if (kRest && src.count() == 0) return;   // uniform: no tile needs more
     const int w = threadIdx.x / 64, lane = threadIdx.x % 64;
     const int S = rp.super_tile, TT = S * S;
-    if ((int64_t)items_total(counters) > capacity) return;   // overflow: the tile lists stay empty
+    const int ns = views->total_supers;
+    const uint32_t* seg_first = seg_first_g;
+    const uint32_t* base = sup_base;
+    if (local) {   // uniform
+        scan_supers<NT>(items, ns, s_base, s_scan);
+        __syncthreads();
+        base = s_base;
+    }
+    // the completing split's lists lie after the prefix lists
+    const uint32_t origin = kRest ? counters[kItems] : 0u;
+    const uint32_t total = base[ns];
+    const bool overflow = (int64_t)sat_add(origin, total) > capacity;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        counters[kRest ? kItemsRest : kItems] = total;
+        if (overflow) atomicOr(&counters[kStatus], (uint32_t)SGS_STATUS_PAIR_OVERFLOW);
+    }
+    if (!kRest) {
+        // lists without a segment, and the flags the compositing sets
+        uint32_t units = 0;
+        for (int s = blockIdx.x * NT + threadIdx.x; s < ns; s += gridDim.x * NT) {
+            sup_redo[s] = 0u;
+            units += list_units(pairs_to_split<kRest>(sup_ranges, sup_redo,
+                                                      (uint32_t)rp.prefix_segs, s));
+            if (seg_first[s + 1] != seg_first[s]) continue;
+            int vi = 0;
+            while (vi + 1 < views->n && s >= views->v[vi + 1].sup_offset) ++vi;
+            const ViewDev& V = views->v[vi];
+            const int ls = s - V.sup_offset;
+            const int tx0 = (ls % V.sup_x) * S, ty0 = (ls / V.sup_x) * S;
+            for (int y = ty0; y < min(ty0 + S, V.tiles_y); ++y)
+                for (int x = tx0; x < min(tx0 + S, V.tiles_x); ++x) {
+                    const int t = V.tile_offset + y * V.tiles_x + x;
+                    tile_ranges[2 * t] = tile_ranges[2 * t + 1] = 0u;
+                    tile_state[t] = kTileWhole;
+                }
+        }
+        units = wave_incl_scan(units);
+        if (lane == 63 && units != 0u) atomicAdd(&counters[kSegments], units);
+    }
     for (uint32_t g = blockIdx.x * kWriteWaves + w;; g += gridDim.x * kWriteWaves) {
         Segment sg;
-        if (!locate_segment(views, seg_first, sup_ranges, S, g, &sg)) return;
+        if (!locate_segment<kRest>(views, seg_first, sup_ranges, rp, g, &sg)) return;   // uniform
         // lane t: next list position of tile t
-        const size_t base = (size_t)seg_first[sg.s] * TT + sg.k;
-        uint32_t run = lane < TT ? seg_off[base + (size_t)lane * sg.nseg] : 0u;
+        uint32_t tot = 0, before = 0;
+        if (lane < TT) {
+            const int kg = (int)(sg.k / (uint32_t)kSegGroup), kr = (int)(sg.k % (uint32_t)kSegGroup);
+            const size_t grp = (size_t)(seg_first[sg.s] / (uint32_t)kSegGroup) + (size_t)sg.s;
+            for_rows(seg_groups + grp * TT + lane, TT, 0,
+                     (int)((sg.nseg + (uint32_t)kSegGroup - 1u) / (uint32_t)kSegGroup), 1,
+                     [&](int j, uint32_t c) {
+                         tot += c;
+                         before += j < kg ? c : 0u;
+                     });
+            for_rows(seg_cnt + (size_t)(g - (uint32_t)kr) * TT + lane, TT, 0, kr, 1,
+                     [&](int, uint32_t c) { before += c; });
+        }
+        const uint32_t first = origin + base[sg.s] + wave_incl_scan(tot) - tot;
+        uint32_t run = first + before;
+        if (sg.k == 0u && lane < TT) {
+            const ViewDev& V = *sg.V;
+            const int x = sg.tx0 + lane % S, y = sg.ty0 + lane / S;
+            if (x < V.tiles_x && y < V.tiles_y) {
+                const int t = V.tile_offset + y * V.tiles_x + x;
+                if (!kRest || tile_state[t] == kTileIncomplete) {
+                    tile_ranges[2 * t] = overflow ? 0u : first;
+                    tile_ranges[2 * t + 1] = overflow ? 0u : first + tot;
+                }
+                if (!kRest) {
+                    const uint32_t len = sup_ranges[2 * sg.s + 1] - sup_ranges[2 * sg.s];
+                    tile_state[t] = list_cut(len, (uint32_t)rp.prefix_segs) ? kTileTruncated
+                                                                            : kTileWhole;
+                }
+            }
+        }
+        // (a second compositing of the same lists completes nothing again)
+        if (kRest && sg.k == 0u && lane == 0) sup_redo[sg.s] = 0u;
+        if (overflow) continue;   // the tile lists stay empty
         for (uint32_t p0 = sg.a; p0 < sg.b; p0 += 64) {
             const uint32_t p = p0 + (uint32_t)lane;
             const bool valid = p < sg.b;
@@ -1090,51 +1190,6 @@ __global__ void __launch_bounds__(kWriteWaves * 64) split_write_kernel(
     }
 }
 
-// [start, end) of tile lists. After the split of the list prefixes (rest =
-// false): every tile's, with its state (whether its super-tile's list was
-// cut by the prefix); it also clears the super-tile redo flags, flags a
-// tile-list overflow (all lists empty then) and records the segment count.
-// After the completing split (rest = true): only the tiles marked
-// incomplete, which now take their whole lists (empty on overflow).
-__global__ void __launch_bounds__(256) tile_ranges_kernel(
-    const Views* __restrict__ views, RasterDev rp, const uint32_t* __restrict__ sup_ranges,
-    const uint32_t* __restrict__ seg_first, const uint32_t* __restrict__ seg_cnt,
-    const uint32_t* __restrict__ seg_off, uint32_t* __restrict__ counters, int64_t capacity,
-    uint32_t* __restrict__ tile_ranges, uint32_t* __restrict__ tile_state,
-    uint32_t* __restrict__ sup_redo, bool rest) {
-    if (rest && counters[kRedo] == 0u) return;
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const bool overflow = (int64_t)items_total(counters) > capacity;
-    if (t == 0) {
-        if (!rest) counters[kSegments] = seg_first[views->total_supers];
-        if (overflow) atomicOr(&counters[kStatus], (uint32_t)SGS_STATUS_PAIR_OVERFLOW);
-    }
-    if (!rest && t < views->total_supers) sup_redo[t] = 0u;
-    if (t >= views->total_tiles) return;
-    if (rest && tile_state[t] != kTileIncomplete) return;
-    int vi = 0;
-    while (vi + 1 < views->n && t >= views->v[vi + 1].tile_offset) ++vi;
-    const ViewDev& V = views->v[vi];
-    const int local = (int)t - V.tile_offset;
-    const int tx = local % V.tiles_x, ty = local / V.tiles_x;
-    const int S = rp.super_tile, TT = S * S;
-    const int s = V.sup_offset + (ty / S) * V.sup_x + tx / S;
-    if (!rest)
-        tile_state[t] = split_segments(list_segments(sup_ranges, s), (uint32_t)rp.prefix_segs) <
-                                list_segments(sup_ranges, s)
-                            ? kTileTruncated
-                            : kTileWhole;
-    const uint32_t nseg = seg_first[s + 1] - seg_first[s];
-    uint32_t a = 0, b = 0;
-    if (nseg > 0 && !overflow) {
-        const size_t i0 = (size_t)seg_first[s] * TT + (size_t)((ty % S) * S + tx % S) * nseg;
-        a = seg_off[i0];
-        b = seg_off[i0 + nseg - 1] + seg_cnt[i0 + nseg - 1];
-    }
-    tile_ranges[2 * t] = a;
-    tile_ranges[2 * t + 1] = b;
-}
-
 }  // namespace
 
 hipError_t launch_store_views(const Views& views, Views* dst, hipStream_t s) {
@@ -1159,13 +1214,12 @@ hipError_t fill_u32(uint32_t* p, int64_t n, uint32_t v, hipStream_t s) {
     return hipGetLastError();
 }
 
-// The split of the sorted super-tile lists into tile lists: of the first
-// rp.prefix_segs segments of the long ones, the others whole, before
-// compositing (rest = false), or
-// of the whole lists of the super-tiles flagged by that compositing, placed
-// after the prefix lists (rest = true; predicated on counters[kRedo]).
-static hipError_t launch_split(const RasterDev& rp, const Layout& L, char* ws, hipStream_t s,
-                               bool rest) {
+// The split of the sorted super-tile lists into tile lists: of the prefixes of
+// the long ones, the others whole, before compositing (kRest = false), or of the
+// whole lists of the super-tiles flagged by that compositing, placed after the
+// prefix lists (kRest = true; predicated on counters[kRedo]).
+template <bool kRest>
+static hipError_t launch_split(const RasterDev& rp, const Layout& L, char* ws, hipStream_t s) {
     if (L.total_supers == 0 || L.total_tiles == 0) return hipSuccess;
     const Views* views = reinterpret_cast<const Views*>(ws + L.views);
     uint32_t* counters = reinterpret_cast<uint32_t*>(ws + L.counters);
@@ -1175,64 +1229,50 @@ static hipError_t launch_split(const RasterDev& rp, const Layout& L, char* ws, h
     const float4* rec = reinterpret_cast<const float4*>(ws + L.records);
     uint32_t* seg_first = reinterpret_cast<uint32_t*>(ws + L.seg_first);
     uint32_t* seg_cnt = reinterpret_cast<uint32_t*>(ws + L.seg_cnt);
-    uint32_t* seg_off = reinterpret_cast<uint32_t*>(ws + L.seg_off);
+    uint32_t* seg_groups = reinterpret_cast<uint32_t*>(ws + L.seg_groups[kRest]);
     uint64_t* mask = reinterpret_cast<uint64_t*>(ws + L.pair_mask);
-    uint32_t* tile_entry = reinterpret_cast<uint32_t*>(ws + L.tile_entry);
-    uint32_t* tile_ranges = reinterpret_cast<uint32_t*>(ws + L.tile_ranges);
-    uint32_t* tile_state = reinterpret_cast<uint32_t*>(ws + L.tile_state);
     uint32_t* sup_redo = reinterpret_cast<uint32_t*>(ws + L.sup_redo);
-    uint32_t* sums = reinterpret_cast<uint32_t*>(ws + L.scan_sums);
-    const int tt = rp.super_tile * rp.super_tile;
+    uint32_t* sup_base = reinterpret_cast<uint32_t*>(ws + L.sup_base);
+    const SegCountSrc<kRest> src{ranges, sup_redo, counters + kRedo, L.total_supers,
+                                 (uint32_t)rp.prefix_segs, rp.seg_log2};
+    const ItemCountSrc items{reinterpret_cast<const uint64_t*>(ws + L.sup_items[kRest]),
+                             L.total_supers};
     hipError_t err;
     // segments to split; their total -> seg_first[total_supers] (formed by
     // the count kernel itself when the super-tiles are few)
-    const RestSegSrc rsrc{ranges, sup_redo, counters + kRedo, L.total_supers};
-    const SegCountSrc psrc{ranges, L.total_supers, (uint32_t)rp.prefix_segs};
     const bool local = L.total_supers <= kLocalSupers;
     if (!local) {
-        if (rest)
-            hipLaunchKernelGGL(seg_scan_kernel<RestSegSrc>, dim3(1), dim3(kSegScanThreads), 0, s,
-                               rsrc, seg_first);
-        else
-            hipLaunchKernelGGL(seg_scan_kernel<SegCountSrc>, dim3(1), dim3(kSegScanThreads), 0, s,
-                               psrc, seg_first);
+        hipLaunchKernelGGL(seg_scan_kernel<SegCountSrc<kRest>>, dim3(1), dim3(kSegScanThreads), 0, s,
+                           src, seg_first);
         if ((err = hipGetLastError()) != hipSuccess) return err;
     }
     // grid-stride over the segments: at most a few resident waves per SIMD
     // (the completing split, usually idle and otherwise a few super-tiles,
     // on a quarter of the grid)
-    const int64_t blocks = rest ? kSplitBlocks / 4 : kSplitBlocks;
-    const dim3 sgrid((unsigned)std::min<int64_t>((L.seg_slots + kSplitWaves - 1) / kSplitWaves,
-                                                 blocks));
+    static_assert(kSplitWaves == kWriteWaves, "one grid");
+    const int64_t blocks = kRest ? kSplitBlocks / 4 : kSplitBlocks;
+    const dim3 grid((unsigned)std::min<int64_t>((L.seg_slots + kSplitWaves - 1) / kSplitWaves,
+                                                blocks));
     const uint32_t entries = (uint32_t)std::max<int64_t>(1, L.entries);
-    if (rest)
-        hipLaunchKernelGGL(split_count_kernel<RestSegSrc>, sgrid, dim3(kSplitWaves * 64), 0, s,
-                           views, rp, rsrc, local, seg_first, ranges, skey, sentry, rec, entries,
-                           mask, seg_cnt);
-    else
-        hipLaunchKernelGGL(split_count_kernel<SegCountSrc>, sgrid, dim3(kSplitWaves * 64), 0, s,
-                           views, rp, psrc, local, seg_first, ranges, skey, sentry, rec, entries,
-                           mask, seg_cnt);
+    hipLaunchKernelGGL(split_count_kernel<kRest>, grid, dim3(kSplitWaves * 64), 0, s, views, rp, src,
+                       local, seg_first, ranges, skey, sentry, rec, entries, mask, seg_cnt,
+                       seg_groups, reinterpret_cast<unsigned long long*>(ws + L.sup_items[kRest]));
     if ((err = hipGetLastError()) != hipSuccess) return err;
-    // list positions (the completing split's after the prefix lists); the
-    // number of entries -> counters[kItems] or counters[kItemsRest]
-    err = device_scan(ItemCountSrc{seg_cnt, seg_first + L.total_supers, tt},
-                      ItemOffSink{seg_off, rest ? counters + kItems : nullptr}, L.seg_slots * tt,
-                      sums, counters + (rest ? kItemsRest : kItems), s);
-    if (err != hipSuccess) return err;
-    const dim3 wgrid((unsigned)std::min<int64_t>((L.seg_slots + kWriteWaves - 1) / kWriteWaves,
-                                                 blocks));
-    hipLaunchKernelGGL(split_write_kernel, wgrid, dim3(kWriteWaves * 64), 0, s, views, rp,
-                       seg_first, ranges, sentry, mask, seg_off, counters, L.capacity, tile_entry);
-    if ((err = hipGetLastError()) != hipSuccess) return err;
-    hipLaunchKernelGGL(tile_ranges_kernel, dim3((unsigned)((L.total_tiles + 255) / 256)), dim3(256),
-                       0, s, views, rp, ranges, seg_first, seg_cnt, seg_off, counters, L.capacity,
-                       tile_ranges, tile_state, sup_redo, rest);
+    if (!local) {
+        hipLaunchKernelGGL(seg_scan_kernel<ItemCountSrc>, dim3(1), dim3(kSegScanThreads), 0, s, items,
+                           sup_base);
+        if ((err = hipGetLastError()) != hipSuccess) return err;
+    }
+    hipLaunchKernelGGL(split_write_kernel<kRest>, grid, dim3(kWriteWaves * 64), 0, s, views, rp, src,
+                       local, seg_first, sup_base, items, ranges, sentry, mask, seg_cnt, seg_groups,
+                       counters, L.capacity, reinterpret_cast<uint32_t*>(ws + L.tile_entry),
+                       reinterpret_cast<uint32_t*>(ws + L.tile_ranges),
+                       reinterpret_cast<uint32_t*>(ws + L.tile_state), sup_redo);
     return hipGetLastError();
 }
 
 hipError_t launch_split_rest(const RasterDev& rp, const Layout& L, char* ws, hipStream_t s) {
-    return launch_split(rp, L, ws, s, true);
+    return launch_split<true>(rp, L, ws, s);
 }
 
 hipError_t launch_bin(const RasterDev& rp, int64_t n, const Layout& L, char* ws, hipStream_t s) {
@@ -1305,7 +1345,7 @@ hipError_t launch_bin(const RasterDev& rp, int64_t n, const Layout& L, char* ws,
         hipLaunchKernelGGL(ranges_kernel, rgrid, dim3(256), 0, s, pkey[L.key_result], counters,
                            L.total_supers, L.key_bits, ranges);
     if ((err = hipGetLastError()) != hipSuccess) return err;
-    return launch_split(rp, L, ws, s, false);
+    return launch_split<false>(rp, L, ws, s);
 }
 
 hipError_t launch_order_tiles(const uint32_t* cost, int64_t tiles, int shift, uint32_t* order,

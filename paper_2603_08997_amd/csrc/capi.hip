@@ -95,6 +95,7 @@ sgs_status prepare(const sgs_raster_params* rp, int64_t n, const sgs_camera* cam
                     "super-tiles", (long long)P->L.total_supers, P->rd.super_tile);
     P->rd.key_bits = P->L.key_bits;
     P->rd.rect_bits = P->L.rect_bits;
+    P->rd.seg_log2 = P->L.seg_log2;
     return SGS_OK;
 }
 
@@ -194,6 +195,7 @@ RasterDev make_raster(const sgs_raster_params* rp) {
     r.prefix_segs = (int32_t)((rp->split_prefix + kSegPairs - 1) / kSegPairs);
     r.key_bits = 0;   // set with the layout
     r.rect_bits = 0;
+    r.seg_log2 = 0;
     for (int k = 0; k < 3; ++k) r.bg[k] = rp->bg[k];
     r.near_z = rp->near_z;
     r.dilation = rp->dilation;
@@ -212,10 +214,10 @@ void make_layout(const Views& views, const RasterDev& rp, int64_t n, int64_t cap
     L->total_pixels = views.total_pixels;
     L->capacity = capacity;
     L->batch = rp.batch;
-    L->seg_slots = segment_slots(capacity, L->total_supers);
+    L->seg_log2 = seg_log2_for(L->entries);
+    L->seg_slots = segment_slots(capacity, L->total_supers, L->seg_log2);
     const int64_t tt = (int64_t)rp.super_tile * rp.super_tile;
-    // the scans run over the entries and over the (segment, tile) counts
-    L->scan_blocks = (std::max(L->entries, L->seg_slots * tt) + 2047) / 2048;
+    L->scan_blocks = (L->entries + 2047) / 2048;
     // few super-tiles: pairs placed directly, in at most 2048 blocks
     L->direct = L->total_supers <= kDirectSupers;
     L->pair_rounds = 1;
@@ -274,11 +276,18 @@ void make_layout(const Views& views, const RasterDev& rp, int64_t n, int64_t cap
                 : 0);
     L->pair_sort_groups =
         take(SC ? sizeof(uint32_t) * (size_t)radix_group_words(capacity, radix_passes(bits)) : 0);
+    // of the split before compositing and of the completing one
+    for (int k = 0; k < 2; ++k) {
+        L->seg_groups[k] =
+            take(sizeof(uint32_t) *
+                 (size_t)(segment_group_slots(L->seg_slots, L->total_supers) * tt));
+        L->sup_items[k] = take(sizeof(uint64_t) * (size_t)L->total_supers);
+    }
     L->clear_words = (off - L->clear_begin) / sizeof(uint32_t);
     L->sup_ranges = take(sizeof(uint32_t) * 2 * (size_t)L->total_supers);
     L->seg_first = take(sizeof(uint32_t) * (size_t)(L->total_supers + 1));
     L->seg_cnt = take(sizeof(uint32_t) * (size_t)(L->seg_slots * tt));
-    L->seg_off = take(sizeof(uint32_t) * (size_t)(L->seg_slots * tt));
+    L->sup_base = take(sizeof(uint32_t) * (size_t)(L->total_supers + 1));
     L->pair_mask = take(sizeof(uint64_t) * (size_t)capacity);
     L->tile_entry = take(sizeof(uint32_t) * (size_t)capacity);
     L->tile_ranges = take(sizeof(uint32_t) * 2 * (size_t)L->total_tiles);

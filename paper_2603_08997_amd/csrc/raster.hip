@@ -774,7 +774,8 @@ hipError_t launch_rasterize(const RasterDev& rp, const Layout& L, char* ws, floa
     uint32_t* cost = reinterpret_cast<uint32_t*>(ws + L.tile_cost);
     uint32_t* stats = reinterpret_cast<uint32_t*>(ws + L.tile_stats);
     const uint32_t entries = (uint32_t)std::max<int64_t>(1, L.entries);
-    uint32_t* state = rp.prefix_segs > 0 ? reinterpret_cast<uint32_t*>(ws + L.tile_state) : nullptr;
+    // (no second pass where no list can be cut)
+    uint32_t* state = lists_cut(rp, L) ? reinterpret_cast<uint32_t*>(ws + L.tile_state) : nullptr;
     uint32_t* sup_redo = reinterpret_cast<uint32_t*>(ws + L.sup_redo);
     uint32_t* resume = reinterpret_cast<uint32_t*>(ws + L.tile_resume);
     // the waves of a tile are one workgroup

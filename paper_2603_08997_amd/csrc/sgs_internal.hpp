@@ -50,7 +50,8 @@ struct RasterDev {
     int32_t batch;         // list entries per compositing batch (and per list chunk)
     int32_t key_bits;      // low bits of a pair key: the super-tile index
     int32_t rect_bits;     // bits per coordinate of the tile rectangle above them
-    int32_t prefix_segs;   // segments of a long super-tile list split before compositing (0: all)
+    int32_t prefix_segs;   // 512-pair segments of a long super-tile list split before compositing (0: all)
+    int32_t seg_log2;      // log2 of the pairs a wave of the split takes
     float bg[3];
     float near_z, dilation, alpha_min, alpha_max, t_min;
     float log2_alpha_min;  // log2(alpha_min), rounded from binary64 (-inf for 0)
@@ -113,22 +114,46 @@ constexpr int64_t emit_windows(int64_t entries, int64_t capacity) {
     return (capacity + kEmitHead * entries + kEmitWindow - 1) / kEmitWindow;
 }
 
-// The split of the super-tile lists into tile lists works on segments of
-// kSegPairs consecutive pairs of one super-tile's list (a super-tile of L
-// pairs has ceil(L / kSegPairs) segments). Segment slots: an upper bound on
-// the number of segments of any batch with `capacity` pairs.
+// The split of the super-tile lists into tile lists. The prefix of a long list
+// counts in units of kSegPairs pairs.
 constexpr int64_t kSegPairs = 512;
-constexpr int64_t segment_slots(int64_t capacity, int64_t supers) {
-    return (capacity + kSegPairs - 1) / kSegPairs + supers;
-}
 
 // With a split prefix, a super-tile list longer than kCutFactor prefixes is
-// split only in its first prefix_segs segments before compositing (the tiles
+// split only in its first prefix_segs units before compositing (the tiles
 // that composite a whole short list, often into the background, never wait
 // for a second split; long lists are where the split's work is).
 constexpr uint32_t kCutFactor = 4;
-__host__ __device__ constexpr uint32_t split_segments(uint32_t segs, uint32_t prefix_segs) {
-    return prefix_segs > 0 && segs > kCutFactor * prefix_segs ? prefix_segs : segs;
+__host__ __device__ constexpr uint32_t list_units(uint32_t len) {
+    return (uint32_t)(((uint64_t)len + kSegPairs - 1) / kSegPairs);
+}
+// Whether a list of at most `len` pairs can be cut, and the pairs of one that
+// are split before compositing.
+__host__ __device__ constexpr bool list_cut(uint32_t len, uint32_t prefix_segs) {
+    return prefix_segs > 0 && list_units(len) > (uint64_t)kCutFactor * prefix_segs;
+}
+__host__ __device__ constexpr uint32_t split_pairs(uint32_t len, uint32_t prefix_segs) {
+    return list_cut(len, prefix_segs) ? prefix_segs * (uint32_t)kSegPairs : len;
+}
+// A wave of the split takes a segment of 2^seg_log2 consecutive pairs (64 to
+// 512) of one super-tile's list: short ones where there are few pairs, since
+// every 64 pairs are a step of a chain of loads, long ones where there are many,
+// since every segment adds to its super-tile's counts by atomics. us of all split
+// kernels for 64 / 128 / 256 / 512 pairs: 1000 entries 16 / 22 / 32 / 51, 30k 23 /
+// 26 / 39 / 66, 300k 78 / 54 / 56 / 78, 1M 105 / 72 / 64 / 84, 3M 153 / 109 / 103 /
+// 109, 6M (with a completing split) 136 / 111 / 117 / 168, 16M 1168 / 712 / 555 /
+// 506.
+constexpr int seg_log2_for(int64_t entries) {
+    return entries <= (1 << 16) ? 6 : entries <= (1 << 19) ? 7 : entries <= (1 << 23) ? 8 : 9;
+}
+// Slots: an upper bound on the segments of any batch with `capacity` pairs, and
+// on the groups of kSegGroup segments whose tile counts are summed up together
+// (group j of super-tile s: slot first segment / kSegGroup + s + j).
+constexpr int64_t kSegGroup = 16;
+constexpr int64_t segment_slots(int64_t capacity, int64_t supers, int seg_log2) {
+    return ((capacity - 1) >> seg_log2) + 1 + supers;
+}
+constexpr int64_t segment_group_slots(int64_t slots, int64_t supers) {
+    return slots / kSegGroup + supers + 1;
 }
 // Per tile (tile_state):
 enum TileState : uint32_t {
@@ -143,17 +168,24 @@ struct Layout {
     int64_t scan_blocks;
     int64_t pair_blocks;   // blocks of the direct pair path
     int pair_rounds;       // kPairEntries entries each there
+    int seg_log2;
     int key_bits, rect_bits, key_result;  // result buffer (0/1) of the super-tile lists
     int batch;
     bool direct;           // pairs counted and placed directly (few super-tiles)
     size_t views, records, tiles, depth, dkey[2], dval[2], offsets, window_first, scan_sums,
         pair_info, pair_sorted, pair_hist, pair_groups, pair_key[2], pair_entry[2], sort_hist, sort_groups,
-        pair_sort_groups, sort_weights, sup_ranges, seg_first, seg_cnt,
-        seg_off, pair_mask, tile_entry, tile_ranges, tile_state, tile_resume, sup_redo, tile_cost,
+        pair_sort_groups, sort_weights, sup_ranges, seg_first, seg_cnt, seg_groups[2],
+        sup_items[2], sup_base, pair_mask, tile_entry, tile_ranges, tile_state, tile_resume, sup_redo, tile_cost,
         tile_stats, tile_order, t_final, n_last, accum, counters, total;
     // the region a binning pass accumulates into and finds cleared
     size_t clear_begin, clear_words;
 };
+
+// Whether a super-tile list of the batch can be cut by the split prefix (a list
+// holds at most one view's Gaussians).
+inline bool lists_cut(const RasterDev& rp, const Layout& L) {
+    return list_cut((uint32_t)(L.entries / L.n_views), (uint32_t)rp.prefix_segs);
+}
 
 bool make_views(const sgs_camera* cams, int n_views, const sgs_raster_params* rp, Views* out,
                 const char** err);
