@@ -634,54 +634,15 @@ __global__ void __launch_bounds__(256) ranges_kernel(const uint32_t* __restrict_
     ranges[2 * t + 1] = empty ? 0u : lo;
 }
 
-// Counting sort of the tiles by cost >> shift, largest first, in one
-// workgroup: bucket counts in LDS, their exclusive scan, then every tile takes
-// the next slot of its bucket.
-constexpr int kOrderThreads = 1024;
-__global__ void __launch_bounds__(kOrderThreads) order_tiles_kernel(
-    const uint32_t* __restrict__ cost, int64_t tiles, int shift, uint32_t* __restrict__ order,
-    const int32_t* __restrict__ gate) {
-    if (gate != nullptr && gate_closed(gate)) return;
-    __shared__ uint32_t slot[kOrderThreads];
-    __shared__ uint32_t smem[kOrderThreads / 64 + 1];
-    const int tid = threadIdx.x;
-    auto bucket = [&](int64_t t) {
-        return (uint32_t)(kOrderThreads - 1) - min(cost[t] >> shift, (uint32_t)(kOrderThreads - 1));
-    };
-    slot[tid] = 0;
-    __syncthreads();
-    for (int64_t t = tid; t < tiles; t += kOrderThreads) atomicAdd(&slot[bucket(t)], 1u);
-    __syncthreads();
-    const uint32_t c = slot[tid];
-    uint32_t tot;
-    const uint32_t first = block_excl_scan<kOrderThreads>(c, smem, &tot);
-    __syncthreads();
-    slot[tid] = first;
-    __syncthreads();
-    for (int64_t t = tid; t < tiles; t += kOrderThreads)
-        order[atomicAdd(&slot[bucket(t)], 1u)] = (uint32_t)t;
-}
-
-// The call's view table into the workspace, word by word: the views passed
-// by value or, with a camera table, its entry *d_view (clamped into range) as
-// view 0 of a one-view batch (table entries are stored for that position).
-__device__ __forceinline__ void store_views(const Views& v, const ViewDev* table, int n_table,
-                                            const int32_t* d_view, Views* dst) {
-    static_assert(sizeof(Views) % 4 == 0 && sizeof(ViewDev) % 4 == 0, "word copy");
-    constexpr int kWords = (int)(sizeof(Views) / 4), kViewWords = (int)(sizeof(ViewDev) / 4);
-    const uint32_t* src = reinterpret_cast<const uint32_t*>(&v);
-    const uint32_t* sel = nullptr;
-    if (table != nullptr) {
-        const int i = min(max(*d_view, 0), n_table - 1);
-        sel = reinterpret_cast<const uint32_t*>(table + i);
-    }
-    uint32_t* out = reinterpret_cast<uint32_t*>(dst);
-    for (int w = threadIdx.x; w < kWords; w += blockDim.x)
-        out[w] = (sel != nullptr && w < kViewWords) ? sel[w] : src[w];
-}
-
-__global__ void __launch_bounds__(64) store_views_kernel(Views v, Views* __restrict__ dst) {
+__global__ void __launch_bounds__(64) store_views_kernel(Views v, Views* __restrict__ dst,
+                                                         uint32_t* __restrict__ counters,
+                                                         int32_t* step,
+                                                         const int32_t* __restrict__ gate) {
     store_views(v, nullptr, 0, nullptr, dst);
+    // what compositing adds up
+    if (counters != nullptr && threadIdx.x < 4) counters[kBlended + threadIdx.x] = 0u;
+    if (counters != nullptr && threadIdx.x == 4) counters[kUsed] = 0u;
+    if (step != nullptr && threadIdx.x == 0 && !gate_closed(gate)) *step += 1;
 }
 
 // The first launch of a call that bins: block 0 stores the views and clears the
@@ -1192,8 +1153,10 @@ __global__ void __launch_bounds__(kWriteWaves * 64) split_write_kernel(
 
 }  // namespace
 
-hipError_t launch_store_views(const Views& views, Views* dst, hipStream_t s) {
-    hipLaunchKernelGGL(store_views_kernel, dim3(1), dim3(64), 0, s, views, dst);
+hipError_t launch_store_views(const Views& views, Views* dst, hipStream_t s, uint32_t* counters,
+                              int32_t* step, const int32_t* gate) {
+    hipLaunchKernelGGL(store_views_kernel, dim3(1), dim3(64), 0, s, views, dst, counters, step,
+                       gate);
     return hipGetLastError();
 }
 
@@ -1346,14 +1309,6 @@ hipError_t launch_bin(const RasterDev& rp, int64_t n, const Layout& L, char* ws,
                            L.total_supers, L.key_bits, ranges);
     if ((err = hipGetLastError()) != hipSuccess) return err;
     return launch_split<false>(rp, L, ws, s);
-}
-
-hipError_t launch_order_tiles(const uint32_t* cost, int64_t tiles, int shift, uint32_t* order,
-                              const int32_t* gate, hipStream_t s) {
-    if (tiles <= 0) return hipSuccess;
-    hipLaunchKernelGGL(order_tiles_kernel, dim3(1), dim3(kOrderThreads), 0, s, cost, tiles, shift,
-                       order, gate);
-    return hipGetLastError();
 }
 
 }  // namespace sgs

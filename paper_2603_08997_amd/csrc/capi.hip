@@ -295,7 +295,7 @@ void make_layout(const Views& views, const RasterDev& rp, int64_t n, int64_t cap
     L->tile_resume = take(sizeof(uint32_t) * (size_t)L->total_tiles);
     L->sup_redo = take(sizeof(uint32_t) * (size_t)L->total_supers);
     L->tile_cost = take(sizeof(uint32_t) * (size_t)L->total_tiles);
-    L->tile_stats = take(sizeof(uint32_t) * 2 * (size_t)L->total_tiles);
+    L->tile_stats = take(sizeof(uint32_t) * 4 * (size_t)L->total_tiles);
     L->tile_order = take(sizeof(uint32_t) * (size_t)L->total_tiles);
     L->t_final = take(sizeof(float) * (size_t)L->total_pixels);
     L->n_last = take(sizeof(uint32_t) * (size_t)L->total_pixels);
@@ -404,20 +404,25 @@ sgs_status sgs_get_workspace_layout(const sgs_raster_params* rp, int64_t n, cons
 
 namespace {
 
-// Validated arguments of a render-path call and the call's view table stored
-// into its workspace (the first launch of every call); bins: the call bins, and
-// what binning accumulates into is cleared too.
+// Validated arguments of a render-path call. What its first launch does besides
+// is up to the call: the views stored into the workspace (kStore), for a call
+// that starts by binning or by compositing also what that adds up cleared (kBin,
+// kComposite), or nothing here, where a later launch takes it along (kLater).
+enum class First { kStore, kBin, kComposite, kLater };
 sgs_status begin_call(const sgs_raster_params* rp, int64_t n, const sgs_camera* cams,
                       int32_t n_views, void* workspace, size_t workspace_bytes,
-                      int64_t pair_capacity, hipStream_t s, Prepared* P, bool bins = false) {
+                      int64_t pair_capacity, hipStream_t s, Prepared* P, First first) {
     sgs_status st = prepare(rp, n, cams, n_views, pair_capacity, P);
     if (st != SGS_OK) return st;
     if ((st = check_ws(*P, workspace, workspace_bytes)) != SGS_OK) return st;
     char* ws = static_cast<char*>(workspace);
-    if (bins)
+    if (first == First::kBin)
         SGS_HIP(sgs::launch_begin_bin(P->views, nullptr, 0, nullptr, P->L, ws, s), "store views");
-    else
-        SGS_HIP(sgs::launch_store_views(P->views, reinterpret_cast<sgs::Views*>(ws + P->L.views), s),
+    else if (first != First::kLater)
+        SGS_HIP(sgs::launch_store_views(P->views, reinterpret_cast<sgs::Views*>(ws + P->L.views), s,
+                                        first == First::kComposite
+                                            ? reinterpret_cast<uint32_t*>(ws + P->L.counters)
+                                            : nullptr),
                 "store views");
     return SGS_OK;
 }
@@ -432,10 +437,11 @@ sgs_status sgs_project(const sgs_gaussians* g, const sgs_camera* cams, int32_t n
     hipStream_t s = static_cast<hipStream_t>(stream);
     Prepared P;
     if ((st = begin_call(rp, g->n, cams, n_views, workspace, workspace_bytes, pair_capacity, s,
-                         &P)) != SGS_OK)
+                         &P, First::kLater)) != SGS_OK)
         return st;
     SGS_HIP(sgs::launch_project(g->data, g->n, g->stride, g->sh_degree, P.rd, P.L,
-                                static_cast<char*>(workspace), s),
+                                static_cast<char*>(workspace),
+                                sgs::CallViews{&P.views, nullptr, 0, nullptr, false}, s),
             "project");
     return SGS_OK;
 }
@@ -451,7 +457,8 @@ sgs_status sgs_load_records(const sgs_camera* cams, int32_t n_views, int64_t n,
     if (P.L.entries > 0 && (!u || !v || !depth || !extent || !conic || !opacity || !rgb))
         return fail(SGS_ERR_INVALID_ARG, "record arrays are null");
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if ((st = begin_call(rp, n, cams, n_views, workspace, workspace_bytes, pair_capacity, s, &P)) !=
+    if ((st = begin_call(rp, n, cams, n_views, workspace, workspace_bytes, pair_capacity, s, &P,
+                         First::kStore)) !=
         SGS_OK)
         return st;
     SGS_HIP(sgs::launch_load_records(u, v, depth, extent, conic, opacity, rgb, n, P.rd, P.L,
@@ -465,7 +472,7 @@ sgs_status sgs_bin(const sgs_camera* cams, int32_t n_views, int64_t n, const sgs
     hipStream_t s = static_cast<hipStream_t>(stream);
     Prepared P;
     sgs_status st = begin_call(rp, n, cams, n_views, workspace, workspace_bytes, pair_capacity, s,
-                               &P, true);
+                               &P, First::kBin);
     if (st != SGS_OK) return st;
     SGS_HIP(sgs::launch_bin(P.rd, n, P.L, static_cast<char*>(workspace), s), "bin");
     return SGS_OK;
@@ -477,7 +484,8 @@ sgs_status sgs_rasterize(const sgs_camera* cams, int32_t n_views, int64_t n,
     if (!out_rgb) return fail(SGS_ERR_INVALID_ARG, "out_rgb is null");
     hipStream_t s = static_cast<hipStream_t>(stream);
     Prepared P;
-    sgs_status st = begin_call(rp, n, cams, n_views, workspace, workspace_bytes, pair_capacity, s, &P);
+    sgs_status st = begin_call(rp, n, cams, n_views, workspace, workspace_bytes, pair_capacity, s, &P,
+                               First::kComposite);
     if (st != SGS_OK) return st;
     SGS_HIP(sgs::launch_rasterize(P.rd, P.L, static_cast<char*>(workspace), out_rgb, s),
             "rasterize");
@@ -493,10 +501,11 @@ sgs_status sgs_render_forward(const sgs_gaussians* g, const sgs_camera* cams, in
     hipStream_t s = static_cast<hipStream_t>(stream);
     Prepared P;
     if ((st = begin_call(rp, g->n, cams, n_views, workspace, workspace_bytes, pair_capacity, s,
-                         &P, true)) != SGS_OK)
+                         &P, First::kLater)) != SGS_OK)
         return st;
     char* ws = static_cast<char*>(workspace);
-    SGS_HIP(sgs::launch_project(g->data, g->n, g->stride, g->sh_degree, P.rd, P.L, ws, s),
+    SGS_HIP(sgs::launch_project(g->data, g->n, g->stride, g->sh_degree, P.rd, P.L, ws,
+                                sgs::CallViews{&P.views, nullptr, 0, nullptr, true}, s),
             "project");
     SGS_HIP(sgs::launch_bin(P.rd, g->n, P.L, ws, s), "bin");
     SGS_HIP(sgs::launch_rasterize(P.rd, P.L, ws, out_rgb, s), "rasterize");
@@ -510,10 +519,11 @@ sgs_status sgs_rasterize_backward(const sgs_camera* cams, int32_t n_views, int64
     if (!dl_drgb) return fail(SGS_ERR_INVALID_ARG, "dl_drgb is null");
     hipStream_t s = static_cast<hipStream_t>(stream);
     Prepared P;
-    sgs_status st = begin_call(rp, n, cams, n_views, workspace, workspace_bytes, pair_capacity, s, &P);
+    sgs_status st = begin_call(rp, n, cams, n_views, workspace, workspace_bytes, pair_capacity, s, &P,
+                               First::kLater);
     if (st != SGS_OK) return st;
     SGS_HIP(sgs::launch_rasterize_backward(P.rd, P.L, static_cast<char*>(workspace), dl_drgb,
-                                           d_gate, s),
+                                           d_gate, s, &P.views),
             "rasterize_backward");
     return SGS_OK;
 }
@@ -528,7 +538,7 @@ sgs_status sgs_project_backward(const sgs_gaussians* g, const sgs_camera* cams, 
     hipStream_t s = static_cast<hipStream_t>(stream);
     Prepared P;
     if ((st = begin_call(rp, g->n, cams, n_views, workspace, workspace_bytes, pair_capacity, s,
-                         &P)) != SGS_OK)
+                         &P, First::kStore)) != SGS_OK)
         return st;
     SGS_HIP(sgs::launch_project_backward(g->data, g->n, g->stride, g->sh_degree, P.rd, P.L,
                                          static_cast<char*>(workspace), d_gate, grads, s),
@@ -548,10 +558,10 @@ sgs_status sgs_render_backward(const sgs_gaussians* g, const sgs_camera* cams, i
     hipStream_t s = static_cast<hipStream_t>(stream);
     Prepared P;
     if ((st = begin_call(rp, g->n, cams, n_views, workspace, workspace_bytes, pair_capacity, s,
-                         &P)) != SGS_OK)
+                         &P, First::kLater)) != SGS_OK)
         return st;
     char* ws = static_cast<char*>(workspace);
-    SGS_HIP(sgs::launch_rasterize_backward(P.rd, P.L, ws, dl_drgb, d_gate, s),
+    SGS_HIP(sgs::launch_rasterize_backward(P.rd, P.L, ws, dl_drgb, d_gate, s, &P.views),
             "rasterize_backward");
     SGS_HIP(sgs::launch_project_backward(g->data, g->n, g->stride, g->sh_degree, P.rd, P.L, ws,
                                          d_gate, grads, s),
@@ -759,8 +769,12 @@ sgs_status sgs_project_backward_adam(const sgs_gaussians* g, const sgs_camera* c
     hipStream_t s = static_cast<hipStream_t>(stream);
     Prepared P;
     if ((st = begin_call(rp, g->n, cams, n_views, workspace, workspace_bytes, pair_capacity, s,
-                         &P)) != SGS_OK)
+                         &P, First::kLater)) != SGS_OK)
         return st;
+    SGS_HIP(sgs::launch_store_views(
+                P.views, reinterpret_cast<sgs::Views*>(static_cast<char*>(workspace) + P.L.views), s,
+                nullptr, d_step, d_gate),
+            "store views");
     SGS_HIP(sgs::launch_project_backward_adam(g->data, g->n, g->stride, g->sh_degree, P.rd, P.L,
                                               static_cast<char*>(workspace), adam,
                                               adam->visible_only != 0, m, v, d_step, d_gate, s),
@@ -782,10 +796,11 @@ sgs_status sgs_render_backward_adam(const sgs_gaussians* g, const sgs_camera* ca
     hipStream_t s = static_cast<hipStream_t>(stream);
     Prepared P;
     if ((st = begin_call(rp, g->n, cams, n_views, workspace, workspace_bytes, pair_capacity, s,
-                         &P)) != SGS_OK)
+                         &P, First::kLater)) != SGS_OK)
         return st;
     char* ws = static_cast<char*>(workspace);
-    SGS_HIP(sgs::launch_rasterize_backward(P.rd, P.L, ws, dl_drgb, d_gate, s),
+    SGS_HIP(sgs::launch_rasterize_backward(P.rd, P.L, ws, dl_drgb, d_gate, s, &P.views,
+                                           d_step),
             "rasterize_backward");
     SGS_HIP(sgs::launch_project_backward_adam(g->data, g->n, g->stride, g->sh_degree, P.rd, P.L,
                                               ws, adam, adam->visible_only != 0, m, v, d_step,
@@ -873,21 +888,20 @@ sgs_status sgs_train_iteration(const sgs_gaussians* g, const sgs_camera* cams,
     char* ws = static_cast<char*>(workspace);
     char* lws = static_cast<char*>(loss_workspace);
     const sgs::TargetRef tgt{targets, d_view, n_cams};
-    SGS_HIP(sgs::launch_begin_bin(P.views, static_cast<const sgs::ViewDev*>(d_table), n_cams,
-                                  d_view, P.L, ws, s),
-            "select view");
-    SGS_HIP(sgs::launch_project(g->data, g->n, g->stride, g->sh_degree, P.rd, P.L, ws, s),
+    SGS_HIP(sgs::launch_project(g->data, g->n, g->stride, g->sh_degree, P.rd, P.L, ws,
+                                sgs::CallViews{&P.views, static_cast<const sgs::ViewDev*>(d_table),
+                                               n_cams, d_view, true},
+                                s),
             "project");
     SGS_HIP(sgs::launch_bin(P.rd, g->n, P.L, ws, s), "bin");
     SGS_HIP(sgs::launch_rasterize(P.rd, P.L, ws, rgb, s), "rasterize");
-    SGS_HIP(sgs::launch_loss_forward(rgb, tgt, w, h, lambda, lws, d_loss, s), "loss");
-    if (gate_state != nullptr)
-        SGS_HIP(sgs::launch_gate_update(gp, gate_state, d_view, d_loss, d_gate, s), "gate");
-    else
-        SGS_HIP(sgs::fill_u32(reinterpret_cast<uint32_t*>(d_gate), 1, 1u, s), "open gate");
+    sgs::LossGate gate{{}, static_cast<char*>(gate_state), d_view, d_gate};
+    if (gate_state != nullptr) gate.args = sgs::gate_args(gp);
+    SGS_HIP(sgs::launch_loss_forward(rgb, tgt, w, h, lambda, lws, d_loss, s, gate), "loss");
     SGS_HIP(sgs::launch_loss_backward(rgb, tgt, w, h, lambda, lws, d_gate, dl_drgb, s),
             "loss backward");
-    SGS_HIP(sgs::launch_rasterize_backward(P.rd, P.L, ws, dl_drgb, d_gate, s), "rasterize_backward");
+    SGS_HIP(sgs::launch_rasterize_backward(P.rd, P.L, ws, dl_drgb, d_gate, s, nullptr, d_step),
+            "rasterize_backward");
     SGS_HIP(sgs::launch_project_backward_adam(g->data, g->n, g->stride, g->sh_degree, P.rd, P.L, ws,
                                               adam, adam->visible_only != 0, m, v, d_step, d_gate,
                                               s),

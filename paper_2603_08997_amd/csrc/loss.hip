@@ -34,8 +34,7 @@
 //   dSSIM/dx(q) = F[dS/dmu_x](q) + 2 x(q) F[dS/dE[x^2]](q) + y(q) F[dS/dE[xy]](q).
 #include <algorithm>
 
-#include "sgs_internal.hpp"
-#include "sgs_device.hpp"
+#include "sgs_gate.hpp"
 
 namespace sgs {
 
@@ -254,10 +253,12 @@ __global__ void __launch_bounds__(kThreads, 4) ssim_forward_kernel(
     }
 }
 
-// Sum of the per-strip partials in index order (binary64), then Eq. 6.
+// Sum of the per-strip partials in index order (binary64), then Eq. 6 and, in a
+// training iteration, the gate's decision (a launch of its own otherwise).
 __global__ void __launch_bounds__(1024) loss_reduce_kernel(const float* __restrict__ partials,
                                                            int64_t nb, double count, float lambda,
-                                                           float* __restrict__ d_loss) {
+                                                           float* __restrict__ d_loss,
+                                                           LossGate g) {
     __shared__ double dred[2][1024];
     const int tid = threadIdx.x;
     double a = 0.0, b = 0.0;
@@ -277,7 +278,14 @@ __global__ void __launch_bounds__(1024) loss_reduce_kernel(const float* __restri
     }
     if (tid == 0) {
         const double l1 = dred[0][0] / count, ssim = dred[1][0] / count;
-        *d_loss = (float)((1.0 - (double)lambda) * l1 + (double)lambda * (1.0 - ssim));
+        const float loss = (float)((1.0 - (double)lambda) * l1 + (double)lambda * (1.0 - ssim));
+        *d_loss = loss;
+        if (g.gate != nullptr) {
+            if (g.state != nullptr)
+                gate_step(g.args, g.state, g.view, loss, g.gate);
+            else
+                *g.gate = 1;
+        }
     }
 }
 
@@ -358,12 +366,13 @@ hipError_t launch_loss_partials(const float* rgb, TargetRef target, int w, int h
     hipLaunchKernelGGL((ssim_forward_kernel<false>), st.grid, dim3(kThreads), 0, s, rgb, target, w,
                        h, st.rows, make_window(), partials, nullptr);
     hipLaunchKernelGGL(loss_reduce_kernel, dim3(1), dim3(1024), 0, s, partials,
-                       (int64_t)st.grid.x * st.grid.y, 3.0 * (double)w * (double)h, lambda, d_loss);
+                       (int64_t)st.grid.x * st.grid.y, 3.0 * (double)w * (double)h, lambda, d_loss,
+                       LossGate{});
     return hipGetLastError();
 }
 
 hipError_t launch_loss_forward(const float* rgb, TargetRef target, int w, int h, float lambda,
-                               char* ws, float* d_loss, hipStream_t s) {
+                               char* ws, float* d_loss, hipStream_t s, const LossGate& gate) {
     const LossLayout L = loss_layout(w, h);
     const Strips st = strips(w, h);
     float* partials = reinterpret_cast<float*>(ws + L.partials);
@@ -371,7 +380,7 @@ hipError_t launch_loss_forward(const float* rgb, TargetRef target, int w, int h,
     hipLaunchKernelGGL((ssim_forward_kernel<true>), st.grid, dim3(kThreads), 0, s, rgb, target, w,
                        h, st.rows, make_window(), partials, maps);
     hipLaunchKernelGGL(loss_reduce_kernel, dim3(1), dim3(1024), 0, s, partials,
-                       (int64_t)st.grid.x * st.grid.y, 3.0 * (double)w * (double)h, lambda, d_loss);
+                       (int64_t)st.grid.x * st.grid.y, 3.0 * (double)w * (double)h, lambda, d_loss, gate);
     return hipGetLastError();
 }
 

@@ -221,7 +221,7 @@ __device__ __forceinline__ void project_entry(const float mu[3], const float ls[
     dkey[e] = __float_as_uint(depth);
 }
 
-// One thread per entry.
+// One thread per entry of a batch of views.
 template <int sh_degree>
 __global__ void __launch_bounds__(256) project_kernel(const float* __restrict__ planes, int64_t n,
                                                       int64_t stride, const Views* __restrict__ views,
@@ -242,6 +242,56 @@ __global__ void __launch_bounds__(256) project_kernel(const float* __restrict__ 
     project_entry<sh_degree>(
         p, p + 3, p + 6, p[10], [&](int j) { return P.load(11 + j, off); }, views->v[vi], rp, e,
         rec, tiles, dkey, info);
+}
+
+// One view, given by value or picked from a camera table: the first launch of
+// its call, which therefore also stores the view for the kernels after it and,
+// for a call that bins, clears the counters and the sums binning accumulates
+// (4.6 us as a launch of its own).
+struct OneView {
+    ViewDev view;
+    const ViewDev* table;
+    int32_t n_table;
+    const int32_t* d_view;
+    int32_t total_tiles, total_supers;
+    int64_t total_pixels;
+    Views* dst;
+    uint32_t* counters;   // nullable: nothing to clear
+    uint4* clear;
+    int64_t n4;
+};
+template <int sh_degree>
+__global__ void __launch_bounds__(256) project_one_kernel(const float* __restrict__ planes,
+                                                          int64_t n, int64_t stride, OneView one,
+                                                          RasterDev rp, float4* __restrict__ rec,
+                                                          uint32_t* __restrict__ tiles,
+                                                          uint32_t* __restrict__ dkey,
+                                                          uint4* __restrict__ info) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    ViewDev V = one.view;
+    if (one.table != nullptr) V = one.table[min(max(*one.d_view, 0), one.n_table - 1)];
+    if (blockIdx.x == 0) {
+        if (threadIdx.x == 0) {
+            one.dst->v[0] = V;
+            one.dst->n = 1;
+            one.dst->total_tiles = one.total_tiles;
+            one.dst->total_pixels = one.total_pixels;
+            one.dst->total_supers = one.total_supers;
+        }
+        if (one.counters != nullptr && threadIdx.x >= kVisible && threadIdx.x <= kRedo)
+            one.counters[threadIdx.x] = 0u;
+    }
+    for (int64_t k = i; k < one.n4; k += (int64_t)gridDim.x * blockDim.x)
+        one.clear[k] = make_uint4(0u, 0u, 0u, 0u);
+    if (i >= n) return;
+    const PlaneBuf P{const_cast<float*>(planes), stride};
+    const uint32_t off = (uint32_t)i * 4u;
+    float p[11];
+#pragma unroll
+    for (int k = 0; k < 11; ++k) p[k] = P.load(k, off);
+    project_entry<sh_degree>(
+        p, p + 3, p + 6, p[10], [&](int j) { return P.load(11 + j, off); }, V, rp, i, rec, tiles,
+        dkey, info);
 }
 
 // One thread per Gaussian, over the views of the batch: its parameters are
@@ -630,9 +680,17 @@ __global__ void __launch_bounds__(kBackwardThreads) project_backward_adam_kernel
 constexpr int64_t kProjectLoop = 65536;
 
 hipError_t launch_project(const float* planes, int64_t n, int64_t stride, int sh_degree,
-                          const RasterDev& rp, const Layout& L, char* ws, hipStream_t s) {
+                          const RasterDev& rp, const Layout& L, char* ws, const CallViews& call,
+                          hipStream_t s) {
     const int64_t entries = L.entries;
-    if (entries == 0) return hipSuccess;
+    const bool one_view = L.n_views == 1 && entries > 0;
+    if (!one_view) {
+        Views* dst = reinterpret_cast<Views*>(ws + L.views);
+        const hipError_t err =
+            call.bins ? launch_begin_bin(*call.views, call.table, call.n_table, call.d_view, L, ws, s)
+                      : launch_store_views(*call.views, dst, s);
+        if (err != hipSuccess || entries == 0) return err;
+    }
     const int nt = 256;
     const bool loop = L.n_views > 1 && n >= kProjectLoop;
     const int64_t nb = ((loop ? n : entries) + nt - 1) / nt;
@@ -641,12 +699,27 @@ hipError_t launch_project(const float* planes, int64_t n, int64_t stride, int sh
     uint32_t* tiles = reinterpret_cast<uint32_t*>(ws + L.tiles);
     uint32_t* dkey = reinterpret_cast<uint32_t*>(ws + L.depth);
     uint4* info = L.direct ? reinterpret_cast<uint4*>(ws + L.pair_info) : nullptr;
-#define SGS_PK(D)                                                                            \
-    if (loop)                                                                                \
+    OneView one;
+    one.view = call.views->v[0];
+    one.table = call.table;
+    one.n_table = call.n_table;
+    one.d_view = call.d_view;
+    one.total_tiles = call.views->total_tiles;
+    one.total_supers = call.views->total_supers;
+    one.total_pixels = call.views->total_pixels;
+    one.dst = reinterpret_cast<Views*>(ws + L.views);
+    one.counters = call.bins ? reinterpret_cast<uint32_t*>(ws + L.counters) : nullptr;
+    one.clear = reinterpret_cast<uint4*>(ws + L.clear_begin);
+    one.n4 = call.bins ? (int64_t)(L.clear_words / 4) : 0;
+#define SGS_PK(D)                                                                              \
+    if (one_view)                                                                              \
+        hipLaunchKernelGGL(project_one_kernel<D>, dim3((unsigned)nb), dim3(nt), 0, s, planes, n, \
+                           stride, one, rp, rec, tiles, dkey, info);                           \
+    else if (loop)                                                                             \
         hipLaunchKernelGGL(project_views_kernel<D>, dim3((unsigned)nb), dim3(nt), 0, s, planes, \
-                           n, stride, views, rp, rec, tiles, dkey, info);                        \
-    else                                                                                     \
-        hipLaunchKernelGGL(project_kernel<D>, dim3((unsigned)nb), dim3(nt), 0, s, planes, n, \
+                           n, stride, views, rp, rec, tiles, dkey, info);                      \
+    else                                                                                       \
+        hipLaunchKernelGGL(project_kernel<D>, dim3((unsigned)nb), dim3(nt), 0, s, planes, n,   \
                            stride, views, rp, rec, tiles, dkey, info)
     switch (sh_degree) {
         case 0: SGS_PK(0); break;
@@ -705,10 +778,9 @@ hipError_t launch_project_backward(const float* planes, int64_t n, int64_t strid
 hipError_t launch_project_backward_adam(float* planes, int64_t n, int64_t stride, int sh_degree,
                                         const RasterDev& rp, const Layout& L, char* ws,
                                         const sgs_adam_params* prm, bool sparse, float* m,
-                                        float* v, int32_t* step, const int32_t* gate,
+                                        float* v, const int32_t* step, const int32_t* gate,
                                         hipStream_t s) {
-    hipError_t err = launch_adam_count(step, gate, s);
-    if (err != hipSuccess || n == 0) return err;
+    if (n == 0) return hipSuccess;
     const AdamDev ad = make_adam(prm);
     const int nt = kBackwardThreads;
     const int64_t nb = std::min<int64_t>((n + nt - 1) / nt, kAdamBlocks);

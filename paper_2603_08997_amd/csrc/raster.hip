@@ -208,6 +208,67 @@ __device__ __forceinline__ uint32_t wave_add_u32(uint32_t v) {
     return v;
 }
 
+// Where the tiles' work is summed into counters[kBlended], [kEvaluated] (uint64)
+// and [kUsed] (uint32). An addition to one address takes 8 ns and three of them
+// a tile, so a few tiles add their own (16 tiles: nothing to be seen, against
+// the 4.6 us of a launch; 2170 tiles: +27 us); otherwise one more block of the
+// resuming launch does it, and resumed tiles add what they did there; a launch of
+// its own where there is no second pass or kUsed could pass 32 bits.
+enum class SumBy { kTile, kRedo, kLaunch };
+constexpr int64_t kTileSums = 128;
+
+__device__ __forceinline__ void add_work(uint32_t* counters, unsigned long long blended,
+                                         unsigned long long evaluated, uint32_t used) {
+    unsigned long long* sum = reinterpret_cast<unsigned long long*>(counters + kBlended);
+    atomicAdd(&sum[0], blended);
+    atomicAdd(&sum[1], evaluated);
+    atomicAdd(&counters[kUsed], used);
+}
+
+// Sums of {blended, evaluated, used} over the tiles by one workgroup, added to
+// the counters (kAdd) or written to them ([kUsed] saturating).
+template <int NT, bool kAdd>
+__device__ __forceinline__ void sum_tiles(const uint4* __restrict__ tile_stats, int64_t tiles,
+                                          uint32_t* counters) {
+    __shared__ unsigned long long s_sum[3][NT / 64];
+    unsigned long long b = 0, e = 0, u = 0;
+#pragma unroll 4
+    for (int64_t t = threadIdx.x; t < tiles; t += NT) {
+        const uint4 v = tile_stats[t];
+        b += v.x;
+        e += v.y;
+        u += v.z;
+    }
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) {
+        b += __shfl_xor(b, d, 64);
+        e += __shfl_xor(e, d, 64);
+        u += __shfl_xor(u, d, 64);
+    }
+    const int w = threadIdx.x / 64;
+    if (threadIdx.x % 64 == 0) {
+        s_sum[0][w] = b;
+        s_sum[1][w] = e;
+        s_sum[2][w] = u;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        b = e = u = 0;
+        for (int k = 0; k < NT / 64; ++k) {
+            b += s_sum[0][k];
+            e += s_sum[1][k];
+            u += s_sum[2][k];
+        }
+        if (kAdd) {
+            add_work(counters, b, e, (uint32_t)u);
+        } else {
+            reinterpret_cast<unsigned long long*>(counters + kBlended)[0] = b;
+            reinterpret_cast<unsigned long long*>(counters + kEvaluated)[0] = e;
+            counters[kUsed] = (uint32_t)min(u, 0xffffffffull);
+        }
+    }
+}
+
 // Forward of one tile by W waves: each composites its strip of TH / W rows
 // front to back over the tile's list in batches of B entries (records
 // gathered and staged in LDS per batch, each wave for itself) and stops when
@@ -218,9 +279,9 @@ __global__ void __launch_bounds__(kLanes * W) raster_forward_kernel(
     const Views* __restrict__ views, RasterDev rp, const uint32_t* __restrict__ tile_ranges,
     const uint32_t* __restrict__ tile_entry, const float4* __restrict__ rec,
     float* __restrict__ out_rgb, float* __restrict__ t_final, uint32_t* __restrict__ n_last,
-    uint32_t* __restrict__ tile_stats, uint32_t* __restrict__ tile_cost, uint32_t entries,
+    uint4* __restrict__ tile_stats, uint32_t* __restrict__ tile_cost, uint32_t entries,
     uint32_t* __restrict__ tile_state, uint32_t* __restrict__ tile_resume,
-    uint32_t* __restrict__ sup_redo, uint32_t* __restrict__ counters, bool redo) {
+    uint32_t* __restrict__ sup_redo, uint32_t* __restrict__ counters, SumBy sum_by, bool redo) {
     constexpr int SH = TH / W;                // rows of a strip
     constexpr int PIX = TW * SH / kLanes;
     constexpr int RS = kLanes / TW;           // row step between a lane's pixels
@@ -233,6 +294,10 @@ __global__ void __launch_bounds__(kLanes * W) raster_forward_kernel(
     __shared__ uint32_t s_tile[W][4];
 
     const int tile = blockIdx.x;
+    if (redo && tile == views->total_tiles) {   // (one block more with SumBy::kRedo)
+        sum_tiles<kLanes * W, true>(tile_stats, tile, counters);
+        return;
+    }
     // the second pass goes on with the tiles the first left incomplete
     if (redo && tile_state[tile] != kTileIncomplete) return;
     const ViewDev& V = views->v[view_of_tile(views, tile)];
@@ -459,9 +524,14 @@ __global__ void __launch_bounds__(kLanes * W) raster_forward_kernel(
     }
     if (W > 1) __syncthreads();   // every wave has read the tile's state
     if (threadIdx.x == 0) {
+        const uint32_t before = redo ? tile_cost[tile] : 0u;
+        if (sum_by == SumBy::kTile || (redo && sum_by == SumBy::kRedo)) {   // uniform
+            add_work(counters, nb, ne2, tile_last - before);
+        } else {
+            const uint4 first = redo ? tile_stats[tile] : make_uint4(0u, 0u, 0u, 0u);
+            tile_stats[tile] = make_uint4(nb + first.x, ne2 + first.y, tile_last, 0u);
+        }
         tile_cost[tile] = tile_last;
-        tile_stats[2 * tile] = nb + (redo ? tile_stats[2 * tile] : 0u);
-        tile_stats[2 * tile + 1] = ne2 + (redo ? tile_stats[2 * tile + 1] : 0u);
         if (redo) {
             tile_state[tile] = kTileWhole;
         } else if (suspend) {
@@ -474,43 +544,11 @@ __global__ void __launch_bounds__(kLanes * W) raster_forward_kernel(
     }
 }
 
-// counters[kBlended], [kEvaluated] (uint64) and [kUsed] (saturating uint32)
-// from the per-tile work of the last compositing forward.
+// The sums alone, where the compositing launches cannot take them (also clears).
 constexpr int kStatThreads = 1024;
 __global__ void __launch_bounds__(kStatThreads) sum_tile_stats_kernel(
-    const uint32_t* __restrict__ tile_stats, const uint32_t* __restrict__ tile_cost,
-    int64_t tiles, uint32_t* __restrict__ counters) {
-    __shared__ unsigned long long s_sum[3][kStatThreads / 64];
-    unsigned long long b = 0, e = 0, u = 0;
-    for (int64_t t = threadIdx.x; t < tiles; t += kStatThreads) {
-        b += tile_stats[2 * t];
-        e += tile_stats[2 * t + 1];
-        u += tile_cost[t];
-    }
-#pragma unroll
-    for (int d = 32; d > 0; d >>= 1) {
-        b += __shfl_xor(b, d, 64);
-        e += __shfl_xor(e, d, 64);
-        u += __shfl_xor(u, d, 64);
-    }
-    const int w = threadIdx.x / 64;
-    if (threadIdx.x % 64 == 0) {
-        s_sum[0][w] = b;
-        s_sum[1][w] = e;
-        s_sum[2][w] = u;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        b = e = u = 0;
-        for (int k = 0; k < kStatThreads / 64; ++k) {
-            b += s_sum[0][k];
-            e += s_sum[1][k];
-            u += s_sum[2][k];
-        }
-        reinterpret_cast<unsigned long long*>(counters + kBlended)[0] = b;
-        reinterpret_cast<unsigned long long*>(counters + kEvaluated)[0] = e;
-        counters[kUsed] = (uint32_t)min(u, 0xffffffffull);
-    }
+    const uint4* __restrict__ tile_stats, int64_t tiles, uint32_t* __restrict__ counters) {
+    sum_tiles<kStatThreads, false>(tile_stats, tiles, counters);
 }
 
 // At most 72 VGPRs (batches of 64), so that 7 waves fit on each SIMD: the
@@ -712,15 +750,46 @@ __global__ void __launch_bounds__(kLanes, backward_waves(B)) raster_backward_ker
     }
 }
 
-// Clears the accumulators in a grid-stride loop over a grid sized for the
-// machine (a closed gate then costs a launch of a few thousand blocks, not
-// one block per 256 float4).
-constexpr int kZeroBlocks = 2048;
-__global__ void zero_f32_gated_kernel(float4* p, int64_t n4, const int32_t* gate) {
+// What the compositing backward needs done before it, in one launch: block 0
+// stores the call's views (nullable), counts Adam's step (nullable) and orders
+// the tiles by the forward's measured work, largest first (a counting sort in
+// LDS: bucket counts, their exclusive scan, then every tile takes the next slot
+// of its bucket), the others clear the accumulators in a grid-stride loop over a
+// grid sized for the machine (a closed gate then costs a launch of a few hundred
+// blocks). As launches of their own the order took 9 us at 6700 tiles, the
+// count and the views 4.6 us each.
+constexpr int kPrepareThreads = 1024;
+constexpr int64_t kPrepareBlocks = 512;
+__global__ void __launch_bounds__(kPrepareThreads) prepare_backward_kernel(
+    Views v, Views* __restrict__ dst, int32_t* step, const int32_t* __restrict__ gate, float4* acc,
+    int64_t n4, const uint32_t* __restrict__ cost, int64_t tiles, uint32_t* __restrict__ order) {
+    __shared__ uint32_t slot[kPrepareThreads];
+    __shared__ uint32_t smem[kPrepareThreads / 64 + 1];
+    const int tid = threadIdx.x;
+    if (blockIdx.x == 0 && dst != nullptr) store_views(v, nullptr, 0, nullptr, dst);
     if (gate_closed(gate)) return;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n4;
-         i += (int64_t)gridDim.x * blockDim.x)
-        p[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (blockIdx.x > 0) {
+        for (int64_t i = (int64_t)(blockIdx.x - 1) * kPrepareThreads + tid; i < n4;
+             i += (int64_t)(gridDim.x - 1) * kPrepareThreads)
+            acc[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+        return;
+    }
+    if (step != nullptr && tid == 0) *step += 1;
+    auto bucket = [&](int64_t t) {
+        return (uint32_t)(kPrepareThreads - 1) - min(cost[t], (uint32_t)(kPrepareThreads - 1));
+    };
+    slot[tid] = 0;
+    __syncthreads();
+    for (int64_t t = tid; t < tiles; t += kPrepareThreads) atomicAdd(&slot[bucket(t)], 1u);
+    __syncthreads();
+    const uint32_t c = slot[tid];
+    uint32_t tot;
+    const uint32_t first = block_excl_scan<kPrepareThreads>(c, smem, &tot);
+    __syncthreads();
+    slot[tid] = first;
+    __syncthreads();
+    for (int64_t t = tid; t < tiles; t += kPrepareThreads)
+        order[atomicAdd(&slot[bucket(t)], 1u)] = (uint32_t)t;
 }
 
 }  // namespace
@@ -772,25 +841,33 @@ hipError_t launch_rasterize(const RasterDev& rp, const Layout& L, char* ws, floa
     uint32_t* nl = reinterpret_cast<uint32_t*>(ws + L.n_last);
     uint32_t* cnt = reinterpret_cast<uint32_t*>(ws + L.counters);
     uint32_t* cost = reinterpret_cast<uint32_t*>(ws + L.tile_cost);
-    uint32_t* stats = reinterpret_cast<uint32_t*>(ws + L.tile_stats);
+    uint4* stats = reinterpret_cast<uint4*>(ws + L.tile_stats);
     const uint32_t entries = (uint32_t)std::max<int64_t>(1, L.entries);
     // (no second pass where no list can be cut)
     uint32_t* state = lists_cut(rp, L) ? reinterpret_cast<uint32_t*>(ws + L.tile_state) : nullptr;
     uint32_t* sup_redo = reinterpret_cast<uint32_t*>(ws + L.sup_redo);
     uint32_t* resume = reinterpret_cast<uint32_t*>(ws + L.tile_resume);
+    // (the sum of the used entries stays below the capacity)
+    const SumBy sum_by = L.capacity > (int64_t)0xffffffffu ? SumBy::kLaunch
+                         : L.total_tiles <= kTileSums      ? SumBy::kTile
+                         : state != nullptr                ? SumBy::kRedo
+                                                           : SumBy::kLaunch;
     // the waves of a tile are one workgroup
 #define SGS_LAUNCH(K, W, ...) \
-    hipLaunchKernelGGL(K, dim3((unsigned)L.total_tiles), dim3(kLanes * W), 0, s, __VA_ARGS__)
+    hipLaunchKernelGGL(K, dim3(blocks), dim3(kLanes * W), 0, s, __VA_ARGS__)
     auto composite = [&](bool redo) {
+        const unsigned blocks =
+            (unsigned)L.total_tiles + (redo && sum_by == SumBy::kRedo ? 1u : 0u);
         if (rp.tile_w == 8)
             SGS_RASTER_BATCHES(raster_forward_kernel, 8, 8, views, rp, ranges, entry, rec, out_rgb,
-                               tf, nl, stats, cost, entries, state, resume, sup_redo, cnt, redo);
+                               tf, nl, stats, cost, entries, state, resume, sup_redo, cnt,
+                               sum_by, redo);
         else if (L.total_tiles <= kForwardFine)
             SGS_RASTER_STRIPS(raster_forward_kernel, 4, views, rp, ranges, entry, rec, out_rgb, tf,
-                              nl, stats, cost, entries, state, resume, sup_redo, cnt, redo);
+                              nl, stats, cost, entries, state, resume, sup_redo, cnt, sum_by, redo);
         else
             SGS_RASTER_STRIPS(raster_forward_kernel, 2, views, rp, ranges, entry, rec, out_rgb, tf,
-                              nl, stats, cost, entries, state, resume, sup_redo, cnt, redo);
+                              nl, stats, cost, entries, state, resume, sup_redo, cnt, sum_by, redo);
         return hipGetLastError();
     };
     if (hipError_t err = composite(false); err != hipSuccess) return err;
@@ -800,20 +877,27 @@ hipError_t launch_rasterize(const RasterDev& rp, const Layout& L, char* ws, floa
         if (hipError_t err = launch_split_rest(rp, L, ws, s); err != hipSuccess) return err;
         if (hipError_t err = composite(true); err != hipSuccess) return err;
     }
-    hipLaunchKernelGGL(sum_tile_stats_kernel, dim3(1), dim3(kStatThreads), 0, s, stats, cost,
-                       L.total_tiles, cnt);
+    if (sum_by == SumBy::kLaunch)
+        hipLaunchKernelGGL(sum_tile_stats_kernel, dim3(1), dim3(kStatThreads), 0, s, stats,
+                           L.total_tiles, cnt);
     return hipGetLastError();
 #undef SGS_LAUNCH
 }
 
 hipError_t launch_rasterize_backward(const RasterDev& rp, const Layout& L, char* ws,
-                                     const float* dl_drgb, const int32_t* gate, hipStream_t s) {
+                                     const float* dl_drgb, const int32_t* gate, hipStream_t s,
+                                     const Views* store, int32_t* step) {
     float* acc = reinterpret_cast<float*>(ws + L.accum);
     const int64_t n4 = L.entries * kAccumFloats / 4;
-    if (n4 > 0)
-        hipLaunchKernelGGL(zero_f32_gated_kernel,
-                           dim3((unsigned)std::min<int64_t>((n4 + 255) / 256, kZeroBlocks)),
-                           dim3(256), 0, s, reinterpret_cast<float4*>(acc), n4, gate);
+    uint32_t* order = reinterpret_cast<uint32_t*>(ws + L.tile_order);
+    const int64_t clear = (n4 + kPrepareThreads - 1) / kPrepareThreads;
+    hipLaunchKernelGGL(prepare_backward_kernel,
+                       dim3((unsigned)(1 + std::min<int64_t>(clear, kPrepareBlocks))),
+                       dim3(kPrepareThreads), 0, s, store != nullptr ? *store : Views{},
+                       store != nullptr ? reinterpret_cast<Views*>(ws + L.views) : nullptr, step,
+                       gate, reinterpret_cast<float4*>(acc), n4,
+                       reinterpret_cast<const uint32_t*>(ws + L.tile_cost),
+                       L.entries > 0 ? L.total_tiles : 0, order);
     if (L.total_tiles == 0 || L.entries == 0) return hipGetLastError();
     const Views* views = reinterpret_cast<const Views*>(ws + L.views);
     const uint32_t* ranges = reinterpret_cast<const uint32_t*>(ws + L.tile_ranges);
@@ -821,13 +905,6 @@ hipError_t launch_rasterize_backward(const RasterDev& rp, const Layout& L, char*
     const float4* rec = reinterpret_cast<const float4*>(ws + L.records);
     const float* tf = reinterpret_cast<const float*>(ws + L.t_final);
     const uint32_t* nl = reinterpret_cast<const uint32_t*>(ws + L.n_last);
-    // the tiles in order of the forward's measured work, largest first, so
-    // that every SIMD gets a mix of long and short tiles
-    uint32_t* order = reinterpret_cast<uint32_t*>(ws + L.tile_order);
-    if (hipError_t err = launch_order_tiles(reinterpret_cast<const uint32_t*>(ws + L.tile_cost),
-                                            L.total_tiles, 0, order, gate, s);
-        err != hipSuccess)
-        return err;
     const int tiles = (int)L.total_tiles;
     // every strip is a workgroup of its own
 #define SGS_LAUNCH(K, W, ...)                                                                  \

@@ -315,6 +315,24 @@ __device__ __forceinline__ void adam_update(float g, float& p, float& m, float& 
     p = p - lr * mh * __builtin_amdgcn_rcpf(__builtin_amdgcn_sqrtf(vh) + a.eps);
 }
 
+// The call's view table into the workspace, word by word: the views passed
+// by value or, with a camera table, its entry *d_view (clamped into range) as
+// view 0 of a one-view batch (table entries are stored for that position).
+__device__ __forceinline__ void store_views(const Views& v, const ViewDev* table, int n_table,
+                                            const int32_t* d_view, Views* dst) {
+    static_assert(sizeof(Views) % 4 == 0 && sizeof(ViewDev) % 4 == 0, "word copy");
+    constexpr int kWords = (int)(sizeof(Views) / 4), kViewWords = (int)(sizeof(ViewDev) / 4);
+    const uint32_t* src = reinterpret_cast<const uint32_t*>(&v);
+    const uint32_t* sel = nullptr;
+    if (table != nullptr) {
+        const int i = min(max(*d_view, 0), n_table - 1);
+        sel = reinterpret_cast<const uint32_t*>(table + i);
+    }
+    uint32_t* out = reinterpret_cast<uint32_t*>(dst);
+    for (int w = threadIdx.x; w < kWords; w += blockDim.x)
+        out[w] = (sel != nullptr && w < kViewWords) ? sel[w] : src[w];
+}
+
 __device__ __forceinline__ bool gate_closed(const int32_t* gate) {
     return gate != nullptr && *gate == 0;
 }

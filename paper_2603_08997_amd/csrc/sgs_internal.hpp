@@ -192,8 +192,12 @@ bool make_views(const sgs_camera* cams, int n_views, const sgs_raster_params* rp
 void make_layout(const Views& views, const RasterDev& rp, int64_t n, int64_t capacity, Layout* L);
 RasterDev make_raster(const sgs_raster_params* rp);
 
-// The call's views into the workspace's view table.
-hipError_t launch_store_views(const Views& views, Views* dst, hipStream_t s);
+// The call's views into the workspace's view table; the sums of compositing's
+// work in counters (nullable) are cleared, step (nullable) is incremented unless
+// the gate is closed.
+hipError_t launch_store_views(const Views& views, Views* dst, hipStream_t s,
+                              uint32_t* counters = nullptr, int32_t* step = nullptr,
+                              const int32_t* gate = nullptr);
 // The same for a call that bins: the views from the host (by value) or, when
 // `table` is non-null, view `*d_view` of a device camera table (clamped into
 // [0, n_table)) as the batch's single view; and the counters and the region of
@@ -203,8 +207,18 @@ hipError_t launch_begin_bin(const Views& views, const ViewDev* table, int n_tabl
 
 // ---- launch wrappers (all asynchronous on `s`). Kernels read the views from
 // the workspace's view table (ws + L.views); L carries the sizes. ----
+// Projection; it also does what the first launch of its call has to (the views
+// stored; with `bins` the counters and sums cleared, as launch_begin_bin).
+struct CallViews {
+    const Views* views;
+    const ViewDev* table;   // as launch_begin_bin
+    int n_table;
+    const int32_t* d_view;
+    bool bins;
+};
 hipError_t launch_project(const float* planes, int64_t n, int64_t stride, int sh_degree,
-                          const RasterDev& rp, const Layout& L, char* ws, hipStream_t s);
+                          const RasterDev& rp, const Layout& L, char* ws, const CallViews& call,
+                          hipStream_t s);
 hipError_t launch_load_records(const float* u, const float* v, const float* depth,
                                const int32_t* extent, const float* conic, const float* opacity,
                                const float* rgb, int64_t n, const RasterDev& rp, const Layout& L,
@@ -217,19 +231,17 @@ hipError_t launch_bin(const RasterDev& rp, int64_t n, const Layout& L, char* ws,
 hipError_t launch_split_rest(const RasterDev& rp, const Layout& L, char* ws, hipStream_t s);
 hipError_t launch_rasterize(const RasterDev& rp, const Layout& L, char* ws, float* out_rgb,
                             hipStream_t s);
+// views (nullable): stored into the workspace first. step (nullable): Adam's
+// step count, incremented unless the gate is closed.
 hipError_t launch_rasterize_backward(const RasterDev& rp, const Layout& L, char* ws,
-                                     const float* dl_drgb, const int32_t* gate, hipStream_t s);
+                                     const float* dl_drgb, const int32_t* gate, hipStream_t s,
+                                     const Views* views, int32_t* step = nullptr);
 hipError_t launch_project_backward(const float* planes, int64_t n, int64_t stride,
                                    int sh_degree, const RasterDev& rp, const Layout& L, char* ws,
                                    const int32_t* gate, float* grads, hipStream_t s);
 
 // p[0..n) = v on stream s (a kernel, so that callers can be captured).
 hipError_t fill_u32(uint32_t* p, int64_t n, uint32_t v, hipStream_t s);
-// order = the tiles sorted by cost >> shift, largest first (ties in any
-// order); a permutation of [0, tiles). Skipped when the gate is closed.
-hipError_t launch_order_tiles(const uint32_t* cost, int64_t tiles, int shift, uint32_t* order,
-                              const int32_t* gate, hipStream_t s);
-
 // Stable LSD radix sorts of (key, uint32 value) pairs. `hist`: 256 words per
 // block; `groups`: radix_group_words words of zeros per call.
 constexpr int64_t kSortGroup = 32;   // blocks whose digit counts are summed up together
@@ -275,8 +287,22 @@ struct TargetRef {
     const int32_t* d_view;
     int32_t n_targets;
 };
+// What a training iteration decides once it has the loss: the gate's update or,
+// without a state, an open gate.
+struct GateArgs {
+    double beta, eps, delta, rho_lo;
+    int32_t warmup, window, calibrate, budget, n_views;
+};
+GateArgs gate_args(const sgs_gate_params* p);
+struct LossGate {
+    GateArgs args;
+    char* state;            // nullable
+    const int32_t* view;
+    int32_t* gate;          // nullable: nothing to decide
+};
 hipError_t launch_loss_forward(const float* rgb, TargetRef target, int w, int h, float lambda,
-                               char* ws, float* d_loss, hipStream_t s);
+                               char* ws, float* d_loss, hipStream_t s,
+                               const LossGate& gate = LossGate{});
 hipError_t launch_loss_backward(const float* rgb, TargetRef target, int w, int h, float lambda,
                                 char* ws, const int32_t* gate, float* dl, hipStream_t s);
 size_t loss_workspace_bytes(int w, int h);
@@ -298,12 +324,13 @@ hipError_t launch_adam(const sgs_adam_params* p, float* params, float* grads, fl
                        int64_t n, int64_t stride, int n_planes, int32_t* step,
                        const int32_t* gate, hipStream_t s);
 hipError_t launch_adam_count(int32_t* step, const int32_t* gate, hipStream_t s);
+// step: the count of this step, incremented by an earlier launch.
 // sparse: update only the Gaussians visible in a view of the batch (the
 // others keep their parameters and moments); dense otherwise.
 hipError_t launch_project_backward_adam(float* planes, int64_t n, int64_t stride, int sh_degree,
                                         const RasterDev& rp, const Layout& L, char* ws,
                                         const sgs_adam_params* prm, bool sparse, float* m,
-                                        float* v, int32_t* step, const int32_t* gate,
+                                        float* v, const int32_t* step, const int32_t* gate,
                                         hipStream_t s);
 
 }  // namespace sgs
