@@ -196,6 +196,14 @@ sgs_status sgs_render_backward(const sgs_gaussians* g, const sgs_camera* cams, i
                                const float* dl_drgb, const int32_t* d_gate /* nullable */,
                                float* grads, void* stream);
 
+/* The same gradients WRITTEN to `grads` instead, all of it: zeros for the
+ * Gaussians no view sees and in the padding past n (what `grads` held is not
+ * read, so it need not be cleared). */
+sgs_status sgs_render_gradients(const sgs_gaussians* g, const sgs_camera* cams, int32_t n_views,
+                                const sgs_raster_params* rp,
+                                void* workspace, size_t workspace_bytes, int64_t pair_capacity,
+                                const float* dl_drgb, float* grads, void* stream);
+
 /* ---------------------------------------------------------------------------
  * Stage entry points (the forward and backward are these in order). They
  * share the workspace of sgs_render_forward and exist so each stage can be
@@ -309,6 +317,13 @@ sgs_status sgs_photometric_loss(const float* rgb, const float* target, int32_t w
 sgs_status sgs_photometric_loss_backward(const float* rgb, const float* target, int32_t width,
                                          int32_t height, float lambda, void* workspace,
                                          size_t workspace_bytes, const int32_t* d_gate,
+                                         float* dl_drgb, void* stream);
+
+/* The same times *d_scale (device float): the gradient of a quantity whose
+ * derivative by the loss is *d_scale. */
+sgs_status sgs_photometric_loss_gradient(const float* rgb, const float* target, int32_t width,
+                                         int32_t height, float lambda, void* workspace,
+                                         size_t workspace_bytes, const float* d_scale,
                                          float* dl_drgb, void* stream);
 
 /* For callers that cannot allocate device memory (code under graph capture,

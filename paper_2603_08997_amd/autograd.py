@@ -53,9 +53,8 @@ class RenderFn(torch.autograd.Function):
         ws = ctx.ws
         if ws is None:
             _, ws, capacity = _forward(planes, n, sh_degree, cams, rp, capacity)
-        grads = torch.zeros_like(planes)
-        sk.render_backward(planes, n, sh_degree, cams, rp, ws, capacity, g_rgb.contiguous(),
-                           None, grads)
+        grads = torch.empty_like(planes)
+        sk.render_gradients(planes, n, sh_degree, cams, rp, ws, capacity, g_rgb.contiguous(), grads)
         ctx.ws = None
         return grads, None, None, None, None, None, None
 
@@ -67,7 +66,8 @@ def render(planes: torch.Tensor, n: int, sh_degree: int, cams, rp: sk.RasterPara
     Gaussian and view, grown once if the forward reports more."""
     rp = rp or sk.RasterParams()
     capacity = capacity or max(4096, 16 * n * len(cams))
-    return RenderFn.apply(planes, n, sh_degree, list(cams), rp, int(capacity), bool(recompute))
+    # marshalled once for the forward and the backward (four calls or more)
+    return RenderFn.apply(planes, n, sh_degree, sk.cameras_c(list(cams)), rp, int(capacity), bool(recompute))
 
 
 class LossFn(torch.autograd.Function):
@@ -87,9 +87,9 @@ class LossFn(torch.autograd.Function):
         rgb, target = ctx.saved_tensors
         width, height, lam, lws = ctx.meta
         dl = torch.empty_like(rgb)
-        sk.photometric_loss_backward(rgb, target, width, height, lam, lws, None, dl)
-        if not (g.numel() == 1 and float(g) == 1.0):
-            dl = dl * g
+        # (the incoming derivative stays on the device: reading it would wait
+        # for the forward)
+        sk.photometric_loss_gradient(rgb, target, width, height, lam, lws, g, dl)
         return dl, None, None, None, None
 
 

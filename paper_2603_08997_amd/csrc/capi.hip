@@ -541,16 +541,16 @@ sgs_status sgs_project_backward(const sgs_gaussians* g, const sgs_camera* cams, 
                          &P, First::kStore)) != SGS_OK)
         return st;
     SGS_HIP(sgs::launch_project_backward(g->data, g->n, g->stride, g->sh_degree, P.rd, P.L,
-                                         static_cast<char*>(workspace), d_gate, grads, s),
+                                         static_cast<char*>(workspace), d_gate, grads, false, s),
             "project_backward");
     return SGS_OK;
 }
 
-sgs_status sgs_render_backward(const sgs_gaussians* g, const sgs_camera* cams, int32_t n_views,
-                               const sgs_raster_params* rp, void* workspace,
-                               size_t workspace_bytes, int64_t pair_capacity,
-                               const float* dl_drgb, const int32_t* d_gate, float* grads,
-                               void* stream) {
+static sgs_status render_backward(const sgs_gaussians* g, const sgs_camera* cams, int32_t n_views,
+                                  const sgs_raster_params* rp, void* workspace,
+                                  size_t workspace_bytes, int64_t pair_capacity,
+                                  const float* dl_drgb, const int32_t* d_gate, float* grads,
+                                  bool write, void* stream) {
     sgs_status st = check_gaussians(g);
     if (st != SGS_OK) return st;
     if (!dl_drgb) return fail(SGS_ERR_INVALID_ARG, "dl_drgb is null");
@@ -564,19 +564,35 @@ sgs_status sgs_render_backward(const sgs_gaussians* g, const sgs_camera* cams, i
     SGS_HIP(sgs::launch_rasterize_backward(P.rd, P.L, ws, dl_drgb, d_gate, s, &P.views),
             "rasterize_backward");
     SGS_HIP(sgs::launch_project_backward(g->data, g->n, g->stride, g->sh_degree, P.rd, P.L, ws,
-                                         d_gate, grads, s),
+                                         d_gate, grads, write, s),
             "project_backward");
     return SGS_OK;
+}
+
+sgs_status sgs_render_backward(const sgs_gaussians* g, const sgs_camera* cams, int32_t n_views,
+                               const sgs_raster_params* rp, void* workspace, size_t workspace_bytes,
+                               int64_t pair_capacity, const float* dl_drgb, const int32_t* d_gate,
+                               float* grads, void* stream) {
+    return render_backward(g, cams, n_views, rp, workspace, workspace_bytes, pair_capacity, dl_drgb,
+                           d_gate, grads, false, stream);
+}
+
+sgs_status sgs_render_gradients(const sgs_gaussians* g, const sgs_camera* cams, int32_t n_views,
+                                const sgs_raster_params* rp, void* workspace,
+                                size_t workspace_bytes, int64_t pair_capacity,
+                                const float* dl_drgb, float* grads, void* stream) {
+    return render_backward(g, cams, n_views, rp, workspace, workspace_bytes, pair_capacity, dl_drgb,
+                           nullptr, grads, true, stream);
 }
 
 sgs_status sgs_read_status(const void* workspace, uint32_t* flags_out, int64_t* visible_out,
                            int64_t* pairs_out, void* stream) {
     if (!workspace) return fail(SGS_ERR_INVALID_ARG, "workspace is null");
     hipStream_t s = static_cast<hipStream_t>(stream);
-    SGS_HIP(hipStreamSynchronize(s), "stream sync");
     uint32_t c[sgs::kNumCounters];
     // the counters region sits at offset 0 of every forward workspace
-    SGS_HIP(hipMemcpy(c, workspace, sizeof(c), hipMemcpyDeviceToHost), "read counters");
+    SGS_HIP(hipMemcpyAsync(c, workspace, sizeof(c), hipMemcpyDeviceToHost, s), "read counters");
+    SGS_HIP(hipStreamSynchronize(s), "stream sync");
     if (flags_out) *flags_out = c[sgs::kStatus];
     if (visible_out) *visible_out = c[sgs::kVisible];
     // list entries of both splits, saturating like the device's own sums
@@ -642,10 +658,10 @@ sgs_status sgs_photometric_loss_static(const float* rgb, const float* target, in
     return SGS_OK;
 }
 
-sgs_status sgs_photometric_loss_backward(const float* rgb, const float* target, int32_t width,
-                                         int32_t height, float lambda, void* workspace,
-                                         size_t workspace_bytes, const int32_t* d_gate,
-                                         float* dl_drgb, void* stream) {
+static sgs_status loss_backward(const float* rgb, const float* target, int32_t width, int32_t height,
+                                float lambda, void* workspace, size_t workspace_bytes,
+                                const int32_t* d_gate, const float* d_scale, float* dl_drgb,
+                                void* stream) {
     if (!rgb || !target || !dl_drgb || !workspace)
         return fail(SGS_ERR_INVALID_ARG, "null pointer argument");
     if (width <= 0 || height <= 0 || width > 32768 || height > 32768)
@@ -655,9 +671,26 @@ sgs_status sgs_photometric_loss_backward(const float* rgb, const float* target, 
         return fail(SGS_ERR_CAPACITY, "loss workspace too small");
     SGS_HIP(sgs::launch_loss_backward(rgb, sgs::TargetRef{target, nullptr, 1}, width, height, lambda,
                                       static_cast<char*>(workspace), d_gate, dl_drgb,
-                                      static_cast<hipStream_t>(stream)),
+                                      static_cast<hipStream_t>(stream), d_scale),
             "loss backward");
     return SGS_OK;
+}
+
+sgs_status sgs_photometric_loss_backward(const float* rgb, const float* target, int32_t width,
+                                         int32_t height, float lambda, void* workspace,
+                                         size_t workspace_bytes, const int32_t* d_gate,
+                                         float* dl_drgb, void* stream) {
+    return loss_backward(rgb, target, width, height, lambda, workspace, workspace_bytes, d_gate,
+                         nullptr, dl_drgb, stream);
+}
+
+sgs_status sgs_photometric_loss_gradient(const float* rgb, const float* target, int32_t width,
+                                         int32_t height, float lambda, void* workspace,
+                                         size_t workspace_bytes, const float* d_scale,
+                                         float* dl_drgb, void* stream) {
+    if (!d_scale) return fail(SGS_ERR_INVALID_ARG, "null pointer argument");
+    return loss_backward(rgb, target, width, height, lambda, workspace, workspace_bytes, nullptr,
+                         d_scale, dl_drgb, stream);
 }
 
 static sgs_status check_gate(const sgs_gate_params* p) {

@@ -292,7 +292,7 @@ __global__ void __launch_bounds__(1024) loss_reduce_kernel(const float* __restri
 __global__ void __launch_bounds__(kThreads) ssim_backward_kernel(
     const float* __restrict__ x, TargetRef target, int w, int h, int rows, float lambda,
     Window W, const float* __restrict__ maps, const int32_t* __restrict__ gate,
-    float* __restrict__ dl) {
+    const float* __restrict__ scale, float* __restrict__ dl) {
     if (gate_closed(gate)) return;
     __shared__ float4 s_m[3][64];   // a row of the three maps
     const Place p(w, h, rows);
@@ -304,6 +304,7 @@ __global__ void __launch_bounds__(kThreads) ssim_backward_kernel(
     float4* m = s_m[p.ch];
     Column c0, c1, c2;
     const float inv = 1.f / (3.f * (float)w * (float)h);
+    const float outer = scale != nullptr ? *scale : 1.f;   // (times 1 is exact)
     // map rows are loaded kAhead rows before they are used, the output row's
     // pixels one row before
     constexpr int kAhead = 3;
@@ -349,7 +350,8 @@ __global__ void __launch_bounds__(kThreads) ssim_backward_kernel(
         if (p.out) {
             const float d_ssim = F0 + 2.f * a * F1 + b * F2;
             const float sgn = a > b ? 1.f : (a < b ? -1.f : 0.f);
-            dc[(int64_t)o * w] = (1.f - lambda) * sgn * inv - lambda * d_ssim * inv;
+            dc[(int64_t)o * w] =
+                ((1.f - lambda) * sgn * inv - lambda * d_ssim * inv) * outer;
         }
     }
 }
@@ -385,12 +387,13 @@ hipError_t launch_loss_forward(const float* rgb, TargetRef target, int w, int h,
 }
 
 hipError_t launch_loss_backward(const float* rgb, TargetRef target, int w, int h, float lambda,
-                                char* ws, const int32_t* gate, float* dl, hipStream_t s) {
+                                char* ws, const int32_t* gate, float* dl, hipStream_t s,
+                                const float* scale) {
     const LossLayout L = loss_layout(w, h);
     const Strips st = strips(w, h);
     const float* maps = reinterpret_cast<const float*>(ws + L.maps);
     hipLaunchKernelGGL(ssim_backward_kernel, st.grid, dim3(kThreads), 0, s, rgb, target, w, h,
-                       st.rows, lambda, make_window(), maps, gate, dl);
+                       st.rows, lambda, make_window(), maps, gate, scale, dl);
     return hipGetLastError();
 }
 

@@ -522,10 +522,11 @@ __device__ __forceinline__ void sh_coef_grad(const ViewSH& o, float* g_sh) {
 // The per-Gaussian backward. All parameters of the Gaussian are loaded at
 // once; the gradient stays in registers, and the update (kFused: Adam on every
 // plane, dense as in the paper's optimiser, also for Gaussians visible in no
-// view; otherwise: gradient ADDED to grads, visible Gaussians only) runs over
+// view; otherwise: gradient ADDED to grads, visible Gaussians only, or with
+// kWrite written there, zero where no view sees the Gaussian) runs over
 // the planes in batches whose moment (or gradient) loads are issued one batch
 // ahead, so that each thread keeps several memory requests in flight.
-template <int sh_degree, bool kFused, bool kMulti, bool kSparse = false>
+template <int sh_degree, bool kFused, bool kMulti, bool kSparse = false, bool kWrite = false>
 __device__ __forceinline__ void gaussian_backward(float* __restrict__ planes, int64_t n,
                                                   int64_t stride, int64_t i,
                                                   const Views* __restrict__ views,
@@ -578,7 +579,7 @@ __device__ __forceinline__ void gaussian_backward(float* __restrict__ planes, in
     }
     // without a visible entry: nothing to add (gradient accumulation), or,
     // for the visible-only (sparse) Adam step, nothing to update
-    if ((!kFused || kSparse) && !any) return;
+    if ((!kFused || kSparse) && !kWrite && !any) return;
     float Y[16];
     if constexpr (!kMulti) {
         if (any) sh_eval(sh_degree, one.d[0], one.d[1], one.d[2], Y);
@@ -603,7 +604,7 @@ __device__ __forceinline__ void gaussian_backward(float* __restrict__ planes, in
                     ma[buf][t] = M.template load<kPlaneCP>(j, off);
                     va[buf][t] = Vb.template load<kPlaneCP>(j, off);
                 } else {
-                    ma[buf][t] = G.load(j, off);
+                    ma[buf][t] = kWrite ? 0.f : G.load(j, off);
                 }
             }
         }
@@ -624,15 +625,21 @@ __device__ __forceinline__ void gaussian_backward(float* __restrict__ planes, in
                     M.template store<kPlaneCP>(j, off, mm);
                     Vb.template store<kPlaneCP>(j, off, vv);
                 } else {
-                    G.store(j, off, ma[b & 1][t] + gj);
+                    // (through L2: 661 us for 6M Gaussians written, streamed 679)
+                    G.template store<0>(j, off, ma[b & 1][t] + gj);
                 }
             }
         }
     }
 }
 
-// Adjoint of the projection: one thread per Gaussian, gradient ADDED to grads.
-template <int sh_degree, bool kMulti>
+// Adjoint of the projection: one thread per Gaussian, gradient ADDED to grads
+// or, with kWrite, written (also the zeros of the padding past n): a gradient
+// that starts at zero then needs neither the clearing nor the reading back of
+// its array. 6M Gaussians, SH 3: 1006 us and 200 us of clearing before, 661 now
+// (4.7 TB/s); with the zeros of unseen Gaussians stored by a branch of their own
+// 820, every line being written in two parts.
+template <int sh_degree, bool kMulti, bool kWrite>
 __global__ void __launch_bounds__(kBackwardThreads) project_backward_kernel(
     const float* __restrict__ planes, int64_t n, int64_t stride, const Views* __restrict__ views,
     RasterDev rp,
@@ -640,10 +647,18 @@ __global__ void __launch_bounds__(kBackwardThreads) project_backward_kernel(
     const float4* __restrict__ acc, const int32_t* __restrict__ gate, float* __restrict__ grads) {
     if (gate_closed(gate)) return;
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    gaussian_backward<sh_degree, false, kMulti>(const_cast<float*>(planes), n, stride, i, views,
-                                                rp, rec, tiles, acc, grads, nullptr, nullptr,
-                                                nullptr, nullptr);
+    if (i >= n) {
+        if constexpr (kWrite) {
+            constexpr int NP = 11 + 3 * (sh_degree + 1) * (sh_degree + 1);
+            const PlaneBuf G{grads, stride};
+            if (i < stride)
+                for (int j = 0; j < NP; ++j) G.store(j, (uint32_t)i * 4u, 0.f);
+        }
+        return;
+    }
+    gaussian_backward<sh_degree, false, kMulti, false, kWrite>(
+        const_cast<float*>(planes), n, stride, i, views, rp, rec, tiles, acc, grads, nullptr,
+        nullptr, nullptr, nullptr);
 }
 
 // Adjoint of the projection fused with the Adam step: every Gaussian (dense
@@ -759,17 +774,22 @@ hipError_t launch_load_records(const float* u, const float* v, const float* dept
 
 hipError_t launch_project_backward(const float* planes, int64_t n, int64_t stride,
                                    int sh_degree, const RasterDev& rp, const Layout& L, char* ws,
-                                   const int32_t* gate, float* grads, hipStream_t s) {
-    if (n == 0) return hipSuccess;
+                                   const int32_t* gate, float* grads, bool write, hipStream_t s) {
+    const int64_t count = write ? stride : n;
+    if (count == 0) return hipSuccess;
     const int nt = kBackwardThreads;
-    const int64_t nb = (n + nt - 1) / nt;
+    const int64_t nb = (count + nt - 1) / nt;
     const Views* views = reinterpret_cast<const Views*>(ws + L.views);
     const float4* rec = reinterpret_cast<const float4*>(ws + L.records);
     const uint32_t* tl = reinterpret_cast<const uint32_t*>(ws + L.tiles);
     const float4* acc = reinterpret_cast<const float4*>(ws + L.accum);
 #define SGS_PB(D, M)                                                                              \
-    hipLaunchKernelGGL((project_backward_kernel<D, M>), dim3((unsigned)nb), dim3(nt), 0, s, planes, \
-                       n, stride, views, rp, rec, tl, acc, gate, grads)
+    if (write)                                                                                    \
+        hipLaunchKernelGGL((project_backward_kernel<D, M, true>), dim3((unsigned)nb), dim3(nt), 0, \
+                           s, planes, n, stride, views, rp, rec, tl, acc, gate, grads);           \
+    else                                                                                          \
+        hipLaunchKernelGGL((project_backward_kernel<D, M, false>), dim3((unsigned)nb), dim3(nt),  \
+                           0, s, planes, n, stride, views, rp, rec, tl, acc, gate, grads)
     SGS_DISPATCH_DEG(SGS_PB, L.n_views > 1)
 #undef SGS_PB
     return hipGetLastError();

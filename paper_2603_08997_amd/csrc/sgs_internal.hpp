@@ -238,7 +238,7 @@ hipError_t launch_rasterize_backward(const RasterDev& rp, const Layout& L, char*
                                      const Views* views, int32_t* step = nullptr);
 hipError_t launch_project_backward(const float* planes, int64_t n, int64_t stride,
                                    int sh_degree, const RasterDev& rp, const Layout& L, char* ws,
-                                   const int32_t* gate, float* grads, hipStream_t s);
+                                   const int32_t* gate, float* grads, bool write, hipStream_t s);
 
 // p[0..n) = v on stream s (a kernel, so that callers can be captured).
 hipError_t fill_u32(uint32_t* p, int64_t n, uint32_t v, hipStream_t s);
@@ -304,7 +304,8 @@ hipError_t launch_loss_forward(const float* rgb, TargetRef target, int w, int h,
                                char* ws, float* d_loss, hipStream_t s,
                                const LossGate& gate = LossGate{});
 hipError_t launch_loss_backward(const float* rgb, TargetRef target, int w, int h, float lambda,
-                                char* ws, const int32_t* gate, float* dl, hipStream_t s);
+                                char* ws, const int32_t* gate, float* dl, hipStream_t s,
+                                const float* scale = nullptr);
 size_t loss_workspace_bytes(int w, int h);
 // The loss forward with the per-tile partial sums (loss_partial_floats(w, h)
 // floats) in caller-provided device memory.

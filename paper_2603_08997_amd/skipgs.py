@@ -87,9 +87,10 @@ class AdamParamsC(C.Structure):
 EXPORTS = [
     "sgs_last_error", "sgs_version", "sgs_default_raster_params", "sgs_forward_workspace_size",
     "sgs_render_forward", "sgs_read_status", "sgs_clear_status", "sgs_render_backward",
-    "sgs_project", "sgs_load_records", "sgs_bin", "sgs_rasterize", "sgs_rasterize_backward",
+    "sgs_render_gradients", "sgs_project", "sgs_load_records", "sgs_bin", "sgs_rasterize", "sgs_rasterize_backward",
     "sgs_project_backward", "sgs_get_workspace_layout", "sgs_loss_workspace_size",
     "sgs_photometric_loss", "sgs_photometric_loss_backward", "sgs_photometric_loss_static",
+    "sgs_photometric_loss_gradient",
     "sgs_gate_state_size",
     "sgs_gate_init", "sgs_gate_update", "sgs_gate_read", "sgs_adam_step",
     "sgs_project_backward_adam", "sgs_render_backward_adam", "sgs_camera_table_size",
@@ -116,6 +117,8 @@ def _load():
         "sgs_clear_status": (i32, [vp, vp]),
         "sgs_render_backward": (i32, [P(GaussiansC), P(CameraC), i32, P(RasterParamsC), vp, sz, i64,
                                       vp, vp, vp, vp]),
+        "sgs_render_gradients": (i32, [P(GaussiansC), P(CameraC), i32, P(RasterParamsC), vp, sz,
+                                       i64, vp, vp, vp]),
         "sgs_project": (i32, [P(GaussiansC), P(CameraC), i32, P(RasterParamsC), vp, sz, i64, vp]),
         "sgs_load_records": (i32, [P(CameraC), i32, i64, P(RasterParamsC), vp, sz, i64, vp, vp, vp,
                                    vp, vp, vp, vp, vp]),
@@ -131,6 +134,7 @@ def _load():
         "sgs_photometric_loss": (i32, [vp, vp, i32, i32, f32, vp, sz, vp, vp]),
         "sgs_photometric_loss_static": (i32, [vp, vp, i32, i32, f32, vp, vp]),
         "sgs_photometric_loss_backward": (i32, [vp, vp, i32, i32, f32, vp, sz, vp, vp, vp]),
+        "sgs_photometric_loss_gradient": (i32, [vp, vp, i32, i32, f32, vp, sz, vp, vp, vp]),
         "sgs_gate_state_size": (i32, [P(GateParamsC), P(sz)]),
         "sgs_gate_init": (i32, [P(GateParamsC), vp, vp]),
         "sgs_gate_update": (i32, [P(GateParamsC), vp, vp, vp, vp, vp]),
@@ -204,33 +208,26 @@ class RasterParams:
     jac_clamp: float = 1.3
 
     def c(self) -> RasterParamsC:
-        r = RasterParamsC()
-        r.struct_size = C.sizeof(RasterParamsC)
-        r.tile_w, r.tile_h = self.tile_w, self.tile_h
-        r.super_tile, r.lds_batch = self.super_tile, self.lds_batch
-        r.split_prefix = self.split_prefix
-        for k in range(3):
-            r.bg[k] = self.bg[k]
-        r.near_z, r.dilation = self.near_z, self.dilation
-        r.alpha_min, r.alpha_max, r.t_min, r.jac_clamp = (self.alpha_min, self.alpha_max,
-                                                          self.t_min, self.jac_clamp)
-        return r
+        return RasterParamsC(C.sizeof(RasterParamsC), self.tile_w, self.tile_h, self.super_tile,
+                             self.lds_batch, self.split_prefix,
+                             (C.c_float * 3)(self.bg[0], self.bg[1], self.bg[2]), self.near_z,
+                             self.dilation, self.alpha_min, self.alpha_max, self.t_min,
+                             self.jac_clamp)
 
 
 def camera_c(cam) -> CameraC:
     c = CameraC()
-    R = np.asarray(cam.R, dtype=np.float32).reshape(9)
-    t = np.asarray(cam.t, dtype=np.float32).reshape(3)
-    for k in range(9):
-        c.R[k] = float(R[k])
-    for k in range(3):
-        c.t[k] = float(t[k])
+    c.R[:] = np.asarray(cam.R, dtype=np.float32).reshape(9).tolist()
+    c.t[:] = np.asarray(cam.t, dtype=np.float32).reshape(3).tolist()
     c.fx, c.fy, c.cx, c.cy = float(cam.fx), float(cam.fy), float(cam.cx), float(cam.cy)
     c.width, c.height = int(cam.width), int(cam.height)
     return c
 
 
 def cameras_c(cams):
+    """``cams`` marshalled (as they are if they already come marshalled)."""
+    if isinstance(cams, C.Array) and cams._type_ is CameraC:
+        return cams
     arr = (CameraC * len(cams))()
     for i, cam in enumerate(cams):
         arr[i] = camera_c(cam)
@@ -290,6 +287,14 @@ def render_backward(planes, n, sh_degree, cams, rp: RasterParams, workspace, pai
     _check(LIB.sgs_render_backward(C.byref(g), cameras_c(cams), len(cams), C.byref(rp.c()),
                                    _ptr(workspace), workspace.numel(), pair_capacity, _ptr(dl_drgb),
                                    _ptr(d_gate), _ptr(grads), _stream(stream)))
+
+
+def render_gradients(planes, n, sh_degree, cams, rp: RasterParams, workspace, pair_capacity, dl_drgb,
+                     grads, stream=None):
+    g = gaussians_c(planes, n, sh_degree)
+    _check(LIB.sgs_render_gradients(C.byref(g), cameras_c(cams), len(cams), C.byref(rp.c()),
+                                    _ptr(workspace), workspace.numel(), pair_capacity,
+                                    _ptr(dl_drgb), _ptr(grads), _stream(stream)))
 
 
 def project(planes, n, sh_degree, cams, rp, workspace, pair_capacity, stream=None):
@@ -382,6 +387,13 @@ def photometric_loss_backward(rgb, target, width, height, lam, workspace, d_gate
                               stream=None):
     _check(LIB.sgs_photometric_loss_backward(_ptr(rgb), _ptr(target), width, height, float(lam),
                                              _ptr(workspace), workspace.numel(), _ptr(d_gate),
+                                             _ptr(dl_drgb), _stream(stream)))
+
+
+def photometric_loss_gradient(rgb, target, width, height, lam, workspace, d_scale, dl_drgb,
+                              stream=None):
+    _check(LIB.sgs_photometric_loss_gradient(_ptr(rgb), _ptr(target), width, height, float(lam),
+                                             _ptr(workspace), workspace.numel(), _ptr(d_scale),
                                              _ptr(dl_drgb), _stream(stream)))
 
 
