@@ -20,12 +20,10 @@
 // thresholds formed in binary64 on the host, and the statistic's sum with
 // threshold * count in binary64, so they are exact for the given inputs.
 //
-// Three launches: per-block counts of the three outcomes (packed in one word
-// per thread), a one-workgroup scan of the block counts that also records the
-// size of the new set, and the write, which repeats the decisions, scans them
-// within the block and streams every plane of every output Gaussian; all
-// outputs of one segment from one block are consecutive, so the stores
-// coalesce. An output set larger than the output planes' stride is reported
+// Two launches: per-block counts of the three outcomes (packed in one word
+// per thread), and the write, which adds up the counts, repeats the decisions,
+// scans them within the block and streams every plane of every output Gaussian;
+// all outputs of one segment from one block are consecutive. An output set larger than the output planes' stride is reported
 // and nothing is written.
 #include <algorithm>
 
@@ -36,9 +34,14 @@ namespace sgs {
 
 namespace {
 
-constexpr int kDensifyThreads = 256;
-constexpr int kDensifyScanThreads = 1024;
+// Inputs of a workgroup: kWriteParts a thread.
+constexpr int kDensifyThreads = 512;
+constexpr int kWriteParts = 4;
+constexpr int kWriteInputs = kDensifyThreads * kWriteParts;
+constexpr uint32_t kNoClone = 0xffffu;
+constexpr int kLineWords = 32;
 // outcome counts packed in one word: keep in bits 0-9, clone 10-19, split 20-29
+// (up to kDensifyThreads of each)
 constexpr int kClonePos = 10, kSplitPos = 20;
 constexpr uint32_t kField = (1u << 10) - 1u;
 
@@ -65,8 +68,8 @@ __global__ void __launch_bounds__(256) densify_stats_kernel(
     }
 }
 
-// Output stores through L2 with the default policy: the outputs of a wave
-// start at arbitrary positions, so their cache lines are filled by several
+// Output stores through L2 with the default policy: the lines at the ends of a
+// workgroup's outputs, and those of clones and children, are filled by several
 // waves and are best merged in L2 before they go to HBM.
 __device__ __forceinline__ void put(const PlaneBuf& B, int j, uint32_t lane_off, float x) {
     __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(x), B.rsrc(j), (int)lane_off, 0, 0);
@@ -83,105 +86,151 @@ __device__ __forceinline__ uint32_t outcome(const PlaneBuf& P, uint32_t off, flo
                            : (1u | (1u << kClonePos));   // keep and clone
 }
 
+// Outcomes of each workgroup of the write: counts[k nblocks + b], k = kept,
+// clones, split.
 __global__ void __launch_bounds__(kDensifyThreads) densify_count_kernel(
     PlaneBuf P, int64_t n, const float* __restrict__ grad_sum, const int32_t* __restrict__ count,
-    DensifyDev d, uint32_t* __restrict__ block_counts) {
-    __shared__ uint32_t smem[kDensifyThreads / 64 + 1];
-    const int64_t i = (int64_t)blockIdx.x * kDensifyThreads + threadIdx.x;
-    const uint32_t o = i < n ? outcome(P, (uint32_t)i * 4u, grad_sum[i], count[i], d) : 0u;
-    uint32_t tot;
-    block_excl_scan<kDensifyThreads>(o, smem, &tot);
-    if (threadIdx.x == 0) block_counts[blockIdx.x] = tot;
-}
-
-// block_off[3 b + k]: outputs of segment k (kept, clones, split Gaussians)
-// before block b; meta[0..2]: the totals; *n_out: the size of the new set.
-__global__ void __launch_bounds__(kDensifyScanThreads) densify_scan_kernel(
-    const uint32_t* __restrict__ block_counts, int64_t nblocks, uint32_t* __restrict__ block_off,
-    uint32_t* __restrict__ meta, int64_t* __restrict__ n_out) {
-    __shared__ uint32_t smem[kDensifyScanThreads / 64 + 1];
-    uint32_t carry[3] = {0u, 0u, 0u};
-    for (int64_t b0 = 0; b0 < nblocks; b0 += kDensifyScanThreads) {
-        const int64_t b = b0 + threadIdx.x;
-        const uint32_t w = b < nblocks ? block_counts[b] : 0u;
-        const uint32_t v[3] = {w & kField, (w >> kClonePos) & kField, (w >> kSplitPos) & kField};
-        uint32_t ex[3];
+    DensifyDev d, uint32_t* __restrict__ counts) {
+    __shared__ uint32_t s_sum[3];
+    if (threadIdx.x < 3) s_sum[threadIdx.x] = 0u;
+    __syncthreads();
+    const int64_t first = (int64_t)blockIdx.x * kWriteInputs + threadIdx.x;
+    uint32_t o = 0;   // (at most kWriteParts of each)
 #pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            uint32_t tot;
-            ex[k] = carry[k] + block_excl_scan<kDensifyScanThreads>(v[k], smem, &tot);
-            carry[k] += tot;
-        }
-        if (b < nblocks) {
-            block_off[3 * b] = ex[0];
-            block_off[3 * b + 1] = ex[1];
-            block_off[3 * b + 2] = ex[2];
-        }
+    for (int part = 0; part < kWriteParts; ++part) {
+        const int64_t i = first + part * kDensifyThreads;
+        if (i < n) o += outcome(P, (uint32_t)i * 4u, grad_sum[i], count[i], d);
     }
-    if (threadIdx.x == 0) {
-        meta[0] = carry[0];
-        meta[1] = carry[1];
-        meta[2] = carry[2];
-        *n_out = (int64_t)carry[0] + (int64_t)carry[1] + 2 * (int64_t)carry[2];
+#pragma unroll
+    for (int k = 32; k > 0; k >>= 1) o += (uint32_t)__shfl_xor((int)o, k, 64);
+    if (threadIdx.x % 64 == 0) {
+        atomicAdd(&s_sum[0], o & kField);
+        atomicAdd(&s_sum[1], (o >> kClonePos) & kField);
+        atomicAdd(&s_sum[2], (o >> kSplitPos) & kField);
     }
+    __syncthreads();
+    if (threadIdx.x < 3)
+        counts[(int64_t)threadIdx.x * gridDim.x + blockIdx.x] = s_sum[threadIdx.x];
 }
 
+// The write. A workgroup adds up the counts of all workgroups (its outputs' places
+// and the size of the new set), repeats the decisions of its inputs and lists
+// its outputs in LDS (the input of each kept output and the rank of its clone,
+// the inputs that split). The kept outputs are then walked in positions aligned
+// to the cache line, so that a line is written by one wave but at the ends of
+// the workgroup's range, and loads, which then straddle lines, go through L2, in
+// groups of kGroup planes whose loads are all issued before their stores; a
+// clone's store takes its parent's value from the same lane. Children take two
+// threads a split Gaussian, and the zero moments of all new Gaussians are one
+// range, cleared in whole lines.
+//
+// What bounds it: HBM (3M Gaussians, SH 3: 4.5 GB). One input a thread with its
+// outputs stored where they fell took 1483 us, every line in parts from several
+// waves on different XCDs; now 1026 (4.3 TB/s). Of the same with cached stores
+// 1171, with streamed loads 1488 (1.5 lines fetched for each one used), in
+// workgroups of 256 threads and 4096 inputs 1057, of 512 and 4096 1045. Adding up
+// 1465 counts in every workgroup replaces a scan launch of 28 us.
 __global__ void __launch_bounds__(kDensifyThreads) densify_write_kernel(
-    PlaneBuf P, PlaneBuf M, PlaneBuf V, int64_t n, int F, const float* __restrict__ grad_sum,
-    const int32_t* __restrict__ count, const float* __restrict__ normals, DensifyDev d,
-    const uint32_t* __restrict__ block_off, const uint32_t* __restrict__ meta,
-    const int64_t* __restrict__ n_out, int64_t out_stride, PlaneBuf PO, PlaneBuf MO, PlaneBuf VO) {
-    __shared__ uint32_t smem[kDensifyThreads / 64 + 1];
-    if (*n_out > out_stride) return;   // the caller provides larger planes and calls again
-    const int64_t i = (int64_t)blockIdx.x * kDensifyThreads + threadIdx.x;
-    const uint32_t off = (uint32_t)i * 4u;
-    const uint32_t o = i < n ? outcome(P, off, grad_sum[i], count[i], d) : 0u;
-    uint32_t tot;
-    const uint32_t ex = block_excl_scan<kDensifyThreads>(o, smem, &tot);
-    if (o == 0u) return;
-    const uint32_t K = meta[0], Cn = meta[1];
-    const uint32_t* bo = block_off + 3 * (int64_t)blockIdx.x;
-    const bool keep = (o & kField) != 0u, clone = ((o >> kClonePos) & kField) != 0u;
-    const bool split = ((o >> kSplitPos) & kField) != 0u;
-    const uint32_t pk = bo[0] + (ex & kField);
-    const uint32_t pc = K + bo[1] + ((ex >> kClonePos) & kField);
-    const uint32_t ps = K + Cn + 2u * (bo[2] + ((ex >> kSplitPos) & kField));
-    if (keep || clone) {
-        // planes in groups of kGroup, every load of a group issued before its
-        // stores, so that each lane keeps many loads in flight
-        constexpr int kGroup = 8;
+    PlaneBuf P, PlaneBuf M, PlaneBuf V, int64_t n, int F,
+    const float* __restrict__ grad_sum, const int32_t* __restrict__ count,
+    const float* __restrict__ normals, DensifyDev d, const uint32_t* __restrict__ counts,
+    int64_t* __restrict__ n_out, int64_t out_stride, PlaneBuf PO, PlaneBuf MO, PlaneBuf VO) {
+    constexpr int kWaves = kDensifyThreads / 64;
+    __shared__ uint32_t smem[kWaves + 1];
+    __shared__ uint32_t s_sum[6];
+    __shared__ uint16_t s_kept[kWriteInputs];    // input (within the workgroup) of a kept output
+    __shared__ uint16_t s_clone[kWriteInputs];   // rank of its clone, or kNoClone
+    __shared__ uint16_t s_split[kWriteInputs];
+    const int tid = threadIdx.x;
+    // neighbouring workgroups on one XCD: the lines they share meet in its L2
+    const int nblocks = (int)gridDim.x;
+    const int blk = xcd_block(blockIdx.x, nblocks);
+    // totals of the three outcomes and those of the workgroups before
+    if (tid < 6) s_sum[tid] = 0u;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        uint32_t all = 0, before = 0;
+        for_rows(counts + (int64_t)k * nblocks, 1, tid, nblocks, kDensifyThreads,
+                 [&](int j, uint32_t c) {
+                     all += c;
+                     before += j < blk ? c : 0u;
+                 });
+#pragma unroll
+        for (int x = 32; x > 0; x >>= 1) {
+            all += (uint32_t)__shfl_xor((int)all, x, 64);
+            before += (uint32_t)__shfl_xor((int)before, x, 64);
+        }
+        if (tid % 64 == 0) {
+            atomicAdd(&s_sum[k], all);
+            atomicAdd(&s_sum[3 + k], before);
+        }
+    }
+    __syncthreads();
+    const uint32_t K = s_sum[0], Cn = s_sum[1];
+    const int64_t out = (int64_t)K + (int64_t)Cn + 2 * (int64_t)s_sum[2];
+    if (blockIdx.x == 0 && tid == 0) *n_out = out;
+    if (out > out_stride) return;   // the caller provides larger planes and calls again
+    const uint32_t k0 = s_sum[3], c0 = K + s_sum[4], s0 = K + Cn + 2u * s_sum[5];
+    const int64_t first = (int64_t)blk * kWriteInputs;
+    uint32_t kept = 0, clones = 0, splits = 0;
+    for (int part = 0; part < kWriteParts; ++part) {
+        const int local = part * kDensifyThreads + tid;
+        const int64_t i = first + local;
+        const uint32_t o = i < n ? outcome(P, (uint32_t)i * 4u, grad_sum[i], count[i], d) : 0u;
+        uint32_t tot;
+        const uint32_t ex = block_excl_scan<kDensifyThreads>(o, smem, &tot);
+        if (o & kField) {
+            const uint32_t at = kept + (ex & kField);
+            s_kept[at] = (uint16_t)local;
+            s_clone[at] = (uint16_t)((o >> kClonePos) & kField
+                                         ? clones + ((ex >> kClonePos) & kField) : kNoClone);
+        }
+        if ((o >> kSplitPos) & kField)
+            s_split[splits + ((ex >> kSplitPos) & kField)] = (uint16_t)local;
+        kept += tot & kField;
+        clones += (tot >> kClonePos) & kField;
+        splits += (tot >> kSplitPos) & kField;
+    }
+    __syncthreads();
+    constexpr int kGroup = 8;
+    // kept Gaussians and clones
+    for (uint32_t p0 = k0 & ~(uint32_t)(kLineWords - 1); p0 < k0 + kept; p0 += kDensifyThreads) {
+        const uint32_t p = p0 + (uint32_t)tid;
+        if (p < k0 || p >= k0 + kept) continue;
+        const uint32_t off = (uint32_t)(first + s_kept[p - k0]) * 4u;
+        const uint32_t clone = s_clone[p - k0];
+        const uint32_t pc = (c0 + clone) * 4u;
         for (int f0 = 0; f0 < F; f0 += kGroup) {
             float x[kGroup], mm[kGroup], vv[kGroup];
 #pragma unroll
             for (int k = 0; k < kGroup; ++k) {
                 const int f = min(f0 + k, F - 1);
-                x[k] = P.load(f, off);
-                mm[k] = keep ? M.load(f, off) : 0.f;
-                vv[k] = keep ? V.load(f, off) : 0.f;
+                x[k] = P.load<0>(f, off);
+                mm[k] = M.load<0>(f, off);
+                vv[k] = V.load<0>(f, off);
             }
 #pragma unroll
             for (int k = 0; k < kGroup; ++k) {
                 const int f = f0 + k;
                 if (f >= F) break;
-                if (keep) {
-                    put(PO, f, pk * 4u, x[k]);
-                    put(MO, f, pk * 4u, mm[k]);
-                    put(VO, f, pk * 4u, vv[k]);
-                }
-                if (clone) {
-                    put(PO, f, pc * 4u, x[k]);
-                    put(MO, f, pc * 4u, 0.f);
-                    put(VO, f, pc * 4u, 0.f);
-                }
+                PO.store(f, p * 4u, x[k]);
+                MO.store(f, p * 4u, mm[k]);
+                VO.store(f, p * 4u, vv[k]);
+                if (clone != kNoClone) put(PO, f, pc, x[k]);
             }
         }
     }
-    if (split) {
-        float mu[3], s[3], q[4];
+    // children
+    for (uint32_t c = tid; c < 2u * splits; c += kDensifyThreads) {
+        const int64_t i = first + s_split[c / 2u];
+        const uint32_t off = (uint32_t)i * 4u, po = (s0 + c) * 4u;
+        float mu[3], ls[3], s[3], q[4];
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
             mu[k] = P.load(k, off);
-            s[k] = expf(P.load(3 + k, off));
+            ls[k] = P.load(3 + k, off);
+            s[k] = expf(ls[k]);
         }
 #pragma unroll
         for (int k = 0; k < 4; ++k) q[k] = P.load(6 + k, off);
@@ -190,27 +239,40 @@ __global__ void __launch_bounds__(kDensifyThreads) densify_write_kernel(
         const float R[9] = {1.f - 2.f * (y * y + z * z), 2.f * (x * y - w * z), 2.f * (x * z + w * y),
                             2.f * (x * y + w * z), 1.f - 2.f * (x * x + z * z), 2.f * (y * z - w * x),
                             2.f * (x * z - w * y), 2.f * (y * z + w * x), 1.f - 2.f * (x * x + y * y)};
-        for (int j = 0; j < 2; ++j) {
-            const uint32_t po = (ps + (uint32_t)j) * 4u;
-            const float* zj = normals + 6 * i + 3 * j;
-            const float t[3] = {s[0] * zj[0], s[1] * zj[1], s[2] * zj[2]};
+        const float* zj = normals + 6 * i + 3 * (c % 2u);
+        const float t[3] = {s[0] * zj[0], s[1] * zj[1], s[2] * zj[2]};
 #pragma unroll
-            for (int r = 0; r < 3; ++r)
-                put(PO, r, po, mu[r] + (R[3 * r] * t[0] + R[3 * r + 1] * t[1] + R[3 * r + 2] * t[2]));
+        for (int r = 0; r < 3; ++r)
+            put(PO, r, po, mu[r] + (R[3 * r] * t[0] + R[3 * r + 1] * t[1] + R[3 * r + 2] * t[2]));
 #pragma unroll
-            for (int k = 0; k < 3; ++k) put(PO, 3 + k, po, P.load(3 + k, off) - d.log_split);
-            for (int f = 6; f < F; ++f) put(PO, f, po, P.load(f, off));
-            for (int f = 0; f < F; ++f) {
-                put(MO, f, po, 0.f);
-                put(VO, f, po, 0.f);
-            }
+        for (int k = 0; k < 3; ++k) put(PO, 3 + k, po, ls[k] - d.log_split);
+        for (int f0 = 6; f0 < F; f0 += kGroup) {
+            float v[kGroup];
+#pragma unroll
+            for (int k = 0; k < kGroup; ++k) v[k] = P.load(min(f0 + k, F - 1), off);
+#pragma unroll
+            for (int k = 0; k < kGroup; ++k)
+                if (f0 + k < F) put(PO, f0 + k, po, v[k]);
+        }
+    }
+    // the moments of the new Gaussians: workgroup after workgroup takes a stretch
+    // of whole lines of every plane
+    const int64_t z0 = K & ~63u;
+    const int64_t each = ((out - z0 + nblocks - 1) / nblocks + 63) & ~(int64_t)63;
+    const int64_t a = z0 + blk * each;
+    for (int64_t p = a + tid % 64; p < min(a + each, out); p += 64) {
+        if (p < (int64_t)K) continue;
+        for (int f = tid / 64; f < F; f += kDensifyThreads / 64) {
+            MO.store(f, (uint32_t)p * 4u, 0.f);
+            VO.store(f, (uint32_t)p * 4u, 0.f);
         }
     }
 }
 
 }  // namespace
 
-int64_t densify_blocks(int64_t n) { return (n + kDensifyThreads - 1) / kDensifyThreads; }
+// (what a caller's scratch is sized by)
+int64_t densify_blocks(int64_t n) { return (n + 255) / 256; }
 
 hipError_t launch_densify_stats(const Layout& L, char* ws, int64_t n, const int32_t* gate,
                                 float* grad_sum, int32_t* count, hipStream_t s) {
@@ -227,21 +289,13 @@ hipError_t launch_densify(const DensifyDev& d, float* params, float* m, float* v
                           int64_t stride, int F, const float* grad_sum, const int32_t* count,
                           const float* normals, float* out_params, float* out_m, float* out_v,
                           int64_t out_stride, uint32_t* scratch, int64_t* n_out, hipStream_t s) {
-    const int64_t nb = densify_blocks(n);
-    uint32_t* block_counts = scratch;
-    uint32_t* block_off = scratch + nb;
-    uint32_t* meta = scratch + 4 * nb;
+    const int64_t nb = std::max<int64_t>(1, (n + kWriteInputs - 1) / kWriteInputs);
     const PlaneBuf P{params, stride}, M{m, stride}, V{v, stride};
     const PlaneBuf PO{out_params, out_stride}, MO{out_m, out_stride}, VO{out_v, out_stride};
-    if (nb > 0)
-        hipLaunchKernelGGL(densify_count_kernel, dim3((unsigned)nb), dim3(kDensifyThreads), 0, s, P,
-                           n, grad_sum, count, d, block_counts);
-    hipLaunchKernelGGL(densify_scan_kernel, dim3(1), dim3(kDensifyScanThreads), 0, s, block_counts,
-                       nb, block_off, meta, n_out);
-    if (nb > 0)
-        hipLaunchKernelGGL(densify_write_kernel, dim3((unsigned)nb), dim3(kDensifyThreads), 0, s, P,
-                           M, V, n, F, grad_sum, count, normals, d, block_off, meta, n_out,
-                           out_stride, PO, MO, VO);
+    hipLaunchKernelGGL(densify_count_kernel, dim3((unsigned)nb), dim3(kDensifyThreads), 0, s, P, n,
+                       grad_sum, count, d, scratch);
+    hipLaunchKernelGGL(densify_write_kernel, dim3((unsigned)nb), dim3(kDensifyThreads), 0, s, P, M,
+                       V, n, F, grad_sum, count, normals, d, scratch, n_out, out_stride, PO, MO, VO);
     return hipGetLastError();
 }
 
