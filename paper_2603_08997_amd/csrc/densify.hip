@@ -34,14 +34,11 @@ namespace sgs {
 
 namespace {
 
-// Inputs of a workgroup: kWriteParts a thread.
-constexpr int kDensifyThreads = 512;
-constexpr int kWriteParts = 4;
-constexpr int kWriteInputs = kDensifyThreads * kWriteParts;
 constexpr uint32_t kNoClone = 0xffffu;
 constexpr int kLineWords = 32;
+constexpr int kGroup = 8;   // planes whose loads are in flight together
 // outcome counts packed in one word: keep in bits 0-9, clone 10-19, split 20-29
-// (up to kDensifyThreads of each)
+// (up to a workgroup's threads of each)
 constexpr int kClonePos = 10, kSplitPos = 20;
 constexpr uint32_t kField = (1u << 10) - 1u;
 
@@ -88,17 +85,19 @@ __device__ __forceinline__ uint32_t outcome(const PlaneBuf& P, uint32_t off, flo
 
 // Outcomes of each workgroup of the write: counts[k nblocks + b], k = kept,
 // clones, split.
-__global__ void __launch_bounds__(kDensifyThreads) densify_count_kernel(
+template <int T, int kParts>
+__global__ void __launch_bounds__(T) densify_count_kernel(
     PlaneBuf P, int64_t n, const float* __restrict__ grad_sum, const int32_t* __restrict__ count,
     DensifyDev d, uint32_t* __restrict__ counts) {
+    constexpr int kWriteInputs = T * kParts;
     __shared__ uint32_t s_sum[3];
     if (threadIdx.x < 3) s_sum[threadIdx.x] = 0u;
     __syncthreads();
     const int64_t first = (int64_t)blockIdx.x * kWriteInputs + threadIdx.x;
-    uint32_t o = 0;   // (at most kWriteParts of each)
+    uint32_t o = 0;   // (at most kParts of each)
 #pragma unroll
-    for (int part = 0; part < kWriteParts; ++part) {
-        const int64_t i = first + part * kDensifyThreads;
+    for (int part = 0; part < kParts; ++part) {
+        const int64_t i = first + part * T;
         if (i < n) o += outcome(P, (uint32_t)i * 4u, grad_sum[i], count[i], d);
     }
 #pragma unroll
@@ -130,12 +129,15 @@ __global__ void __launch_bounds__(kDensifyThreads) densify_count_kernel(
 // 1171, with streamed loads 1488 (1.5 lines fetched for each one used), in
 // workgroups of 256 threads and 4096 inputs 1057, of 512 and 4096 1045. Adding up
 // 1465 counts in every workgroup replaces a scan launch of 28 us.
-__global__ void __launch_bounds__(kDensifyThreads) densify_write_kernel(
+template <int T, int kParts>
+__global__ void __launch_bounds__(T) densify_write_kernel(
     PlaneBuf P, PlaneBuf M, PlaneBuf V, int64_t n, int F,
     const float* __restrict__ grad_sum, const int32_t* __restrict__ count,
     const float* __restrict__ normals, DensifyDev d, const uint32_t* __restrict__ counts,
     int64_t* __restrict__ n_out, int64_t out_stride, PlaneBuf PO, PlaneBuf MO, PlaneBuf VO) {
-    constexpr int kWaves = kDensifyThreads / 64;
+    constexpr int kWaves = T / 64, kWriteInputs = T * kParts;
+    // (three counts a workgroup: the scratch has four words per 256 inputs)
+    static_assert(T * kParts >= 256 && T <= 512, "scratch and packed counts");
     __shared__ uint32_t smem[kWaves + 1];
     __shared__ uint32_t s_sum[6];
     __shared__ uint16_t s_kept[kWriteInputs];    // input (within the workgroup) of a kept output
@@ -151,7 +153,7 @@ __global__ void __launch_bounds__(kDensifyThreads) densify_write_kernel(
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
         uint32_t all = 0, before = 0;
-        for_rows(counts + (int64_t)k * nblocks, 1, tid, nblocks, kDensifyThreads,
+        for_rows(counts + (int64_t)k * nblocks, 1, tid, nblocks, T,
                  [&](int j, uint32_t c) {
                      all += c;
                      before += j < blk ? c : 0u;
@@ -169,17 +171,17 @@ __global__ void __launch_bounds__(kDensifyThreads) densify_write_kernel(
     __syncthreads();
     const uint32_t K = s_sum[0], Cn = s_sum[1];
     const int64_t out = (int64_t)K + (int64_t)Cn + 2 * (int64_t)s_sum[2];
-    if (blockIdx.x == 0 && tid == 0) *n_out = out;
+    if (blockIdx.x == 0 && blockIdx.y == 0 && tid == 0) *n_out = out;
     if (out > out_stride) return;   // the caller provides larger planes and calls again
     const uint32_t k0 = s_sum[3], c0 = K + s_sum[4], s0 = K + Cn + 2u * s_sum[5];
     const int64_t first = (int64_t)blk * kWriteInputs;
     uint32_t kept = 0, clones = 0, splits = 0;
-    for (int part = 0; part < kWriteParts; ++part) {
-        const int local = part * kDensifyThreads + tid;
+    for (int r = 0; r < kParts; ++r) {
+        const int local = r * T + tid;
         const int64_t i = first + local;
         const uint32_t o = i < n ? outcome(P, (uint32_t)i * 4u, grad_sum[i], count[i], d) : 0u;
         uint32_t tot;
-        const uint32_t ex = block_excl_scan<kDensifyThreads>(o, smem, &tot);
+        const uint32_t ex = block_excl_scan<T>(o, smem, &tot);
         if (o & kField) {
             const uint32_t at = kept + (ex & kField);
             s_kept[at] = (uint16_t)local;
@@ -193,15 +195,15 @@ __global__ void __launch_bounds__(kDensifyThreads) densify_write_kernel(
         splits += (tot >> kSplitPos) & kField;
     }
     __syncthreads();
-    constexpr int kGroup = 8;
+    const int part = blockIdx.y, parts = gridDim.y;   // which groups of planes
     // kept Gaussians and clones
-    for (uint32_t p0 = k0 & ~(uint32_t)(kLineWords - 1); p0 < k0 + kept; p0 += kDensifyThreads) {
+    for (uint32_t p0 = k0 & ~(uint32_t)(kLineWords - 1); p0 < k0 + kept; p0 += T) {
         const uint32_t p = p0 + (uint32_t)tid;
         if (p < k0 || p >= k0 + kept) continue;
         const uint32_t off = (uint32_t)(first + s_kept[p - k0]) * 4u;
         const uint32_t clone = s_clone[p - k0];
         const uint32_t pc = (c0 + clone) * 4u;
-        for (int f0 = 0; f0 < F; f0 += kGroup) {
+        for (int f0 = part * kGroup; f0 < F; f0 += parts * kGroup) {
             float x[kGroup], mm[kGroup], vv[kGroup];
 #pragma unroll
             for (int k = 0; k < kGroup; ++k) {
@@ -222,31 +224,33 @@ __global__ void __launch_bounds__(kDensifyThreads) densify_write_kernel(
         }
     }
     // children
-    for (uint32_t c = tid; c < 2u * splits; c += kDensifyThreads) {
+    for (uint32_t c = tid; c < 2u * splits; c += T) {
         const int64_t i = first + s_split[c / 2u];
         const uint32_t off = (uint32_t)i * 4u, po = (s0 + c) * 4u;
-        float mu[3], ls[3], s[3], q[4];
+        if (part == 0) {
+            float mu[3], ls[3], s[3], q[4];
 #pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            mu[k] = P.load(k, off);
-            ls[k] = P.load(3 + k, off);
-            s[k] = expf(ls[k]);
+            for (int k = 0; k < 3; ++k) {
+                mu[k] = P.load(k, off);
+                ls[k] = P.load(3 + k, off);
+                s[k] = expf(ls[k]);
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) q[k] = P.load(6 + k, off);
+            const float qn = 1.f / sqrtf(q[0] * q[0] + q[1] * q[1] + q[2] * q[2] + q[3] * q[3]);
+            const float w = q[0] * qn, x = q[1] * qn, y = q[2] * qn, z = q[3] * qn;
+            const float R[9] = {1.f - 2.f * (y * y + z * z), 2.f * (x * y - w * z), 2.f * (x * z + w * y),
+                                2.f * (x * y + w * z), 1.f - 2.f * (x * x + z * z), 2.f * (y * z - w * x),
+                                2.f * (x * z - w * y), 2.f * (y * z + w * x), 1.f - 2.f * (x * x + y * y)};
+            const float* zj = normals + 6 * i + 3 * (c % 2u);
+            const float t[3] = {s[0] * zj[0], s[1] * zj[1], s[2] * zj[2]};
+#pragma unroll
+            for (int r = 0; r < 3; ++r)
+                put(PO, r, po, mu[r] + (R[3 * r] * t[0] + R[3 * r + 1] * t[1] + R[3 * r + 2] * t[2]));
+#pragma unroll
+            for (int k = 0; k < 3; ++k) put(PO, 3 + k, po, ls[k] - d.log_split);
         }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) q[k] = P.load(6 + k, off);
-        const float qn = 1.f / sqrtf(q[0] * q[0] + q[1] * q[1] + q[2] * q[2] + q[3] * q[3]);
-        const float w = q[0] * qn, x = q[1] * qn, y = q[2] * qn, z = q[3] * qn;
-        const float R[9] = {1.f - 2.f * (y * y + z * z), 2.f * (x * y - w * z), 2.f * (x * z + w * y),
-                            2.f * (x * y + w * z), 1.f - 2.f * (x * x + z * z), 2.f * (y * z - w * x),
-                            2.f * (x * z - w * y), 2.f * (y * z + w * x), 1.f - 2.f * (x * x + y * y)};
-        const float* zj = normals + 6 * i + 3 * (c % 2u);
-        const float t[3] = {s[0] * zj[0], s[1] * zj[1], s[2] * zj[2]};
-#pragma unroll
-        for (int r = 0; r < 3; ++r)
-            put(PO, r, po, mu[r] + (R[3 * r] * t[0] + R[3 * r + 1] * t[1] + R[3 * r + 2] * t[2]));
-#pragma unroll
-        for (int k = 0; k < 3; ++k) put(PO, 3 + k, po, ls[k] - d.log_split);
-        for (int f0 = 6; f0 < F; f0 += kGroup) {
+        for (int f0 = 6 + part * kGroup; f0 < F; f0 += parts * kGroup) {
             float v[kGroup];
 #pragma unroll
             for (int k = 0; k < kGroup; ++k) v[k] = P.load(min(f0 + k, F - 1), off);
@@ -262,7 +266,7 @@ __global__ void __launch_bounds__(kDensifyThreads) densify_write_kernel(
     const int64_t a = z0 + blk * each;
     for (int64_t p = a + tid % 64; p < min(a + each, out); p += 64) {
         if (p < (int64_t)K) continue;
-        for (int f = tid / 64; f < F; f += kDensifyThreads / 64) {
+        for (int f = tid / 64 + part * (T / 64); f < F; f += parts * (T / 64)) {
             MO.store(f, (uint32_t)p * 4u, 0.f);
             VO.store(f, (uint32_t)p * 4u, 0.f);
         }
@@ -285,17 +289,38 @@ hipError_t launch_densify_stats(const Layout& L, char* ws, int64_t n, const int3
     return hipGetLastError();
 }
 
+// Inputs up to which a workgroup takes 256 of them, 2048 beyond: fewer leave
+// the chip idle, more share fewer lines (SH 3, us of a step with 256 / 2048:
+// 120k inputs 58 / 121, 250k 94 / 137, 500k 203 / 178, 2M 792 / 691). And
+// workgroups from which the planes are no longer dealt out to several workgroups
+// of the same inputs: below, a workgroup's chain of groups of planes is the time
+// (5k inputs 34 us without, 14 with; 30k 36 / 21, 120k 58 / 53). With one scan
+// launch and a thread an input: 5k 42, 30k 92, 120k 123, 500k 342, 2M 1041.
+constexpr int64_t kDensifySmall = 1 << 18;
+constexpr int64_t kDensifyBlocks = 1024;
+
 hipError_t launch_densify(const DensifyDev& d, float* params, float* m, float* v, int64_t n,
                           int64_t stride, int F, const float* grad_sum, const int32_t* count,
                           const float* normals, float* out_params, float* out_m, float* out_v,
                           int64_t out_stride, uint32_t* scratch, int64_t* n_out, hipStream_t s) {
-    const int64_t nb = std::max<int64_t>(1, (n + kWriteInputs - 1) / kWriteInputs);
     const PlaneBuf P{params, stride}, M{m, stride}, V{v, stride};
     const PlaneBuf PO{out_params, out_stride}, MO{out_m, out_stride}, VO{out_v, out_stride};
-    hipLaunchKernelGGL(densify_count_kernel, dim3((unsigned)nb), dim3(kDensifyThreads), 0, s, P, n,
-                       grad_sum, count, d, scratch);
-    hipLaunchKernelGGL(densify_write_kernel, dim3((unsigned)nb), dim3(kDensifyThreads), 0, s, P, M,
-                       V, n, F, grad_sum, count, normals, d, scratch, n_out, out_stride, PO, MO, VO);
+    const int64_t groups = (F + kGroup - 1) / kGroup;
+#define SGS_DENSIFY(T, PARTS, SPLIT)                                                             \
+    do {                                                                                         \
+        const int64_t nb = std::max<int64_t>(1, (n + T * PARTS - 1) / (T * PARTS));              \
+        const int64_t py = SPLIT ? std::clamp<int64_t>(kDensifyBlocks / nb, 1, groups) : 1;      \
+        hipLaunchKernelGGL((densify_count_kernel<T, PARTS>), dim3((unsigned)nb), dim3(T), 0, s, P, \
+                           n, grad_sum, count, d, scratch);                                      \
+        hipLaunchKernelGGL((densify_write_kernel<T, PARTS>), dim3((unsigned)nb, (unsigned)py),   \
+                           dim3(T), 0, s, P, M, V, n, F, grad_sum, count, normals, d, scratch,   \
+                           n_out, out_stride, PO, MO, VO);                                       \
+    } while (0)
+    if (n <= kDensifySmall)
+        SGS_DENSIFY(256, 1, true);
+    else
+        SGS_DENSIFY(512, 4, false);
+#undef SGS_DENSIFY
     return hipGetLastError();
 }
 

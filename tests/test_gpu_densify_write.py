@@ -12,7 +12,7 @@ from tests.test_gpu_densify import _gpu_densify, _inputs
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n", [1, 511, 513, 2048, 2049, 6200])
+@pytest.mark.parametrize("n", [1, 255, 257, 2049, 6200, 262145])
 @pytest.mark.parametrize("outcome", ["mixed", "keep", "clone", "split", "prune"])
 def test_write(n, outcome):
     require_gpu()
