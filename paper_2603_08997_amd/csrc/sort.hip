@@ -282,23 +282,29 @@ __global__ void __launch_bounds__(kThreads) radix_scatter_kernel(
 // The depth sort of a set that one workgroup holds: every pass in LDS, in one
 // launch instead of eight that each last a launch's latency (a few us). Wave w
 // ranks positions [w 64 R, (w+1) 64 R) as in the scatter above. 1000 entries: 49 us
-// before, 8.9 now. Whole binning with the sort in one workgroup / in eight
-// launches: 1k entries 42 / 88 us, 4k 54 / 88, 8k 69 / 88; a workgroup twice that
-// long would gain nothing and its 16 keys a thread don't fit the registers.
-constexpr int kSmallThreads = 1024;
-constexpr int kSmallWaves = kSmallThreads / 64;
-constexpr int64_t kSmallSort = (int64_t)kSmallThreads * 8;
-template <int R>
-__global__ void __launch_bounds__(kSmallThreads) small_sort_kernel(
-    EntrySrc src, uint32_t* __restrict__ vals_out, uint32_t* __restrict__ kept,
-    uint32_t* __restrict__ weight_sum) {
-    __shared__ uint32_t lkeys[kSmallThreads * R];
-    __shared__ uint32_t lvals[kSmallThreads * R];
-    __shared__ uint32_t wcnt[kSmallWaves][kRadix];   // keys of each digit per wave
-    __shared__ uint32_t smem[kSmallWaves + 1];
-    __shared__ uint64_t wsum[kSmallWaves];
+// before, 8.9 now. The whole binning of 2000 entries: 45 us, 51 by sorted runs,
+// 77 in eight launches; with 8 keys a thread 4k / 8k entries took 62 / 67 us where
+// runs take 53 / 54.
+//
+// kRuns: every workgroup sorts its own range of inputs into a run (keys and
+// values at the range's start), for merge_runs_kernel; run_count and run_weight
+// get the number of its visible entries and their weights' sum.
+constexpr int64_t kSmallSort = 2048;
+template <int T, int R, bool kRuns>
+__global__ void __launch_bounds__(T) small_sort_kernel(
+    EntrySrc src, uint32_t* __restrict__ keys_out, uint32_t* __restrict__ vals_out,
+    uint32_t* __restrict__ kept, uint32_t* __restrict__ weight_sum,
+    uint32_t* __restrict__ run_count, uint64_t* __restrict__ run_weight) {
+    constexpr int NW = T / 64;
+    static_assert(T >= kRadix, "a digit a thread");
+    __shared__ uint32_t lkeys[T * R];
+    __shared__ uint32_t lvals[T * R];
+    __shared__ uint32_t wcnt[NW][kRadix];   // keys of each digit per wave
+    __shared__ uint32_t smem[NW + 1];
+    __shared__ uint64_t wsum[NW];
     const int tid = threadIdx.x, w = tid / 64, lane = tid % 64;
-    int n = (int)src.n;
+    const int64_t base = kRuns ? (int64_t)blockIdx.x * (T * R) : 0;
+    int n = (int)min(src.n - base, (int64_t)(T * R));
     uint32_t key[R], val[R], rank[R];
     uint32_t ok = 0;
     uint64_t sum = 0;
@@ -307,8 +313,8 @@ __global__ void __launch_bounds__(kSmallThreads) small_sort_kernel(
         const int i = (w * R + it) * 64 + lane;
         key[it] = val[it] = 0u;
         if (i < n) {
-            if (src.load(i, key[it], val[it])) ok |= 1u << it;
-            sum += src.weight(i);
+            if (src.load(base + i, key[it], val[it])) ok |= 1u << it;
+            sum += src.weight(base + i);
         }
     }
 #pragma unroll
@@ -334,18 +340,18 @@ __global__ void __launch_bounds__(kSmallThreads) small_sort_kernel(
         }
         __syncthreads();
         // per digit (thread tid): the start of every wave's keys
-        uint32_t c[kSmallWaves], total = 0, all;
+        uint32_t c[NW], total = 0, all;
         if (tid < kRadix) {
 #pragma unroll
-            for (int k = 0; k < kSmallWaves; ++k) {
+            for (int k = 0; k < NW; ++k) {
                 c[k] = wcnt[k][tid];
                 total += c[k];
             }
         }
-        uint32_t start = block_excl_scan<kSmallThreads>(total, smem, &all);
+        uint32_t start = block_excl_scan<T>(total, smem, &all);
         if (tid < kRadix) {
 #pragma unroll
-            for (int k = 0; k < kSmallWaves; ++k) {
+            for (int k = 0; k < NW; ++k) {
                 wcnt[k][tid] = start;
                 start += c[k];
             }
@@ -373,13 +379,160 @@ __global__ void __launch_bounds__(kSmallThreads) small_sort_kernel(
             }
         }
     }
-    for (int i = tid; i < n; i += kSmallThreads) vals_out[i] = lvals[i];
+    for (int i = tid; i < n; i += T) {
+        if (kRuns) keys_out[base + i] = lkeys[i];
+        vals_out[base + i] = lvals[i];
+    }
     if (tid == 0) {
         sum = 0;
-        for (int k = 0; k < kSmallWaves; ++k) sum += wsum[k];
-        *kept = (uint32_t)n;
-        *weight_sum = (uint32_t)min(sum, (uint64_t)0xffffffffull);
+        for (int k = 0; k < NW; ++k) sum += wsum[k];
+        if (kRuns) {
+            run_count[blockIdx.x] = (uint32_t)n;
+            run_weight[blockIdx.x] = sum;
+        } else {
+            *kept = (uint32_t)n;
+            *weight_sum = (uint32_t)min(sum, (uint64_t)0xffffffffull);
+        }
     }
+}
+
+// Merge of all runs in one launch: a thread an entry, whose place is its place
+// in its run and, in every other run, the number of entries before it (equal
+// keys: those of earlier runs, whose inputs come first). A workgroup takes
+// kMergeThreads neighbouring entries of a run: it finds the stretches of the
+// other runs between its smallest and its largest key, brings them into LDS, and
+// its threads search there (stretches that don't fit are searched where they
+// are).
+//
+// What bounds it: latency, and with the number of runs the searches, which grow
+// with the square of the set. The whole binning, two launches / eight: 8k entries
+// 54 / 86 us, 16k 58 / 87, 30k 66 / 90, 65k 81 / 94, 131k 153 / 101 (64 runs). With
+// every search in global memory 30k took 80 us and 65k 119.
+constexpr int kRunThreads = 1024;
+constexpr int kRunKeys = 2;
+constexpr int kRun = kRunThreads * kRunKeys;
+constexpr int kMergeThreads = 256;
+constexpr int kMaxRuns = 32;
+constexpr int kSearches = 4;        // at a time
+constexpr int kStretch = 10240;     // keys in LDS
+constexpr int64_t kRunSort = (int64_t)kRun * kMaxRuns;   // entries up to which runs are merged
+__global__ void __launch_bounds__(kMergeThreads) merge_runs_kernel(
+    const uint32_t* __restrict__ keys, const uint32_t* __restrict__ vals, int runs,
+    const uint32_t* __restrict__ run_count, const uint64_t* __restrict__ run_weight,
+    uint32_t* __restrict__ vals_out, uint32_t* __restrict__ kept,
+    uint32_t* __restrict__ weight_sum) {
+    constexpr int kParts = kRun / kMergeThreads;
+    __shared__ uint32_t s_keys[kStretch];
+    __shared__ int s_end[2][kMaxRuns];   // per run: first and past the last key of the stretch
+    __shared__ int s_at[kMaxRuns];       // its place in s_keys, or -1
+    const int tid = threadIdx.x;
+    const int run = blockIdx.x / kParts, first = (int)(blockIdx.x % kParts) * kMergeThreads;
+    if (blockIdx.x == 0 && tid < 64) {
+        uint32_t n = 0;
+        uint64_t w = 0;
+        if (tid < runs) {
+            n = run_count[tid];
+            w = run_weight[tid];
+        }
+#pragma unroll
+        for (int d = 32; d > 0; d >>= 1) {
+            n += (uint32_t)__shfl_xor((int)n, d, 64);
+            w += __shfl_xor(w, d, 64);
+        }
+        if (tid == 0) {
+            *kept = n;
+            *weight_sum = (uint32_t)min(w, (uint64_t)0xffffffffull);
+        }
+    }
+    const int mine = (int)run_count[run] - first;   // entries of this workgroup and after
+    if (mine <= 0) return;                          // uniform
+    const uint32_t* own = keys + (int64_t)run * kRun + first;
+    const uint32_t lo = own[0], hi = own[min(mine, kMergeThreads) - 1];
+    {
+        // keys below lo and up to hi in every run, runs side by side: of 64 evenly
+        // spaced keys, then of the 32 from the last such key that counts
+        constexpr int NQ = kMaxRuns / (kMergeThreads / 64), kStep = kRun / 64;
+        static_assert(2 * kStep == 64, "two searches a wave");
+        const int w = tid / 64, lane = tid % 64;
+        int n[NQ], from[NQ];
+        uint32_t k[NQ];
+#pragma unroll
+        for (int j = 0; j < NQ; ++j) {
+            const int q = w + j * (kMergeThreads / 64), at = (lane + 1) * kStep - 1;
+            n[j] = q < runs && q != run ? (int)run_count[min(q, runs - 1)] : 0;
+            k[j] = at < n[j] ? keys[(int64_t)q * kRun + at] : 0u;
+        }
+#pragma unroll
+        for (int j = 0; j < NQ; ++j) {
+            const int q = w + j * (kMergeThreads / 64), at = (lane + 1) * kStep - 1;
+            const int a = kStep * popc64(ballot(at < n[j] && k[j] < lo));
+            const int b = kStep * popc64(ballot(at < n[j] && k[j] <= hi));
+            from[j] = lane < kStep ? a : b;
+            const int i = from[j] + lane % kStep;
+            k[j] = i < n[j] ? keys[(int64_t)q * kRun + i] : 0u;
+        }
+#pragma unroll
+        for (int j = 0; j < NQ; ++j) {
+            const int q = w + j * (kMergeThreads / 64), i = from[j] + lane % kStep;
+            const uint64_t m =
+                ballot(i < n[j] && (lane < kStep ? k[j] < lo : k[j] <= hi));
+            if (lane % kStep == 0)
+                s_end[lane / kStep][q] = from[j] + popc64(lane ? m >> kStep : m & 0xffffffffull);
+        }
+    }
+    __syncthreads();
+    if (tid < kMaxRuns) {
+        const int n = s_end[1][tid] - s_end[0][tid];
+        const int at = (int)wave_incl_scan((uint32_t)n) - n;
+        s_at[tid] = at + n <= kStretch ? at : -1;
+    }
+    __syncthreads();
+    for (int q = tid / 64; q < runs; q += kMergeThreads / 64) {
+        const int a = s_end[0][q], n = s_end[1][q] - a, at = s_at[q];
+        if (at < 0) continue;
+        for (int k = tid % 64; k < n; k += 64) s_keys[at + k] = keys[(int64_t)q * kRun + a + k];
+    }
+    __syncthreads();
+    if (tid >= mine) return;
+    const uint32_t key = own[tid];
+    int place = first + tid;
+    for (int q0 = 0; q0 < runs; q0 += kSearches) {
+        int pos[kSearches], n[kSearches], at[kSearches], longest = 0;
+        bool fits = true;
+#pragma unroll
+        for (int u = 0; u < kSearches; ++u) {
+            const int q = min(q0 + u, kMaxRuns - 1);
+            const int a = __builtin_amdgcn_readfirstlane(s_end[0][q]);
+            n[u] = __builtin_amdgcn_readfirstlane(s_end[1][q]) - a;   // (0 past the last run)
+            at[u] = __builtin_amdgcn_readfirstlane(s_at[q]);
+            place += a;
+            pos[u] = 0;
+            longest = max(longest, n[u]);
+            fits &= at[u] >= 0;
+        }
+        if (longest == 0) continue;
+        auto search = [&](auto key_at) {
+            for (int half = 1 << (31 - __builtin_clz((unsigned)longest)); half > 0; half >>= 1) {
+#pragma unroll
+                for (int u = 0; u < kSearches; ++u) {
+                    const int i = pos[u] + half - 1;
+                    const uint32_t k = key_at(u, max(min(i, n[u] - 1), 0));
+                    const bool before = k < key || (q0 + u < run && k == key);
+                    pos[u] += i < n[u] && before ? half : 0;
+                }
+            }
+        };
+        if (fits)   // uniform
+            search([&](int u, int i) { return s_keys[min(at[u] + i, kStretch - 1)]; });
+        else
+            search([&](int u, int i) {
+                const int q = min(q0 + u, runs - 1);
+                return keys[(int64_t)q * kRun + min(s_end[0][q] + i, kRun - 1)];
+            });
+#pragma unroll
+        for (int u = 0; u < kSearches; ++u) place += pos[u];
+    }
+    vals_out[place] = vals[(int64_t)run * kRun + first + tid];
 }
 
 struct Pass {
@@ -428,13 +581,25 @@ hipError_t sort_entries(const uint32_t* depth, const uint32_t* tiles, int64_t en
                         uint64_t* weights, uint32_t* n_visible, uint32_t* pairs, hipStream_t s) {
     if (entries <= kSmallSort) {
         const EntrySrc src{depth, tiles, entries};
-        const dim3 one(1), block(kSmallThreads);
-        if (entries <= kSmallThreads)
-            hipLaunchKernelGGL(small_sort_kernel<1>, one, block, 0, s, src, vals[1], n_visible, pairs);
-        else if (entries <= 4 * kSmallThreads)
-            hipLaunchKernelGGL(small_sort_kernel<4>, one, block, 0, s, src, vals[1], n_visible, pairs);
+        if (entries <= 1024)
+            hipLaunchKernelGGL((small_sort_kernel<1024, 1, false>), dim3(1), dim3(1024), 0, s, src,
+                               nullptr, vals[1], n_visible, pairs, nullptr, nullptr);
         else
-            hipLaunchKernelGGL(small_sort_kernel<8>, one, block, 0, s, src, vals[1], n_visible, pairs);
+            hipLaunchKernelGGL((small_sort_kernel<1024, 2, false>), dim3(1), dim3(1024), 0, s, src,
+                               nullptr, vals[1], n_visible, pairs, nullptr, nullptr);
+        return hipGetLastError();
+    }
+    if (entries <= kRunSort) {
+        const EntrySrc src{depth, tiles, entries};
+        const int runs = (int)((entries + kRun - 1) / kRun);
+        uint64_t* run_weight = reinterpret_cast<uint64_t*>(hist);
+        uint32_t* run_count = hist + 2 * runs;
+        hipLaunchKernelGGL((small_sort_kernel<kRunThreads, kRunKeys, true>), dim3(runs),
+                           dim3(kRunThreads), 0, s, src, keys[0], vals[0], nullptr, nullptr,
+                           run_count, run_weight);
+        hipLaunchKernelGGL(merge_runs_kernel, dim3(runs * (kRun / kMergeThreads)),
+                           dim3(kMergeThreads), 0, s, keys[0], vals[0], runs, run_count, run_weight,
+                           vals[1], n_visible, pairs);
         return hipGetLastError();
     }
     const int64_t gw = radix_group_words(entries, 1);
