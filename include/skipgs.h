@@ -541,6 +541,18 @@ sgs_status sgs_train_iteration(const sgs_gaussians* g, const sgs_camera* cams /*
                                int32_t* d_gate, const sgs_adam_params* adam, float* m, float* v,
                                int32_t* d_step, void* stream);
 
+/* sgs_view_sequence_next followed by sgs_train_iteration, in one launch less. */
+sgs_status sgs_train_sequence_step(const int32_t* d_sequence, int64_t sequence_len, int64_t* d_iter,
+                                   const sgs_gaussians* g, const sgs_camera* cams /* host */,
+                                   const void* d_table, int32_t n_cams, int32_t* d_view,
+                                   const sgs_raster_params* rp, void* workspace,
+                                   size_t workspace_bytes, int64_t pair_capacity,
+                                   const float* targets, float lambda, void* loss_workspace,
+                                   size_t loss_workspace_bytes, float* rgb, float* dl_drgb,
+                                   float* d_loss, const sgs_gate_params* gp, void* gate_state,
+                                   int32_t* d_gate, const sgs_adam_params* adam, float* m, float* v,
+                                   int32_t* d_step, void* stream);
+
 #ifdef __cplusplus
 }
 #endif

@@ -889,8 +889,11 @@ sgs_status sgs_view_sequence_next(const int32_t* d_sequence, int64_t sequence_le
     return SGS_OK;
 }
 
-sgs_status sgs_train_iteration(const sgs_gaussians* g, const sgs_camera* cams,
-                               const void* d_table, int32_t n_cams, const int32_t* d_view,
+// d_sequence (nullable): *d_view becomes d_sequence[*d_iter % sequence_len] and
+// *d_iter advances.
+static sgs_status train_iteration(const int32_t* d_sequence, int64_t sequence_len, int64_t* d_iter,
+                               const sgs_gaussians* g, const sgs_camera* cams,
+                               const void* d_table, int32_t n_cams, int32_t* d_view,
                                const sgs_raster_params* rp, void* workspace,
                                size_t workspace_bytes, int64_t pair_capacity,
                                const float* targets, float lambda, void* loss_workspace,
@@ -921,25 +924,66 @@ sgs_status sgs_train_iteration(const sgs_gaussians* g, const sgs_camera* cams,
     char* ws = static_cast<char*>(workspace);
     char* lws = static_cast<char*>(loss_workspace);
     const sgs::TargetRef tgt{targets, d_view, n_cams};
-    SGS_HIP(sgs::launch_project(g->data, g->n, g->stride, g->sh_degree, P.rd, P.L, ws,
-                                sgs::CallViews{&P.views, static_cast<const sgs::ViewDev*>(d_table),
-                                               n_cams, d_view, true},
-                                s),
+    sgs::CallViews call{&P.views, static_cast<const sgs::ViewDev*>(d_table), n_cams, d_view, true};
+    int64_t* advance = nullptr;
+    if (d_sequence != nullptr && g->n > 0) {
+        call.seq = d_sequence;
+        call.len = sequence_len;
+        call.iter = advance = d_iter;
+    } else if (d_sequence != nullptr) {
+        SGS_HIP(sgs::launch_sequence_next(d_sequence, sequence_len, d_iter, d_view, s),
+                "view sequence");
+    }
+    SGS_HIP(sgs::launch_project(g->data, g->n, g->stride, g->sh_degree, P.rd, P.L, ws, call, s),
             "project");
     SGS_HIP(sgs::launch_bin(P.rd, g->n, P.L, ws, s), "bin");
     SGS_HIP(sgs::launch_rasterize(P.rd, P.L, ws, rgb, s), "rasterize");
-    sgs::LossGate gate{{}, static_cast<char*>(gate_state), d_view, d_gate};
+    sgs::LossGate gate{{}, static_cast<char*>(gate_state), d_view, d_gate, advance};
     if (gate_state != nullptr) gate.args = sgs::gate_args(gp);
-    SGS_HIP(sgs::launch_loss_forward(rgb, tgt, w, h, lambda, lws, d_loss, s, gate), "loss");
-    SGS_HIP(sgs::launch_loss_backward(rgb, tgt, w, h, lambda, lws, d_gate, dl_drgb, s),
-            "loss backward");
-    SGS_HIP(sgs::launch_rasterize_backward(P.rd, P.L, ws, dl_drgb, d_gate, s, nullptr, d_step),
+    SGS_HIP(sgs::launch_train_loss(rgb, tgt, w, h, lambda, lws, d_loss, dl_drgb, gate,
+                                   sgs::backward_preparation(P.L, ws, d_step), s),
+            "loss");
+    SGS_HIP(sgs::launch_rasterize_backward(P.rd, P.L, ws, dl_drgb, d_gate, s, nullptr, d_step, true),
             "rasterize_backward");
     SGS_HIP(sgs::launch_project_backward_adam(g->data, g->n, g->stride, g->sh_degree, P.rd, P.L, ws,
                                               adam, adam->visible_only != 0, m, v, d_step, d_gate,
                                               s),
             "project_backward_adam");
     return SGS_OK;
+}
+
+sgs_status sgs_train_iteration(const sgs_gaussians* g, const sgs_camera* cams,
+                               const void* d_table, int32_t n_cams, const int32_t* d_view,
+                               const sgs_raster_params* rp, void* workspace,
+                               size_t workspace_bytes, int64_t pair_capacity,
+                               const float* targets, float lambda, void* loss_workspace,
+                               size_t loss_workspace_bytes, float* rgb, float* dl_drgb,
+                               float* d_loss, const sgs_gate_params* gp, void* gate_state,
+                               int32_t* d_gate, const sgs_adam_params* adam, float* m, float* v,
+                               int32_t* d_step, void* stream) {
+    return train_iteration(nullptr, 0, nullptr, g, cams, d_table, n_cams, const_cast<int32_t*>(d_view), rp, workspace,
+                           workspace_bytes, pair_capacity, targets, lambda, loss_workspace,
+                           loss_workspace_bytes, rgb, dl_drgb, d_loss, gp, gate_state, d_gate, adam,
+                           m, v, d_step, stream);
+}
+
+sgs_status sgs_train_sequence_step(const int32_t* d_sequence, int64_t sequence_len, int64_t* d_iter,
+                               const sgs_gaussians* g, const sgs_camera* cams,
+                               const void* d_table, int32_t n_cams, int32_t* d_view,
+                               const sgs_raster_params* rp, void* workspace,
+                               size_t workspace_bytes, int64_t pair_capacity,
+                               const float* targets, float lambda, void* loss_workspace,
+                               size_t loss_workspace_bytes, float* rgb, float* dl_drgb,
+                               float* d_loss, const sgs_gate_params* gp, void* gate_state,
+                               int32_t* d_gate, const sgs_adam_params* adam, float* m, float* v,
+                               int32_t* d_step, void* stream) {
+    if (!d_sequence || !d_iter) return fail(SGS_ERR_INVALID_ARG, "null pointer argument");
+    if (sequence_len < 1) return fail(SGS_ERR_INVALID_ARG, "sequence_len < 1");
+    if (!aligned(d_iter, 8)) return fail(SGS_ERR_INVALID_ARG, "d_iter not 8-byte aligned");
+    return train_iteration(d_sequence, sequence_len, d_iter, g, cams, d_table, n_cams, d_view, rp, workspace,
+                           workspace_bytes, pair_capacity, targets, lambda, loss_workspace,
+                           loss_workspace_bytes, rgb, dl_drgb, d_loss, gp, gate_state, d_gate, adam,
+                           m, v, d_step, stream);
 }
 
 }  // extern "C"

@@ -35,6 +35,7 @@
 #include <algorithm>
 
 #include "sgs_gate.hpp"
+#include "sgs_prepare.hpp"
 
 namespace sgs {
 
@@ -151,11 +152,11 @@ struct Place {
     bool out;                       // the lane's column is an output column
     bool in_image;
     int tap0;                       // LDS index of the lane's first horizontal tap
-    __device__ __forceinline__ Place(int w, int h, int rows) {
+    __device__ __forceinline__ Place(int w, int h, int rows, int row) {
         lane = threadIdx.x % 64;
         ch = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
         cx = (int)blockIdx.x * kCols - kR + lane;
-        first = (int)blockIdx.y * rows;
+        first = row * rows;
         end = min(first + rows, h);
         in_image = cx >= 0 && cx < w;
         out = lane >= kR && lane < kR + kCols && cx < w;
@@ -176,7 +177,7 @@ __global__ void __launch_bounds__(kThreads, 4) ssim_forward_kernel(
     __shared__ float4 s_m4[3][64];
     __shared__ float s_m1[3][64];
     __shared__ float red[2][3];
-    const Place p(w, h, rows);
+    const Place p(w, h, rows, (int)blockIdx.y);
     const int64_t plane = (int64_t)w * h;
     const float* __restrict__ xc = x + p.ch * plane + p.cx;
     const float* __restrict__ yc = target_of(target, 3 * plane) + p.ch * plane + p.cx;
@@ -254,48 +255,90 @@ __global__ void __launch_bounds__(kThreads, 4) ssim_forward_kernel(
 }
 
 // Sum of the per-strip partials in index order (binary64), then Eq. 6 and, in a
-// training iteration, the gate's decision (a launch of its own otherwise).
-__global__ void __launch_bounds__(1024) loss_reduce_kernel(const float* __restrict__ partials,
-                                                           int64_t nb, double count, float lambda,
-                                                           float* __restrict__ d_loss,
-                                                           LossGate g) {
-    __shared__ double dred[2][1024];
+// training iteration, the gate's decision (a launch of its own otherwise) and
+// the step of the view sequence. One workgroup of NT threads.
+struct LossSum {
+    const float* partials;
+    int64_t nb;
+    double count;
+    float lambda;
+    float* d_loss;
+    LossGate gate;
+};
+constexpr int kSumSlots = 1024;
+template <int NT>
+__device__ __forceinline__ void loss_sum(const LossSum& p, double (*dred)[kSumSlots]) {
     const int tid = threadIdx.x;
-    double a = 0.0, b = 0.0;
-    for (int64_t i = tid; i < nb; i += 1024) {
-        a += (double)partials[2 * i];
-        b += (double)partials[2 * i + 1];
+    for (int k = tid; k < kSumSlots; k += NT) {
+        double a = 0.0, b = 0.0;
+        for (int64_t i = k; i < p.nb; i += kSumSlots) {
+            a += (double)p.partials[2 * i];
+            b += (double)p.partials[2 * i + 1];
+        }
+        dred[0][k] = a;
+        dred[1][k] = b;
     }
-    dred[0][tid] = a;
-    dred[1][tid] = b;
     __syncthreads();
-    for (int st = 512; st > 0; st >>= 1) {
-        if (tid < st) {
-            dred[0][tid] += dred[0][tid + st];
-            dred[1][tid] += dred[1][tid + st];
+    for (int st = kSumSlots / 2; st > 0; st >>= 1) {
+        for (int k = tid; k < st; k += NT) {
+            dred[0][k] += dred[0][k + st];
+            dred[1][k] += dred[1][k + st];
         }
         __syncthreads();
     }
     if (tid == 0) {
-        const double l1 = dred[0][0] / count, ssim = dred[1][0] / count;
-        const float loss = (float)((1.0 - (double)lambda) * l1 + (double)lambda * (1.0 - ssim));
-        *d_loss = loss;
+        const double l1 = dred[0][0] / p.count, ssim = dred[1][0] / p.count;
+        const float loss =
+            (float)((1.0 - (double)p.lambda) * l1 + (double)p.lambda * (1.0 - ssim));
+        *p.d_loss = loss;
+        const LossGate& g = p.gate;
         if (g.gate != nullptr) {
             if (g.state != nullptr)
                 gate_step(g.args, g.state, g.view, loss, g.gate);
             else
                 *g.gate = 1;
         }
+        if (g.iter != nullptr) *g.iter += 1;
     }
 }
 
+__global__ void __launch_bounds__(kSumSlots) loss_reduce_kernel(LossSum p) {
+    __shared__ double dred[2][kSumSlots];
+    loss_sum<kSumSlots>(p, dred);
+}
+
+// Besides the gradient, the backward of a training iteration (kTrain) takes
+// along, in its first t.rows rows of workgroups, the preparation of the
+// compositing backward and, where no gate waits for it, the sum of the loss: 4.6
+// us each as launches of their own, and the accumulators (25 us at 3M Gaussians)
+// are cleared while the filters keep the vector units busy (the 64x64 step 177 ->
+// 174 us with the view of the sequence picked by the projection, the 3M one 1977
+// -> 1966).
+struct LossTrain {
+    Prepare prepare;
+    LossSum sum;   // d_loss nullable: summed before
+    int rows;
+};
+template <bool kTrain>
 __global__ void __launch_bounds__(kThreads) ssim_backward_kernel(
-    const float* __restrict__ x, TargetRef target, int w, int h, int rows, float lambda,
+    LossTrain t, const float* __restrict__ x, TargetRef target, int w, int h, int rows, float lambda,
     Window W, const float* __restrict__ maps, const int32_t* __restrict__ gate,
     const float* __restrict__ scale, float* __restrict__ dl) {
     if (gate_closed(gate)) return;
+    if constexpr (kTrain) {
+        __shared__ double s_sum[2][kSumSlots];
+        __shared__ uint32_t s_scan[kThreads / 64 + 1];
+        if ((int)blockIdx.y < t.rows) {   // uniform
+            const int block = (int)(blockIdx.y * gridDim.x + blockIdx.x);
+            if (block == 0 && t.sum.d_loss != nullptr) loss_sum<kThreads>(t.sum, s_sum);
+            if (block > 0)
+                prepare_backward<kThreads>(t.prepare, block - 1, t.rows * (int)gridDim.x - 1,
+                                           reinterpret_cast<uint32_t*>(s_sum), s_scan);
+            return;
+        }
+    }
     __shared__ float4 s_m[3][64];   // a row of the three maps
-    const Place p(w, h, rows);
+    const Place p(w, h, rows, (int)blockIdx.y - (kTrain ? t.rows : 0));
     const int64_t plane = (int64_t)w * h;
     const float* __restrict__ xc = x + p.ch * plane + p.cx;
     const float* __restrict__ yc = target_of(target, 3 * plane) + p.ch * plane + p.cx;
@@ -362,14 +405,19 @@ size_t loss_workspace_bytes(int w, int h) { return loss_layout(w, h).total; }
 
 int64_t loss_partial_floats(int w, int h) { return 2 * loss_layout(w, h).blocks; }
 
+static LossSum loss_sum_of(const Strips& st, int w, int h, float lambda, const float* partials,
+                           float* d_loss, const LossGate& gate) {
+    return {partials, (int64_t)st.grid.x * st.grid.y, 3.0 * (double)w * (double)h, lambda, d_loss,
+            gate};
+}
+
 hipError_t launch_loss_partials(const float* rgb, TargetRef target, int w, int h, float lambda,
                                 float* partials, float* d_loss, hipStream_t s) {
     const Strips st = strips(w, h);
     hipLaunchKernelGGL((ssim_forward_kernel<false>), st.grid, dim3(kThreads), 0, s, rgb, target, w,
                        h, st.rows, make_window(), partials, nullptr);
-    hipLaunchKernelGGL(loss_reduce_kernel, dim3(1), dim3(1024), 0, s, partials,
-                       (int64_t)st.grid.x * st.grid.y, 3.0 * (double)w * (double)h, lambda, d_loss,
-                       LossGate{});
+    hipLaunchKernelGGL(loss_reduce_kernel, dim3(1), dim3(kSumSlots), 0, s,
+                       loss_sum_of(st, w, h, lambda, partials, d_loss, LossGate{}));
     return hipGetLastError();
 }
 
@@ -381,8 +429,9 @@ hipError_t launch_loss_forward(const float* rgb, TargetRef target, int w, int h,
     float* maps = reinterpret_cast<float*>(ws + L.maps);
     hipLaunchKernelGGL((ssim_forward_kernel<true>), st.grid, dim3(kThreads), 0, s, rgb, target, w,
                        h, st.rows, make_window(), partials, maps);
-    hipLaunchKernelGGL(loss_reduce_kernel, dim3(1), dim3(1024), 0, s, partials,
-                       (int64_t)st.grid.x * st.grid.y, 3.0 * (double)w * (double)h, lambda, d_loss, gate);
+    if (d_loss != nullptr)
+        hipLaunchKernelGGL(loss_reduce_kernel, dim3(1), dim3(kSumSlots), 0, s,
+                           loss_sum_of(st, w, h, lambda, partials, d_loss, gate));
     return hipGetLastError();
 }
 
@@ -392,8 +441,30 @@ hipError_t launch_loss_backward(const float* rgb, TargetRef target, int w, int h
     const LossLayout L = loss_layout(w, h);
     const Strips st = strips(w, h);
     const float* maps = reinterpret_cast<const float*>(ws + L.maps);
-    hipLaunchKernelGGL(ssim_backward_kernel, st.grid, dim3(kThreads), 0, s, rgb, target, w, h,
-                       st.rows, lambda, make_window(), maps, gate, scale, dl);
+    hipLaunchKernelGGL(ssim_backward_kernel<false>, st.grid, dim3(kThreads), 0, s, LossTrain{}, rgb,
+                       target, w, h, st.rows, lambda, make_window(), maps, gate, scale, dl);
+    return hipGetLastError();
+}
+
+hipError_t launch_train_loss(const float* rgb, TargetRef target, int w, int h, float lambda,
+                             char* ws, float* d_loss, float* dl, const LossGate& gate,
+                             const Prepare& prepare, hipStream_t s) {
+    const bool gated = gate.state != nullptr;
+    hipError_t err = launch_loss_forward(rgb, target, w, h, lambda, ws, gated ? d_loss : nullptr, s, gate);
+    if (err != hipSuccess) return err;
+    const LossLayout L = loss_layout(w, h);
+    const Strips st = strips(w, h);
+    const float* partials = reinterpret_cast<const float*>(ws + L.partials);
+    const float* maps = reinterpret_cast<const float*>(ws + L.maps);
+    LossTrain t{prepare, loss_sum_of(st, w, h, lambda, partials, gated ? nullptr : d_loss, gate), 0};
+    // the sum, the order, and a workgroup for every kClearEach float4s, up to kClearBlocks
+    constexpr int64_t kClearEach = 4 * kThreads, kClearBlocks = 1024;
+    const int64_t blocks =
+        2 + std::min<int64_t>((prepare.n4 + kClearEach - 1) / kClearEach, kClearBlocks);
+    t.rows = (int)((blocks + st.grid.x - 1) / st.grid.x);
+    hipLaunchKernelGGL(ssim_backward_kernel<true>, dim3(st.grid.x, st.grid.y + (unsigned)t.rows),
+                       dim3(kThreads), 0, s, t, rgb, target, w, h, st.rows, lambda, make_window(),
+                       maps, gated ? gate.gate : nullptr, nullptr, dl);
     return hipGetLastError();
 }
 

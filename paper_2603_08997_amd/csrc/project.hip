@@ -244,6 +244,12 @@ __global__ void __launch_bounds__(256) project_kernel(const float* __restrict__ 
         rec, tiles, dkey, info);
 }
 
+// The view at position k of a sequence (32-bit division where it does).
+__device__ __forceinline__ int32_t sequence_view(const int32_t* seq, int64_t len, int64_t k) {
+    const bool small = (uint64_t)k <= 0xffffffffull && len <= (int64_t)0xffffffffu;
+    return seq[small ? (int64_t)((uint32_t)k % (uint32_t)len) : k % len];
+}
+
 // One view, given by value or picked from a camera table: the first launch of
 // its call, which therefore also stores the view for the kernels after it and,
 // for a call that bins, clears the counters and the sums binning accumulates
@@ -252,7 +258,10 @@ struct OneView {
     ViewDev view;
     const ViewDev* table;
     int32_t n_table;
-    const int32_t* d_view;
+    int32_t* d_view;
+    const int32_t* seq;   // nullable: *d_view becomes seq[*iter % len]
+    int64_t len;
+    const int64_t* iter;
     int32_t total_tiles, total_supers;
     int64_t total_pixels;
     Views* dst;
@@ -269,7 +278,11 @@ __global__ void __launch_bounds__(256) project_one_kernel(const float* __restric
                                                           uint4* __restrict__ info) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     ViewDev V = one.view;
-    if (one.table != nullptr) V = one.table[min(max(*one.d_view, 0), one.n_table - 1)];
+    if (one.table != nullptr) {
+        const int32_t vi = one.seq == nullptr ? *one.d_view : sequence_view(one.seq, one.len, *one.iter);
+        V = one.table[min(max(vi, 0), one.n_table - 1)];
+        if (one.seq != nullptr && i == 0) *one.d_view = vi;
+    }
     if (blockIdx.x == 0) {
         if (threadIdx.x == 0) {
             one.dst->v[0] = V;
@@ -719,6 +732,9 @@ hipError_t launch_project(const float* planes, int64_t n, int64_t stride, int sh
     one.table = call.table;
     one.n_table = call.n_table;
     one.d_view = call.d_view;
+    one.seq = call.seq;
+    one.len = call.len;
+    one.iter = call.iter;
     one.total_tiles = call.views->total_tiles;
     one.total_supers = call.views->total_supers;
     one.total_pixels = call.views->total_pixels;

@@ -39,8 +39,7 @@
 // different SIMDs, so every SIMD gets a mix of long and short tiles.
 #include <algorithm>
 
-#include "sgs_internal.hpp"
-#include "sgs_device.hpp"
+#include "sgs_prepare.hpp"
 
 namespace sgs {
 
@@ -750,46 +749,19 @@ __global__ void __launch_bounds__(kLanes, backward_waves(B)) raster_backward_ker
     }
 }
 
-// What the compositing backward needs done before it, in one launch: block 0
-// stores the call's views (nullable), counts Adam's step (nullable) and orders
-// the tiles by the forward's measured work, largest first (a counting sort in
-// LDS: bucket counts, their exclusive scan, then every tile takes the next slot
-// of its bucket), the others clear the accumulators in a grid-stride loop over a
-// grid sized for the machine (a closed gate then costs a launch of a few hundred
-// blocks). As launches of their own the order took 9 us at 6700 tiles, the
-// count and the views 4.6 us each.
+// What the compositing backward needs done before it, in one launch: the call's
+// views stored (nullable) and prepare_backward, on a grid sized for the machine
+// (a closed gate then costs a launch of a few hundred blocks). As launches of
+// their own the order took 9 us at 6700 tiles, the count and the views 4.6 us each.
 constexpr int kPrepareThreads = 1024;
 constexpr int64_t kPrepareBlocks = 512;
 __global__ void __launch_bounds__(kPrepareThreads) prepare_backward_kernel(
-    Views v, Views* __restrict__ dst, int32_t* step, const int32_t* __restrict__ gate, float4* acc,
-    int64_t n4, const uint32_t* __restrict__ cost, int64_t tiles, uint32_t* __restrict__ order) {
-    __shared__ uint32_t slot[kPrepareThreads];
+    Views v, Views* __restrict__ dst, const int32_t* __restrict__ gate, Prepare p) {
+    __shared__ uint32_t slot[kOrderSlots];
     __shared__ uint32_t smem[kPrepareThreads / 64 + 1];
-    const int tid = threadIdx.x;
     if (blockIdx.x == 0 && dst != nullptr) store_views(v, nullptr, 0, nullptr, dst);
     if (gate_closed(gate)) return;
-    if (blockIdx.x > 0) {
-        for (int64_t i = (int64_t)(blockIdx.x - 1) * kPrepareThreads + tid; i < n4;
-             i += (int64_t)(gridDim.x - 1) * kPrepareThreads)
-            acc[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-        return;
-    }
-    if (step != nullptr && tid == 0) *step += 1;
-    auto bucket = [&](int64_t t) {
-        return (uint32_t)(kPrepareThreads - 1) - min(cost[t], (uint32_t)(kPrepareThreads - 1));
-    };
-    slot[tid] = 0;
-    __syncthreads();
-    for (int64_t t = tid; t < tiles; t += kPrepareThreads) atomicAdd(&slot[bucket(t)], 1u);
-    __syncthreads();
-    const uint32_t c = slot[tid];
-    uint32_t tot;
-    const uint32_t first = block_excl_scan<kPrepareThreads>(c, smem, &tot);
-    __syncthreads();
-    slot[tid] = first;
-    __syncthreads();
-    for (int64_t t = tid; t < tiles; t += kPrepareThreads)
-        order[atomicAdd(&slot[bucket(t)], 1u)] = (uint32_t)t;
+    prepare_backward<kPrepareThreads>(p, (int)blockIdx.x, (int)gridDim.x, slot, smem);
 }
 
 }  // namespace
@@ -884,20 +856,29 @@ hipError_t launch_rasterize(const RasterDev& rp, const Layout& L, char* ws, floa
 #undef SGS_LAUNCH
 }
 
+Prepare backward_preparation(const Layout& L, char* ws, int32_t* step) {
+    return {step,
+            reinterpret_cast<float4*>(ws + L.accum),
+            L.entries * kAccumFloats / 4,
+            reinterpret_cast<const uint32_t*>(ws + L.tile_cost),
+            L.entries > 0 ? L.total_tiles : 0,
+            reinterpret_cast<uint32_t*>(ws + L.tile_order)};
+}
+
 hipError_t launch_rasterize_backward(const RasterDev& rp, const Layout& L, char* ws,
                                      const float* dl_drgb, const int32_t* gate, hipStream_t s,
-                                     const Views* store, int32_t* step) {
+                                     const Views* store, int32_t* step, bool prepared) {
+    const Prepare prep = backward_preparation(L, ws, step);
+    if (!prepared) {
+        const int64_t clear = (prep.n4 + kPrepareThreads - 1) / kPrepareThreads;
+        hipLaunchKernelGGL(prepare_backward_kernel,
+                           dim3((unsigned)(1 + std::min<int64_t>(clear, kPrepareBlocks))),
+                           dim3(kPrepareThreads), 0, s, store != nullptr ? *store : Views{},
+                           store != nullptr ? reinterpret_cast<Views*>(ws + L.views) : nullptr,
+                           gate, prep);
+    }
     float* acc = reinterpret_cast<float*>(ws + L.accum);
-    const int64_t n4 = L.entries * kAccumFloats / 4;
-    uint32_t* order = reinterpret_cast<uint32_t*>(ws + L.tile_order);
-    const int64_t clear = (n4 + kPrepareThreads - 1) / kPrepareThreads;
-    hipLaunchKernelGGL(prepare_backward_kernel,
-                       dim3((unsigned)(1 + std::min<int64_t>(clear, kPrepareBlocks))),
-                       dim3(kPrepareThreads), 0, s, store != nullptr ? *store : Views{},
-                       store != nullptr ? reinterpret_cast<Views*>(ws + L.views) : nullptr, step,
-                       gate, reinterpret_cast<float4*>(acc), n4,
-                       reinterpret_cast<const uint32_t*>(ws + L.tile_cost),
-                       L.entries > 0 ? L.total_tiles : 0, order);
+    const uint32_t* order = prep.order;
     if (L.total_tiles == 0 || L.entries == 0) return hipGetLastError();
     const Views* views = reinterpret_cast<const Views*>(ws + L.views);
     const uint32_t* ranges = reinterpret_cast<const uint32_t*>(ws + L.tile_ranges);

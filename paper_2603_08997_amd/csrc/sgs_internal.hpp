@@ -213,8 +213,11 @@ struct CallViews {
     const Views* views;
     const ViewDev* table;   // as launch_begin_bin
     int n_table;
-    const int32_t* d_view;
+    int32_t* d_view;
     bool bins;
+    const int32_t* seq = nullptr;   // nullable; otherwise *d_view = seq[*iter % len] first
+    int64_t len = 0;
+    const int64_t* iter = nullptr;
 };
 hipError_t launch_project(const float* planes, int64_t n, int64_t stride, int sh_degree,
                           const RasterDev& rp, const Layout& L, char* ws, const CallViews& call,
@@ -231,11 +234,24 @@ hipError_t launch_bin(const RasterDev& rp, int64_t n, const Layout& L, char* ws,
 hipError_t launch_split_rest(const RasterDev& rp, const Layout& L, char* ws, hipStream_t s);
 hipError_t launch_rasterize(const RasterDev& rp, const Layout& L, char* ws, float* out_rgb,
                             hipStream_t s);
+// What comes before the compositing backward: Adam's step count (nullable), the
+// accumulators to clear (float4s), the tiles to order by their cost.
+struct Prepare {
+    int32_t* step;
+    float4* accum;
+    int64_t n4;
+    const uint32_t* cost;
+    int64_t tiles;
+    uint32_t* order;
+};
+Prepare backward_preparation(const Layout& L, char* ws, int32_t* step);
 // views (nullable): stored into the workspace first. step (nullable): Adam's
-// step count, incremented unless the gate is closed.
+// step count, incremented unless the gate is closed. prepared: an earlier launch
+// has done backward_preparation(L, ws, step).
 hipError_t launch_rasterize_backward(const RasterDev& rp, const Layout& L, char* ws,
                                      const float* dl_drgb, const int32_t* gate, hipStream_t s,
-                                     const Views* views, int32_t* step = nullptr);
+                                     const Views* views, int32_t* step = nullptr,
+                                     bool prepared = false);
 hipError_t launch_project_backward(const float* planes, int64_t n, int64_t stride,
                                    int sh_degree, const RasterDev& rp, const Layout& L, char* ws,
                                    const int32_t* gate, float* grads, bool write, hipStream_t s);
@@ -299,6 +315,7 @@ struct LossGate {
     char* state;            // nullable
     const int32_t* view;
     int32_t* gate;          // nullable: nothing to decide
+    int64_t* iter;          // nullable: the position in the view sequence, advanced
 };
 hipError_t launch_loss_forward(const float* rgb, TargetRef target, int w, int h, float lambda,
                                char* ws, float* d_loss, hipStream_t s,
@@ -306,6 +323,12 @@ hipError_t launch_loss_forward(const float* rgb, TargetRef target, int w, int h,
 hipError_t launch_loss_backward(const float* rgb, TargetRef target, int w, int h, float lambda,
                                 char* ws, const int32_t* gate, float* dl, hipStream_t s,
                                 const float* scale = nullptr);
+// The backward of a training iteration: the loss's gradient and the preparation
+// of the compositing backward and, where no gate decides on the loss, the sum of
+// the loss itself (launch_loss_forward then leaves it: gate.gate null).
+hipError_t launch_train_loss(const float* rgb, TargetRef target, int w, int h, float lambda,
+                             char* ws, float* d_loss, float* dl, const LossGate& gate,
+                             const Prepare& prepare, hipStream_t s);
 size_t loss_workspace_bytes(int w, int h);
 // The loss forward with the per-tile partial sums (loss_partial_floats(w, h)
 // floats) in caller-provided device memory.

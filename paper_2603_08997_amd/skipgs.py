@@ -95,8 +95,8 @@ EXPORTS = [
     "sgs_gate_init", "sgs_gate_update", "sgs_gate_read", "sgs_adam_step",
     "sgs_project_backward_adam", "sgs_render_backward_adam", "sgs_camera_table_size",
     "sgs_camera_table_init", "sgs_view_sequence_next", "sgs_train_iteration",
-    "sgs_default_densify_params", "sgs_densify_stats", "sgs_densify_workspace_size",
-    "sgs_densify",
+    "sgs_train_sequence_step", "sgs_default_densify_params", "sgs_densify_stats",
+    "sgs_densify_workspace_size", "sgs_densify",
 ]
 
 
@@ -150,6 +150,10 @@ def _load():
         "sgs_train_iteration": (i32, [P(GaussiansC), P(CameraC), vp, i32, vp, P(RasterParamsC),
                                       vp, sz, i64, vp, f32, vp, sz, vp, vp, vp, P(GateParamsC),
                                       vp, vp, P(AdamParamsC), vp, vp, vp, vp]),
+        "sgs_train_sequence_step": (i32, [vp, i64, vp, P(GaussiansC), P(CameraC), vp, i32, vp,
+                                          P(RasterParamsC), vp, sz, i64, vp, f32, vp, sz, vp, vp,
+                                          vp, P(GateParamsC), vp, vp, P(AdamParamsC), vp, vp, vp,
+                                          vp]),
         "sgs_default_densify_params": (None, [P(DensifyParamsC)]),
         "sgs_densify_stats": (i32, [P(CameraC), i32, i64, P(RasterParamsC), vp, sz, i64, vp, vp,
                                     vp, vp]),
@@ -629,10 +633,16 @@ class TrainStep:
                       gate_state, d_gate, m, v, d_step)
 
     def __call__(self, stream):
+        _check(LIB.sgs_train_iteration(*self._call(), stream))
+
+    def sequence_step(self, d_sequence: torch.Tensor, d_iter: torch.Tensor, stream):
+        """sgs_train_sequence_step: the view comes from the sequence."""
+        _check(LIB.sgs_train_sequence_step(d_sequence.data_ptr(), int(d_sequence.numel()),
+                                           d_iter.data_ptr(), *self._call(), stream))
+
+    def _call(self):
         (tab, ncam, dview, wsb, cap, tgt, lam, lws, lwsb, rgb, dl, dloss, gst, dgate, m, v,
          step) = self.args
         gp = C.byref(self.gp) if self.gp is not None else None
-        _check(LIB.sgs_train_iteration(C.byref(self.g), self.cams, tab, ncam, dview,
-                                       C.byref(self.rp), self.ws, wsb, cap, tgt, lam, lws, lwsb,
-                                       rgb, dl, dloss, gp, gst, dgate, C.byref(self.adam), m, v,
-                                       step, stream))
+        return (C.byref(self.g), self.cams, tab, ncam, dview, C.byref(self.rp), self.ws, wsb, cap,
+                tgt, lam, lws, lwsb, rgb, dl, dloss, gp, gst, dgate, C.byref(self.adam), m, v, step)

@@ -118,12 +118,10 @@ class Trainer:
             self.gstate_p = self.gstate.data_ptr()
 
     def step(self, stream=None):
-        """Enqueue the next iteration of the sequence (two calls, no host
+        """Enqueue the next iteration of the sequence (one call, no host
         synchronisation; capturable)."""
         s = torch.cuda.current_stream().cuda_stream if stream is None else stream
-        sk._check(sk.LIB.sgs_view_sequence_next(self.seq.data_ptr(), int(self.seq.numel()),
-                                                self.seq_pos.data_ptr(), self.view.data_ptr(), s))
-        self.train_step(s)
+        self.train_step.sequence_step(self.seq, self.seq_pos, s)
 
     def iteration(self, view: int, d_view: torch.Tensor, gate_slot: torch.Tensor,
                   loss_slot: torch.Tensor | None = None, timer: StageTimer | None = None):
