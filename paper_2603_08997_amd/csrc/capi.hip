@@ -247,6 +247,7 @@ void make_layout(const Views& views, const RasterDev& rp, int64_t n, int64_t cap
     L->records = take(sizeof(float) * kRecordFloats * (size_t)E);
     L->accum = take(sizeof(float) * kAccumFloats * (size_t)E);
     L->tiles = take(sizeof(uint32_t) * (size_t)E);
+    L->marks = take((size_t)E);
     L->depth = take(sizeof(uint32_t) * (size_t)E);
     L->dkey[0] = take(sizeof(uint32_t) * (size_t)E);
     L->dkey[1] = take(sizeof(uint32_t) * (size_t)E);

@@ -85,13 +85,8 @@ struct Geometry {
     float sxx, sxy, syy;       // 2D covariance incl. dilation
 };
 
-__device__ __forceinline__ bool compute_geometry(const float mu[3], const float ls[3],
-                                                 const float q[4], const ViewDev& V,
-                                                 const RasterDev& rp, Geometry& G) {
-    G.tx = V.R[0] * mu[0] + V.R[1] * mu[1] + V.R[2] * mu[2] + V.t[0];
-    G.ty = V.R[3] * mu[0] + V.R[4] * mu[1] + V.R[5] * mu[2] + V.t[1];
-    G.tz = V.R[6] * mu[0] + V.R[7] * mu[1] + V.R[8] * mu[2] + V.t[2];
-    if (!(G.tz > rp.near_z)) return false;
+// What of the geometry no view changes; false for a degenerate quaternion.
+__device__ __forceinline__ bool compute_shape(const float ls[3], const float q[4], Geometry& G) {
     const float qq = q[0] * q[0] + q[1] * q[1] + q[2] * q[2] + q[3] * q[3];
     G.qnorm = sqrtf(qq);
     if (!(G.qnorm > 0.f) || !isfinite(G.qnorm)) return false;
@@ -114,6 +109,16 @@ __device__ __forceinline__ bool compute_geometry(const float mu[3], const float 
     G.Sig[3] = M[3] * M[3] + M[4] * M[4] + M[5] * M[5];
     G.Sig[4] = M[3] * M[6] + M[4] * M[7] + M[5] * M[8];
     G.Sig[5] = M[6] * M[6] + M[7] * M[7] + M[8] * M[8];
+    return true;
+}
+
+// The rest, in one view; false for a centre in front of the near plane.
+__device__ __forceinline__ bool compute_view(const float mu[3], const ViewDev& V,
+                                             const RasterDev& rp, Geometry& G) {
+    G.tx = V.R[0] * mu[0] + V.R[1] * mu[1] + V.R[2] * mu[2] + V.t[0];
+    G.ty = V.R[3] * mu[0] + V.R[4] * mu[1] + V.R[5] * mu[2] + V.t[1];
+    G.tz = V.R[6] * mu[0] + V.R[7] * mu[1] + V.R[8] * mu[2] + V.t[2];
+    if (!(G.tz > rp.near_z)) return false;
     // EWA Jacobian at the centre (Eq. 3), clamped ray direction.
     const float xr = G.tx / G.tz, yr = G.ty / G.tz;
     G.clx = !(xr >= -V.lim_x && xr <= V.lim_x);
@@ -142,6 +147,12 @@ __device__ __forceinline__ bool compute_geometry(const float mu[3], const float 
     return true;
 }
 
+__device__ __forceinline__ bool compute_geometry(const float mu[3], const float ls[3],
+                                                 const float q[4], const ViewDev& V,
+                                                 const RasterDev& rp, Geometry& G) {
+    return compute_shape(ls, q, G) && compute_view(mu, V, rp, G);
+}
+
 __device__ __forceinline__ int find_view(int64_t e, int64_t n, int64_t* i) {
     const int v = (int)(e / n);
     *i = e - (int64_t)v * n;
@@ -157,8 +168,9 @@ __device__ __forceinline__ void project_entry(const float mu[3], const float ls[
                                               float4* __restrict__ rec,
                                               uint32_t* __restrict__ tiles,
                                               uint32_t* __restrict__ dkey,
+                                              uint8_t* __restrict__ marks,
                                               uint4* __restrict__ info) {
-    uint32_t ntiles = 0;
+    uint32_t ntiles = 0, mask = 0;
     float depth = 0.f;
     float4 r0 = make_float4(0.f, 0.f, 0.f, 0.f), r1 = r0, r2 = r0;
     Geometry G;
@@ -203,8 +215,8 @@ __device__ __forceinline__ void project_entry(const float mu[3], const float ls[
                       &y0, &y1);
             if (x1 > x0 && y1 > y0) {
                 ntiles = super_count(x0, x1, y0, y1, rp.super_tile);
-                const uint32_t mask = (col[0] >= 0.f ? 1u : 0u) | (col[1] >= 0.f ? 2u : 0u) |
-                                      (col[2] >= 0.f ? 4u : 0u);
+                mask = (col[0] >= 0.f ? 1u : 0u) | (col[1] >= 0.f ? 2u : 0u) |
+                       (col[2] >= 0.f ? 4u : 0u);
                 r0 = make_float4(u, v, ca, cb);
                 r1 = make_float4(cc, o, ex, ey);
                 r2 = make_float4(fmaxf(col[0], 0.f), fmaxf(col[1], 0.f), fmaxf(col[2], 0.f),
@@ -218,6 +230,7 @@ __device__ __forceinline__ void project_entry(const float mu[3], const float ls[
     rec[3 * e + 1] = r1;
     rec[3 * e + 2] = r2;
     tiles[e] = ntiles;
+    marks[e] = (uint8_t)(ntiles != 0u ? mask | kMarkVisible : 0u);
     dkey[e] = __float_as_uint(depth);
 }
 
@@ -228,6 +241,7 @@ __global__ void __launch_bounds__(256) project_kernel(const float* __restrict__ 
                                                       RasterDev rp, float4* __restrict__ rec,
                                                       uint32_t* __restrict__ tiles,
                                                       uint32_t* __restrict__ dkey,
+                                                      uint8_t* __restrict__ marks,
                                                       uint4* __restrict__ info) {
     const int64_t entries = n * views->n;
     const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -241,7 +255,7 @@ __global__ void __launch_bounds__(256) project_kernel(const float* __restrict__ 
     for (int k = 0; k < 11; ++k) p[k] = P.load(k, off);
     project_entry<sh_degree>(
         p, p + 3, p + 6, p[10], [&](int j) { return P.load(11 + j, off); }, views->v[vi], rp, e,
-        rec, tiles, dkey, info);
+        rec, tiles, dkey, marks, info);
 }
 
 // The view at position k of a sequence (32-bit division where it does).
@@ -275,6 +289,7 @@ __global__ void __launch_bounds__(256) project_one_kernel(const float* __restric
                                                           RasterDev rp, float4* __restrict__ rec,
                                                           uint32_t* __restrict__ tiles,
                                                           uint32_t* __restrict__ dkey,
+                                                          uint8_t* __restrict__ marks,
                                                           uint4* __restrict__ info) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     ViewDev V = one.view;
@@ -304,7 +319,7 @@ __global__ void __launch_bounds__(256) project_one_kernel(const float* __restric
     for (int k = 0; k < 11; ++k) p[k] = P.load(k, off);
     project_entry<sh_degree>(
         p, p + 3, p + 6, p[10], [&](int j) { return P.load(11 + j, off); }, V, rp, i, rec, tiles,
-        dkey, info);
+        dkey, marks, info);
 }
 
 // One thread per Gaussian, over the views of the batch: its parameters are
@@ -315,7 +330,7 @@ template <int sh_degree>
 __global__ void __launch_bounds__(256) project_views_kernel(
     const float* __restrict__ planes, int64_t n, int64_t stride, const Views* __restrict__ views,
     RasterDev rp, float4* __restrict__ rec, uint32_t* __restrict__ tiles,
-    uint32_t* __restrict__ dkey, uint4* __restrict__ info) {
+    uint32_t* __restrict__ dkey, uint8_t* __restrict__ marks, uint4* __restrict__ info) {
     constexpr int NP = 11 + 3 * (sh_degree + 1) * (sh_degree + 1);
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
@@ -327,7 +342,7 @@ __global__ void __launch_bounds__(256) project_views_kernel(
     for (int vi = 0; vi < views->n; ++vi)
         project_entry<sh_degree>(
             p, p + 3, p + 6, p[10], [&](int j) { return p[11 + j]; }, views->v[vi], rp,
-            (int64_t)vi * n + i, rec, tiles, dkey, info);
+            (int64_t)vi * n + i, rec, tiles, dkey, marks, info);
 }
 
 __global__ void __launch_bounds__(256) load_records_kernel(
@@ -336,7 +351,8 @@ __global__ void __launch_bounds__(256) load_records_kernel(
     const float* __restrict__ conic, const float* __restrict__ opacity,
     const float* __restrict__ rgb, const Views* __restrict__ views, RasterDev rp,
     float4* __restrict__ rec,
-    uint32_t* __restrict__ tiles, uint32_t* __restrict__ dkey, uint4* __restrict__ info) {
+    uint32_t* __restrict__ tiles, uint32_t* __restrict__ dkey, uint8_t* __restrict__ marks,
+    uint4* __restrict__ info) {
     const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= entries) return;
     int64_t i;
@@ -361,6 +377,7 @@ __global__ void __launch_bounds__(256) load_records_kernel(
     rec[3 * e + 1] = r1;
     rec[3 * e + 2] = r2;
     tiles[e] = ntiles;
+    marks[e] = (uint8_t)(ntiles != 0u ? 7u | kMarkVisible : 0u);
     dkey[e] = __float_as_uint(ntiles ? depth[e] : 0.f);
 }
 
@@ -372,30 +389,21 @@ struct ViewSH {
 };
 
 __device__ __forceinline__ void view_sh(const float mu[3], const ViewDev& V, float4 a1, float4 a2,
-                                        float4 r2, ViewSH& o) {
+                                        uint32_t mark, ViewSH& o) {
     const float dir[3] = {mu[0] - V.C[0], mu[1] - V.C[1], mu[2] - V.C[2]};
     o.dn = sqrtf(dir[0] * dir[0] + dir[1] * dir[1] + dir[2] * dir[2]);
 #pragma unroll
     for (int c = 0; c < 3; ++c) o.d[c] = dir[c] / o.dn;
-    const uint32_t mask = __float_as_uint(r2.w);
-    o.draw[0] = (mask & 1u) ? a1.z : 0.f;
-    o.draw[1] = (mask & 2u) ? a1.w : 0.f;
-    o.draw[2] = (mask & 4u) ? a2.x : 0.f;
+    o.draw[0] = (mark & 1u) ? a1.z : 0.f;
+    o.draw[1] = (mark & 2u) ? a1.w : 0.f;
+    o.draw[2] = (mark & 4u) ? a2.x : 0.f;
 }
 
-// Gradient of the non-SH raw parameters of one visible entry (mean through
-// the projection, log-scale, quaternion, opacity logit), ADDED to the outputs.
-// Returns false if the geometry is culled (never for a visible entry).
-__device__ __forceinline__ bool geom_grads(const float mu[3], const float ls[3], const float q[4],
-                                           float logit, const ViewDev& V, const RasterDev& rp,
-                                           float4 a0, float4 a1, float g_mu[3], float g_ls[3],
-                                           float g_q[4], float* g_logit) {
-    const float d_u = a0.x, d_v = a0.y, d_ca = a0.z, d_cb = a0.w, d_cc = a1.x, d_o = a1.y;
-    Geometry G;
-    if (!compute_geometry(mu, ls, q, V, rp, G)) return false;
-    // opacity = sigmoid(logit)
-    const float o = sigmoidf(logit);
-    *g_logit += d_o * o * (1.f - o);
+// Gradient by a visible entry's centre, ADDED to g_mu, and by its 3D covariance
+// (dS, symmetric, row-major), G in the entry's view.
+__device__ __forceinline__ void view_grads(const Geometry& G, const ViewDev& V, float4 a0,
+                                           float4 a1, float g_mu[3], float dS[9]) {
+    const float d_u = a0.x, d_v = a0.y, d_ca = a0.z, d_cb = a0.w, d_cc = a1.x;
     // conic = inverse of Sigma2D': dSigma' = -Q G Q with G the symmetric
     // gradient [[da, db/2], [db/2, dc]].
     const float det = G.sxx * G.syy - G.sxy * G.sxy;
@@ -415,7 +423,6 @@ __device__ __forceinline__ bool geom_grads(const float mu[3], const float ls[3],
         HT[c] = h00 * T[c] + h01 * T[3 + c];
         HT[3 + c] = h01 * T[c] + h11 * T[3 + c];
     }
-    float dS[9];
 #pragma unroll
     for (int r = 0; r < 3; ++r)
 #pragma unroll
@@ -448,6 +455,11 @@ __device__ __forceinline__ bool geom_grads(const float mu[3], const float ls[3],
     // t = R mu + t0
 #pragma unroll
     for (int c = 0; c < 3; ++c) g_mu[c] += V.R[c] * d_tx + V.R[3 + c] * d_ty + V.R[6 + c] * d_tz;
+}
+
+// Gradient of log-scale and quaternion from that of the covariance, ADDED.
+__device__ __forceinline__ void shape_grads(const Geometry& G, const float dS[9], float g_ls[3],
+                                            float g_q[4]) {
     // Sigma = M M^T, M = Rq diag(s): dM = 2 dSigma M; dRq = dM diag(s); ds_j = sum_i dM_ij Rq_ij
     float M[9];
 #pragma unroll
@@ -486,6 +498,23 @@ __device__ __forceinline__ bool geom_grads(const float mu[3], const float ls[3],
     const float dot = dqn[0] * w + dqn[1] * x + dqn[2] * y + dqn[3] * z;
 #pragma unroll
     for (int c = 0; c < 4; ++c) g_q[c] += (dqn[c] - G.qn[c] * dot) / G.qnorm;
+}
+
+// Gradient of the non-SH raw parameters of one visible entry (mean through
+// the projection, log-scale, quaternion, opacity logit), ADDED to the outputs.
+// Returns false if the geometry is culled (never for a visible entry).
+__device__ __forceinline__ bool geom_grads(const float mu[3], const float ls[3], const float q[4],
+                                           float logit, const ViewDev& V, const RasterDev& rp,
+                                           float4 a0, float4 a1, float g_mu[3], float g_ls[3],
+                                           float g_q[4], float* g_logit) {
+    Geometry G;
+    if (!compute_geometry(mu, ls, q, V, rp, G)) return false;
+    // opacity = sigmoid(logit)
+    const float o = sigmoidf(logit);
+    *g_logit += a1.y * o * (1.f - o);
+    float dS[9];
+    view_grads(G, V, a0, a1, g_mu, dS);
+    shape_grads(G, dS, g_ls, g_q);
     return true;
 }
 
@@ -532,6 +561,13 @@ __device__ __forceinline__ void sh_coef_grad(const ViewSH& o, float* g_sh) {
         for (int c = 0; c < 3; ++c) g_sh[3 * k + c] += o.draw[c] * Y[k];
 }
 
+// What bounds the per-Gaussian backward: HBM. Whether a view sees the Gaussian and
+// which colour channels were clamped comes from a byte an entry; read from the
+// tile counts and the records' last words, whose lines are those of all records,
+// the fused step took 907 us at 3M Gaussians (SH 3; 865 now), the written
+// gradient 659 at 6M (601), the added one of 8 views 668 at 2M (538, and 709
+// before the parts that no view changes came out of the loop over the views).
+//
 // The per-Gaussian backward. All parameters of the Gaussian are loaded at
 // once; the gradient stays in registers, and the update (kFused: Adam on every
 // plane, dense as in the paper's optimiser, also for Gaussians visible in no
@@ -544,8 +580,7 @@ __device__ __forceinline__ void gaussian_backward(float* __restrict__ planes, in
                                                   int64_t stride, int64_t i,
                                                   const Views* __restrict__ views,
                                                   const RasterDev& rp,
-                                                  const float4* __restrict__ rec,
-                                                  const uint32_t* __restrict__ tiles,
+                                                  const uint8_t* __restrict__ marks,
                                                   const float4* __restrict__ acc,
                                                   float* __restrict__ grads, const AdamDev* ad,
                                                   const AdamStep* as, float* __restrict__ m,
@@ -577,17 +612,55 @@ __device__ __forceinline__ void gaussian_backward(float* __restrict__ planes, in
     }
     bool any = false;
     ViewSH one;
-    for (int vi = 0; vi < views->n; ++vi) {
-        const int64_t e = (int64_t)vi * n + i;
-        if (tiles[e] == 0) continue;
-        const float4 a0 = acc[3 * e], a1 = acc[3 * e + 1];
-        if (geom_grads(mu, ls, q, p[10], views->v[vi], rp, a0, a1, g, g + 3, g + 6, g + 10)) {
+    if constexpr (kMulti) {
+        // What no view changes is formed once before the views, and what is
+        // linear in the gradients of covariance and opacity once after them; the
+        // accumulators of a view are loaded while the one before is worked on.
+        const int nv = views->n;
+        uint64_t seen = 0;   // the views' marks
+        for (int vi = 0; vi < nv; ++vi) seen |= (uint64_t)marks[(int64_t)vi * n + i] << (4 * vi);
+        Geometry G;
+        if (!compute_shape(ls, q, G)) seen = 0;
+        float dS[9], d_o = 0.f;
+#pragma unroll
+        for (int k = 0; k < 9; ++k) dS[k] = 0.f;
+        auto mark = [&](int vi) { return (uint32_t)(seen >> (4 * vi)) & 15u; };
+        float4 n0, n1, n2;
+        auto fetch = [&](int vi) {
+            if (mark(vi) == 0u) return;
+            const int64_t e = (int64_t)vi * n + i;
+            n0 = acc[3 * e];
+            n1 = acc[3 * e + 1];
+            n2 = acc[3 * e + 2];
+        };
+        fetch(0);
+        for (int vi = 0; vi < nv; ++vi) {
+            const float4 a0 = n0, a1 = n1, a2 = n2;
+            if (vi + 1 < nv) fetch(vi + 1);
+            const ViewDev& V = views->v[vi];
+            if (mark(vi) == 0u || !compute_view(mu, V, rp, G)) continue;
             any = true;
+            float dv[9];
+            view_grads(G, V, a0, a1, g, dv);
+#pragma unroll
+            for (int k = 0; k < 9; ++k) dS[k] += dv[k];
+            d_o += a1.y;
             ViewSH o;
-            view_sh(mu, views->v[vi], a1, acc[3 * e + 2], rec[3 * e + 2], o);
+            view_sh(mu, V, a1, a2, mark(vi), o);
             sh_mean_grad<sh_degree>(o, f, g);
-            if constexpr (kMulti) sh_coef_grad<sh_degree>(o, g_sh);
-            else one = o;
+            sh_coef_grad<sh_degree>(o, g_sh);
+        }
+        if (any) {
+            const float o = sigmoidf(p[10]);
+            g[10] = d_o * o * (1.f - o);
+            shape_grads(G, dS, g + 3, g + 6);
+        }
+    } else if (const uint32_t mark = marks[i]; mark != 0u) {
+        const float4 a0 = acc[3 * i], a1 = acc[3 * i + 1];
+        if (geom_grads(mu, ls, q, p[10], views->v[0], rp, a0, a1, g, g + 3, g + 6, g + 10)) {
+            any = true;
+            view_sh(mu, views->v[0], a1, acc[3 * i + 2], mark, one);
+            sh_mean_grad<sh_degree>(one, f, g);
         }
     }
     // without a visible entry: nothing to add (gradient accumulation), or,
@@ -638,7 +711,7 @@ __device__ __forceinline__ void gaussian_backward(float* __restrict__ planes, in
                     M.template store<kPlaneCP>(j, off, mm);
                     Vb.template store<kPlaneCP>(j, off, vv);
                 } else {
-                    // (through L2: 661 us for 6M Gaussians written, streamed 679)
+                    // (through L2: 661 us for 6M Gaussians written, streamed 679 us)
                     G.template store<0>(j, off, ma[b & 1][t] + gj);
                 }
             }
@@ -649,14 +722,13 @@ __device__ __forceinline__ void gaussian_backward(float* __restrict__ planes, in
 // Adjoint of the projection: one thread per Gaussian, gradient ADDED to grads
 // or, with kWrite, written (also the zeros of the padding past n): a gradient
 // that starts at zero then needs neither the clearing nor the reading back of
-// its array. 6M Gaussians, SH 3: 1006 us and 200 us of clearing before, 661 now
-// (4.7 TB/s); with the zeros of unseen Gaussians stored by a branch of their own
+// its array. 6M Gaussians, SH 3: 1006 us and 200 us of clearing, then 661; with the zeros of unseen Gaussians stored by a branch of their own
 // 820, every line being written in two parts.
 template <int sh_degree, bool kMulti, bool kWrite>
 __global__ void __launch_bounds__(kBackwardThreads) project_backward_kernel(
     const float* __restrict__ planes, int64_t n, int64_t stride, const Views* __restrict__ views,
     RasterDev rp,
-    const float4* __restrict__ rec, const uint32_t* __restrict__ tiles,
+    const uint8_t* __restrict__ marks,
     const float4* __restrict__ acc, const int32_t* __restrict__ gate, float* __restrict__ grads) {
     if (gate_closed(gate)) return;
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -670,7 +742,7 @@ __global__ void __launch_bounds__(kBackwardThreads) project_backward_kernel(
         return;
     }
     gaussian_backward<sh_degree, false, kMulti, false, kWrite>(
-        const_cast<float*>(planes), n, stride, i, views, rp, rec, tiles, acc, grads, nullptr,
+        const_cast<float*>(planes), n, stride, i, views, rp, marks, acc, grads, nullptr,
         nullptr, nullptr, nullptr);
 }
 
@@ -681,7 +753,7 @@ __global__ void __launch_bounds__(kBackwardThreads) project_backward_kernel(
 template <int sh_degree, bool kMulti, bool kSparse>
 __global__ void __launch_bounds__(kBackwardThreads) project_backward_adam_kernel(
     float* __restrict__ planes, int64_t n, int64_t stride, const Views* __restrict__ views,
-    RasterDev rp, const float4* __restrict__ rec, const uint32_t* __restrict__ tiles,
+    RasterDev rp, const uint8_t* __restrict__ marks,
     const float4* __restrict__ acc, AdamDev ad, float* __restrict__ m, float* __restrict__ v,
     const int32_t* __restrict__ step, const int32_t* __restrict__ gate) {
     if (gate_closed(gate)) return;
@@ -694,8 +766,8 @@ __global__ void __launch_bounds__(kBackwardThreads) project_backward_adam_kernel
     // 256 Gaussians
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * blockDim.x)
-        gaussian_backward<sh_degree, true, kMulti, kSparse>(planes, n, stride, i, views, rp, rec,
-                                                            tiles, acc, nullptr, &ad, &as, m, v);
+        gaussian_backward<sh_degree, true, kMulti, kSparse>(planes, n, stride, i, views, rp, marks,
+                                                            acc, nullptr, &ad, &as, m, v);
 }
 
 }  // namespace
@@ -726,6 +798,7 @@ hipError_t launch_project(const float* planes, int64_t n, int64_t stride, int sh
     float4* rec = reinterpret_cast<float4*>(ws + L.records);
     uint32_t* tiles = reinterpret_cast<uint32_t*>(ws + L.tiles);
     uint32_t* dkey = reinterpret_cast<uint32_t*>(ws + L.depth);
+    uint8_t* marks = reinterpret_cast<uint8_t*>(ws + L.marks);
     uint4* info = L.direct ? reinterpret_cast<uint4*>(ws + L.pair_info) : nullptr;
     OneView one;
     one.view = call.views->v[0];
@@ -745,13 +818,13 @@ hipError_t launch_project(const float* planes, int64_t n, int64_t stride, int sh
 #define SGS_PK(D)                                                                              \
     if (one_view)                                                                              \
         hipLaunchKernelGGL(project_one_kernel<D>, dim3((unsigned)nb), dim3(nt), 0, s, planes, n, \
-                           stride, one, rp, rec, tiles, dkey, info);                           \
+                           stride, one, rp, rec, tiles, dkey, marks, info);                    \
     else if (loop)                                                                             \
         hipLaunchKernelGGL(project_views_kernel<D>, dim3((unsigned)nb), dim3(nt), 0, s, planes, \
-                           n, stride, views, rp, rec, tiles, dkey, info);                      \
+                           n, stride, views, rp, rec, tiles, dkey, marks, info);               \
     else                                                                                       \
         hipLaunchKernelGGL(project_kernel<D>, dim3((unsigned)nb), dim3(nt), 0, s, planes, n,   \
-                           stride, views, rp, rec, tiles, dkey, info)
+                           stride, views, rp, rec, tiles, dkey, marks, info)
     switch (sh_degree) {
         case 0: SGS_PK(0); break;
         case 1: SGS_PK(1); break;
@@ -776,6 +849,7 @@ hipError_t launch_load_records(const float* u, const float* v, const float* dept
                        reinterpret_cast<float4*>(ws + L.records),
                        reinterpret_cast<uint32_t*>(ws + L.tiles),
                        reinterpret_cast<uint32_t*>(ws + L.depth),
+                       reinterpret_cast<uint8_t*>(ws + L.marks),
                        L.direct ? reinterpret_cast<uint4*>(ws + L.pair_info) : nullptr);
     return hipGetLastError();
 }
@@ -796,16 +870,15 @@ hipError_t launch_project_backward(const float* planes, int64_t n, int64_t strid
     const int nt = kBackwardThreads;
     const int64_t nb = (count + nt - 1) / nt;
     const Views* views = reinterpret_cast<const Views*>(ws + L.views);
-    const float4* rec = reinterpret_cast<const float4*>(ws + L.records);
-    const uint32_t* tl = reinterpret_cast<const uint32_t*>(ws + L.tiles);
+    const uint8_t* marks = reinterpret_cast<const uint8_t*>(ws + L.marks);
     const float4* acc = reinterpret_cast<const float4*>(ws + L.accum);
 #define SGS_PB(D, M)                                                                              \
     if (write)                                                                                    \
         hipLaunchKernelGGL((project_backward_kernel<D, M, true>), dim3((unsigned)nb), dim3(nt), 0, \
-                           s, planes, n, stride, views, rp, rec, tl, acc, gate, grads);           \
+                           s, planes, n, stride, views, rp, marks, acc, gate, grads);           \
     else                                                                                          \
         hipLaunchKernelGGL((project_backward_kernel<D, M, false>), dim3((unsigned)nb), dim3(nt),  \
-                           0, s, planes, n, stride, views, rp, rec, tl, acc, gate, grads)
+                           0, s, planes, n, stride, views, rp, marks, acc, gate, grads)
     SGS_DISPATCH_DEG(SGS_PB, L.n_views > 1)
 #undef SGS_PB
     return hipGetLastError();
@@ -821,12 +894,11 @@ hipError_t launch_project_backward_adam(float* planes, int64_t n, int64_t stride
     const int nt = kBackwardThreads;
     const int64_t nb = std::min<int64_t>((n + nt - 1) / nt, kAdamBlocks);
     const Views* views = reinterpret_cast<const Views*>(ws + L.views);
-    const float4* rec = reinterpret_cast<const float4*>(ws + L.records);
-    const uint32_t* tl = reinterpret_cast<const uint32_t*>(ws + L.tiles);
+    const uint8_t* marks = reinterpret_cast<const uint8_t*>(ws + L.marks);
     const float4* acc = reinterpret_cast<const float4*>(ws + L.accum);
 #define SGS_PBA_S(D, M, SP)                                                                     \
     hipLaunchKernelGGL((project_backward_adam_kernel<D, M, SP>), dim3((unsigned)nb), dim3(nt), 0, \
-                       s, planes, n, stride, views, rp, rec, tl, acc, ad, m, v, step, gate)
+                       s, planes, n, stride, views, rp, marks, acc, ad, m, v, step, gate)
 #define SGS_PBA(D, M) \
     if (sparse) SGS_PBA_S(D, M, true); else SGS_PBA_S(D, M, false)
     SGS_DISPATCH_DEG(SGS_PBA, L.n_views > 1)

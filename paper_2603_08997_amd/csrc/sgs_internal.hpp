@@ -85,6 +85,12 @@ enum Counter : int {
     kNumCounters = 16
 };
 
+// A visible entry's mark (one byte; 0 for the others): this bit, and bits 0-2
+// for the colour channels the forward did not clamp at 0. The same bits lie in
+// the record's last word, but a backward that reads them there fetches all
+// records.
+constexpr uint32_t kMarkVisible = 8u;
+
 // Pair key (uint32): the super-tile index in the low key_bits bits (a value
 // below 2^key_bits - 1, so that no key has all bits set), and above them the
 // entry's tile rectangle inside the super-tile, four coordinates of
@@ -176,7 +182,7 @@ struct Layout {
         pair_info, pair_sorted, pair_hist, pair_groups, pair_key[2], pair_entry[2], sort_hist, sort_groups,
         pair_sort_groups, sort_weights, sup_ranges, seg_first, seg_cnt, seg_groups[2],
         sup_items[2], sup_base, pair_mask, tile_entry, tile_ranges, tile_state, tile_resume, sup_redo, tile_cost,
-        tile_stats, tile_order, t_final, n_last, accum, counters, total;
+        marks, tile_stats, tile_order, t_final, n_last, accum, counters, total;
     // the region a binning pass accumulates into and finds cleared
     size_t clear_begin, clear_words;
 };
