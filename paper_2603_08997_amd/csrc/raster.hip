@@ -1,13 +1,13 @@
 // Front-to-back compositing (paper Sec. 3, Eqs. 4-5) over the per-tile
 // depth-ordered lists, and its reverse-order adjoint.
 //
-// One or several wavefronts (64 lanes) per tile, each owning a strip of its
-// rows (a launch rule on the number of tiles picks 1, 2 or 4); lane l owns
-// column l % TW of the strip and the rows l / TW + k * 64 / TW, so every
+// One or several wavefronts (64 lanes) per tile, each owning a part of it, SW x
+// SH pixels (a launch rule on the number of tiles picks 1, 2 or 4 parts); lane l
+// owns column l % SW of the part and the rows l / SW + k * 64 / SW, so every
 // per-pixel load or store of the wave is a run of contiguous row segments. The
 // tile's list is staged through LDS B records at a time, each wave for itself;
 // while staging, each lane turns one record into the coefficients the inner
-// loop needs, and a wave of a strip leaves out the entries that cannot take
+// loop needs, and a wave of a part leaves out the entries that cannot take
 // part in its pixels. Every lane then walks the batch with broadcast LDS reads.
 //
 // The exponent of Eq. 5 is evaluated in base 2 with the opacity folded in,
@@ -15,7 +15,7 @@
 // C = -c log2(e)/2), so that o exp(P) = 2^E. The part that depends on dx only
 // is formed once per lane and Gaussian (the lane's pixels share a column);
 // each pixel then costs two fused multiply-adds. A pixel takes part when it
-// lies in the overlap box (bit masks over the strip's columns and rows, formed
+// lies in the overlap box (bit masks over the part's columns and rows, formed
 // exactly at staging), E >= log2(alpha_min) (alpha' >= alpha_min;
 // alpha_min <= alpha_max) and E <= log2(o) (P <= 0); only then is 2^E
 // evaluated. Forward and backward share these functions, so their skip
@@ -29,8 +29,8 @@
 // Gaussian's gradient is gathered per lane as moments of dL/dP over its
 // pixels, turned into the 9 parameter gradients per lane, summed over the 64
 // lanes reduce-scatter style (lane 8 k ends with gradient k), and added with one
-// hardware float atomic instruction over 9 lanes for that (strip, Gaussian)
-// pair; Gaussians that touch no pixel of the strip skip both.
+// hardware float atomic instruction over 9 lanes for that (part, Gaussian)
+// pair; Gaussians that touch no pixel of the part skip both.
 //
 // All tiles of a launch are resident at once, so a launch lasts as long as
 // its busiest SIMD. The forward records each tile's work for the backward
@@ -46,6 +46,12 @@ namespace sgs {
 namespace {
 
 constexpr int kLanes = 64;
+
+// Width of the part of a TW x TH tile that each of W waves takes: parts as
+// square as they can be, which the fewest Gaussians reach (4 parts of 8x8 pixels
+// against 16x4: forward 51.4 -> 46.9 us at 16 tiles, 37.0 -> 34.6 at 1200, 100
+// -> 96 at 4056, backward 78.7 -> 76.8 at 1200).
+constexpr int part_width(int tw, int w) { return w == 4 ? 8 : (w == 2 ? 16 : tw); }
 constexpr float kNegHalfLog2e = -0.721347520444481703680f;  // -log2(e) / 2
 constexpr float kNegLog2e = -1.44269504088896340736f;       // -log2(e)
 
@@ -98,12 +104,12 @@ __device__ __forceinline__ bool stage_entry(const float4& r0, const float4& r1, 
 }
 
 // Whether an entry can take part in a pixel of the rectangle: its box holds
-// one and, for a strip of a tile (the tile lists hold no entry that fails on
+// one and, for a part of a tile (the tile lists hold no entry that fails on
 // the whole tile), it can reach alpha_min there.
-template <bool kStrip>
+template <bool kPart>
 __device__ __forceinline__ bool entry_reaches(bool box, const float4& r0, const float4& r1,
                                               const RasterDev& rp, int x0, int y0, int w, int h) {
-    if constexpr (kStrip) {
+    if constexpr (kPart) {
         // (the test needs a convex exponent: a, c and det = ac - b^2 > 0, det
         // by Kahan's fused form; other conics keep their box)
         const float a = r0.z, b = r0.w, c = r1.x, bb = b * b;
@@ -268,11 +274,11 @@ __device__ __forceinline__ void sum_tiles(const uint4* __restrict__ tile_stats, 
     }
 }
 
-// Forward of one tile by W waves: each composites its strip of TH / W rows
+// Forward of one tile by W waves: each composites its SW x SH pixels
 // front to back over the tile's list in batches of B entries (records
 // gathered and staged in LDS per batch, each wave for itself) and stops when
-// every pixel of the strip has terminated. A wave leaves the entries that
-// cannot take part in its strip out at staging.
+// every pixel of the part has terminated. A wave leaves the entries that
+// cannot take part in its pixels out at staging.
 template <int TW, int TH, int B, int W>
 __global__ void __launch_bounds__(kLanes * W) raster_forward_kernel(
     const Views* __restrict__ views, RasterDev rp, const uint32_t* __restrict__ tile_ranges,
@@ -281,11 +287,12 @@ __global__ void __launch_bounds__(kLanes * W) raster_forward_kernel(
     uint4* __restrict__ tile_stats, uint32_t* __restrict__ tile_cost, uint32_t entries,
     uint32_t* __restrict__ tile_state, uint32_t* __restrict__ tile_resume,
     uint32_t* __restrict__ sup_redo, uint32_t* __restrict__ counters, SumBy sum_by, bool redo) {
-    constexpr int SH = TH / W;                // rows of a strip
-    constexpr int PIX = TW * SH / kLanes;
-    constexpr int RS = kLanes / TW;           // row step between a lane's pixels
+    constexpr int SW = part_width(TW, W);     // a wave's part of the tile
+    constexpr int SH = TW * TH / (W * SW);
+    constexpr int PIX = SW * SH / kLanes;
+    constexpr int RS = kLanes / SW;           // row step between a lane's pixels
     static_assert(B % 32 == 0 && B >= 32 && B <= 256, "batch size");
-    static_assert(PIX >= 1 && PIX * kLanes == TW * SH, "whole waves");
+    static_assert(PIX >= 1 && PIX * kLanes * W == TW * TH && TW % SW == 0, "whole waves");
     // (the last entries: padding and the read ahead past it)
     __shared__ float4 s_geo[W][B + 4];
     __shared__ float4 s_aux[W][B + 4];
@@ -304,10 +311,10 @@ __global__ void __launch_bounds__(kLanes * W) raster_forward_kernel(
     const int tx = local % V.tiles_x, ty = local / V.tiles_x;
     const int wv = W > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes) : 0;
     const int tid = threadIdx.x % kLanes;
-    const int col = tid % TW, row0 = tid / TW;
+    const int col = tid % SW, row0 = tid / SW;
     const uint32_t start = tile_ranges[2 * tile], end = tile_ranges[2 * tile + 1];
     const float lmin = rp.log2_alpha_min, amax = rp.alpha_max, tmin = rp.t_min;
-    const int px0 = tx * TW, py0 = ty * TH + wv * SH;
+    const int px0 = tx * TW + wv % (TW / SW) * SW, py0 = ty * TH + wv / (TW / SW) * SH;
     float4* geo = s_geo[wv];
     float4* aux = s_aux[wv];
     float4* rgb = s_col[wv];
@@ -318,7 +325,7 @@ __global__ void __launch_bounds__(kLanes * W) raster_forward_kernel(
     // a pixel outside the view or stopped has py = NaN: its E is NaN and takes
     // part in nothing
     float py[PIX], T[PIX], C0[PIX], C1[PIX], C2[PIX];
-    BoxBits<TW, SH> bits[PIX];
+    BoxBits<SW, SH> bits[PIX];
     uint32_t last[PIX];
     // the second pass resumes each pixel where the first stopped, at the end
     // of the tile's list prefix (which begins its whole list): transmittance,
@@ -328,7 +335,7 @@ __global__ void __launch_bounds__(kLanes * W) raster_forward_kernel(
     for (int k = 0; k < PIX; ++k) {
         const int y = py0 + row0 + RS * k;
         py[k] = __builtin_nanf("");
-        bits[k] = BoxBits<TW, SH>(col, row0 + RS * k);
+        bits[k] = BoxBits<SW, SH>(col, row0 + RS * k);
         T[k] = 1.f;
         C0[k] = C1[k] = C2[k] = 0.f;
         last[k] = 0;
@@ -389,10 +396,10 @@ __global__ void __launch_bounds__(kLanes * W) raster_forward_kernel(
         int cnt = 0;   // staged entries
         auto stage = [&](int j, const float4& r0, const float4& r1, const float4& r2) {
             float4 g, x;
-            const bool box = stage_entry<TW, SH>(r0, r1, px0, py0, g, x);
+            const bool box = stage_entry<SW, SH>(r0, r1, px0, py0, g, x);
             const bool keep =
                 j < in_batch && entry_reaches<(W > 1)>(box, r0, r1, rp, px0, py0,
-                                                       min(TW, V.width - px0),
+                                                       min(SW, V.width - px0),
                                                        min(SH, V.height - py0));
             const uint64_t m = ballot(keep);
             if (keep) {
@@ -572,10 +579,11 @@ __global__ void __launch_bounds__(kLanes, backward_waves(B)) raster_backward_ker
     const float* __restrict__ dl_drgb, const int32_t* __restrict__ gate,
     float* __restrict__ accum, const uint32_t* __restrict__ order, int total_tiles,
     uint32_t entries) {
-    constexpr int SH = TH / W;   // rows of a strip
-    constexpr int PIX = TW * SH / kLanes;
-    constexpr int RS = kLanes / TW;
-    static_assert(PIX >= 1 && PIX * kLanes == TW * SH, "whole waves");
+    constexpr int SW = part_width(TW, W);   // a wave's part of the tile
+    constexpr int SH = TW * TH / (W * SW);
+    constexpr int PIX = SW * SH / kLanes;
+    constexpr int RS = kLanes / SW;
+    static_assert(PIX >= 1 && PIX * kLanes * W == TW * TH && TW % SW == 0, "whole waves");
     __shared__ float4 s_geo[B + 1];
     __shared__ float4 s_aux[B + 1];
     __shared__ float4 s_col[B + 1];   // r, g, b, entry (bits)
@@ -583,30 +591,31 @@ __global__ void __launch_bounds__(kLanes, backward_waves(B)) raster_backward_ker
     __shared__ uint32_t s_rel[B + 1];
     if (gate_closed(gate)) return;
 
-    // the W strips of a tile are consecutive workgroups
+    // the W parts of a tile are consecutive workgroups
     const int tile = (int)order[blockIdx.x / W];
     if (tile >= total_tiles) return;   // order is a permutation of the tiles
     const ViewDev& V = views->v[view_of_tile(views, tile)];
     const int local = tile - V.tile_offset;
     const int tx = local % V.tiles_x, ty = local / V.tiles_x;
     const int tid = threadIdx.x;
-    const int col = tid % TW, row0 = tid / TW;
+    const int col = tid % SW, row0 = tid / SW;
     const float lmin = rp.log2_alpha_min, amax = rp.alpha_max;
 
     const int64_t plane = (int64_t)V.width * V.height;
     const float* dl = dl_drgb + 3 * V.px_offset;
-    const int py0 = ty * TH + (int)(blockIdx.x % W) * SH;
-    const int x = tx * TW + col;
+    const int wv = (int)(blockIdx.x % W);
+    const int px0 = tx * TW + wv % (TW / SW) * SW, py0 = ty * TH + wv / (TW / SW) * SH;
+    const int x = px0 + col;
     const float px = (float)x + 0.5f;
     float py[PIX], T[PIX], G0[PIX], G1[PIX], G2[PIX], GS[PIX];
-    BoxBits<TW, SH> bits[PIX];
+    BoxBits<SW, SH> bits[PIX];
     uint32_t last[PIX];
     uint32_t my_max = 0;
 #pragma unroll
     for (int k = 0; k < PIX; ++k) {
         const int y = py0 + row0 + RS * k;
         py[k] = (float)y + 0.5f;
-        bits[k] = BoxBits<TW, SH>(col, row0 + RS * k);
+        bits[k] = BoxBits<SW, SH>(col, row0 + RS * k);
         T[k] = 1.f;
         G0[k] = G1[k] = G2[k] = 0.f;
         last[k] = 0;
@@ -644,10 +653,10 @@ __global__ void __launch_bounds__(kLanes, backward_waves(B)) raster_backward_ker
             const float4 r0 = rec[3 * (int64_t)e], r1 = rec[3 * (int64_t)e + 1],
                          r2 = rec[3 * (int64_t)e + 2];
             float4 g, xm;
-            const bool box = stage_entry<TW, SH>(r0, r1, tx * TW, py0, g, xm);
+            const bool box = stage_entry<SW, SH>(r0, r1, px0, py0, g, xm);
             const bool keep =
-                k < in_batch && entry_reaches<(W > 1)>(box, r0, r1, rp, tx * TW, py0,
-                                                       min(TW, V.width - tx * TW),
+                k < in_batch && entry_reaches<(W > 1)>(box, r0, r1, rp, px0, py0,
+                                                       min(SW, V.width - px0),
                                                        min(SH, V.height - py0));
             const uint64_t m = ballot(keep);
             if (keep) {
@@ -663,7 +672,7 @@ __global__ void __launch_bounds__(kLanes, backward_waves(B)) raster_backward_ker
             cnt += popc64(m);
         }
         __syncthreads();
-        // With few waves on a SIMD (strips) the next entry's LDS reads are
+        // With few waves on a SIMD (parts) the next entry's LDS reads are
         // issued before the current entry is processed (the last one reads
         // ahead into the spare element); with one wave per tile the other
         // waves cover them, and the registers are worth more.
@@ -769,26 +778,26 @@ __global__ void __launch_bounds__(kPrepareThreads) prepare_backward_kernel(
 // Waves per tile. A wave's time is its instruction count (a wave alone on a
 // SIMD issues one instruction every 4 cycles), so a launch with fewer waves
 // than the chip's 1024 SIMDs hold ends with its longest tile, and cutting a
-// tile into strips of rows shortens exactly that; strips also drop the entries
-// that miss them. 8x8 tiles have one pixel per lane already.
+// tile into parts shortens exactly that; parts also drop the entries that miss
+// them. 8x8 tiles have one pixel per lane already.
 //
-// Forward: strips win at every size, the finer ones until the per-strip work
+// Forward: parts win at every size, the finer ones until the per-part work
 // (LDS broadcasts, 24 cycles an entry and wave) catches up. us for 1 / 2 / 4
-// waves: 16 tiles 74 / 45 / 27 (one pass), 1200 tiles 89 / 55 / 39, 2170 tiles
-// 124 / 73 / 61, 4056 tiles 149 / 105 / 100, 6700 tiles 167 / 135 / 141,
-// 28000 tiles 746 / 568 / 599.
+// waves: 16 tiles 74 / 45 / 27 (one pass), 1200 tiles 89 / 55 / 35, 2170 tiles
+// 124 / 73 / 58, 4056 tiles 149 / 105 / 96, 6700 tiles 167 / 135 / 137 (many
+// Gaussians a pixel: 2 x 74 / 68), 28000 tiles 746 / 562 / 570.
 //
-// Backward: each strip repeats the wave reduction and the atomic of a pair, so
-// strips pay only while SIMDs would idle: 16 tiles 68 / 42 / 29, 1200 tiles
-// 135 / 88 / 76, 2170 tiles 188 / 131 / 153, 4056 tiles 228 / 220 / 264, 6700
-// tiles 276 / 293 / 403, 28000 tiles 925 / 1208 / 1704.
+// Backward: each part repeats the wave reduction and the atomic of a pair, so
+// parts pay only while SIMDs would idle: 16 tiles 68 / 42 / 29, 1200 tiles
+// 135 / 88 / 75, 2170 tiles 188 / 131 / 144, 4056 tiles 228 / 222 / 249, 6700
+// tiles 284 / 290 / 403, 28000 tiles 910 / 1177 / 1704.
 constexpr int64_t kForwardFine = 5120;    // tiles up to which the forward takes 4 waves, else 2
 constexpr int64_t kBackwardFine = 1536;   // tiles up to which the backward takes 4 waves
 constexpr int64_t kBackwardHalf = 5120;   // ... 2 waves, else 1
 
 // Kernel instantiations: tile shapes 16x16, 8x8, 32x8; the batches 32, 64,
 // 128, 256 the raster parameters accept where one wave takes a tile, batches
-// of 64 in strips.
+// of 64 in parts.
 #define SGS_RASTER_BATCHES(KERNEL, TW, TH, ...)                                       \
     do {                                                                             \
         if (rp.batch == 32) SGS_LAUNCH((KERNEL<TW, TH, 32, 1>), 1, __VA_ARGS__);       \
@@ -796,7 +805,7 @@ constexpr int64_t kBackwardHalf = 5120;   // ... 2 waves, else 1
         else if (rp.batch == 256) SGS_LAUNCH((KERNEL<TW, TH, 256, 1>), 1, __VA_ARGS__); \
         else SGS_LAUNCH((KERNEL<TW, TH, 64, 1>), 1, __VA_ARGS__);                      \
     } while (0)
-#define SGS_RASTER_STRIPS(KERNEL, W, ...)                                             \
+#define SGS_RASTER_PARTS(KERNEL, W, ...)                                             \
     do {                                                                             \
         if (rp.tile_w == 16) SGS_LAUNCH((KERNEL<16, 16, 64, W>), W, __VA_ARGS__);      \
         else SGS_LAUNCH((KERNEL<32, 8, 64, W>), W, __VA_ARGS__);                       \
@@ -835,10 +844,10 @@ hipError_t launch_rasterize(const RasterDev& rp, const Layout& L, char* ws, floa
                                tf, nl, stats, cost, entries, state, resume, sup_redo, cnt,
                                sum_by, redo);
         else if (L.total_tiles <= kForwardFine)
-            SGS_RASTER_STRIPS(raster_forward_kernel, 4, views, rp, ranges, entry, rec, out_rgb, tf,
+            SGS_RASTER_PARTS(raster_forward_kernel, 4, views, rp, ranges, entry, rec, out_rgb, tf,
                               nl, stats, cost, entries, state, resume, sup_redo, cnt, sum_by, redo);
         else
-            SGS_RASTER_STRIPS(raster_forward_kernel, 2, views, rp, ranges, entry, rec, out_rgb, tf,
+            SGS_RASTER_PARTS(raster_forward_kernel, 2, views, rp, ranges, entry, rec, out_rgb, tf,
                               nl, stats, cost, entries, state, resume, sup_redo, cnt, sum_by, redo);
         return hipGetLastError();
     };
@@ -887,7 +896,7 @@ hipError_t launch_rasterize_backward(const RasterDev& rp, const Layout& L, char*
     const float* tf = reinterpret_cast<const float*>(ws + L.t_final);
     const uint32_t* nl = reinterpret_cast<const uint32_t*>(ws + L.n_last);
     const int tiles = (int)L.total_tiles;
-    // every strip is a workgroup of its own
+    // every part is a workgroup of its own
 #define SGS_LAUNCH(K, W, ...)                                                                  \
     hipLaunchKernelGGL(K, dim3((unsigned)(L.total_tiles * W)), dim3(kLanes), 0, s, __VA_ARGS__)
 #define SGS_ARGS                                                                              \
@@ -895,9 +904,9 @@ hipError_t launch_rasterize_backward(const RasterDev& rp, const Layout& L, char*
     if (rp.tile_w == 8)
         SGS_RASTER_BATCHES(raster_backward_kernel, 8, 8, SGS_ARGS);
     else if (L.total_tiles <= kBackwardFine)
-        SGS_RASTER_STRIPS(raster_backward_kernel, 4, SGS_ARGS);
+        SGS_RASTER_PARTS(raster_backward_kernel, 4, SGS_ARGS);
     else if (L.total_tiles <= kBackwardHalf)
-        SGS_RASTER_STRIPS(raster_backward_kernel, 2, SGS_ARGS);
+        SGS_RASTER_PARTS(raster_backward_kernel, 2, SGS_ARGS);
     else if (rp.tile_w == 16)
         SGS_RASTER_BATCHES(raster_backward_kernel, 16, 16, SGS_ARGS);
     else
@@ -907,7 +916,7 @@ hipError_t launch_rasterize_backward(const RasterDev& rp, const Layout& L, char*
     return hipGetLastError();
 }
 
-#undef SGS_RASTER_STRIPS
+#undef SGS_RASTER_PARTS
 #undef SGS_RASTER_BATCHES
 
 }  // namespace sgs
