@@ -100,7 +100,8 @@ typedef struct {
     int32_t super_tile;      /* binning granularity: squares of super_tile tiles,   */
                              /* 1..8 (0: 8)                                         */
     int32_t lds_batch;       /* list entries per compositing batch staged in LDS:   */
-                             /* 32, 64, 128 or 256 (0: 64)                          */
+                             /* 32, 64, 128 or 256 (0: 64), where one wave takes a  */
+                             /* tile; the waves of a tile shared by several take 64 */
     int32_t split_prefix;    /* pairs of a long super-tile list split into tile     */
                              /* lists before compositing (rounded up to 512-pair    */
                              /* segments), 0 <= split_prefix <= 2^30, 0: all; see   */
@@ -138,8 +139,8 @@ void sgs_default_raster_params(sgs_raster_params* rp);
  * A tile rarely composites more than the front of its list, so with
  * split_prefix > 0 binning splits a super-tile list of more than
  * 4 x split_prefix pairs (both counted in whole 512-pair segments) only in its
- * first split_prefix pairs (shorter lists whole): a tile's list is then the prefix of its whole list made of the
- * entries from those pairs. A tile whose pixels are not all terminated when
+ * first split_prefix pairs (shorter lists whole): a tile's list is then the
+ * prefix of its whole list made of the entries from those pairs. A tile whose pixels are not all terminated when
  * its prefix runs out is marked, the whole lists of the marked tiles'
  * super-tiles are split (after the prefix lists, in the same pair capacity)
  * and the marked tiles resume their compositing over their whole lists, all
