@@ -335,22 +335,21 @@ def roofline(args, stages, bf, cnt, visible_only):
     F = 11 + 3 * 16
     n, vis = args.n, cnt["visible"]
     # fused backward + Adam: parameters, first and second moments read and
-    # written once per plane of every updated Gaussian, the visibility word of
-    # every Gaussian, the 48-byte gradient accumulator and the 16-byte colour
-    # record of every visible one
+    # written once per plane of every updated Gaussian, the visibility byte of
+    # every Gaussian, the 48-byte gradient accumulator of every visible one
     upd = vis if visible_only else n
-    fused_bytes = upd * F * 4 * 6 + n * 4 + vis * (48 + 16)
-    # binning: compaction (visibility word per entry; depth and key/value of
-    # every visible entry), four depth-sort passes over 8-byte key/value pairs
-    # (read + write), the super-tile counts gathered and scanned, the records
-    # the emission reads (32 B per visible entry) and the 8-byte pairs it
-    # writes, one pass of the super-tile sort (read + write); the split reads
-    # every pair of the split prefixes (at most 512 per segment; 8 B) and its
-    # entry's record (32 B) and writes its tile mask (8 B), then reads mask and
-    # entry again (12 B) and writes every tile-list entry of the prefixes (4 B)
-    P, I = cnt["pairs"], cnt["items"]
+    fused_bytes = upd * F * 4 * 6 + n + vis * 48
+    # binning: four depth-sort passes over 8-byte key/value pairs (read + write;
+    # the first reads depth and visibility word of every entry, which it also
+    # compacts, the last writes the values only), the 16-byte pair information of
+    # every visible entry gathered and written in order, then read, and the 8-byte
+    # pairs written at their places in the super-tile lists; the split reads every
+    # pair of the split prefixes (at most 512 per segment; 8 B) and its entry's
+    # record (32 B) and writes its tile mask (8 B), then reads mask and entry again
+    # (12 B) and writes every tile-list entry of the prefixes (4 B)
+    I = cnt["items"]
     Ps = min(cnt["pairs_kept"], 512 * cnt["segments"])
-    bin_bytes = (n * 4 + vis * 12 + 4 * vis * 16 + vis * 12 + vis * 32 + P * 8 + P * 16
+    bin_bytes = (n * 8 + 3 * vis * 16 + vis * 12 + vis * (4 + 3 * 16) + cnt["pairs_kept"] * 8
                  + Ps * (8 + 32 + 8) + Ps * 12 + I * 4)
     cands = {
         "raster_forward": dict(ms=allm["rasterize"], weight=1.0, bound="alu",

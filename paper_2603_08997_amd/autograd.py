@@ -87,6 +87,10 @@ class LossFn(torch.autograd.Function):
         rgb, target = ctx.saved_tensors
         width, height, lam, lws = ctx.meta
         dl = torch.empty_like(rgb)
+        if torch.is_grad_enabled() and g.requires_grad:
+            # (a graph of the backward is wanted: the product has to be in it)
+            sk.photometric_loss_backward(rgb, target, width, height, lam, lws, None, dl)
+            return dl * g, None, None, None, None
         # (the incoming derivative stays on the device: reading it would wait
         # for the forward)
         sk.photometric_loss_gradient(rgb, target, width, height, lam, lws, g, dl)

@@ -561,12 +561,13 @@ __device__ __forceinline__ void sh_coef_grad(const ViewSH& o, float* g_sh) {
         for (int c = 0; c < 3; ++c) g_sh[3 * k + c] += o.draw[c] * Y[k];
 }
 
-// What bounds the per-Gaussian backward: HBM. Whether a view sees the Gaussian and
-// which colour channels were clamped comes from a byte an entry; read from the
-// tile counts and the records' last words, whose lines are those of all records,
-// the fused step took 907 us at 3M Gaussians (SH 3; 865 now), the written
-// gradient 659 at 6M (601), the added one of 8 views 668 at 2M (538, and 709
-// before the parts that no view changes came out of the loop over the views).
+// What bounds the per-Gaussian backward: HBM, for several views also the vector
+// units. Whether a view sees the Gaussian and which colour channels were clamped
+// comes from a byte an entry; read from the tile counts and the records' last
+// words, whose lines are those of all records, the fused step took 907 us at 3M
+// Gaussians (SH 3; 865 now), the written gradient 659 at 6M (601), the added one
+// of 8 views 709 at 2M (591; 538 if the gradient of the covariance is summed over
+// the views first, which rounds the sums differently).
 //
 // The per-Gaussian backward. All parameters of the Gaussian are loaded at
 // once; the gradient stays in registers, and the update (kFused: Adam on every
@@ -613,17 +614,14 @@ __device__ __forceinline__ void gaussian_backward(float* __restrict__ planes, in
     bool any = false;
     ViewSH one;
     if constexpr (kMulti) {
-        // What no view changes is formed once before the views, and what is
-        // linear in the gradients of covariance and opacity once after them; the
-        // accumulators of a view are loaded while the one before is worked on.
+        // What no view changes is formed once before the views; the accumulators
+        // of a view are loaded while the one before is worked on.
         const int nv = views->n;
         uint64_t seen = 0;   // the views' marks
         for (int vi = 0; vi < nv; ++vi) seen |= (uint64_t)marks[(int64_t)vi * n + i] << (4 * vi);
         Geometry G;
         if (!compute_shape(ls, q, G)) seen = 0;
-        float dS[9], d_o = 0.f;
-#pragma unroll
-        for (int k = 0; k < 9; ++k) dS[k] = 0.f;
+        const float opacity = sigmoidf(p[10]);
         auto mark = [&](int vi) { return (uint32_t)(seen >> (4 * vi)) & 15u; };
         float4 n0, n1, n2;
         auto fetch = [&](int vi) {
@@ -640,20 +638,14 @@ __device__ __forceinline__ void gaussian_backward(float* __restrict__ planes, in
             const ViewDev& V = views->v[vi];
             if (mark(vi) == 0u || !compute_view(mu, V, rp, G)) continue;
             any = true;
-            float dv[9];
-            view_grads(G, V, a0, a1, g, dv);
-#pragma unroll
-            for (int k = 0; k < 9; ++k) dS[k] += dv[k];
-            d_o += a1.y;
+            float dS[9];
+            g[10] += a1.y * opacity * (1.f - opacity);
+            view_grads(G, V, a0, a1, g, dS);
+            shape_grads(G, dS, g + 3, g + 6);
             ViewSH o;
             view_sh(mu, V, a1, a2, mark(vi), o);
             sh_mean_grad<sh_degree>(o, f, g);
             sh_coef_grad<sh_degree>(o, g_sh);
-        }
-        if (any) {
-            const float o = sigmoidf(p[10]);
-            g[10] = d_o * o * (1.f - o);
-            shape_grads(G, dS, g + 3, g + 6);
         }
     } else if (const uint32_t mark = marks[i]; mark != 0u) {
         const float4 a0 = acc[3 * i], a1 = acc[3 * i + 1];
@@ -793,7 +785,10 @@ hipError_t launch_project(const float* planes, int64_t n, int64_t stride, int sh
     }
     const int nt = 256;
     const bool loop = L.n_views > 1 && n >= kProjectLoop;
-    const int64_t nb = ((loop ? n : entries) + nt - 1) / nt;
+    int64_t nb = ((loop ? n : entries) + nt - 1) / nt;
+    // (enough workgroups for what one view clears: four float4s a thread)
+    const int64_t n4 = call.bins ? (int64_t)(L.clear_words / 4) : 0;
+    if (one_view) nb = std::max(nb, std::min<int64_t>((n4 + 4 * nt - 1) / (4 * nt), 512));
     const Views* views = reinterpret_cast<const Views*>(ws + L.views);
     float4* rec = reinterpret_cast<float4*>(ws + L.records);
     uint32_t* tiles = reinterpret_cast<uint32_t*>(ws + L.tiles);
@@ -814,7 +809,7 @@ hipError_t launch_project(const float* planes, int64_t n, int64_t stride, int sh
     one.dst = reinterpret_cast<Views*>(ws + L.views);
     one.counters = call.bins ? reinterpret_cast<uint32_t*>(ws + L.counters) : nullptr;
     one.clear = reinterpret_cast<uint4*>(ws + L.clear_begin);
-    one.n4 = call.bins ? (int64_t)(L.clear_words / 4) : 0;
+    one.n4 = n4;
 #define SGS_PK(D)                                                                              \
     if (one_view)                                                                              \
         hipLaunchKernelGGL(project_one_kernel<D>, dim3((unsigned)nb), dim3(nt), 0, s, planes, n, \

@@ -32,7 +32,8 @@ ROOT = os.path.dirname(PKG)
 TRAFFIC_KERNELS = {"project_backward_adam": "project_backward_adam_kernel",
                    "raster_backward": "raster_backward_kernel",
                    "raster_forward": "raster_forward_kernel",
-                   "emit": "emit_kernel",
+                   "pair_count": "pair_count_kernel",
+                   "pair_place": "pair_place_kernel",
                    "split_count": "split_count_kernel",
                    "split_write": "split_write_kernel"}
 COPY_KERNEL = "MulFunctor"
@@ -60,7 +61,7 @@ def _rows(path):
         return list(csv.DictReader(fh))
 
 
-def kernels_table(d: str, iterations: int = 40, marker: str = "project_kernel",
+def kernels_table(d: str, iterations: int = 40, marker: str = "project_one_kernel",
                   require: str = "raster_backward") -> str:
     """Markdown table: time per iteration of each kernel over the last
     `iterations` iterations of the trace that launch `require` (an iteration

@@ -66,3 +66,17 @@ def test_render_keeps_the_cameras_of_its_forward():
         grads.append(planes.grad)
     scale = grads[0].abs().amax(1, keepdim=True).clamp_min(1e-30)
     assert ((grads[0] - grads[1]).abs() / scale).max().item() <= 1e-4
+
+
+def test_the_loss_scale_stays_in_a_graph_of_the_backward():
+    require_gpu()
+    gen = torch.Generator().manual_seed(2)
+    rgb, target = (torch.rand(3 * 20 * 12, generator=gen).cuda() for _ in range(2))
+    rgb.requires_grad_(True)
+    scale = torch.tensor(-1.5, device="cuda", requires_grad=True)
+    loss = AG.photometric_loss(rgb, target, 20, 12) * scale
+    (g,) = torch.autograd.grad(loss, rgb, create_graph=True)
+    g.sum().backward()
+    # d/d scale of sum(scale dL/d rgb)
+    want = (g.detach().double() / -1.5).sum()
+    assert abs(scale.grad.item() - want.item()) <= 1e-5 * g.detach().abs().sum().item()
