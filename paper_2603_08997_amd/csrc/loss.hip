@@ -457,8 +457,11 @@ hipError_t launch_train_loss(const float* rgb, TargetRef target, int w, int h, f
     const float* partials = reinterpret_cast<const float*>(ws + L.partials);
     const float* maps = reinterpret_cast<const float*>(ws + L.maps);
     LossTrain t{prepare, loss_sum_of(st, w, h, lambda, partials, gated ? nullptr : d_loss, gate), 0};
-    // the sum, the order, and a workgroup for every kClearEach float4s, up to kClearBlocks
-    constexpr int64_t kClearEach = 4 * kThreads, kClearBlocks = 1024;
+    // the sum, the order, and a workgroup for every kClearEach float4s, up to
+    // kClearBlocks (us of the launch at 1M / 3M Gaussians with 64 40.2 / 75.5, 128
+    // 39.4 / 71.4, 256 37.6 / 69.4, 1024 40.7 / 70.4, 4096 46.0 / 71.3: more stores
+    // in flight hold up the filters' loads)
+    constexpr int64_t kClearEach = 4 * kThreads, kClearBlocks = 256;
     const int64_t blocks =
         2 + std::min<int64_t>((prepare.n4 + kClearEach - 1) / kClearEach, kClearBlocks);
     t.rows = (int)((blocks + st.grid.x - 1) / st.grid.x);
