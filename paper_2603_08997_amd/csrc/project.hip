@@ -2,6 +2,7 @@
 // adjoint. One thread per (view, Gaussian) entry, or per Gaussian for a large
 // batch; parameters are read as coalesced planes of the [F][stride] layout.
 #include <algorithm>
+#include <type_traits>
 
 #include "sgs_internal.hpp"
 #include "sgs_device.hpp"
@@ -569,6 +570,11 @@ __device__ __forceinline__ void sh_coef_grad(const ViewSH& o, float* g_sh) {
 // of 8 views 709 at 2M (591; 538 if the gradient of the covariance is summed over
 // the views first, which rounds the sums differently).
 //
+// Visible-only Adam: not, on a set that stays in the caches, on a larger one
+// (30k Gaussians: 3 us slower with the larger one's two ways).
+enum class Sparse { kNo, kCached, kStreamed };
+constexpr int64_t kStreamFrom = 1 << 17;   // Gaussians
+
 // The per-Gaussian backward. All parameters of the Gaussian are loaded at
 // once; the gradient stays in registers, and the update (kFused: Adam on every
 // plane, dense as in the paper's optimiser, also for Gaussians visible in no
@@ -576,7 +582,8 @@ __device__ __forceinline__ void sh_coef_grad(const ViewSH& o, float* g_sh) {
 // kWrite written there, zero where no view sees the Gaussian) runs over
 // the planes in batches whose moment (or gradient) loads are issued one batch
 // ahead, so that each thread keeps several memory requests in flight.
-template <int sh_degree, bool kFused, bool kMulti, bool kSparse = false, bool kWrite = false>
+template <int sh_degree, bool kFused, bool kMulti, Sparse kSparse = Sparse::kNo,
+          bool kWrite = false>
 __device__ __forceinline__ void gaussian_backward(float* __restrict__ planes, int64_t n,
                                                   int64_t stride, int64_t i,
                                                   const Views* __restrict__ views,
@@ -588,15 +595,18 @@ __device__ __forceinline__ void gaussian_backward(float* __restrict__ planes, in
                                                   float* __restrict__ v) {
     constexpr int K = (sh_degree + 1) * (sh_degree + 1);
     constexpr int NP = 11 + 3 * K;
-    // the visible-only step updates a scattered subset of each wave's lines:
-    // its accesses go through L2, where the partly written lines meet the
-    // full lines its loads brought in; the dense step streams every line
-    constexpr int kPlaneCP = kSparse ? 0 : SGS_PLANE_CPOL;
+    if constexpr (kSparse == Sparse::kStreamed) {
+        // a wave that sees none of its Gaussians loads none
+        uint32_t seen = 0;
+        for (int vi = 0; vi < views->n; ++vi) seen |= marks[(int64_t)vi * n + i];
+        if (ballot(seen != 0u) == 0) return;
+    }
     const PlaneBuf P{planes, stride}, M{m, stride}, Vb{v, stride}, G{grads, stride};
     const uint32_t off = (uint32_t)i * 4u;
     float p[NP];
 #pragma unroll
-    for (int j = 0; j < NP; ++j) p[j] = P.template load<kPlaneCP>(j, off);
+    for (int j = 0; j < NP; ++j)
+        p[j] = P.template load<kSparse == Sparse::kNo ? SGS_PLANE_CPOL : 0>(j, off);
     const float* mu = p;
     const float* ls = p + 3;
     const float* q = p + 6;
@@ -657,7 +667,18 @@ __device__ __forceinline__ void gaussian_backward(float* __restrict__ planes, in
     }
     // without a visible entry: nothing to add (gradient accumulation), or,
     // for the visible-only (sparse) Adam step, nothing to update
-    if ((!kFused || kSparse) && !kWrite && !any) return;
+    if (!kFused && !kWrite && !any) return;
+    // The visible-only step on a large set: a wave that sees more than a few of
+    // its Gaussians streams whole lines like the dense step, writing back what it
+    // loaded for the others, since lines written in part go to HBM as more and
+    // smaller writes; with fewer, only the seen ones are stored, through L2. 1M
+    // Gaussians, SH 3, us in part / now: 72% visible 322 / 261, 22% 360 / 253, 7%
+    // 322 / 232, 2.3% 202 / 177, 0.9% 115 / 108, 0.2% 68 / 58 (whole wherever one is
+    // seen: 283, 285, 287, 247, 169, 91).
+    constexpr int kWholeFrom = 4;   // Gaussians of a wave
+    bool whole = kSparse == Sparse::kNo;   // uniform
+    if constexpr (kSparse == Sparse::kStreamed) whole = popc64(ballot(any)) >= kWholeFrom;
+    if (kSparse != Sparse::kNo && !whole && !any) return;
     float Y[16];
     if constexpr (!kMulti) {
         if (any) sh_eval(sh_degree, one.d[0], one.d[1], one.d[2], Y);
@@ -672,43 +693,50 @@ __device__ __forceinline__ void gaussian_backward(float* __restrict__ planes, in
     };
     constexpr int B = kUpdateBatch;
     constexpr int NB = (NP + B - 1) / B;
-    float ma[2][B], va[2][B];
-    auto load = [&](int b, int buf) {
+    auto update = [&](auto policy) {
+        constexpr int CP = decltype(policy)::value;
+        float ma[2][B], va[2][B];
+        auto load = [&](int b, int buf) {
 #pragma unroll
-        for (int t = 0; t < B; ++t) {
-            const int j = b * B + t;
-            if (j < NP) {
-                if constexpr (kFused) {
-                    ma[buf][t] = M.template load<kPlaneCP>(j, off);
-                    va[buf][t] = Vb.template load<kPlaneCP>(j, off);
-                } else {
-                    ma[buf][t] = kWrite ? 0.f : G.load(j, off);
+            for (int t = 0; t < B; ++t) {
+                const int j = b * B + t;
+                if (j < NP) {
+                    if constexpr (kFused) {
+                        ma[buf][t] = M.template load<CP>(j, off);
+                        va[buf][t] = Vb.template load<CP>(j, off);
+                    } else {
+                        ma[buf][t] = kWrite ? 0.f : G.load(j, off);
+                    }
+                }
+            }
+        };
+        load(0, 0);
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            if (b + 1 < NB) load(b + 1, (b + 1) & 1);
+#pragma unroll
+            for (int t = 0; t < B; ++t) {
+                const int j = b * B + t;
+                if (j < NP) {
+                    const float gj = grad_of(j);
+                    if constexpr (kFused) {
+                        float pj = p[j], mm = ma[b & 1][t], vv = va[b & 1][t];
+                        if (kSparse != Sparse::kStreamed || any)
+                            adam_update(gj, pj, mm, vv, ad->lr[j], *ad, *as);
+                        P.template store<CP>(j, off, pj);
+                        M.template store<CP>(j, off, mm);
+                        Vb.template store<CP>(j, off, vv);
+                    } else {
+                        // (through L2: 661 us for 6M Gaussians written, streamed 679 us)
+                        G.template store<0>(j, off, ma[b & 1][t] + gj);
+                    }
                 }
             }
         }
     };
-    load(0, 0);
-#pragma unroll
-    for (int b = 0; b < NB; ++b) {
-        if (b + 1 < NB) load(b + 1, (b + 1) & 1);
-#pragma unroll
-        for (int t = 0; t < B; ++t) {
-            const int j = b * B + t;
-            if (j < NP) {
-                const float gj = grad_of(j);
-                if constexpr (kFused) {
-                    float pj = p[j], mm = ma[b & 1][t], vv = va[b & 1][t];
-                    adam_update(gj, pj, mm, vv, ad->lr[j], *ad, *as);
-                    P.template store<kPlaneCP>(j, off, pj);
-                    M.template store<kPlaneCP>(j, off, mm);
-                    Vb.template store<kPlaneCP>(j, off, vv);
-                } else {
-                    // (through L2: 661 us for 6M Gaussians written, streamed 679 us)
-                    G.template store<0>(j, off, ma[b & 1][t] + gj);
-                }
-            }
-        }
-    }
+    if constexpr (kSparse != Sparse::kCached)
+        if (whole) return update(std::integral_constant<int, SGS_PLANE_CPOL>{});
+    if constexpr (kSparse != Sparse::kNo) update(std::integral_constant<int, 0>{});
 }
 
 // Adjoint of the projection: one thread per Gaussian, gradient ADDED to grads
@@ -733,7 +761,7 @@ __global__ void __launch_bounds__(kBackwardThreads) project_backward_kernel(
         }
         return;
     }
-    gaussian_backward<sh_degree, false, kMulti, false, kWrite>(
+    gaussian_backward<sh_degree, false, kMulti, Sparse::kNo, kWrite>(
         const_cast<float*>(planes), n, stride, i, views, rp, marks, acc, grads, nullptr,
         nullptr, nullptr, nullptr);
 }
@@ -742,7 +770,7 @@ __global__ void __launch_bounds__(kBackwardThreads) project_backward_kernel(
 // Adam: visible or not) or only the Gaussians visible in a view of the batch
 // (kSparse) gets its gradient computed in registers and its parameters, first
 // and second moments updated in place; no gradient array is written or read.
-template <int sh_degree, bool kMulti, bool kSparse>
+template <int sh_degree, bool kMulti, Sparse kSparse>
 __global__ void __launch_bounds__(kBackwardThreads) project_backward_adam_kernel(
     float* __restrict__ planes, int64_t n, int64_t stride, const Views* __restrict__ views,
     RasterDev rp, const uint8_t* __restrict__ marks,
@@ -849,12 +877,12 @@ hipError_t launch_load_records(const float* u, const float* v, const float* dept
     return hipGetLastError();
 }
 
-#define SGS_DISPATCH_DEG(MACRO, multi)                                      \
-    switch (sh_degree) {                                                    \
-        case 0: if (multi) MACRO(0, true); else MACRO(0, false); break;    \
-        case 1: if (multi) MACRO(1, true); else MACRO(1, false); break;    \
-        case 2: if (multi) MACRO(2, true); else MACRO(2, false); break;    \
-        default: if (multi) MACRO(3, true); else MACRO(3, false); break;   \
+#define SGS_DISPATCH_DEG(MACRO, multi)                                            \
+    switch (sh_degree) {                                                          \
+        case 0: if (multi) { MACRO(0, true); } else { MACRO(0, false); } break;   \
+        case 1: if (multi) { MACRO(1, true); } else { MACRO(1, false); } break;   \
+        case 2: if (multi) { MACRO(2, true); } else { MACRO(2, false); } break;   \
+        default: if (multi) { MACRO(3, true); } else { MACRO(3, false); } break;  \
     }
 
 hipError_t launch_project_backward(const float* planes, int64_t n, int64_t stride,
@@ -894,8 +922,10 @@ hipError_t launch_project_backward_adam(float* planes, int64_t n, int64_t stride
 #define SGS_PBA_S(D, M, SP)                                                                     \
     hipLaunchKernelGGL((project_backward_adam_kernel<D, M, SP>), dim3((unsigned)nb), dim3(nt), 0, \
                        s, planes, n, stride, views, rp, marks, acc, ad, m, v, step, gate)
-#define SGS_PBA(D, M) \
-    if (sparse) SGS_PBA_S(D, M, true); else SGS_PBA_S(D, M, false)
+#define SGS_PBA(D, M)                                              \
+    if (!sparse) SGS_PBA_S(D, M, Sparse::kNo);                     \
+    else if (n < kStreamFrom) SGS_PBA_S(D, M, Sparse::kCached);    \
+    else SGS_PBA_S(D, M, Sparse::kStreamed)
     SGS_DISPATCH_DEG(SGS_PBA, L.n_views > 1)
 #undef SGS_PBA
 #undef SGS_PBA_S
