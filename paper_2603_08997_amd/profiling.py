@@ -53,6 +53,7 @@ def source_digest() -> str:
 
 def short_name(n: str) -> str:
     n = n.replace("void ", "").replace("sgs::(anonymous namespace)::", "")
+    n = re.sub(r"\(\w+\)(?=\d)", "", n)   # the type of an enumeration's template argument
     return n.split("(")[0]
 
 
