@@ -14,6 +14,7 @@ from __future__ import annotations
 import torch
 
 from . import skipgs as sk
+from .scenes import n_planes
 
 
 def _forward(planes, n, sh_degree, cams, rp, capacity):
@@ -54,6 +55,9 @@ class RenderFn(torch.autograd.Function):
         if ws is None:
             _, ws, capacity = _forward(planes, n, sh_degree, cams, rp, capacity)
         grads = torch.empty_like(planes)
+        used = n_planes(sh_degree)
+        if planes.shape[0] > used:   # the planes of higher degrees have no part in the image
+            grads[used:].zero_()
         sk.render_gradients(planes, n, sh_degree, cams, rp, ws, capacity, g_rgb.contiguous(), grads)
         ctx.ws = None
         return grads, None, None, None, None, None, None
