@@ -472,13 +472,16 @@ __global__ void __launch_bounds__(kPairThreads, 4) pair_place_kernel(
                     tot += lkey[k * sp + tid];
                     before += lent[k * sp + tid];
                 }
+            // (saturating over the super-tiles, like the scans above, and never
+            // past the capacity, below 2^31: a place that adding a chunk's pairs
+            // to cannot wrap, and the ranges' lengths sum to the capacity at most)
             uint32_t all;
-            const uint32_t ex = carry + block_excl_scan<kPairThreads>(tot, smem, &all);
-            carry += all;
+            const uint32_t ex = sat_add(carry, block_excl_sat_scan<kPairThreads>(tot, smem, &all));
+            carry = sat_add(carry, all);
             if (tid < sp && s < ns) {
-                gpos[s] = ex + before;
+                gpos[s] = min(sat_add(ex, before), cap);
                 if (blockIdx.x == 0) {
-                    const uint32_t a = min(ex, cap), b = min(ex + tot, cap);
+                    const uint32_t a = min(ex, cap), b = min(sat_add(ex, tot), cap);
                     ranges[2 * s] = a < b ? a : 0u;
                     ranges[2 * s + 1] = a < b ? b : 0u;
                 }
@@ -576,7 +579,7 @@ __global__ void __launch_bounds__(kPairThreads, 4) pair_place_kernel(
                 if (s < ns) {
                     // start[s] turns a local position into the global one
                     start[s] = gpos[s] - run;
-                    gpos[s] += sum;
+                    gpos[s] = min(gpos[s] + sum, (uint32_t)capacity);
 #pragma unroll
                     for (int k = 0; k < NW; ++k) {
                         const uint32_t x = wcnt[k * ns + s];
