@@ -330,10 +330,10 @@ sgs_status sgs_photometric_loss_gradient(const float* rgb, const float* target, 
 /* For callers that cannot allocate device memory (code under graph capture,
  * serving loops, harnesses that forbid allocation): sgs_photometric_loss
  * without a workspace: the same loss value, bit for bit (it leaves no SSIM maps
- * for a backward: use it where only the loss is wanted). The per-tile partial
- * sums live in a file-scope device array of the library (one per GPU, 512 KiB,
- * held until the process ends), so images are limited to 65536 tiles of 16x16 pixels
- * (e.g. 4096x4096); larger ones fail with SGS_ERR_CAPACITY before anything is
+ * for a backward: use it where only the loss is wanted). The partial sums live
+ * in a file-scope device array of the library (one per GPU, 16 KiB, held until
+ * the process ends). Images are limited to 65536 tiles of 16x16 pixels (e.g.
+ * 4096x4096); larger ones fail with SGS_ERR_CAPACITY before anything is
  * enqueued. Allocates nothing. All calls on one GPU share that array: calls
  * that overlap in time on one GPU (different streams, or threads) race and
  * must be serialised by the caller. */

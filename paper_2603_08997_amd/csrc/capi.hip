@@ -307,20 +307,22 @@ void make_layout(const Views& views, const RasterDev& rp, int64_t n, int64_t cap
 
 using sgs::Layout;
 
-// Scratch of sgs_photometric_loss_static: the per-tile partial sums of the
+// Scratch of sgs_photometric_loss_static: the per-strip partial sums of the
 // loss forward (every call overwrites all it reads, so nothing needs
 // clearing). One copy per GPU, at its own device address, held until the
 // process ends; its address is looked up once per device and kept.
-constexpr int64_t kStaticLossPartials = int64_t(1) << 17;   // 65536 tiles of 16x16 pixels
-static __device__ __align__(256) float scratch[kStaticLossPartials];
+static __device__ __align__(256) double scratch[sgs::kLossPartials];
+// 16x16 tiles of the largest image that call takes (the bound its interface
+// states; the scratch would do for any image).
+constexpr int64_t kStaticLossTiles = 65536;
 
 namespace {
 
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
-float* g_scratch_ptr[kMaxDevices] = {};
+double* g_scratch_ptr[kMaxDevices] = {};
 
-sgs_status static_scratch(float** out) {
+sgs_status static_scratch(double** out) {
     int dev = -1;
     SGS_HIP(hipGetDevice(&dev), "hipGetDevice");
     if (dev < 0 || dev >= kMaxDevices)
@@ -330,7 +332,7 @@ sgs_status static_scratch(float** out) {
     if (g_scratch_ptr[dev] == nullptr) {
         void* p = nullptr;
         SGS_HIP(hipGetSymbolAddress(&p, HIP_SYMBOL(scratch)), "hipGetSymbolAddress(scratch)");
-        g_scratch_ptr[dev] = static_cast<float*>(p);
+        g_scratch_ptr[dev] = static_cast<double*>(p);
     }
     *out = g_scratch_ptr[dev];
     return SGS_OK;
@@ -645,13 +647,11 @@ sgs_status sgs_photometric_loss_static(const float* rgb, const float* target, in
     if (width <= 0 || height <= 0 || width > 32768 || height > 32768)
         return fail(SGS_ERR_INVALID_ARG, "image size not in [1, 32768]");
     if (!(lambda >= 0.f && lambda <= 1.f)) return fail(SGS_ERR_INVALID_ARG, "lambda not in [0, 1]");
-    if (sgs::loss_partial_floats(width, height) > kStaticLossPartials)
+    if ((int64_t)((width + 15) / 16) * ((height + 15) / 16) > kStaticLossTiles)
         return fail(SGS_ERR_CAPACITY,
-                    "%dx%d image needs %lld partial sums; the static scratch holds %lld "
-                    "(images up to %lld tiles of 16x16 pixels)",
-                    width, height, (long long)sgs::loss_partial_floats(width, height),
-                    (long long)kStaticLossPartials, (long long)(kStaticLossPartials / 2));
-    float* partials = nullptr;
+                    "%dx%d image: the loss in the static scratch takes images up to %lld tiles of "
+                    "16x16 pixels", width, height, (long long)kStaticLossTiles);
+    double* partials = nullptr;
     if (sgs_status st = static_scratch(&partials); st != SGS_OK) return st;
     SGS_HIP(sgs::launch_loss_partials(rgb, sgs::TargetRef{target, nullptr, 1}, width, height,
                                       lambda, partials, d_loss, static_cast<hipStream_t>(stream)),

@@ -24,8 +24,11 @@
 // both, as the halo rows skip the horizontal taps, but rounds differently: 3e-6
 // of the gradient, as far as either is from 64 bits.)
 //
-// Per-strip sums go to a partials array that a one-workgroup kernel reduces in
-// index order in binary64, so the loss is bit-reproducible.
+// A lane adds the values of its column in FP32 over kFold rows and these in
+// binary64, as all sums after it are: a strip has the more rows the larger the
+// image (32 at 1600x1060, 1366 at 8192x8192), and FP32 over all of them is off by
+// 2e-5 there for a flat difference. Per-strip sums go to a partials array that a
+// one-workgroup kernel reduces in index order, so the loss is bit-reproducible.
 //
 // Backward: per pixel p the SSIM value S(p) depends on x through mu_x(p),
 // E[x^2](p) and E[xy](p); the map derivatives dS/dmu_x, dS/dE[x^2],
@@ -41,11 +44,11 @@ namespace sgs {
 
 namespace {
 
-constexpr int kT = 16;                  // tiles the partials array is sized by
 constexpr int kR = 5;                   // window radius
 constexpr int kTaps = 2 * kR + 1;
 constexpr int kCols = 64 - 2 * kR;      // output columns of a wave
 constexpr int kThreads = 3 * 64;        // one wave a channel
+constexpr int kFold = 8;                // rows added up in FP32
 constexpr float kC1 = 0.01f * 0.01f;
 constexpr float kC2 = 0.03f * 0.03f;
 
@@ -85,21 +88,27 @@ Strips strips(int w, int h) {
     return {(int)rows, dim3((unsigned)nx, (unsigned)((h + rows - 1) / rows))};
 }
 
-// Loss workspace: [partials: 2 * blocks floats][maps: 9 * H * W floats]
+// Loss workspace: [partials: kLossPartials doubles][maps: 9 * H * W floats].
+// There are at most kResident strips (images of up to 32768 columns have fewer
+// strips side by side).
+static_assert(32768 / kCols + 1 <= kResident && kLossPartials == 2 * kResident, "two sums a strip");
 struct LossLayout {
-    int64_t blocks;   // at least the number of strips
     size_t partials, maps, total;
 };
 
-// (at most kResident strips, or one row of them)
 LossLayout loss_layout(int w, int h) {
     LossLayout L;
-    L.blocks = std::max<int64_t>((int64_t)((w + kT - 1) / kT) * ((h + kT - 1) / kT), kResident);
     auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
     L.partials = 0;
-    L.maps = al(L.partials + sizeof(float) * 2 * L.blocks);
+    L.maps = al(sizeof(double) * kLossPartials);
     L.total = al(L.maps + sizeof(float) * 9 * (size_t)w * h);
     return L;
+}
+
+__device__ __forceinline__ double wave_sum(double v) {
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d, 64);
+    return v;
 }
 
 // The reference image of a call: the given one, or image *d_view (clamped)
@@ -173,10 +182,10 @@ struct Place {
 template <bool kMaps>
 __global__ void __launch_bounds__(kThreads, 4) ssim_forward_kernel(
     const float* __restrict__ x, TargetRef target, int w, int h, int rows, Window W,
-    float* __restrict__ partials, float* __restrict__ maps) {
+    double* __restrict__ partials, float* __restrict__ maps) {
     __shared__ float4 s_m4[3][64];
     __shared__ float s_m1[3][64];
-    __shared__ float red[2][3];
+    __shared__ double red[2][3];
     const Place p(w, h, rows, (int)blockIdx.y);
     const int64_t plane = (int64_t)w * h;
     const float* __restrict__ xc = x + p.ch * plane + p.cx;
@@ -185,6 +194,12 @@ __global__ void __launch_bounds__(kThreads, 4) ssim_forward_kernel(
     float* m1 = s_m1[p.ch];
     Column cx_, cy_, cxx, cyy, cxy;
     float s_l1 = 0.f, s_ssim = 0.f;
+    double l1 = 0.0, ssim = 0.0;
+    auto fold = [&]() {
+        l1 += (double)s_l1;
+        ssim += (double)s_ssim;
+        s_l1 = s_ssim = 0.f;
+    };
     // rows are loaded kAhead rows before they are used
     constexpr int kAhead = 2;
     float a[kAhead], b[kAhead];
@@ -196,6 +211,7 @@ __global__ void __launch_bounds__(kThreads, 4) ssim_forward_kernel(
 #pragma unroll
     for (int k = 0; k < kAhead; ++k) load(p.first - kR + k, a[k], b[k]);
     for (int r = p.first - kR; r < p.end + kR; ++r) {
+        if (r % kFold == 0) fold();   // uniform
         const float av = a[0], bv = b[0];
 #pragma unroll
         for (int k = 0; k + 1 < kAhead; ++k) {
@@ -240,11 +256,12 @@ __global__ void __launch_bounds__(kThreads, 4) ssim_forward_kernel(
         }
     }
     // fixed-order workgroup sum
-    s_l1 = wave_sum(s_l1);
-    s_ssim = wave_sum(s_ssim);
+    fold();
+    l1 = wave_sum(l1);
+    ssim = wave_sum(ssim);
     if (p.lane == 0) {
-        red[0][p.ch] = s_l1;
-        red[1][p.ch] = s_ssim;
+        red[0][p.ch] = l1;
+        red[1][p.ch] = ssim;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -258,7 +275,7 @@ __global__ void __launch_bounds__(kThreads, 4) ssim_forward_kernel(
 // training iteration, the gate's decision (a launch of its own otherwise) and
 // the step of the view sequence. One workgroup of NT threads.
 struct LossSum {
-    const float* partials;
+    const double* partials;
     int64_t nb;
     double count;
     float lambda;
@@ -272,8 +289,8 @@ __device__ __forceinline__ void loss_sum(const LossSum& p, double (*dred)[kSumSl
     for (int k = tid; k < kSumSlots; k += NT) {
         double a = 0.0, b = 0.0;
         for (int64_t i = k; i < p.nb; i += kSumSlots) {
-            a += (double)p.partials[2 * i];
-            b += (double)p.partials[2 * i + 1];
+            a += p.partials[2 * i];
+            b += p.partials[2 * i + 1];
         }
         dred[0][k] = a;
         dred[1][k] = b;
@@ -403,16 +420,14 @@ __global__ void __launch_bounds__(kThreads) ssim_backward_kernel(
 
 size_t loss_workspace_bytes(int w, int h) { return loss_layout(w, h).total; }
 
-int64_t loss_partial_floats(int w, int h) { return 2 * loss_layout(w, h).blocks; }
-
-static LossSum loss_sum_of(const Strips& st, int w, int h, float lambda, const float* partials,
+static LossSum loss_sum_of(const Strips& st, int w, int h, float lambda, const double* partials,
                            float* d_loss, const LossGate& gate) {
     return {partials, (int64_t)st.grid.x * st.grid.y, 3.0 * (double)w * (double)h, lambda, d_loss,
             gate};
 }
 
 hipError_t launch_loss_partials(const float* rgb, TargetRef target, int w, int h, float lambda,
-                                float* partials, float* d_loss, hipStream_t s) {
+                                double* partials, float* d_loss, hipStream_t s) {
     const Strips st = strips(w, h);
     hipLaunchKernelGGL((ssim_forward_kernel<false>), st.grid, dim3(kThreads), 0, s, rgb, target, w,
                        h, st.rows, make_window(), partials, nullptr);
@@ -425,7 +440,7 @@ hipError_t launch_loss_forward(const float* rgb, TargetRef target, int w, int h,
                                char* ws, float* d_loss, hipStream_t s, const LossGate& gate) {
     const LossLayout L = loss_layout(w, h);
     const Strips st = strips(w, h);
-    float* partials = reinterpret_cast<float*>(ws + L.partials);
+    double* partials = reinterpret_cast<double*>(ws + L.partials);
     float* maps = reinterpret_cast<float*>(ws + L.maps);
     hipLaunchKernelGGL((ssim_forward_kernel<true>), st.grid, dim3(kThreads), 0, s, rgb, target, w,
                        h, st.rows, make_window(), partials, maps);
@@ -454,7 +469,7 @@ hipError_t launch_train_loss(const float* rgb, TargetRef target, int w, int h, f
     if (err != hipSuccess) return err;
     const LossLayout L = loss_layout(w, h);
     const Strips st = strips(w, h);
-    const float* partials = reinterpret_cast<const float*>(ws + L.partials);
+    const double* partials = reinterpret_cast<const double*>(ws + L.partials);
     const float* maps = reinterpret_cast<const float*>(ws + L.maps);
     LossTrain t{prepare, loss_sum_of(st, w, h, lambda, partials, gated ? nullptr : d_loss, gate), 0};
     // the sum, the order, and a workgroup for every kClearEach float4s, up to
