@@ -122,8 +122,12 @@ __device__ __forceinline__ const float* target_of(const TargetRef& t, int64_t im
 // Quotients by one divisor, each rounded as an IEEE division rounds it: the
 // reciprocal is refined to the nearest float (two Newton steps), and a quotient
 // a r corrected once by its exact remainder is then the nearest one (Markstein
-// 1990), without the scaling of the general sequence: divisors lie far from the
-// ends of the float range (C1 C2 = 9e-8 and up) and so do the quotients.
+// 1990), without the scaling of the general sequence. That needs divisors and
+// quotients far from the ends of the float range: B1 >= C1, and B2 is C2 plus
+// multiples of the last places of the squared means, so with 0 < |B1 B2| < 2^40
+// (pixel values into the thousands) nothing here comes near them. Other pixels
+// are divided in full (NaN, infinities, zero and subnormal reciprocals included).
+constexpr float kDivisorEnd = 0x1p40f;
 struct Divisor {
     float d, r;
     __device__ __forceinline__ explicit Divisor(float x) : d(x) {
@@ -243,15 +247,30 @@ __global__ void __launch_bounds__(kThreads, 4) ssim_forward_kernel(
             const float sxx = exx - mx * mx, syy = eyy - my * my, sxy = exy - mx * my;
             const float A1 = 2.f * mx * my + kC1, A2 = 2.f * sxy + kC2;
             const float B1 = mx * mx + my * my + kC1, B2 = sxx + syy + kC2;
-            const Divisor d1(B1), d2(B2), dd(B1 * B2);
-            const float S = dd.of(A1 * A2);
+            const float D = B1 * B2;
+            float S = 0.f, m0 = 0.f, m1 = 0.f, m2 = 0.f;
+            auto quotients = [&](float r1, float r2, auto by_d, auto by_2) {
+                S = by_d(A1 * A2);
+                if (kMaps) {
+                    m0 = by_d(2.f * my * (A2 - A1)) - 2.f * mx * S * (r1 - r2);
+                    m1 = by_2(-S);
+                    m2 = by_d(2.f * A1);
+                }
+            };
+            if (fabsf(D) < kDivisorEnd && D != 0.f) {
+                const Divisor d1(B1), d2(B2), dd(D);
+                quotients(d1.r, d2.r, [&](float a) { return dd.of(a); },
+                          [&](float a) { return d2.of(a); });
+            } else {
+                quotients(1.f / B1, 1.f / B2, [&](float a) { return a / D; },
+                          [&](float a) { return a / B2; });
+            }
             s_ssim += S;
             if (kMaps) {
                 const int64_t pix = (int64_t)o * w + p.cx;
-                maps[(0 * 3 + p.ch) * plane + pix] =
-                    dd.of(2.f * my * (A2 - A1)) - 2.f * mx * S * (d1.r - d2.r);
-                maps[(1 * 3 + p.ch) * plane + pix] = d2.of(-S);
-                maps[(2 * 3 + p.ch) * plane + pix] = dd.of(2.f * A1);
+                maps[(0 * 3 + p.ch) * plane + pix] = m0;
+                maps[(1 * 3 + p.ch) * plane + pix] = m1;
+                maps[(2 * 3 + p.ch) * plane + pix] = m2;
             }
         }
     }
