@@ -369,41 +369,133 @@ __device__ __forceinline__ const ViewDev& view_of_entry(const Views* views, uint
     return views->v[views->n > 1 ? e / n : 0u];
 }
 
+// Entries with many pairs (few large Gaussians, small super-tiles) would leave the
+// pairs to a few blocks and there to a few threads. So a block takes kPairEntries
+// a round or, where an entry has more than kWideMean candidates in the mean, as
+// many as have a chunk of them, if the grid covers all entries so; and in a round
+// where a thread has more than kWideAlone candidates, the threads of the block
+// take the pairs of all its entries, each by its place (ten steps to its entry,
+// five to its bit). us of the whole binning, every thread walking its own
+// entries' pairs / now / pairs emitted and sorted: 1000 Gaussians on 41 of 117
+// super-tiles each 943 / 83 / 204, 30k 1370 / 359 / 480, 30k on 49 of 425 3090 /
+// 192 / 261; 300k, 50 of them of image size 163 / 141. By kWideMean 2 / 4 / 8: 1M
+// Gaussians with 3.9 candidates 297 / 276 / 278, 30k with 6.6 122 / 119 / 140; by
+// kWideAlone 4 / 16 / 64: 3M with 1.9 312 / 300 / 307, 100k with 6.6 207 / 201 / 226.
+constexpr int kChunkEach = 8;                            // pairs of a chunk per thread
+constexpr int kChunk = kPairThreads * kChunkEach;         // pairs expanded at a time
+constexpr uint32_t kWideMean = 4;
+__device__ __forceinline__ int64_t block_entries(const uint32_t* counters, int rounds) {
+    const uint32_t nvis = counters[kVisible], pairs = counters[kPairs];
+    const int64_t most = (int64_t)kPairEntries * rounds;
+    if (pairs / kWideMean <= nvis) return most;
+    const uint32_t least = (nvis + gridDim.x - 1u) / gridDim.x;
+    return min(most, (int64_t)max(least, max((uint32_t)kChunk / (pairs / nvis), 1u)));
+}
+
+constexpr uint32_t kWideAlone = 16;
+
+// The entry that owns place p: the last one whose first place is at most p.
+__device__ __forceinline__ int pair_owner(const uint32_t* first, uint32_t p) {
+    int i = 0;
+#pragma unroll
+    for (int half = 512; half > 0; half >>= 1)
+        if (i + half < kPairEntries && first[i + half] <= p) i += half;
+    return i;
+}
+static_assert(kPairEntries <= 1024, "ten halvings");
+
+// Super-tile column and row of the q-th kept pair of an entry.
+__device__ __forceinline__ void kept_pair_at(int S, const uint4& info, uint32_t q, int* x, int* y) {
+    const uint32_t tested = (uint32_t)__builtin_popcount(info.z);
+    uint32_t c = kTested + q - tested;
+    if (q < tested) {   // the q-th bit set
+        c = 0;
+#pragma unroll
+        for (int half = 16; half > 0; half >>= 1) {
+            const uint32_t below =
+                (uint32_t)__builtin_popcount((info.z >> c) & ((1u << half) - 1u));
+            const bool up = q >= below;
+            q -= up ? below : 0u;
+            c += up ? (uint32_t)half : 0u;
+        }
+    }
+    int sx0, sx1, sy0, sy1;
+    super_rect((int)(info.x & 0xffffu), (int)(info.x >> 16), (int)(info.y & 0xffffu),
+               (int)(info.y >> 16), S, &sx0, &sx1, &sy0, &sy1);
+    // (c + 1/2 is at least 1 / (2 w) > 2^-10 from a multiple of the width w, c < 512)
+    const uint32_t w = (uint32_t)(sx1 - sx0);
+    const uint32_t row = (uint32_t)(((float)c + 0.5f) * __builtin_amdgcn_rcpf((float)w));
+    *x = sx0 + (int)(c - row * w);
+    *y = sy0 + (int)row;
+}
+
 __global__ void __launch_bounds__(kPairThreads) pair_count_kernel(
     const Views* __restrict__ views, RasterDev rp, uint32_t n,
     const uint32_t* __restrict__ sorted_entry, const uint4* __restrict__ info,
     const uint32_t* __restrict__ counters, int rounds, uint4* __restrict__ sorted_info,
     uint32_t* __restrict__ hist, uint32_t* __restrict__ groups) {
     extern __shared__ uint32_t s_cnt[];   // per super-tile
+    __shared__ uint4 s_info[kPairEntries];
+    __shared__ uint32_t s_first[kPairEntries];
+    __shared__ uint32_t smem[kPairThreads / 64 + 1];
     const int tid = threadIdx.x;
     const int ns = views->total_supers, S = rp.super_tile;
     const int64_t nvis = counters[kVisible];
-    const int64_t tile = (int64_t)kPairEntries * rounds;
+    const int64_t tile = block_entries(counters, rounds);
     const int active = (int)((nvis + tile - 1) / tile);
     if ((int)blockIdx.x >= active) return;   // uniform
     const int blk = xcd_block(blockIdx.x, active);
     for (int s = tid; s < ns; s += kPairThreads) s_cnt[s] = 0u;
     __syncthreads();
     constexpr int kEach = kPairEntries / kPairThreads;
-    for (int r = 0; r < rounds; ++r) {
-        const int64_t k0 = (int64_t)blk * tile + (int64_t)r * kPairEntries + tid;
+    const int64_t end = min(nvis, (blk + 1) * tile);
+    for (int64_t k0 = blk * tile; k0 < end; k0 += kPairEntries) {
         uint32_t e[kEach];
         uint4 c[kEach];
 #pragma unroll
         for (int j = 0; j < kEach; ++j) {
-            const int64_t k = k0 + j * kPairThreads;
-            e[j] = k < nvis ? sorted_entry[k] : 0u;
+            const int64_t k = k0 + j * kPairThreads + tid;
+            e[j] = k < end ? sorted_entry[k] : 0u;
         }
+        uint32_t candidates = 0;
 #pragma unroll
         for (int j = 0; j < kEach; ++j) {
             c[j] = info[e[j]];
             c[j].w = e[j];
+            const int64_t k = k0 + j * kPairThreads + tid;
+            if (k >= end) continue;
+            sorted_info[k] = c[j];
+            candidates += candidate_pairs(c[j], S);
+        }
+        if (__syncthreads_or(candidates > kWideAlone)) {
+            uint32_t kept[kEach], mine = 0, total;
+#pragma unroll
+            for (int j = 0; j < kEach; ++j) {
+                kept[j] = k0 + j * kPairThreads + tid < end ? kept_pairs(c[j], S) : 0u;
+                mine += kept[j];
+            }
+            uint32_t first = block_excl_scan<kPairThreads>(mine, smem, &total);
+#pragma unroll
+            for (int j = 0; j < kEach; ++j) {
+                s_first[tid * kEach + j] = first;
+                s_info[tid * kEach + j] = c[j];
+                first += kept[j];
+            }
+            __syncthreads();
+            for (uint32_t p = tid; p < total; p += kPairThreads) {
+                const int o = pair_owner(s_first, p);
+                const uint4 f = s_info[o];
+                const ViewDev& V = view_of_entry(views, f.w, n);
+                int x, y;
+                kept_pair_at(S, f, p - s_first[o], &x, &y);
+                atomicAdd(&s_cnt[V.sup_offset + y * V.sup_x + x], 1u);
+            }
+            __syncthreads();
+            continue;
         }
 #pragma unroll
         for (int j = 0; j < kEach; ++j) {
-            const int64_t k = k0 + j * kPairThreads;
-            if (k >= nvis) break;
-            sorted_info[k] = c[j];
+            if (k0 + j * kPairThreads + tid >= end) break;
             for_candidates(view_of_entry(views, e[j], n), S, c[j],
                            [&](int, int, uint32_t s) { atomicAdd(&s_cnt[s], 1u); });
         }
@@ -419,8 +511,6 @@ __global__ void __launch_bounds__(kPairThreads) pair_count_kernel(
 // Position, key and entry of every kept pair; block 0 also writes the super-tile
 // ranges and the pair counts. Pairs past the capacity are not written (the
 // overflow is flagged when more pairs are needed than fit).
-constexpr int kChunkEach = 8;                            // pairs of a chunk per thread
-constexpr int kChunk = kPairThreads * kChunkEach;         // pairs expanded at a time
 __global__ void __launch_bounds__(kPairThreads, 4) pair_place_kernel(
     const Views* __restrict__ views, RasterDev rp, uint32_t n, uint32_t* __restrict__ counters,
     int rounds, const uint4* __restrict__ sorted_info, const uint32_t* __restrict__ hist,
@@ -432,6 +522,7 @@ __global__ void __launch_bounds__(kPairThreads, 4) pair_place_kernel(
     extern __shared__ uint32_t s_dyn[];   // [NW][ns] counts, [ns] next positions, [ns] starts
     __shared__ uint32_t lkey[kChunk];
     __shared__ uint32_t lent[kChunk];
+    __shared__ uint32_t s_first[kPairEntries];   // first place of an entry's pairs
     __shared__ uint32_t smem[NW + 1];
     const int tid = threadIdx.x, w = tid / 64, lane = tid % 64;
     const int ns = views->total_supers, S = rp.super_tile;
@@ -439,7 +530,7 @@ __global__ void __launch_bounds__(kPairThreads, 4) pair_place_kernel(
     uint32_t* gpos = s_dyn + NW * ns;
     uint32_t* start = gpos + ns;
     const int64_t nvis = counters[kVisible];
-    const int64_t tile = (int64_t)kPairEntries * rounds;
+    const int64_t tile = block_entries(counters, rounds);
     const int active = (int)((nvis + tile - 1) / tile);
     if ((int)blockIdx.x >= max(active, 1)) return;   // uniform; block 0 always writes the ranges
     const int blk = active > 0 ? xcd_block(blockIdx.x, active) : 0;
@@ -497,43 +588,71 @@ __global__ void __launch_bounds__(kPairThreads, 4) pair_place_kernel(
     if (active == 0) return;
     const int rb = rp.rect_bits, kb = rp.key_bits;
     const uint32_t kmask = (1u << kb) - 1u;
-    for (int r = 0; r < rounds; ++r) {
-        const int64_t k0 = (int64_t)blk * tile + (int64_t)r * kPairEntries;
-        if (k0 >= nvis) break;   // uniform
-        // thread t expands entries k0 + kEach t ...
+    const int64_t end = min(nvis, (blk + 1) * tile);
+    for (int64_t k0 = blk * tile; k0 < end; k0 += kPairEntries) {
+        // thread t's entries: k0 + kEach t ...; in one scan the place of their
+        // pairs and, above kPlaceBits, the threads that have many candidates
+        constexpr int kPlaceBits = 20;
+        static_assert(kPairEntries * kDirectSupers < 1 << kPlaceBits, "places of a round");
         uint4 c[kEach];
-        uint32_t mine = 0;
+        uint32_t kept[kEach], mine = 0, candidates = 0;
 #pragma unroll
         for (int j = 0; j < kEach; ++j) {
             const int64_t k = k0 + (int64_t)tid * kEach + j;
-            c[j] = k < nvis ? sorted_info[k] : make_uint4(0u, 0u, 0u, 0u);
-            mine += k < nvis ? kept_pairs(c[j], S) : 0u;
+            c[j] = k < end ? sorted_info[k] : make_uint4(0u, 0u, 0u, 0u);
+            kept[j] = k < end ? kept_pairs(c[j], S) : 0u;
+            candidates += k < end ? candidate_pairs(c[j], S) : 0u;
+            mine += kept[j];
         }
         uint32_t total;
-        const uint32_t first = block_excl_scan<kPairThreads>(mine, smem, &total);
-        for (uint32_t c0 = 0; c0 < total; c0 += (uint32_t)kChunk) {
-            uint32_t at = first - c0;   // wraps below the chunk, which no check passes
+        uint32_t first = block_excl_scan<kPairThreads>(
+            mine | (candidates > kWideAlone ? 1u << kPlaceBits : 0u), smem, &total);
+        first &= (1u << kPlaceBits) - 1u;
+        const bool wide = total >> kPlaceBits != 0u;   // uniform
+        total &= (1u << kPlaceBits) - 1u;
+        if (wide) {
+            uint32_t at = first;
 #pragma unroll
             for (int j = 0; j < kEach; ++j) {
-                if (k0 + (int64_t)tid * kEach + j >= nvis) break;
-                const int x0 = (int)(c[j].x & 0xffffu), x1 = (int)(c[j].x >> 16);
-                const int y0 = (int)(c[j].y & 0xffffu), y1 = (int)(c[j].y >> 16);
-                for_candidates(view_of_entry(views, c[j].w, n), S, c[j],
-                               [&](int x, int y, uint32_t s) {
-                    if (at < (uint32_t)kChunk) {
-                        // the tile rectangle inside the super-tile, relative to its first tile
-                        const int ox = x * S, oy = y * S;
-                        const uint32_t lx0 = (uint32_t)(max(x0, ox) - ox);
-                        const uint32_t lx1 = (uint32_t)(min(x1, ox + S) - 1 - ox);
-                        const uint32_t ly0 = (uint32_t)(max(y0, oy) - oy);
-                        const uint32_t ly1 = (uint32_t)(min(y1, oy + S) - 1 - oy);
-                        const uint32_t rect =
-                            lx0 | (lx1 << rb) | (ly0 << (2 * rb)) | (ly1 << (3 * rb));
-                        lkey[at] = s | (rect << kb);
-                        lent[at] = c[j].w;
-                    }
-                    ++at;
-                });
+                s_first[tid * kEach + j] = at;
+                at += kept[j];
+            }
+            __syncthreads();
+        }
+        for (uint32_t c0 = 0; c0 < total; c0 += (uint32_t)kChunk) {
+            auto put = [&](uint32_t at, const uint4& f, int x, int y, uint32_t s) {
+                // the tile rectangle inside the super-tile, relative to its first tile
+                const int ox = x * S, oy = y * S;
+                const uint32_t lx0 = (uint32_t)(max((int)(f.x & 0xffffu), ox) - ox);
+                const uint32_t lx1 = (uint32_t)(min((int)(f.x >> 16), ox + S) - 1 - ox);
+                const uint32_t ly0 = (uint32_t)(max((int)(f.y & 0xffffu), oy) - oy);
+                const uint32_t ly1 = (uint32_t)(min((int)(f.y >> 16), oy + S) - 1 - oy);
+                const uint32_t rect = lx0 | (lx1 << rb) | (ly0 << (2 * rb)) | (ly1 << (3 * rb));
+                lkey[at] = s | (rect << kb);
+                lent[at] = f.w;
+            };
+            if (wide) {
+#pragma unroll 2
+                for (uint32_t at = tid; at < (uint32_t)kChunk && c0 + at < total;
+                     at += kPairThreads) {
+                    const int o = pair_owner(s_first, c0 + at);
+                    const uint4 f = sorted_info[k0 + o];
+                    const ViewDev& V = view_of_entry(views, f.w, n);
+                    int x, y;
+                    kept_pair_at(S, f, c0 + at - s_first[o], &x, &y);
+                    put(at, f, x, y, (uint32_t)(V.sup_offset + y * V.sup_x + x));
+                }
+            } else {
+                uint32_t at = first - c0;   // wraps below the chunk, which no check passes
+#pragma unroll
+                for (int j = 0; j < kEach; ++j) {
+                    if (k0 + (int64_t)tid * kEach + j >= end) break;
+                    for_candidates(view_of_entry(views, c[j].w, n), S, c[j],
+                                   [&](int x, int y, uint32_t s) {
+                        if (at < (uint32_t)kChunk) put(at, c[j], x, y, s);
+                        ++at;
+                    });
+                }
             }
             for (int i = tid; i < NW * ns; i += kPairThreads) wcnt[i] = 0u;
             __syncthreads();

@@ -274,9 +274,12 @@ constexpr uint32_t kTested = 32;
 __device__ __forceinline__ bool pair_kept(const uint4& info, uint32_t q) {
     return q >= kTested || ((info.z >> q) & 1u) != 0u;
 }
+__device__ __forceinline__ uint32_t candidate_pairs(const uint4& info, int S) {
+    return super_count((int)(info.x & 0xffffu), (int)(info.x >> 16), (int)(info.y & 0xffffu),
+                       (int)(info.y >> 16), S);
+}
 __device__ __forceinline__ uint32_t kept_pairs(const uint4& info, int S) {
-    const uint32_t c = super_count((int)(info.x & 0xffffu), (int)(info.x >> 16),
-                                   (int)(info.y & 0xffffu), (int)(info.y >> 16), S);
+    const uint32_t c = candidate_pairs(info, S);
     return (uint32_t)__builtin_popcount(info.z) + (c > kTested ? c - kTested : 0u);
 }
 __device__ __forceinline__ uint4 pair_info(const float4& r0, const float4& r1, int x0, int x1,
