@@ -297,6 +297,12 @@ sgs_status sgs_get_workspace_layout(const sgs_raster_params* rp, int64_t n, cons
                                     int32_t n_views, int64_t pair_capacity,
                                     sgs_workspace_layout* out);
 
+/* Waves that share a tile in the compositing forward and backward of these views
+ * (1, 2 or 4 by the tile shape and the number of tiles). lds_batch takes effect in
+ * the passes where it is 1. */
+sgs_status sgs_tile_waves(const sgs_raster_params* rp, const sgs_camera* cams, int32_t n_views,
+                          int32_t* forward_out, int32_t* backward_out);
+
 /* ---------------------------------------------------------------------------
  * Photometric loss (Eq. 6): L = (1 - lambda) L1 + lambda (1 - SSIM), mean over
  * the 3 H W values; SSIM with an 11x11 Gaussian window (sigma 1.5), C1 = 1e-4,

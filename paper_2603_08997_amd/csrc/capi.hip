@@ -376,6 +376,18 @@ sgs_status sgs_forward_workspace_size(const sgs_raster_params* rp, int64_t n,
     return SGS_OK;
 }
 
+sgs_status sgs_tile_waves(const sgs_raster_params* rp, const sgs_camera* cams, int32_t n_views,
+                          int32_t* forward_out, int32_t* backward_out) {
+    if (!forward_out || !backward_out) return fail(SGS_ERR_INVALID_ARG, "output is null");
+    Prepared P;
+    sgs_status st = prepare(rp, 0, cams, n_views, 0, &P);
+    if (st != SGS_OK) return st;
+    const sgs::TileWaves w = sgs::tile_waves(P.rd.tile_w, P.L.total_tiles);
+    *forward_out = w.forward;
+    *backward_out = w.backward;
+    return SGS_OK;
+}
+
 sgs_status sgs_get_workspace_layout(const sgs_raster_params* rp, int64_t n, const sgs_camera* cams,
                                     int32_t n_views, int64_t pair_capacity,
                                     sgs_workspace_layout* out) {

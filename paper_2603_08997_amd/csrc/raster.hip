@@ -794,10 +794,17 @@ __global__ void __launch_bounds__(kPrepareThreads) prepare_backward_kernel(
 constexpr int64_t kForwardFine = 5120;    // tiles up to which the forward takes 4 waves, else 2
 constexpr int64_t kBackwardFine = 1536;   // tiles up to which the backward takes 4 waves
 constexpr int64_t kBackwardHalf = 5120;   // ... 2 waves, else 1
+TileWaves tile_waves(int tile_w, int64_t tiles) {
+    if (tile_w == 8) return {1, 1};
+    return {tiles <= kForwardFine ? 4 : 2,
+            tiles <= kBackwardFine ? 4 : (tiles <= kBackwardHalf ? 2 : 1)};
+}
 
 // Kernel instantiations: tile shapes 16x16, 8x8, 32x8; the batches 32, 64,
 // 128, 256 the raster parameters accept where one wave takes a tile, batches
-// of 64 in parts.
+// of 64 in parts (us of the forward with 32 / 64 / 128 / 256: 2170 tiles 86 / 77 /
+// 80 / 105, 4056 131 / 116 / 124 / 177, 6700 168 / 155 / 160 / 214: every wave
+// holds a batch of its own).
 #define SGS_RASTER_BATCHES(KERNEL, TW, TH, ...)                                       \
     do {                                                                             \
         if (rp.batch == 32) SGS_LAUNCH((KERNEL<TW, TH, 32, 1>), 1, __VA_ARGS__);       \
@@ -836,14 +843,15 @@ hipError_t launch_rasterize(const RasterDev& rp, const Layout& L, char* ws, floa
     // the waves of a tile are one workgroup
 #define SGS_LAUNCH(K, W, ...) \
     hipLaunchKernelGGL(K, dim3(blocks), dim3(kLanes * W), 0, s, __VA_ARGS__)
+    const int waves = tile_waves(rp.tile_w, L.total_tiles).forward;
     auto composite = [&](bool redo) {
         const unsigned blocks =
             (unsigned)L.total_tiles + (redo && sum_by == SumBy::kRedo ? 1u : 0u);
-        if (rp.tile_w == 8)
+        if (waves == 1)
             SGS_RASTER_BATCHES(raster_forward_kernel, 8, 8, views, rp, ranges, entry, rec, out_rgb,
                                tf, nl, stats, cost, entries, state, resume, sup_redo, cnt,
                                sum_by, redo);
-        else if (L.total_tiles <= kForwardFine)
+        else if (waves == 4)
             SGS_RASTER_PARTS(raster_forward_kernel, 4, views, rp, ranges, entry, rec, out_rgb, tf,
                               nl, stats, cost, entries, state, resume, sup_redo, cnt, sum_by, redo);
         else
@@ -901,12 +909,13 @@ hipError_t launch_rasterize_backward(const RasterDev& rp, const Layout& L, char*
     hipLaunchKernelGGL(K, dim3((unsigned)(L.total_tiles * W)), dim3(kLanes), 0, s, __VA_ARGS__)
 #define SGS_ARGS                                                                              \
     views, rp, ranges, entry, rec, tf, nl, dl_drgb, gate, acc, order, tiles, (uint32_t)L.entries
-    if (rp.tile_w == 8)
-        SGS_RASTER_BATCHES(raster_backward_kernel, 8, 8, SGS_ARGS);
-    else if (L.total_tiles <= kBackwardFine)
+    const int waves = tile_waves(rp.tile_w, L.total_tiles).backward;
+    if (waves == 4)
         SGS_RASTER_PARTS(raster_backward_kernel, 4, SGS_ARGS);
-    else if (L.total_tiles <= kBackwardHalf)
+    else if (waves == 2)
         SGS_RASTER_PARTS(raster_backward_kernel, 2, SGS_ARGS);
+    else if (rp.tile_w == 8)
+        SGS_RASTER_BATCHES(raster_backward_kernel, 8, 8, SGS_ARGS);
     else if (rp.tile_w == 16)
         SGS_RASTER_BATCHES(raster_backward_kernel, 16, 16, SGS_ARGS);
     else

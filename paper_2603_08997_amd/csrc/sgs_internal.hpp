@@ -238,6 +238,11 @@ hipError_t launch_bin(const RasterDev& rp, int64_t n, const Layout& L, char* ws,
 // after the prefix lists, and the new ranges of the incomplete tiles. Every
 // kernel returns at once unless counters[kRedo] is set.
 hipError_t launch_split_rest(const RasterDev& rp, const Layout& L, char* ws, hipStream_t s);
+// Waves that take a tile in the compositing passes of a batch.
+struct TileWaves {
+    int forward, backward;
+};
+TileWaves tile_waves(int tile_w, int64_t tiles);
 hipError_t launch_rasterize(const RasterDev& rp, const Layout& L, char* ws, float* out_rgb,
                             hipStream_t s);
 // What comes before the compositing backward: Adam's step count (nullable), the

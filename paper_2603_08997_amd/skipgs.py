@@ -88,7 +88,7 @@ EXPORTS = [
     "sgs_last_error", "sgs_version", "sgs_default_raster_params", "sgs_forward_workspace_size",
     "sgs_render_forward", "sgs_read_status", "sgs_clear_status", "sgs_render_backward",
     "sgs_render_gradients", "sgs_project", "sgs_load_records", "sgs_bin", "sgs_rasterize",
-    "sgs_rasterize_backward", "sgs_project_backward", "sgs_get_workspace_layout",
+    "sgs_rasterize_backward", "sgs_project_backward", "sgs_get_workspace_layout", "sgs_tile_waves",
     "sgs_loss_workspace_size", "sgs_photometric_loss", "sgs_photometric_loss_backward",
     "sgs_photometric_loss_static", "sgs_photometric_loss_gradient", "sgs_gate_state_size",
     "sgs_gate_init", "sgs_gate_update", "sgs_gate_read", "sgs_adam_step",
@@ -130,6 +130,7 @@ def _load():
         "sgs_get_workspace_layout": (i32, [P(RasterParamsC), i64, P(CameraC), i32, i64,
                                            P(WorkspaceLayoutC)]),
         "sgs_loss_workspace_size": (i32, [i32, i32, P(sz)]),
+        "sgs_tile_waves": (i32, [P(RasterParamsC), P(CameraC), i32, P(i32), P(i32)]),
         "sgs_photometric_loss": (i32, [vp, vp, i32, i32, f32, vp, sz, vp, vp]),
         "sgs_photometric_loss_static": (i32, [vp, vp, i32, i32, f32, vp, vp]),
         "sgs_photometric_loss_backward": (i32, [vp, vp, i32, i32, f32, vp, sz, vp, vp, vp]),
@@ -277,6 +278,13 @@ def get_workspace_layout(rp: RasterParams, n: int, cams, pair_capacity: int) -> 
     _check(LIB.sgs_get_workspace_layout(C.byref(rp.c()), n, cameras_c(cams), len(cams),
                                         pair_capacity, C.byref(out)))
     return out
+
+
+def tile_waves(rp: RasterParams, cams) -> tuple[int, int]:
+    """Waves that share a tile in the compositing forward and backward."""
+    f, b = C.c_int32(), C.c_int32()
+    _check(LIB.sgs_tile_waves(C.byref(rp.c()), cameras_c(cams), len(cams), C.byref(f), C.byref(b)))
+    return f.value, b.value
 
 
 def render_forward(planes, n, sh_degree, cams, rp: RasterParams, workspace, pair_capacity, out_rgb,

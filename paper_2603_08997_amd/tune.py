@@ -6,6 +6,9 @@ sizes, and returns the stored choice on later calls.
 
 The candidates change how the work is laid out, never the image or the
 gradients (the compositing order is the lists' depth order in every case).
+The LDS batch has an effect only in a pass where one wave takes a tile; the
+candidates that differ by it alone are otherwise one program, timed once, and the
+default batch stands for them.
 """
 from __future__ import annotations
 
@@ -20,7 +23,7 @@ import torch
 from . import skipgs as sk
 
 TILES = ((16, 16), (32, 8), (8, 8))
-BATCHES = (32, 64, 128, 256)
+BATCHES = (64, 32, 128, 256)   # (of equal ones the first is chosen)
 SUPER_TILES = (4, 8)
 
 
@@ -107,14 +110,17 @@ def tune(planes, n: int, sh_degree: int, cams, dl, store: str | None = None,
                                    lds_batch=ch["lds_batch"], super_tile=ch["super_tile"]), \
             dict(rec, reused=True)
     t0 = time.perf_counter()
-    trials = []
+    trials, timed = [], {}
     for (tw, th), bsz, st in itertools.product(TILES, BATCHES, SUPER_TILES):
         rp = dataclasses.replace(base, tile_w=tw, tile_h=th, lds_batch=bsz, super_tile=st)
-        ms = time_candidate(planes, n, sh_degree, cams, dl, rp)
+        program = (tw, th, st, bsz if 1 in sk.tile_waves(rp, cams) else None)
+        if program not in timed:
+            timed[program] = time_candidate(planes, n, sh_degree, cams, dl, rp)
+            torch.cuda.empty_cache()
+        ms = timed[program]
         trials.append({"tile_w": tw, "tile_h": th, "lds_batch": bsz, "super_tile": st, "ms": ms})
         if log is not None:
             log(f"tune {tw}x{th} B{bsz} S{st}: {ms:.3f} ms")
-        torch.cuda.empty_cache()
     best = min(trials, key=lambda t: t["ms"])
     rec = {"choice": {k: best[k] for k in ("tile_w", "tile_h", "lds_batch", "super_tile")},
            "ms": best["ms"], "trials": trials, "seconds": time.perf_counter() - t0}
