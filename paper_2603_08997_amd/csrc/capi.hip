@@ -225,7 +225,7 @@ void make_layout(const Views& views, const RasterDev& rp, int64_t n, int64_t cap
     const int64_t pair_tile = (int64_t)kPairEntries * L->pair_rounds;
     // (more blocks than that where entries have many pairs)
     L->pair_blocks = std::max<int64_t>({1, (L->entries + pair_tile - 1) / pair_tile,
-                                        std::min<int64_t>((L->entries + 15) / 16, 1024)});
+                                        std::min<int64_t>((L->entries + 15) / 16, 512)});
     const int64_t sort_blocks =
         std::max(radix_blocks(L->entries), L->direct ? 0 : radix_blocks(capacity));
     // super-tile index bits: 2^bits > total_supers, so that no index has all
