@@ -1,23 +1,24 @@
 // Binning: the depth-ordered tile lists the tile-based rasteriser composites.
 //
 // The lists are built in two levels. First at the granularity of super-tiles
-// (squares of S x S tiles): the stage sorts the visible entries once by depth
-// (a short array), emits their (super-tile, entry) pairs in that order, and
-// sorts the pairs stably by super-tile alone; stability keeps the depth order
-// inside each super-tile, as a sort of 64-bit (super-tile << 32 | depth) keys
-// would, on the bits of the super-tile index (the entry's tile rectangle
-// inside the super-tile rides along in the key's upper bits). A super-tile's
-// list holds the visible entries whose overlap box reaches it and that can
-// reach alpha_min at one of its pixel centres.
+// (squares of S x S tiles): the stage sorts the visible entries once by depth (a
+// short array) and lists them, in that order, under every super-tile they reach.
+// Up to kDirectSupers super-tiles the places in these lists are counted and the
+// pairs written there; beyond, the (super-tile, entry) pairs are emitted in depth
+// order and sorted stably by super-tile alone, which keeps the depth order inside
+// each, as a sort of 64-bit (super-tile << 32 | depth) keys would. A pair's key is
+// the super-tile index and, in its upper bits, the entry's tile rectangle inside
+// the super-tile. A super-tile's list holds the visible entries whose overlap box
+// reaches it and that can reach alpha_min at one of its pixel centres.
 //
 // Then every super-tile list is split into the lists of its S x S tiles, in
 // list order: per segment of a super-tile list, each pair's tile mask (the
-// tiles of its rectangle on which the entry can reach alpha_min), per-tile
-// counts, one scan over all (super-tile, tile, segment) counts for the list
-// positions, and a stable scatter of the entries. A tile's list is therefore
-// its depth-ordered list of entries whose overlap box reaches it and that can
-// reach alpha_min on it; the sort never sees the (far more numerous) tile
-// pairs.
+// tiles of its rectangle on which the entry can reach alpha_min) and per-tile
+// counts with their sums over groups of segments and over super-tiles, from which
+// every segment finds its list positions, and a stable scatter of the entries. A
+// tile's list is therefore its depth-ordered list of entries whose overlap box
+// reaches it and that can reach alpha_min on it; no sort sees the (far more
+// numerous) tile pairs.
 //
 // A tile composites only the front of its list, so a long super-tile list is
 // split only in a prefix of its segments before compositing (a tile's list is

@@ -18,9 +18,13 @@
 // (16x16 pixels per workgroup, 26x26 staged values, the products formed again at
 // every tap, both passes through LDS) issued twice as many instructions. The
 // order of every sum and the rounding of every quotient are the tiled form's,
-// so the maps and the gradient are the same bit for bit. At 1600x1060: forward
-// 90 -> 53 us, backward 72 -> 41 us (122 MB of images, maps and gradient, 3
-// TB/s); at 980x545 38 -> 27 and 30 -> 21 us. (Vertical pass first takes 7% off
+// so the maps and the gradient are the same bit for bit. Repeated on the same
+// 1600x1060 images: forward 90 -> 53 us, backward 72 -> 41 us (122 MB of images,
+// maps and gradient, 3 TB/s); at 980x545 38 -> 27 and 30 -> 21 us; at 640x480 and
+// below the forward alone is 1 to 2 us slower than the tiled one (25 and 23 us
+// with its reduction at 640x480) and the backward 4 faster. In a training iteration
+// of 3M Gaussians, which leaves little of the images in the caches, the forward
+// takes 71 us and the backward, with the clearing it takes along, 69. (Vertical pass first takes 7% off
 // both, as the halo rows skip the horizontal taps, but rounds differently: 3e-6
 // of the gradient, as far as either is from 64 bits.)
 //

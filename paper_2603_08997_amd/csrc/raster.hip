@@ -218,7 +218,7 @@ __device__ __forceinline__ uint32_t wave_add_u32(uint32_t v) {
 // a tile, so a few tiles add their own (16 tiles: nothing to be seen, against
 // the 4.6 us of a launch; 2170 tiles: +27 us); otherwise one more block of the
 // resuming launch does it, and resumed tiles add what they did there; a launch of
-// its own where there is no second pass or kUsed could pass 32 bits.
+// its own where there is no second pass.
 enum class SumBy { kTile, kRedo, kLaunch };
 constexpr int64_t kTileSums = 128;
 
@@ -231,7 +231,7 @@ __device__ __forceinline__ void add_work(uint32_t* counters, unsigned long long 
 }
 
 // Sums of {blended, evaluated, used} over the tiles by one workgroup, added to
-// the counters (kAdd) or written to them ([kUsed] saturating).
+// the counters (kAdd) or written to them.
 template <int NT, bool kAdd>
 __device__ __forceinline__ void sum_tiles(const uint4* __restrict__ tile_stats, int64_t tiles,
                                           uint32_t* counters) {
@@ -269,7 +269,7 @@ __device__ __forceinline__ void sum_tiles(const uint4* __restrict__ tile_stats, 
         } else {
             reinterpret_cast<unsigned long long*>(counters + kBlended)[0] = b;
             reinterpret_cast<unsigned long long*>(counters + kEvaluated)[0] = e;
-            counters[kUsed] = (uint32_t)min(u, 0xffffffffull);
+            counters[kUsed] = (uint32_t)u;
         }
     }
 }
@@ -480,10 +480,8 @@ __global__ void __launch_bounds__(kLanes * W) raster_forward_kernel(
         n_eval += stop_pos[k] != 0u ? stop_pos[k] - skipped : (py[k] == py[k] ? end - begin : 0u);
 
     // the backward walks every pixel's list up to its last blended Gaussian:
-    // the tile's longest such prefix is its work. The work counters go to the
-    // tile and are summed by a small kernel after the launch (atomics of
-    // every tile on the one counters line serialise across the chip and would
-    // lengthen the launch by a fifth)
+    // the tile's longest such prefix is its work (where its counters are summed
+    // up: SumBy)
     uint32_t my_last = 0;
 #pragma unroll
     for (int k = 0; k < PIX; ++k) my_last = max(my_last, last[k]);
@@ -790,7 +788,12 @@ __global__ void __launch_bounds__(kPrepareThreads) prepare_backward_kernel(
 // Backward: each part repeats the wave reduction and the atomic of a pair, so
 // parts pay only while SIMDs would idle: 16 tiles 68 / 42 / 29, 1200 tiles
 // 135 / 88 / 75, 2170 tiles 188 / 131 / 144, 4056 tiles 228 / 222 / 249, 6700
-// tiles 284 / 290 / 403, 28000 tiles 910 / 1177 / 1704.
+// tiles 284 / 290 / 403, 28000 tiles 910 / 1177 / 1704. Gaussians that cover much
+// of a tile have more pairs with every part: 1000 of a third of the image take 80 /
+// 114 with 2 / 4 waves at 1200 tiles, 85 / 112 with 1 / 2 at 2170 and 131 / 202 at
+// 4056, where their forward gains 40 to 70 from its parts; where between 3000 and
+// 5120 tiles one wave or two are better depends on the view (4056 tiles, 1M small
+// Gaussians: 214 / 238 in one, 244 / 211 in another).
 constexpr int64_t kForwardFine = 5120;    // tiles up to which the forward takes 4 waves, else 2
 constexpr int64_t kBackwardFine = 1536;   // tiles up to which the backward takes 4 waves
 constexpr int64_t kBackwardHalf = 5120;   // ... 2 waves, else 1
@@ -835,11 +838,10 @@ hipError_t launch_rasterize(const RasterDev& rp, const Layout& L, char* ws, floa
     uint32_t* state = lists_cut(rp, L) ? reinterpret_cast<uint32_t*>(ws + L.tile_state) : nullptr;
     uint32_t* sup_redo = reinterpret_cast<uint32_t*>(ws + L.sup_redo);
     uint32_t* resume = reinterpret_cast<uint32_t*>(ws + L.tile_resume);
-    // (the sum of the used entries stays below the capacity)
-    const SumBy sum_by = L.capacity > (int64_t)0xffffffffu ? SumBy::kLaunch
-                         : L.total_tiles <= kTileSums      ? SumBy::kTile
-                         : state != nullptr                ? SumBy::kRedo
-                                                           : SumBy::kLaunch;
+    // (the sum of the used entries stays below the capacity, below 2^31)
+    const SumBy sum_by = L.total_tiles <= kTileSums ? SumBy::kTile
+                         : state != nullptr         ? SumBy::kRedo
+                                                    : SumBy::kLaunch;
     // the waves of a tile are one workgroup
 #define SGS_LAUNCH(K, W, ...) \
     hipLaunchKernelGGL(K, dim3(blocks), dim3(kLanes * W), 0, s, __VA_ARGS__)

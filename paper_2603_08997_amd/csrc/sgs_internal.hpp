@@ -19,9 +19,10 @@ constexpr int kDefaultBatch = 64;           // list entries per compositing batc
 constexpr int kDefaultSplitPrefix = 8192;   // super-tile list pairs split before compositing
 
 // Per-view constants. A call's views live in device memory (the workspace's
-// view table): a one-thread kernel stores them there at the start of every
-// call, from its arguments or from a camera table picked by a device-side
-// view index, and every other kernel reads them through a pointer.
+// view table): the first launch of the call (the projection of one view, the
+// preparation of the compositing backward, a launch of its own otherwise) stores
+// them there, from the call's arguments or from a camera table picked by a
+// device-side view index, and the kernels after it read them through a pointer.
 struct ViewDev {
     float R[9];
     float t[3];
@@ -108,8 +109,12 @@ constexpr int kMaxSuperTile = 8;   // S x S tiles of a super-tile fit a 64-bit t
 // most kEmitWindow / (kEmitHead + 1) + 2 Gaussians.
 constexpr int64_t kEmitWindow = 1024;
 constexpr int64_t kEmitHead = 2;
-// Super-tiles up to which the pairs are counted and placed without a sort (the
-// place kernel keeps 24 bytes of LDS for each).
+// Super-tiles up to which the pairs are counted and placed without a sort: the
+// place kernel keeps 24 bytes of LDS for each, and a wave's counts are the sparser
+// the more there are. us of projection and binning, placed / sorted: 425
+// super-tiles (3M Gaussians) 605 / 656, 468 (1M in 4 views) 613 / 751, 494 (2M in 8)
+// 1687 / 2076; beyond the line 782 (3M) 796 / 810, 936 (2M in 8) 2265 / 2407, 936
+// (300k in 8) 653 / 631.
 constexpr int64_t kDirectSupers = 512;
 constexpr int kPairThreads = 256;
 constexpr int kPairEntries = 768;   // entries expanded at a time
