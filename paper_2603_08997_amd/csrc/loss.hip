@@ -24,9 +24,9 @@
 // below the forward alone is 1 to 2 us slower than the tiled one (25 and 23 us
 // with its reduction at 640x480) and the backward 4 faster. In a training iteration
 // of 3M Gaussians, which leaves little of the images in the caches, the forward
-// takes 71 us and the backward, with the clearing it takes along, 69. (Vertical pass first takes 7% off
-// both, as the halo rows skip the horizontal taps, but rounds differently: 3e-6
-// of the gradient, as far as either is from 64 bits.)
+// takes 71 us and the backward, with the clearing it takes along, 69. (Vertical
+// pass first takes 7% off both, as the halo rows skip the horizontal taps, but
+// rounds differently: 3e-6 of the gradient, as far as either is from 64 bits.)
 //
 // A lane adds the values of its column in FP32 over kFold rows and these in
 // binary64, as all sums after it are: a strip has the more rows the larger the
