@@ -219,12 +219,13 @@ __device__ __forceinline__ uint32_t super_count(int x0, int x1, int y0, int y1, 
 // that fails cannot pass the compositing kernels' skip test at any pixel of
 // the rectangle. The limit 2 ln(o / alpha_min) = 2 ln 2 (log2 o - log2 alpha_min)
 // is formed with the hardware log2 and inflated by 1% + 0.01, far more than
-// the rounding of either; +inf for alpha_min = 0, also where o is 0 and the
-// difference of the logarithms undefined.
+// the rounding of either; +inf for alpha_min = 0 (log2 alpha_min = -inf), also for
+// o = 0, whose logarithm is taken as the lowest float (a branch on alpha_min costs
+// 4 us at 3M Gaussians).
 __device__ __forceinline__ float reach_limit(float o, const RasterDev& rp) {
     constexpr float kTwoLn2 = 1.38629436111989061883f;
-    if (rp.alpha_min == 0.f) return INFINITY;   // uniform
-    return (kTwoLn2 * 1.01f) * (__builtin_amdgcn_logf(o) - rp.log2_alpha_min) + 0.01f;
+    const float log2_o = fmaxf(__builtin_amdgcn_logf(o), -3.402823466e38f);
+    return (kTwoLn2 * 1.01f) * (log2_o - rp.log2_alpha_min) + 0.01f;
 }
 
 __device__ __forceinline__ bool rect_reachable(float u, float v, float a, float b, float c,
