@@ -374,14 +374,15 @@ __device__ __forceinline__ const ViewDev& view_of_entry(const Views* views, uint
 // pairs to a few blocks and there to a few threads. So a block takes kPairEntries
 // a round or, where an entry has more than kWideMean candidates in the mean, as
 // many as have a chunk of them, if the grid covers all entries so; and in a round
-// where a thread has more than kWideAlone candidates, the threads of the block
-// take the pairs of all its entries, each by its place (ten steps to its entry,
-// five to its bit). us of the whole binning, every thread walking its own
-// entries' pairs / now / pairs emitted and sorted: 1000 Gaussians on 41 of 117
-// super-tiles each 943 / 83 / 204, 30k 1370 / 359 / 480, 30k on 49 of 425 3090 /
-// 192 / 261; 300k, 50 of them of image size 163 / 141. By kWideMean 2 / 4 / 8: 1M
-// Gaussians with 3.9 candidates 297 / 276 / 278, 30k with 6.6 122 / 119 / 140; by
-// kWideAlone 4 / 16 / 64: 3M with 1.9 312 / 300 / 307, 100k with 6.6 207 / 201 / 226.
+// where a thread has more than kWideAlone candidates, the threads of the block (of
+// the wave in the count, which then needs no barrier: 0.7 us at 3M) take the pairs
+// of all its entries, each by its place (ten steps to its entry, five to its bit).
+// us of the whole binning, every thread walking its own entries' pairs / now /
+// pairs emitted and sorted: 1000 Gaussians on 41 of 117 super-tiles each 943 / 84 /
+// 204, 30k 1370 / 365 / 480, 30k on 49 of 425 3090 / 196 / 261; 300k, 50 of them of
+// image size 163 / 141. By kWideMean 2 / 4 / 8: 1M Gaussians with 3.9 candidates
+// 297 / 276 / 278, 30k with 6.6 122 / 119 / 140; by kWideAlone 4 / 16 / 64: 3M with
+// 1.9 312 / 300 / 307, 100k with 6.6 207 / 201 / 226.
 constexpr int kChunkEach = 8;                            // pairs of a chunk per thread
 constexpr int kChunk = kPairThreads * kChunkEach;         // pairs expanded at a time
 constexpr uint32_t kWideMean = 4;
@@ -395,12 +396,13 @@ __device__ __forceinline__ int64_t block_entries(const uint32_t* counters, int r
 
 constexpr uint32_t kWideAlone = 16;
 
-// The entry that owns place p: the last one whose first place is at most p.
+// The entry of N that owns place p: the last one whose first place is at most p.
+template <int N>
 __device__ __forceinline__ int pair_owner(const uint32_t* first, uint32_t p) {
     int i = 0;
 #pragma unroll
     for (int half = 512; half > 0; half >>= 1)
-        if (i + half < kPairEntries && first[i + half] <= p) i += half;
+        if (half < N && i + half < N && first[i + half] <= p) i += half;
     return i;
 }
 static_assert(kPairEntries <= 1024, "ten halvings");
@@ -436,10 +438,11 @@ __global__ void __launch_bounds__(kPairThreads) pair_count_kernel(
     const uint32_t* __restrict__ counters, int rounds, uint4* __restrict__ sorted_info,
     uint32_t* __restrict__ hist, uint32_t* __restrict__ groups) {
     extern __shared__ uint32_t s_cnt[];   // per super-tile
-    __shared__ uint4 s_info[kPairEntries];
-    __shared__ uint32_t s_first[kPairEntries];
-    __shared__ uint32_t smem[kPairThreads / 64 + 1];
-    const int tid = threadIdx.x;
+    constexpr int NW = kPairThreads / 64, kEach = kPairEntries / kPairThreads;
+    constexpr int kWaveEntries = kPairEntries / NW;
+    __shared__ uint4 s_info[NW][kWaveEntries];
+    __shared__ uint32_t s_first[NW][kWaveEntries];
+    const int tid = threadIdx.x, w = tid / 64, lane = tid % 64;
     const int ns = views->total_supers, S = rp.super_tile;
     const int64_t nvis = counters[kVisible];
     const int64_t tile = block_entries(counters, rounds);
@@ -448,55 +451,59 @@ __global__ void __launch_bounds__(kPairThreads) pair_count_kernel(
     const int blk = xcd_block(blockIdx.x, active);
     for (int s = tid; s < ns; s += kPairThreads) s_cnt[s] = 0u;
     __syncthreads();
-    constexpr int kEach = kPairEntries / kPairThreads;
     const int64_t end = min(nvis, (blk + 1) * tile);
     for (int64_t k0 = blk * tile; k0 < end; k0 += kPairEntries) {
+        // the round's entries dealt out to the waves, which work on their own
+        const int m = (int)min((int64_t)kPairEntries, end - k0), per = (m + NW - 1) / NW;
+        const int mine = min(per, m - w * per);   // (none: not positive)
+        const int64_t k1 = k0 + (int64_t)w * per;
         uint32_t e[kEach];
         uint4 c[kEach];
 #pragma unroll
         for (int j = 0; j < kEach; ++j) {
-            const int64_t k = k0 + j * kPairThreads + tid;
-            e[j] = k < end ? sorted_entry[k] : 0u;
+            const int i = j * 64 + lane;
+            e[j] = i < mine ? sorted_entry[k1 + i] : 0u;
         }
         uint32_t candidates = 0;
 #pragma unroll
         for (int j = 0; j < kEach; ++j) {
             c[j] = info[e[j]];
             c[j].w = e[j];
-            const int64_t k = k0 + j * kPairThreads + tid;
-            if (k >= end) continue;
-            sorted_info[k] = c[j];
+            if (j * 64 + lane >= mine) continue;
+            sorted_info[k1 + j * 64 + lane] = c[j];
             candidates += candidate_pairs(c[j], S);
         }
-        if (__syncthreads_or(candidates > kWideAlone)) {
-            uint32_t kept[kEach], mine = 0, total;
+        if (ballot(candidates > kWideAlone) != 0ull) {
+            uint32_t kept[kEach], sum = 0;
 #pragma unroll
             for (int j = 0; j < kEach; ++j) {
-                kept[j] = k0 + j * kPairThreads + tid < end ? kept_pairs(c[j], S) : 0u;
-                mine += kept[j];
+                kept[j] = j * 64 + lane < mine ? kept_pairs(c[j], S) : 0u;
+                sum += kept[j];
             }
-            uint32_t first = block_excl_scan<kPairThreads>(mine, smem, &total);
+            const uint32_t incl = wave_incl_scan(sum);
+            const uint32_t total = __builtin_amdgcn_readlane(incl, 63);
+            uint32_t first = incl - sum;
 #pragma unroll
             for (int j = 0; j < kEach; ++j) {
-                s_first[tid * kEach + j] = first;
-                s_info[tid * kEach + j] = c[j];
+                s_first[w][lane * kEach + j] = first;
+                s_info[w][lane * kEach + j] = c[j];
                 first += kept[j];
             }
-            __syncthreads();
-            for (uint32_t p = tid; p < total; p += kPairThreads) {
-                const int o = pair_owner(s_first, p);
-                const uint4 f = s_info[o];
+            wave_lds_sync();
+            for (uint32_t p = lane; p < total; p += 64) {
+                const int o = pair_owner<kWaveEntries>(s_first[w], p);
+                const uint4 f = s_info[w][o];
                 const ViewDev& V = view_of_entry(views, f.w, n);
                 int x, y;
-                kept_pair_at(S, f, p - s_first[o], &x, &y);
+                kept_pair_at(S, f, p - s_first[w][o], &x, &y);
                 atomicAdd(&s_cnt[V.sup_offset + y * V.sup_x + x], 1u);
             }
-            __syncthreads();
+            wave_lds_sync();
             continue;
         }
 #pragma unroll
         for (int j = 0; j < kEach; ++j) {
-            if (k0 + j * kPairThreads + tid >= end) break;
+            if (j * 64 + lane >= mine) break;
             for_candidates(view_of_entry(views, e[j], n), S, c[j],
                            [&](int, int, uint32_t s) { atomicAdd(&s_cnt[s], 1u); });
         }
@@ -636,7 +643,7 @@ __global__ void __launch_bounds__(kPairThreads, 4) pair_place_kernel(
 #pragma unroll 2
                 for (uint32_t at = tid; at < (uint32_t)kChunk && c0 + at < total;
                      at += kPairThreads) {
-                    const int o = pair_owner(s_first, c0 + at);
+                    const int o = pair_owner<kPairEntries>(s_first, c0 + at);
                     const uint4 f = sorted_info[k0 + o];
                     const ViewDev& V = view_of_entry(views, f.w, n);
                     int x, y;
